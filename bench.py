@@ -369,7 +369,7 @@ def main():
         alg_bytes += (2 * int(pix_need.sum()) + 2 * int(pix_act.sum())) * cfg.M * esize + int(pix_act.sum()) * cfg.C * esize
     achieved_gbs = alg_bytes / fused_s / 1e9
     schedule = "generic" if not fast else "tiled" if tiled else "stream" if (cfg.C, cfg.M, S) == (256, 64, 8) else "fused"
-    kernel_name = {"generic": "bneck_generic_kernel", "stream": "stream_bneck_kernel", "fused": "fused_bneck_kernel",
+    kernel_name = {"generic": "rows_conv1_kernel + rows_conv2_kernel + rows_conv3_kernel", "stream": "stream_bneck_kernel", "fused": "fused_bneck_kernel",
                    "tiled": "tiled_conv1_kernel + tiled_conv2_kernel + tiled_conv3_kernel (one block = three launches; "
                             "per-kernel durations: profiles/)"}[schedule]
     # the bound is whichever ideal time is longer: active FLOPs at the MFMA peak or these bytes at the HBM peak

@@ -22,7 +22,7 @@
  *     contents of the output buffers are then unspecified.
  *   - Alignment: none is required.  The matrix-core kernels move 16 bytes per lane, so they
  *     are used only when x, out and the weight buffers are 16-byte aligned (device allocations
- *     are); other pointers are served by the slower shape-generic kernel (lasnet_*_packed, which
+ *     are); other pointers are served by the slower shape-generic path (lasnet_*_packed, which
  *     has no such fallback, returns LASNET_EUNSUPPORTED).
  *   - A process that has no usable gfx950 device gets LASNET_EHIP from every compute
  *     call; there is no CPU fallback.
@@ -66,8 +66,8 @@ typedef struct {
 /* Flags for lasnet_sparse_bottleneck_ex / lasnet_dense_bottleneck. */
 enum {
   LASNET_POST_RELU = 1,        /* ReLU after the residual add, on active patches only       */
-  LASNET_FORCE_GENERIC = 2,    /* use the shape-generic scalar-FMA kernel (fp32 accumulate,
-                                  no intermediate rounding) even where an MFMA kernel exists */
+  LASNET_FORCE_GENERIC = 2,    /* use the shape-generic path (fp32 accumulate, no intermediate
+                                  rounding) even where an MFMA kernel of the shape exists   */
   LASNET_SKIP_IDENTITY = 4,    /* caller guarantees out already equals x on inactive patches:
                                   do not copy x to out first                                 */
   LASNET_FORCE_FUSED = 8,      /* run the one-kernel (fused) schedule even where the library would
@@ -187,9 +187,12 @@ LASNET_API size_t lasnet_workspace_bytes(int dtype, int N, int H, int W, int C, 
  * tensors and repack them on every call, on the caller's stream, into device memory the
  * library owns: one buffer per device and stream, allocated with hipMalloc (the only call of
  * these entry points that may block) on first use and again when a shape needs a larger one --
- * the smaller buffer is then kept, not freed, because enqueued work may still read it; at most
- * 8.5 MiB each, all kept until the process ends.  So those entry points cannot be
- * stream-captured before the stream's buffer has its final size.
+ * the smaller buffer is then kept, not freed, because enqueued work may still read it (the new one is at
+ * least twice as large, so what is left behind never exceeds what is in use); all are kept until
+ * the process ends.  So those entry points cannot be stream-captured before the stream's buffer has its
+ * final size.  Shapes and types without a matrix-core kernel of their own (all of fp32) keep y1 and y2 there as
+ * well, at most 256 MiB of them at a time; where that memory cannot be had (under capture, for one)
+ * they run a slower kernel that needs none.
  * Weights of an inference model do not change, so a caller can instead
  * repack once, like it folded BN once (Sec. 3.4), and pass the result to
  * lasnet_sparse_bottleneck_packed, which allocates nothing:
@@ -241,8 +244,10 @@ LASNET_API int lasnet_sparse_bottleneck_planned(const lasnet_tensor* x, const in
  *     it, so nothing has to be cleared between calls): calls that overlap on one GPU -- different
  *     streams, or host threads on different streams -- race on it.  Calls on one stream are
  *     ordered and safe.
- *   - Shapes without a matrix-core kernel run the generic kernel, which needs no scratch.
- * Arguments, semantics, flags and results are those of lasnet_sparse_bottleneck_ex, bit for bit.
+ *   - Shapes without a matrix-core kernel run the generic one-kernel path, which needs no scratch (it sums
+ *     in another order than the path lasnet_sparse_bottleneck_ex takes for them, in fp32 like that one).
+ * Arguments, semantics and flags are those of lasnet_sparse_bottleneck_ex, and so are the results of shapes
+ * with a matrix-core kernel, bit for bit.
  */
 #define LASNET_NOALLOC_MAX_PACKED_BYTES (4u << 20)
 LASNET_API int lasnet_sparse_bottleneck_noalloc(const lasnet_tensor* x, const int32_t* idx,

@@ -3,37 +3,54 @@
 
 #include <map>
 #include <mutex>
-#include <utility>
+#include <thread>
+#include <tuple>
 
 using namespace lasnet;
 
 namespace {
 
-// Device memory the library owns: one buffer per (device, stream) for the repacked weights
-// of calls that pass raw W1/W2/W3.  Work on one stream is ordered, so calls on the same stream
-// may share it; calls on different streams get different buffers.  A buffer that turns out too
-// small is not freed (work already enqueued may still read it): a larger one is allocated beside
-// it and the old one is kept until the process ends.  Shapes with a matrix-core kernel need at
-// most 8.5 MiB, so what accumulates is bounded by a few buffers of that size per stream.
-struct Workspace { void* ptr = nullptr; size_t cap = 0; };
+// Device memory the library owns: one buffer per (device, stream) for what a call needs beyond its arguments
+// (repacked weights, the intermediates of the tiled and the row schedule).  Work on one stream is ordered, so calls on
+// the same stream may share it; calls on different streams get different buffers.  The launches of one call go out
+// while its lease holds the buffer's lock, so two threads that call on one stream do not interleave theirs.
+// A buffer that turns out too small is not freed (work already enqueued, or a captured graph, may still use it): one
+// of at least twice its size takes its place and the old one is kept until the process ends, so what a stream has
+// left behind is never more than what it holds.
+struct Workspace { std::mutex mu; void* ptr = nullptr; size_t cap = 0; };
 std::mutex g_ws_mu;
-std::map<std::pair<int, hipStream_t>, Workspace> g_ws;
+// (hipStreamPerThread names another stream in every thread: there the thread is part of the key)
+std::map<std::tuple<int, hipStream_t, std::thread::id>, Workspace> g_ws;
 
-void* get_workspace(hipStream_t st, size_t bytes) {
+struct Lease { std::unique_lock<std::mutex> lock; void* ptr = nullptr; };
+
+// lease.ptr stays nullptr where the memory cannot be had: the device is full, or the buffer would have to grow
+// while the stream is being captured.
+void get_workspace(Lease& lease, hipStream_t st, size_t bytes) {
   int dev = 0;
-  if (hipGetDevice(&dev) != hipSuccess) return nullptr;
-  std::lock_guard<std::mutex> lock(g_ws_mu);
-  Workspace& w = g_ws[std::make_pair(dev, st)];
-  if (w.cap < bytes) {
+  if (hipGetDevice(&dev) != hipSuccess) return;
+  Workspace* w;
+  {
+    std::lock_guard<std::mutex> lock(g_ws_mu);
+    w = &g_ws[std::make_tuple(dev, st, st == hipStreamPerThread ? std::this_thread::get_id() : std::thread::id())];
+  }
+  lease.lock = std::unique_lock<std::mutex>(w->mu);
+  if (w->cap < bytes) {
+    hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
+    if (hipStreamIsCapturing(st, &cap) != hipSuccess || cap != hipStreamCaptureStatusNone) {
+      (void)hipGetLastError();
+      return;
+    }
+    if (bytes < 2 * w->cap) bytes = 2 * w->cap;
     void* p = nullptr;
     if (hipMalloc(&p, bytes) != hipSuccess) {
       (void)hipGetLastError();
-      return nullptr;
+      return;
     }
-    w.ptr = p;                                   // the previous buffer, if any, stays allocated
-    w.cap = bytes;
+    w->ptr = p;                                  // the previous buffer, if any, stays allocated
+    w->cap = bytes;
   }
-  return w.ptr;
+  lease.ptr = w->ptr;
 }
 
 // Repacked weights for callers that cannot allocate (lasnet_sparse_bottleneck_noalloc): a fixed
@@ -184,6 +201,11 @@ int run_block(const lasnet_tensor* x, const int32_t* idx, const int32_t* count, 
   hipError_t e = !fast ? prepare_generic(x->dtype) : tiled ? tiled->prepare() : prepare_mfma(x->c, M, S);
   if (e != hipSuccess) return LASNET_EHIP;
   unsigned char* tiled_ws = nullptr;
+  // Without a matrix-core kernel of its own the shape runs the row schedule; where there is no memory for that (the
+  // caller forbids it, a capture is under way, the map is too large), the one-kernel generic path.
+  const size_t rows_need = !fast && !pad.fixed_array && !pad.from_caller ? rows_workspace_bytes(x->dtype, g) : 0;
+  void* rows_ws = nullptr;
+  Lease lease;
   if (pad.from_caller) {
     tiled_ws = (unsigned char*)pad.workspace;              // (this entry takes packed weights: packed_need is 0)
   } else if (pad.fixed_array) {
@@ -194,8 +216,12 @@ int run_block(const lasnet_tensor* x, const int32_t* idx, const int32_t* count, 
       if (e != hipSuccess) return LASNET_EHIP;
       packed = p;
     }
+  } else if (rows_need) {
+    get_workspace(lease, st, rows_need);
+    rows_ws = lease.ptr;
   } else if (packed_need + tiled_need) {
-    unsigned char* ws = (unsigned char*)get_workspace(st, packed_need + tiled_need);
+    get_workspace(lease, st, packed_need + tiled_need);
+    unsigned char* ws = (unsigned char*)lease.ptr;
     if (!ws) return LASNET_EHIP;
     if (packed_need) {
       e = launch_pack(x->c, M, S, W1, W2, W3, ws, st);
@@ -214,6 +240,8 @@ int run_block(const lasnet_tensor* x, const int32_t* idx, const int32_t* count, 
                       tiled_ws, st);
   else if (fast)
     e = launch_mfma(g, x->data, idx, count, packed, b1, b2, b3, out->data, relu, st);
+  else if (rows_ws)
+    e = launch_rows(x->dtype, g, x->data, idx, count, w, out->data, relu, rows_ws, st);
   else
     e = launch_generic(x->dtype, g, x->data, idx, count, w, out->data, relu, st);
   return e == hipSuccess ? LASNET_OK : LASNET_EHIP;

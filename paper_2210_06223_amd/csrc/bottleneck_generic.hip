@@ -3,8 +3,10 @@
 // (S+2)x(S+2) window straight from NHWC global memory while computing conv1 (Sec. 3.4,
 // gather fused into the dynamic convolution), keep y1 and y2 in LDS as fp32, add the
 // residual and write the S x S result in place of the patch (scatter fused with the add).
-// This is the correctness path for shapes without a matrix-core kernel (and all of fp32):
-// fp32 accumulation, no intermediate rounding.
+// Shapes without a matrix-core kernel (and all of fp32) run the row schedule (bottleneck_rows.hpp); this kernel
+// is what they run where that may have no workspace: lasnet_sparse_bottleneck_noalloc, a stream that is being
+// captured before its buffer exists, maps beyond the row schedule's 32-bit offsets.  fp32 accumulation, no
+// intermediate rounding, as there.
 #include "common.hpp"
 
 namespace lasnet {

@@ -1,0 +1,617 @@
+// The row schedule of the sparse bottleneck: the three convolutions as three GEMMs over rows of pixels, y1 and y2
+// through a workspace, for shapes and types without a kernel of their own (all of fp32, and bf16 at any width).
+//
+//   plan   (a) the weights -> MFMA A-fragments in the order a wave reads them, zero-padded to whole fragments
+//          (b) one byte per pixel: does some active patch's (S+2)x(S+2) window hold it
+//   conv1  rows = the needed pixels of a run of consecutive pixels           y1[pixel] = ReLU(b1 + W1 x)
+//   conv2  rows = the list's pixels, S*S per entry, in the list's order      y2[pixel] = ReLU(b2 + W2 * y1 around it)
+//   conv3  the same rows                                                     out[pixel] = x + b3 + W3 y2
+//
+// What bounds it: the matrix cores at batch size (fp32: 256 FLOP per clock and CU), launches and load latency
+// at a few images.  So the work is cut fine -- a wave computes NB blocks of 16 pixels times 32 output channels,
+// and nothing but the four waves of a workgroup has to meet -- and both operands come straight from memory
+// into registers, D k-steps ahead: a 32-deep fp32 k-step is 8 MFMAs of 32 clocks per 16x16 tile, so even with
+// no reuse through LDS a CU asks its L1 for less than half of the 64 bytes a clock it delivers.  When the
+// rows are too few to fill the chip the four waves share one tile and split its reduction (KS = 4, partial sums
+// added in a fixed order through LDS); else they take four neighbouring groups of 32 channels (KS = 1).
+//
+// Measured, whole call sequence (masker, list, block) against the scalar one-kernel path: fp32 56x56x256, S=4, r=0.6, one
+// image 672 -> 35 us; fp32 14x14x1024, S=2, r=0.5, 16 images 7900 -> 87 us (conv1 28, conv2 30, conv3 17 us: 50 TFLOP/s
+// of the 154 that a large fp32 matrix product reaches); bf16 28x20x192, mid 48, S=4, 13 images 371 -> 36 us.
+//
+// Number formats (products and sums are never narrower than fp32, and nothing is rounded between the convolutions):
+//   Fp32     v_mfma_f32_16x16x4_f32 throughout
+//   Bf16Wide bf16 x and weights: conv1 multiplies them as they are (a bf16 product is exact in fp32); y1 and y2 are kept
+//            as three bf16 terms whose sum is the fp32 value (8 + 8 + 8 significant bits), so conv2 and
+//            conv3 run on the bf16 matrix cores, three MFMAs of 16 clocks where fp32 ones would take 256
+#pragma once
+#include "common.hpp"
+
+namespace lasnet {
+namespace {
+
+// (the global and LDS address spaces are named: through generic pointers these would be FLAT accesses)
+#define ROWS_LDS __attribute__((address_space(3)))
+
+constexpr int kRowsThreads = 256;                 // four waves
+constexpr unsigned kOutOfRange = 0x80000000u;     // a buffer offset past every descriptor's end: such a load returns zeros
+
+typedef __amdgpu_buffer_rsrc_t rows_rsrc_t;
+__device__ __forceinline__ int rows_uni(int v) { return __builtin_amdgcn_readfirstlane(v); }
+__device__ __forceinline__ rows_rsrc_t rows_rsrc(const void* p, unsigned bytes) {
+  const unsigned long long v = (unsigned long long)p;
+  const unsigned lo = rows_uni((int)(unsigned)v), hi = rows_uni((int)(unsigned)(v >> 32));
+  return __builtin_amdgcn_make_buffer_rsrc((void*)(((unsigned long long)hi << 32) | lo), 0, rows_uni((int)bytes), 0x00020000);
+}
+template <class V>
+__device__ __forceinline__ V rows_load16(rows_rsrc_t r, unsigned lane_bytes, unsigned uniform_bytes) {
+  return __builtin_bit_cast(V, __builtin_amdgcn_raw_buffer_load_b128(r, (int)lane_bytes, (int)uniform_bytes, 0));
+}
+
+// One call (or one chunk of images of it), by value into every kernel.
+struct RowsArgs {
+  Geom g;
+  int px0, npx;            // pixels [px0, px0 + npx) of the map are this chunk's; y1, y2 and `need` are relative to px0
+  int ks1, ksm;            // 32-deep k-steps of the C and the M channels
+  int pairs1, pairs3;      // groups of 32 output channels of conv1 / conv2, and of conv3
+  const int32_t* idx;      // nullptr: every cell
+  const int32_t* count;
+  const uint8_t* need;     // nullptr: every pixel
+  unsigned w1_bytes, w2_bytes, w3_bytes;    // packed
+};
+
+// The active list as rows: row r is pixel (r mod S*S) of entry r / (S*S).
+__device__ __forceinline__ int rows_active(const RowsArgs& a) {
+  return rows_uni(a.idx ? min(*a.count, a.g.P) : a.g.P) * (a.g.S * a.g.S);
+}
+// Its pixel, or -1: past the end of the list, not a cell of the map, or not of this chunk.
+struct RowPixel { int px, h, w; };
+__device__ __forceinline__ RowPixel row_pixel(const RowsArgs& a, int r, int nrows) {
+  RowPixel p{-1, 0, 0};
+  if (r >= nrows) return p;
+  const int S = a.g.S, s2 = S * S, e = r / s2, q = r - e * s2;
+  const int cell = a.idx ? a.idx[e] : e;
+  if ((unsigned)cell >= (unsigned)a.g.P) return p;
+  const int cpi = a.g.G * a.g.GW, n = cell / cpi, rem = cell - n * cpi, gy = rem / a.g.GW, gx = rem - gy * a.g.GW;
+  p.h = gy * S + q / S;
+  p.w = gx * S + q % S;
+  const int px = (n * a.g.H + p.h) * a.g.W + p.w;
+  if (px >= a.px0 && px < a.px0 + a.npx) p.px = px;
+  return p;
+}
+
+// ---- number formats -----------------------------------------------------------------------------------
+// KPL pieces of 16 bytes a lane holds of one 32-deep fragment; YP terms a y value is stored as.  Lane (i = lane % 16,
+// lg = lane / 16) holds row i, and the k of its piece h, element e are 16*h + 4*lg + e (fp32) or 8*lg + e
+// (bf16), for A and B alike: one load instruction then reads 64 contiguous bytes of each of 16 rows.
+struct Fp32 {
+  typedef float T;
+  typedef floatx4 V;
+  static constexpr int ES = 4, KPL = 2, XP = 1, YP = 1, EPP = 4;     // EPP: elements per piece
+  static constexpr int STEP = 128;                                   // bytes of a 32-deep k-step of one row
+  struct Frag { V v[KPL]; };
+  static __device__ __forceinline__ void mma(floatx4& acc, const Frag& a, const Frag& b, int h, int e) {
+    acc = __builtin_amdgcn_mfma_f32_16x16x4f32(a.v[h][e], b.v[h][e], acc, 0, 0, 0);
+  }
+  static constexpr int SUB = 4;                                      // MFMAs per piece
+};
+struct Bf16Wide {
+  typedef uint16_t T;
+  typedef bf16x8 V;
+  static constexpr int ES = 2, KPL = 1, XP = 1, YP = 3, EPP = 8;
+  static constexpr int STEP = 64;
+  struct Frag { V v[KPL]; };
+  static __device__ __forceinline__ void mma(floatx4& acc, const Frag& a, const Frag& b, int, int) {
+    acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a.v[0], b.v[0], acc, 0, 0, 0);
+  }
+  static constexpr int SUB = 1;
+};
+
+__device__ __forceinline__ float rows_widen(float v) { return v; }
+__device__ __forceinline__ float rows_widen(uint16_t v) { return __uint_as_float((uint32_t)v << 16); }
+
+// Channel of a lane's accumulator element: tiles 0 and 1 of a group of 32 channels give lane group lg the 8 consecutive
+// channels 8*lg .. 8*lg+7 (tile j: + 4*j + v), so that a lane stores whole 16-byte pieces.
+__device__ __forceinline__ int rows_channel(int pair, int lg) { return pair * 32 + lg * 8; }
+
+// y rows: YP terms of [ksm * 32] elements each.
+template <class F>
+__device__ __host__ __forceinline__ unsigned y_pitch(int ksm) { return (unsigned)ksm * 32 * F::ES * F::YP; }
+
+template <class F>
+__device__ __forceinline__ void store_y(unsigned char* row, int ch, int ksm, const float (&v)[8]);
+template <>
+__device__ __forceinline__ void store_y<Fp32>(unsigned char* row, int ch, int, const float (&v)[8]) {
+  floatx4* p = reinterpret_cast<floatx4*>(row + ch * 4);
+  p[0] = floatx4{v[0], v[1], v[2], v[3]};
+  p[1] = floatx4{v[4], v[5], v[6], v[7]};
+}
+template <>
+__device__ __forceinline__ void store_y<Bf16Wide>(unsigned char* row, int ch, int ksm, const float (&v)[8]) {
+  bf16x8 t[3];
+#pragma unroll
+  for (int i = 0; i < 8; ++i) {                  // v = t0 + t1 + t2: each term takes the next 8 significant bits
+    float r = v[i];
+#pragma unroll
+    for (int k = 0; k < 3; ++k) {
+      t[k][i] = (__bf16)r;
+      r = __builtin_isfinite((float)t[k][i]) ? r - (float)t[k][i] : 0.f;   // (an infinite y stays one)
+    }
+  }
+#pragma unroll
+  for (int k = 0; k < 3; ++k) *reinterpret_cast<bf16x8*>(row + (k * ksm * 32 + ch) * 2) = t[k];
+}
+
+// ---- the GEMM of one wave: NB blocks of 16 rows x one group of 32 channels ------------------------------
+// k-steps [s0, s1) of `total`.  Weights: fragments (step, tile) at wbase + (step * 2 + tile) * KPL KiB.  B rows by `rows`,
+// which yields the byte offset of each row block's lane for the k-step it is advanced to.
+template <class F, int NB, int PL, int D, class Rows>
+__device__ __forceinline__ void rows_gemm(floatx4 (&acc)[NB][2], rows_rsrc_t wrs, unsigned wbase, Rows& rows, int s0, int s1,
+                                          int lane) {
+  using Frag = typename F::Frag;
+  using V = typename F::V;
+  Frag a[D][2], b[D][NB][PL];
+  const unsigned lane16 = lane * 16;
+  auto load = [&](int d, int s) {
+    const unsigned so = wbase + (unsigned)s * (2 * F::KPL * 1024);
+#pragma unroll
+    for (int j = 0; j < 2; ++j)
+#pragma unroll
+      for (int h = 0; h < F::KPL; ++h) a[d][j].v[h] = rows_load16<V>(wrs, lane16 + (j * F::KPL + h) * 1024, so);
+    rows.template load<F, NB, PL>(b[d], s);
+  };
+  auto compute = [&](int d) {
+#pragma unroll
+    for (int p = 0; p < PL; ++p)
+#pragma unroll
+      for (int h = 0; h < F::KPL; ++h)
+#pragma unroll
+        for (int e = 0; e < F::SUB; ++e)
+#pragma unroll
+          for (int i = 0; i < NB; ++i)
+#pragma unroll
+            for (int j = 0; j < 2; ++j) F::mma(acc[i][j], a[d][j], b[d][i][p], h, e);
+  };
+#pragma unroll
+  for (int d = 0; d < D; ++d) load(d, min(s0 + d, s1 - 1));
+  int s = s0;
+  for (; s + D <= s1; s += D) {
+#pragma unroll
+    for (int d = 0; d < D; ++d) {
+      compute(d);
+      load(d, min(s + D + d, s1 - 1));           // (past the end the last step again: not used)
+      __builtin_amdgcn_sched_barrier(0);
+    }
+  }
+#pragma unroll
+  for (int d = 0; d < D - 1; ++d)
+    if (s + d < s1) compute(d);
+}
+
+// B rows of conv1: pixels of x.  VEC: 16-byte pieces (C and the pointers allow them), else element by element; the
+// pieces past channel C are zeros (the next pixel's values, which may be anything, must not meet the zero weights).
+template <bool VEC>
+struct XRows {
+  rows_rsrc_t rs;
+  unsigned off[4];         // byte offset of the lane's row in the chunk, kOutOfRange for rows that do not exist
+  int C, lg;
+  template <class F, int NB, int PL>
+  __device__ __forceinline__ void load(typename F::Frag (&b)[NB][PL], int s) {
+    static_assert(PL == 1, "x is one term");
+#pragma unroll
+    for (int h = 0; h < F::KPL; ++h) {
+      const int k = s * 32 + h * 16 * (F::KPL - 1) + lg * F::EPP;    // first channel of the lane's piece
+#pragma unroll
+      for (int i = 0; i < NB; ++i) {
+        if constexpr (VEC) {
+          b[i][0].v[h] = rows_load16<typename F::V>(rs, k < C ? off[i] + (unsigned)k * F::ES : kOutOfRange, 0);
+        } else {
+#pragma unroll
+          for (int e = 0; e < F::EPP; ++e) {
+            const unsigned o = k + e < C ? off[i] + (unsigned)(k + e) * F::ES : kOutOfRange;
+            if constexpr (F::ES == 4)
+              b[i][0].v[h][e] = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(rs, (int)o, 0, 0));
+            else
+              b[i][0].v[h][e] = __builtin_bit_cast(__bf16, (uint16_t)__builtin_amdgcn_raw_buffer_load_b16(rs, (int)o, 0, 0));
+          }
+        }
+      }
+    }
+  }
+};
+
+// B rows of conv3: the row's own y2; of conv2: y1 of the pixel that tap s / ksm names, zeros outside the image.
+template <bool TAPS>
+struct YRows {
+  rows_rsrc_t rs;
+  unsigned off[4];         // TAPS: of the current tap
+  unsigned pitch;
+  int ksm, lg;
+  int px[4], h[4], w[4], H, W;
+  int at, in_tap, tap;     // the k-step last loaded = tap * ksm + in_tap (k-steps are asked for in order)
+  __device__ __forceinline__ void set_tap(int nb) {
+    const int dy = tap / 3 - 1, dx = tap - tap / 3 * 3 - 1;
+#pragma unroll
+    for (int i = 0; i < 4; ++i)
+      if (i < nb) {
+        const bool in = px[i] >= 0 && (unsigned)(h[i] + dy) < (unsigned)H && (unsigned)(w[i] + dx) < (unsigned)W;
+        off[i] = in ? (unsigned)(px[i] + dy * W + dx) * pitch + lg * 16 : kOutOfRange;
+      }
+  }
+  __device__ __forceinline__ void seek(int s, int nb) {
+    at = s;
+    tap = s / ksm;
+    in_tap = s - tap * ksm;
+    set_tap(nb);
+  }
+  template <class F, int NB, int PL>
+  __device__ __forceinline__ void load(typename F::Frag (&b)[NB][PL], int s) {
+    int so = s;
+    if constexpr (TAPS) {
+      if (s != at) {
+        at = s;
+        if (++in_tap == ksm) {
+          in_tap = 0;
+          ++tap;
+          set_tap(NB);
+        }
+      }
+      so = in_tap;
+    }
+#pragma unroll
+    for (int p = 0; p < PL; ++p)
+#pragma unroll
+      for (int i = 0; i < NB; ++i)
+#pragma unroll
+        for (int h2 = 0; h2 < F::KPL; ++h2)
+          b[i][p].v[h2] = rows_load16<typename F::V>(rs, off[i], (unsigned)(so * F::STEP + p * ksm * F::STEP + h2 * 64));
+  }
+};
+
+// Biases of a lane's 8 channels (zeros past n), as the accumulators' start.
+template <int NB>
+__device__ __forceinline__ void start_at_bias(floatx4 (&acc)[NB][2], const float* bias, int n, int ch, bool mine) {
+  const rows_rsrc_t rs = rows_rsrc(bias, (unsigned)n * 4);
+#pragma unroll
+  for (int j = 0; j < 2; ++j)
+#pragma unroll
+    for (int v = 0; v < 4; ++v) {
+      const float b = mine ? __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(rs, (ch + j * 4 + v) * 4, 0, 0)) : 0.f;
+#pragma unroll
+      for (int i = 0; i < NB; ++i) acc[i][j][v] = b;
+    }
+}
+
+// Adds the partial sums of the KS waves that share a tile, in the order of the waves; wave k is left with the row
+// blocks i = k, k + KS, ..
+template <int NB, int KS>
+__device__ __forceinline__ void reduce_over_waves(floatx4 (&acc)[NB][2], ROWS_LDS float* part, int wave, int lane) {
+  if constexpr (KS > 1) {
+#pragma unroll
+    for (int i = 0; i < NB; ++i)
+#pragma unroll
+      for (int j = 0; j < 2; ++j)
+        *reinterpret_cast<ROWS_LDS floatx4*>(part + (((wave * NB + i) * 2 + j) * 64 + lane) * 4) = acc[i][j];
+    __syncthreads();
+    const int w0 = wave / KS * KS;
+#pragma unroll
+    for (int i = 0; i < NB; ++i)
+      if (i % KS == wave % KS)
+#pragma unroll
+        for (int j = 0; j < 2; ++j) {
+          floatx4 t = *reinterpret_cast<ROWS_LDS floatx4*>(part + (((w0 * NB + i) * 2 + j) * 64 + lane) * 4);
+#pragma unroll
+          for (int k = 1; k < KS; ++k)
+            t += *reinterpret_cast<ROWS_LDS floatx4*>(part + ((((w0 + k) * NB + i) * 2 + j) * 64 + lane) * 4);
+          acc[i][j] = t;
+        }
+    __syncthreads();
+  }
+}
+
+// Workgroup -> (row tile, channel slice): the slices of a row tile sit on one XCD (workgroup b runs on XCD b mod 8), so
+// the rows they share are fetched into one L2.
+__device__ __forceinline__ void rows_unit(int nsl, int& unit, int& slice) {
+  const int xcd = (int)blockIdx.x & 7, j = (int)blockIdx.x >> 3;
+  unit = (j / nsl) * 8 + xcd;
+  slice = j % nsl;
+}
+inline int rows_grid(int units, int nsl) { return (units + 7) / 8 * 8 * nsl; }
+
+// Calls f(integral_constant<n>) for the run-time n in [1, HI] (2 and 3 blocks share an instantiation of 4's size class).
+template <int HI, class Fn>
+__device__ __forceinline__ void rows_blocks(int n, Fn&& f) {
+  if constexpr (HI == 1) {
+    f(std::integral_constant<int, 1>{});
+  } else {
+    if (n <= HI / 2) rows_blocks<HI / 2>(n, static_cast<Fn&&>(f));
+    else f(std::integral_constant<int, HI>{});
+  }
+}
+
+// ---- conv1 -----------------------------------------------------------------------------------------------
+template <class F, bool VEC, int NB, int KS>
+__global__ __launch_bounds__(kRowsThreads, 2) void rows_conv1_kernel(RowsArgs a, int nsl, const typename F::T* __restrict__ x,
+                                                                     const unsigned char* __restrict__ wp,
+                                                                     const float* __restrict__ b1,
+                                                                     unsigned char* __restrict__ y1) {
+  __shared__ int rowpx[NB * 16];
+  __shared__ __attribute__((aligned(16))) float part[KS > 1 ? 4 * NB * 2 * 64 * 4 : 4];
+  const int tid = threadIdx.x, lane = tid & 63, l16 = lane & 15, lg = lane >> 4, wave = rows_uni(tid >> 6);
+  int unit, slice;
+  rows_unit(nsl, unit, slice);
+  const int p0 = unit * NB * 16;
+  if (p0 >= a.npx) return;
+  // the needed pixels of this run, ascending
+  static_assert(NB * 16 <= 64, "one ballot");
+  const bool on = lane < NB * 16 && p0 + lane < a.npx && (!a.need || a.need[p0 + lane] != 0);
+  const unsigned long long b = __ballot(on);
+  const int U = __popcll(b);
+  if (U == 0) return;                            // uniform over the workgroup
+  if (wave == 0) {
+    if (on) rowpx[__popcll(b & ((1ull << lane) - 1ull))] = p0 + lane;
+    if (lane < NB * 16 && lane >= U) rowpx[lane] = -1;
+  }
+  __syncthreads();
+  constexpr int WC = 4 / KS;
+  rows_blocks<NB>((U + 15) >> 4, [&](auto nbc) {
+    constexpr int N = decltype(nbc)::value;
+    XRows<VEC> rows;
+    rows.rs = rows_rsrc(x + (size_t)a.px0 * a.g.C, (unsigned)a.npx * a.g.C * F::ES);
+    rows.C = a.g.C;
+    rows.lg = lg;
+#pragma unroll
+    for (int i = 0; i < N; ++i) {
+      const int px = rowpx[i * 16 + l16];
+      rows.off[i] = px >= 0 ? (unsigned)px * a.g.C * F::ES : kOutOfRange;
+    }
+    const int kq = (a.ks1 + KS - 1) / KS, s0 = min(wave % KS * kq, a.ks1), s1 = min(s0 + kq, a.ks1);
+    for (int pair = slice * WC + wave / KS; pair < (KS > 1 ? (a.pairs1 + WC - 1) / WC * WC : a.pairs1); pair += nsl * WC) {
+      floatx4 acc[N][2];
+      start_at_bias<N>(acc, b1, a.g.M, rows_channel(pair, lg), wave % KS == 0);
+      if (s0 < s1 && pair < a.pairs1)
+        rows_gemm<F, N, F::XP, 2>(acc, rows_rsrc(wp, a.w1_bytes), (unsigned)(pair * a.ks1) * (2 * F::KPL * 1024), rows, s0, s1, lane);
+      reduce_over_waves<N, KS>(acc, (ROWS_LDS float*)part, wave, lane);
+#pragma unroll
+      for (int i = 0; i < N; ++i) {
+        const int px = rowpx[i * 16 + l16];
+        if ((KS == 1 || i % KS == wave % KS) && pair < a.pairs1 && px >= 0) {
+          float v[8];
+#pragma unroll
+          for (int u = 0; u < 8; ++u) v[u] = fmaxf(acc[i][u / 4][u % 4], 0.f);
+          store_y<F>(y1 + (size_t)px * y_pitch<F>(a.ksm), rows_channel(pair, lg), a.ksm, v);
+        }
+      }
+    }
+  });
+}
+
+// ---- conv2 -----------------------------------------------------------------------------------------------
+template <class F, int NB, int KS>
+__global__ __launch_bounds__(kRowsThreads, 2) void rows_conv2_kernel(RowsArgs a, int nsl, const unsigned char* __restrict__ wp,
+                                                                     const float* __restrict__ b2,
+                                                                     const unsigned char* __restrict__ y1,
+                                                                     unsigned char* __restrict__ y2) {
+  __shared__ __attribute__((aligned(16))) float part[KS > 1 ? 4 * NB * 2 * 64 * 4 : 4];
+  const int tid = threadIdx.x, lane = tid & 63, l16 = lane & 15, lg = lane >> 4, wave = rows_uni(tid >> 6);
+  int unit, slice;
+  rows_unit(nsl, unit, slice);
+  const int nrows = rows_active(a), r0 = unit * NB * 16;
+  if (r0 >= nrows) return;
+  YRows<true> rows;
+  const unsigned pitch = y_pitch<F>(a.ksm);
+  bool any = false;
+#pragma unroll
+  for (int i = 0; i < NB; ++i) {
+    const RowPixel p = row_pixel(a, r0 + i * 16 + l16, nrows);
+    rows.px[i] = p.px < 0 ? -1 : p.px - a.px0;
+    rows.h[i] = p.h;
+    rows.w[i] = p.w;
+    any |= p.px >= 0;
+  }
+  if (!__any(any)) return;                       // (the same rows in every wave)
+  rows.rs = rows_rsrc(y1, (unsigned)a.npx * pitch);
+  rows.pitch = pitch;
+  rows.ksm = a.ksm;
+  rows.lg = lg;
+  rows.H = a.g.H;
+  rows.W = a.g.W;
+  constexpr int WC = 4 / KS;
+  const int total = 9 * a.ksm, kq = (total + KS - 1) / KS, s0 = min(wave % KS * kq, total), s1 = min(s0 + kq, total);
+  for (int pair = slice * WC + wave / KS; pair < (KS > 1 ? (a.pairs1 + WC - 1) / WC * WC : a.pairs1); pair += nsl * WC) {
+    floatx4 acc[NB][2];
+    start_at_bias<NB>(acc, b2, a.g.M, rows_channel(pair, lg), wave % KS == 0);
+    rows.seek(min(s0, total - 1), NB);
+    if (s0 < s1 && pair < a.pairs1)
+      rows_gemm<F, NB, F::YP, 2>(acc, rows_rsrc(wp, a.w2_bytes), (unsigned)(pair * total) * (2 * F::KPL * 1024), rows, s0, s1, lane);
+    reduce_over_waves<NB, KS>(acc, (ROWS_LDS float*)part, wave, lane);
+#pragma unroll
+    for (int i = 0; i < NB; ++i)
+      if ((KS == 1 || i % KS == wave % KS) && pair < a.pairs1 && rows.px[i] >= 0) {
+        float v[8];
+#pragma unroll
+        for (int u = 0; u < 8; ++u) v[u] = fmaxf(acc[i][u / 4][u % 4], 0.f);
+        store_y<F>(y2 + (size_t)rows.px[i] * pitch, rows_channel(pair, lg), a.ksm, v);
+      }
+  }
+}
+
+// ---- conv3 + residual ------------------------------------------------------------------------------------
+template <class F, bool VEC, int NB, int KS>
+__global__ __launch_bounds__(kRowsThreads, 2) void rows_conv3_kernel(RowsArgs a, int nsl, const typename F::T* __restrict__ x,
+                                                                     const unsigned char* __restrict__ wp,
+                                                                     const float* __restrict__ b3,
+                                                                     const unsigned char* __restrict__ y2,
+                                                                     typename F::T* __restrict__ out, int post_relu) {
+  __shared__ __attribute__((aligned(16))) float part[KS > 1 ? 4 * NB * 2 * 64 * 4 : 4];
+  typedef typename F::T T;
+  const int tid = threadIdx.x, lane = tid & 63, l16 = lane & 15, lg = lane >> 4, wave = rows_uni(tid >> 6);
+  int unit, slice;
+  rows_unit(nsl, unit, slice);
+  const int nrows = rows_active(a), r0 = unit * NB * 16;
+  if (r0 >= nrows) return;
+  YRows<false> rows;
+  const unsigned pitch = y_pitch<F>(a.ksm);
+  int px[NB];
+  bool any = false;
+#pragma unroll
+  for (int i = 0; i < NB; ++i) {
+    px[i] = row_pixel(a, r0 + i * 16 + l16, nrows).px;
+    rows.off[i] = px[i] < 0 ? kOutOfRange : (unsigned)(px[i] - a.px0) * pitch + lg * 16;
+    any |= px[i] >= 0;
+  }
+  if (!__any(any)) return;
+  rows.rs = rows_rsrc(y2, (unsigned)a.npx * pitch);
+  rows.ksm = a.ksm;
+  rows.lg = lg;
+  constexpr int WC = 4 / KS;
+  const int C = a.g.C, kq = (a.ksm + KS - 1) / KS, s0 = min(wave % KS * kq, a.ksm), s1 = min(s0 + kq, a.ksm);
+  for (int pair = slice * WC + wave / KS; pair < (KS > 1 ? (a.pairs3 + WC - 1) / WC * WC : a.pairs3); pair += nsl * WC) {
+    floatx4 acc[NB][2];
+    const int ch = rows_channel(pair, lg);
+    start_at_bias<NB>(acc, b3, C, ch, wave % KS == 0);
+    if (s0 < s1 && pair < a.pairs3)
+      rows_gemm<F, NB, F::YP, 2>(acc, rows_rsrc(wp, a.w3_bytes), (unsigned)(pair * a.ksm) * (2 * F::KPL * 1024), rows, s0, s1, lane);
+    reduce_over_waves<NB, KS>(acc, (ROWS_LDS float*)part, wave, lane);
+#pragma unroll
+    for (int i = 0; i < NB; ++i)
+      if ((KS == 1 || i % KS == wave % KS) && px[i] >= 0 && ch < C) {
+        const T* xp = x + (size_t)px[i] * C + ch;
+        T* op = out + (size_t)px[i] * C + ch;
+        auto result = [&](int u, T xv) {
+          float r = rows_widen(xv) + acc[i][u / 4][u % 4];
+          if (post_relu) r = fmaxf(r, 0.f);
+          if constexpr (F::ES == 4) return r;
+          else return __builtin_bit_cast(uint16_t, (__bf16)r);
+        };
+        if constexpr (VEC) {                     // (C is then a whole number of the lane's 16-byte pieces)
+          typedef T Piece __attribute__((ext_vector_type(16 / F::ES)));
+          constexpr int E = 16 / F::ES;
+#pragma unroll
+          for (int q = 0; q < 8 / E; ++q)
+            if (q == 0 || ch + q * E < C) {
+              const Piece xv = reinterpret_cast<const Piece*>(xp)[q];
+              Piece o;
+#pragma unroll
+              for (int u = 0; u < E; ++u) o[u] = result(q * E + u, xv[u]);
+              reinterpret_cast<Piece*>(op)[q] = o;
+            }
+        } else {
+#pragma unroll
+          for (int u = 0; u < 8; ++u)
+            if (ch + u < C) op[u] = result(u, xp[u]);
+        }
+      }
+  }
+}
+
+// ---- plan ------------------------------------------------------------------------------------------------
+constexpr int kNeedPixels = 16384;                // pixels whose bytes one workgroup of the plan makes (in LDS)
+
+// Blocks [0, pack_blocks): the weight fragments, one 8-element lane share per thread.  The others: the need
+// bytes of kNeedPixels pixels each, by a scan of the list (it may be in any order).
+template <class F>
+__global__ __launch_bounds__(kRowsThreads) void rows_plan_kernel(RowsArgs a, int pack_blocks, const typename F::T* __restrict__ W1,
+                                                                 const typename F::T* __restrict__ W2,
+                                                                 const typename F::T* __restrict__ W3,
+                                                                 unsigned char* __restrict__ wp, uint8_t* __restrict__ need) {
+  typedef typename F::T T;
+  const int tid = threadIdx.x, C = a.g.C, M = a.g.M;
+  if ((int)blockIdx.x < pack_blocks) {
+    const int n1 = a.pairs1 * a.ks1, n2 = a.pairs1 * 9 * a.ksm, n3 = a.pairs3 * a.ksm;   // k-steps of 2 tiles
+    const int t = (int)blockIdx.x * kRowsThreads + tid;
+    const int lane = t & 63, j = (t >> 6) & 1;
+    int f = t >> 7;
+    if (f >= n1 + n2 + n3) return;
+    const int i = lane & 15, lg = lane >> 4;
+    unsigned char* dst = wp + (size_t)(t >> 6) * (F::KPL * 1024) + lane * 16;
+    const T* src;
+    int rows, kmax, pair, k0;
+    if (f < n1) {
+      pair = f / a.ks1;
+      k0 = (f - pair * a.ks1) * 32;
+      src = W1; rows = M; kmax = C;
+    } else if (f < n1 + n2) {
+      f -= n1;
+      pair = f / (9 * a.ksm);
+      const int s = f - pair * 9 * a.ksm, tap = s / a.ksm;
+      k0 = (s - tap * a.ksm) * 32;
+      src = W2 + (size_t)tap * M; rows = M; kmax = M;
+    } else {
+      f -= n1 + n2;
+      pair = f / a.ksm;
+      k0 = (f - pair * a.ksm) * 32;
+      src = W3; rows = C; kmax = M;
+    }
+    const size_t pitch = src == W1 ? (size_t)C : src == W3 ? (size_t)M : (size_t)9 * M;
+    const int ch = rows_channel(pair, i >> 2) + j * 4 + (i & 3);
+    const T* row = src + (size_t)ch * pitch;
+#pragma unroll
+    for (int h = 0; h < F::KPL; ++h) {
+      T v[F::EPP];
+#pragma unroll
+      for (int e = 0; e < F::EPP; ++e) {
+        const int k = k0 + h * 16 * (F::KPL - 1) + lg * F::EPP + e;
+        v[e] = ch < rows && k < kmax ? row[k] : T(0);
+      }
+      typename F::V o;
+      __builtin_memcpy(&o, v, 16);
+      *reinterpret_cast<typename F::V*>(dst + h * 1024) = o;
+    }
+    return;
+  }
+  __shared__ __attribute__((aligned(16))) uint8_t flag[kNeedPixels];
+  const int q0 = ((int)blockIdx.x - pack_blocks) * kNeedPixels, nq = min(kNeedPixels, a.npx - q0);
+  for (int i = tid; i < kNeedPixels / 16; i += kRowsThreads) reinterpret_cast<uint4*>(flag)[i] = uint4{0, 0, 0, 0};
+  __syncthreads();
+  const int nact = rows_uni(min(*a.count, a.g.P)), S = a.g.S, H = a.g.H, W = a.g.W, cpi = a.g.G * a.g.GW;
+  for (int e = tid; e < nact; e += kRowsThreads) {
+    const int cell = a.idx[e];
+    if ((unsigned)cell >= (unsigned)a.g.P) continue;
+    const int n = cell / cpi, rem = cell - n * cpi, gy = rem / a.g.GW, gx = rem - gy * a.g.GW;
+    const int h0 = max(gy * S - 1, 0), h1 = min(gy * S + S, H - 1), w0 = max(gx * S - 1, 0), w1 = min(gx * S + S, W - 1);
+    const int base = n * H * W - a.px0 - q0;     // of the image, relative to this workgroup's pixels
+    if (base + h1 * W + w1 < 0 || base + h0 * W + w0 >= nq) continue;
+    for (int h = h0; h <= h1; ++h)
+      for (int w = w0; w <= w1; ++w)
+        if ((unsigned)(base + h * W + w) < (unsigned)nq) flag[base + h * W + w] = 1;
+  }
+  __syncthreads();
+  // (need has room for whole workgroups' pixels)
+  for (int i = tid; i * 16 < nq; i += kRowsThreads) reinterpret_cast<uint4*>(need + q0)[i] = reinterpret_cast<uint4*>(flag)[i];
+}
+
+// ---- host ------------------------------------------------------------------------------------------------
+// Bytes a chunk of images may take for y1 and y2: a larger batch runs chunk after chunk (at 256 MiB every ResNet-101
+// stage at batch 128 is one chunk in fp32, and a chunk is thousands of row tiles, so nothing is lost by the cut).
+constexpr size_t kRowsYBytes = (size_t)256 << 20;
+
+struct RowsLayout {
+  int images;                       // per chunk
+  size_t w1, w2, w3, need, y, total; // bytes: packed weights, need bytes of a chunk, y1 (= y2) of a chunk
+};
+inline size_t rows_round(size_t v) { return (v + 255) / 256 * 256; }
+
+// false: even one image does not fit (or exceeds the 32-bit offsets of the loads).
+template <class F>
+bool rows_layout(const Geom& g, RowsLayout& l) {
+  const size_t pairs1 = (g.M + 31) / 32, pairs3 = (g.C + 31) / 32, ks1 = pairs3, ksm = pairs1;
+  const size_t hw = (size_t)g.H * g.W, ypx = y_pitch<F>((int)ksm), xpx = (size_t)g.C * F::ES;
+  l.w1 = pairs1 * ks1 * 2 * F::KPL * 1024;
+  l.w2 = pairs1 * 9 * ksm * 2 * F::KPL * 1024;
+  l.w3 = pairs3 * ksm * 2 * F::KPL * 1024;
+  const size_t lim = (size_t)1 << 31;            // every descriptor stays below kOutOfRange
+  if (hw * 2 * ypx > kRowsYBytes || hw * xpx >= lim || l.w1 >= lim || l.w2 >= lim || l.w3 >= lim) return false;
+  size_t n = kRowsYBytes / (hw * 2 * ypx), nx = (lim - 1) / (hw * xpx);
+  if (n > nx) n = nx;
+  if (n > (size_t)g.N) n = (size_t)g.N;
+  if (n == 0) return false;
+  l.images = (int)n;
+  l.need = (n * hw + kNeedPixels - 1) / kNeedPixels * kNeedPixels;
+  l.y = rows_round(n * hw * ypx);
+  l.total = rows_round(l.w1) + rows_round(l.w2) + rows_round(l.w3) + l.need + 2 * l.y;
+  return true;
+}
+
+}  // namespace
+}  // namespace lasnet
