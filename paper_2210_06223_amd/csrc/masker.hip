@@ -43,13 +43,11 @@ __device__ inline void fma_piece(double& acc, const uint4& q, const float4& w0, 
   acc = fma((double)w0.w, (double)__uint_as_float(q.w), acc);
 }
 
-// One wave per cell.  A patch row is one contiguous segment of S*C elements; a wave reads it
-// in groups of four 1 KiB pieces (16 bytes per lane each) that are all requested before the
-// first one is used, so that enough bytes are in flight to keep HBM busy.
-// VEC: 16-byte loads (needs C*sizeof(T) % 16 == 0 and aligned bases).  HOIST: the segment is
-// exactly one group (S*C*sizeof(T) == 4 KiB, true for every ResNet stage in bf16), so a lane
-// meets the same channels in every row and keeps their masker weights in registers.
-template <typename T, bool VEC, bool HOIST>
+// One wave per cell, for what the kernels below do not take: cells beyond 128 KiB and maps that 16-byte loads cannot
+// read.  A patch row is one contiguous segment of S*C elements; a wave reads it in groups of four 1 KiB pieces (16
+// bytes per lane each) that are all requested before the first one is used.
+// VEC: 16-byte loads (needs C*sizeof(T) % 16 == 0 and aligned bases).
+template <typename T, bool VEC>
 __global__ __launch_bounds__(kMaskerThreads) void masker_logit_kernel(
     const T* __restrict__ x, const float* __restrict__ Wm, double bm, double thr, int S, int H,
     int W, int C, int G, int GW, int P, uint8_t* __restrict__ mask, double* __restrict__ logits,
@@ -67,66 +65,30 @@ __global__ __launch_bounds__(kMaskerThreads) void masker_logit_kernel(
   if constexpr (VEC) {
     constexpr int V = 16 / (int)sizeof(T);    // elements per 16-byte piece
     constexpr int GRP = 4 * 64 * V;           // elements per group of four pieces
-    if constexpr (HOIST) {
-      float4 w[4][2];
-#pragma unroll
-      for (int u = 0; u < 4; ++u) {
-        const int c = ((lane + 64 * u) * V) % C;
-        w[u][0] = *reinterpret_cast<const float4*>(Wm + c);
-        w[u][1] = V == 8 ? *reinterpret_cast<const float4*>(Wm + c + 4) : float4{0.f, 0.f, 0.f, 0.f};
-      }
-      int i = 0;
-      for (; i + 2 <= S; i += 2) {            // two rows = eight pieces in flight per lane
-        const T* row = cell0 + i * pitch;
-        uint4 q[2][4];
-#pragma unroll
-        for (int r = 0; r < 2; ++r)
-#pragma unroll
-          for (int u = 0; u < 4; ++u) q[r][u] = *reinterpret_cast<const uint4*>(row + r * pitch + (lane + 64 * u) * V);
-#pragma unroll
-        for (int r = 0; r < 2; ++r) {
-          fma_piece(acc0, q[r][0], w[0][0], w[0][1], T{});
-          fma_piece(acc1, q[r][1], w[1][0], w[1][1], T{});
-          fma_piece(acc2, q[r][2], w[2][0], w[2][1], T{});
-          fma_piece(acc3, q[r][3], w[3][0], w[3][1], T{});
-        }
-      }
-      for (; i < S; ++i) {
-        const T* row = cell0 + i * pitch;
+    for (int i = 0; i < S; ++i) {
+      const T* row = cell0 + i * pitch;
+      int e0 = 0;
+      for (; e0 + GRP <= seg; e0 += GRP) {
         uint4 q[4];
+        float4 w[4][2];
 #pragma unroll
-        for (int u = 0; u < 4; ++u) q[u] = *reinterpret_cast<const uint4*>(row + (lane + 64 * u) * V);
+        for (int u = 0; u < 4; ++u) {
+          const int e = e0 + (lane + 64 * u) * V, c = e % C;
+          q[u] = *reinterpret_cast<const uint4*>(row + e);
+          w[u][0] = *reinterpret_cast<const float4*>(Wm + c);
+          w[u][1] = V == 8 ? *reinterpret_cast<const float4*>(Wm + c + 4) : float4{0.f, 0.f, 0.f, 0.f};
+        }
         fma_piece(acc0, q[0], w[0][0], w[0][1], T{});
         fma_piece(acc1, q[1], w[1][0], w[1][1], T{});
         fma_piece(acc2, q[2], w[2][0], w[2][1], T{});
         fma_piece(acc3, q[3], w[3][0], w[3][1], T{});
       }
-    } else {
-      for (int i = 0; i < S; ++i) {
-        const T* row = cell0 + i * pitch;
-        int e0 = 0;
-        for (; e0 + GRP <= seg; e0 += GRP) {
-          uint4 q[4];
-          float4 w[4][2];
-#pragma unroll
-          for (int u = 0; u < 4; ++u) {
-            const int e = e0 + (lane + 64 * u) * V, c = e % C;
-            q[u] = *reinterpret_cast<const uint4*>(row + e);
-            w[u][0] = *reinterpret_cast<const float4*>(Wm + c);
-            w[u][1] = V == 8 ? *reinterpret_cast<const float4*>(Wm + c + 4) : float4{0.f, 0.f, 0.f, 0.f};
-          }
-          fma_piece(acc0, q[0], w[0][0], w[0][1], T{});
-          fma_piece(acc1, q[1], w[1][0], w[1][1], T{});
-          fma_piece(acc2, q[2], w[2][0], w[2][1], T{});
-          fma_piece(acc3, q[3], w[3][0], w[3][1], T{});
-        }
-        for (int e = e0 + lane * V; e < seg; e += 64 * V) {      // pieces left over
-          const int c = e % C;
-          const uint4 q = *reinterpret_cast<const uint4*>(row + e);
-          const float4 w0 = *reinterpret_cast<const float4*>(Wm + c);
-          const float4 w1 = V == 8 ? *reinterpret_cast<const float4*>(Wm + c + 4) : float4{0.f, 0.f, 0.f, 0.f};
-          fma_piece(acc0, q, w0, w1, T{});
-        }
+      for (int e = e0 + lane * V; e < seg; e += 64 * V) {      // pieces left over
+        const int c = e % C;
+        const uint4 q = *reinterpret_cast<const uint4*>(row + e);
+        const float4 w0 = *reinterpret_cast<const float4*>(Wm + c);
+        const float4 w1 = V == 8 ? *reinterpret_cast<const float4*>(Wm + c + 4) : float4{0.f, 0.f, 0.f, 0.f};
+        fma_piece(acc0, q, w0, w1, T{});
       }
     }
   } else {
@@ -158,20 +120,6 @@ __global__ __launch_bounds__(kMaskerThreads) void masker_logit_kernel(
         const T* row = cell0 + i * pitch;
         T* orow = out0 + i * pitch;
         int e = lane * V;
-        if (HOIST && i + 2 <= S) {            // two whole rows = eight pieces in flight per lane
-          uint4 q[2][4];
-#pragma unroll
-          for (int r = 0; r < 2; ++r)
-#pragma unroll
-            for (int u = 0; u < 4; ++u) q[r][u] = *reinterpret_cast<const uint4*>(row + r * pitch + e + u * 64 * V);
-#pragma unroll
-          for (int r = 0; r < 2; ++r)
-#pragma unroll
-            for (int u = 0; u < 4; ++u)
-              store_nt16(orow + r * pitch + e + u * 64 * V, q[r][u]);
-          ++i;
-          continue;
-        }
         for (; e + GRP - 64 * V < seg; e += GRP) {
           uint4 q[4];
 #pragma unroll
@@ -253,35 +201,123 @@ __global__ __launch_bounds__(kMaskerThreads) void masker_rows_kernel(
   }
 }
 
-// Ordered stream compaction by one workgroup.  A thread takes V consecutive cells (one 8-byte
-// load when V = 8), a shuffle scan over the per-thread counts gives each thread its rank
-// inside its wave, a scan over the 16 wave totals its rank inside the 1024*V-cell round, and
-// a running base its rank overall.  Integer work only: the list is the ascending sequence
-// of active cell ids whatever the timing.
-constexpr int kCompactThreads = 1024;
+// A cell of any size, spread over TPC threads: piece q (16 bytes) of the cell goes to thread q % TPC, at most UP pieces
+// a thread, all requested before the first is used and kept in registers for the pass-through.  Latency-bound
+// when cells are few and large: at 14x14x1024, S=7, 96 cells of 100 KB, one wave per cell took 31 us to read 9.6 MB
+// (at most 8 KiB in flight per wave); a 1024-thread workgroup per cell holds the whole cell in flight: 6.9 us.
+// Small cells gain from the registers (no second read for the pass-through): 56x56x256, S=4, batch 256: 132 -> 114 us, 5.8 TB/s.
+// The divisions of q by the pieces of a patch row and of a row piece by those of a pixel are multiplications:
+// floor(q * ceil(2^32 / d) / 2^32) is exact for q * d < 2^32.
+struct CellPieces {
+  int np, pr, pc;             // pieces of a cell, of a patch row, of a pixel
+  unsigned m_pr, m_pc;        // ceil(2^32 / .) of the latter two (0 for a divisor of 1)
+};
+__device__ __forceinline__ int div_by(int q, unsigned m) { return m ? (int)(((unsigned long long)(unsigned)q * m) >> 32) : q; }
 
-template <int V>
+constexpr int kCellPieces = 8;                          // (UP)
+
+template <typename T, int TPC, int UP>
+__global__ __launch_bounds__(TPC < kMaskerThreads ? kMaskerThreads : TPC) void masker_cells_kernel(
+    const T* __restrict__ x, const float* __restrict__ Wm, double bm, double thr, int S, int H, int W, int C, int G, int GW,
+    int P, CellPieces cp, uint8_t* __restrict__ mask, double* __restrict__ logits, T* __restrict__ pass_out) {
+  constexpr int V = 16 / (int)sizeof(T), NT = TPC < kMaskerThreads ? kMaskerThreads : TPC;
+  constexpr int CPB = NT / TPC, WPC = TPC / 64;           // cells per workgroup, waves per cell
+  __shared__ double part[NT / 64];
+  const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
+  const int t = threadIdx.x % TPC, cell = blockIdx.x * CPB + (int)threadIdx.x / TPC;
+  const bool valid = cell < P;
+  const int cc = valid ? cell : 0;
+  const int n = cc / (G * GW), rem = cc - n * (G * GW), gy = rem / GW, gx = rem - gy * GW;
+  const size_t cell0 = ((size_t)(n * H + gy * S) * W + (size_t)gx * S) * C, pitch = (size_t)W * C;
+  uint4 q[UP];
+  size_t off[UP];
+  int ch[UP];
+#pragma unroll
+  for (int u = 0; u < UP; ++u) {
+    const int k = t + u * TPC;
+    if (k < cp.np) {
+      const int row = div_by(k, cp.m_pr), e = k - row * cp.pr;
+      off[u] = cell0 + row * pitch + (size_t)e * V;
+      ch[u] = (e - div_by(e, cp.m_pc) * cp.pc) * V;
+      q[u] = *reinterpret_cast<const uint4*>(x + off[u]);
+    }
+  }
+  double acc[2] = {0.0, 0.0};
+#pragma unroll
+  for (int u = 0; u < UP; ++u)
+    if (t + u * TPC < cp.np) {
+      const float4 w0 = *reinterpret_cast<const float4*>(Wm + ch[u]);
+      const float4 w1 = V == 8 ? *reinterpret_cast<const float4*>(Wm + ch[u] + 4) : float4{0.f, 0.f, 0.f, 0.f};
+      fma_piece(acc[u & 1], q[u], w0, w1, T{});
+    }
+  double tot = wave_sum(acc[0] + acc[1]);
+  if constexpr (WPC > 1) {
+    if (lane == 0) part[wave] = tot;
+    __syncthreads();
+    tot = 0.0;
+#pragma unroll
+    for (int k = 0; k < WPC; ++k) tot += part[wave / WPC * WPC + k];
+  }
+  const double logit = bm + tot / (double)(S * S);
+  const bool on = logit > thr;
+  if (!valid) return;
+  if (t == 0) {
+    if (logits) logits[cell] = logit;
+    if (mask) mask[cell] = on ? 1 : 0;
+  }
+  if (pass_out != nullptr && !on) {
+#pragma unroll
+    for (int u = 0; u < UP; ++u)
+      if (t + u * TPC < cp.np) store_nt16(pass_out + off[u], q[u]);
+  }
+}
+
+// Ordered stream compaction.  A workgroup takes a run of consecutive cells and counts the set bytes of all cells
+// before it by itself (16 per load and thread: the mask is a few KB to a few hundred, in L2), so that no
+// workgroup waits for another; within its run a shuffle scan and the four wave totals give every cell its
+// place.  Integer work only: the list is the ascending sequence of active cell ids whatever the timing.
+// One 1024-thread workgroup for the whole mask took 2.4 us for 49 cells, 4.8 for 6272 and 13.6 for 50176; this 2.1, 3.8
+// and 5.6.
+constexpr int kCompactThreads = 256;
+constexpr int kCompactRound = kCompactThreads * 4;      // cells a workgroup places per round: four bytes per thread
+constexpr int kCompactBlocks = 64;                      // most workgroups: bounds the bytes counted again (32 * P)
+
+template <bool ALIGNED>
 __global__ __launch_bounds__(kCompactThreads) void compact_kernel(
-    const uint8_t* __restrict__ mask, int P, int32_t* __restrict__ idx,
-    int32_t* __restrict__ count) {
+    const uint8_t* __restrict__ mask, int P, int run, int32_t* __restrict__ idx, int32_t* __restrict__ count) {
   __shared__ int wave_tot[kCompactThreads / 64];
   const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
-  int base = 0;                                // identical in every thread
-  for (int start = 0; start < P; start += kCompactThreads * V) {
-    const int i0 = start + tid * V;
-    unsigned on = 0;                           // bit b: cell i0 + b is active
-    if constexpr (V == 8) {
-      if (i0 + 8 <= P) {
-        const unsigned long long q = *reinterpret_cast<const unsigned long long*>(mask + i0);
+  const int start = blockIdx.x * run, end = min(start + run, P);     // (run is a multiple of kCompactRound)
+  auto four = [&](int i0) {                    // the bytes of cells i0 .. i0 + 3 (zeros past the end), the masker's 0 / 1
+    if (ALIGNED && i0 + 4 <= end) return *reinterpret_cast<const unsigned*>(mask + i0);
+    unsigned v = 0;
 #pragma unroll
-        for (int b = 0; b < 8; ++b) on |= ((q >> (8 * b)) & 0xffull) != 0 ? (1u << b) : 0u;
-      } else {
-        for (int b = 0; b < 8; ++b)
-          if (i0 + b < P && mask[i0 + b] != 0) on |= 1u << b;
-      }
-    } else {
-      on = (i0 < P && mask[i0] != 0) ? 1u : 0u;
+    for (int b = 0; b < 4; ++b)
+      if (i0 + b < end) v |= (unsigned)mask[i0 + b] << (8 * b);
+    return v;
+  };
+  unsigned next = four(start + tid * 4);       // requested before the long count
+  int mine = 0;
+  if constexpr (ALIGNED) {
+    for (int i = tid * 16; i < start; i += kCompactThreads * 16) {
+      const uint4 q = *reinterpret_cast<const uint4*>(mask + i);
+      mine += __popc(q.x) + __popc(q.y) + __popc(q.z) + __popc(q.w);
     }
+  } else {
+    for (int i = tid; i < start; i += kCompactThreads) mine += mask[i];
+  }
+#pragma unroll
+  for (int o = 32; o > 0; o >>= 1) mine += __shfl_xor(mine, o, 64);
+  if (lane == 0) wave_tot[wv] = mine;
+  __syncthreads();
+  int base = 0;                                // identical in every thread
+#pragma unroll
+  for (int k = 0; k < kCompactThreads / 64; ++k) base += wave_tot[k];
+  __syncthreads();
+  for (int r0 = start; r0 < end; r0 += kCompactRound) {
+    const int i0 = r0 + tid * 4;
+    const unsigned on = next;
+    if (r0 + kCompactRound < end) next = four(i0 + kCompactRound);
     const int c = __popc(on);
     int incl = c;                              // inclusive scan over the wave
 #pragma unroll
@@ -299,15 +335,13 @@ __global__ __launch_bounds__(kCompactThreads) void compact_kernel(
       total += t;
     }
     int pos = base + before + incl - c;
-    while (on) {
-      const int b = __ffs(on) - 1;
-      idx[pos++] = i0 + b;
-      on &= on - 1;
-    }
+#pragma unroll
+    for (int b = 0; b < 4; ++b)
+      if ((on >> (8 * b)) & 1u) idx[pos++] = i0 + b;
     base += total;
     __syncthreads();                           // wave_tot is rewritten next round
   }
-  if (tid == 0) *count = base;
+  if (tid == 0 && (end == P)) *count = base;
 }
 
 }  // namespace
@@ -320,18 +354,44 @@ hipError_t launch_masker(const lasnet_tensor& x, const float* Wm, float bm, int 
   const size_t esz = x.dtype == LASNET_BF16 ? 2 : 4;
   const bool vec = ((size_t)x.c * esz) % 16 == 0 && ((uintptr_t)x.data % 16) == 0 &&
                    ((uintptr_t)Wm % 16) == 0 && (x.c % 8 == 0) && ((uintptr_t)pass_out % 16) == 0;
-  const bool hoist = vec && (size_t)S * x.c * esz == 4096;   // one group of four pieces per patch row
-#define LASNET_MASKER_LAUNCH(T, VEC, HOIST)                                                   \
-  hipLaunchKernelGGL((masker_logit_kernel<T, VEC, HOIST>), grid, block, 0, st, (const T*)x.data, \
+#define LASNET_MASKER_LAUNCH(T, VEC)                                                             \
+  hipLaunchKernelGGL((masker_logit_kernel<T, VEC>), grid, block, 0, st, (const T*)x.data, \
                      Wm, (double)bm, (double)thr, S, x.h, x.w, x.c, G, GW, P, mask, logits,      \
                      (T*)pass_out)
 #define LASNET_MASKER_ROWS(T, WPC, ...)                                                          \
   hipLaunchKernelGGL((masker_rows_kernel<T, WPC, ##__VA_ARGS__>), dim3((P + kCellsPerBlock / WPC - 1) / (kCellsPerBlock / WPC)), \
                      block, 0, st, (const T*)x.data, Wm, (double)bm, (double)thr, x.h, x.w, x.c, G, GW, P,     \
                      mask, logits, (T*)pass_out)
+#define LASNET_MASKER_CELLS(T, TPC)                                                              \
+  hipLaunchKernelGGL((masker_cells_kernel<T, TPC, kCellPieces>),                                 \
+                     dim3(TPC < kMaskerThreads ? (P + kMaskerThreads / TPC - 1) / (kMaskerThreads / TPC) : P), \
+                     dim3(TPC < kMaskerThreads ? kMaskerThreads : TPC), 0, st, (const T*)x.data, Wm, (double)bm, (double)thr, \
+                     S, x.h, x.w, x.c, G, GW, P, cp, mask, logits, (T*)pass_out)
+#define LASNET_MASKER_CELLS_ANY(T)                                                               \
+  switch (tpc) {                                                                                 \
+    case 64: LASNET_MASKER_CELLS(T, 64); break;                                                  \
+    case 128: LASNET_MASKER_CELLS(T, 128); break;                                                \
+    case 256: LASNET_MASKER_CELLS(T, 256); break;                                                \
+    case 512: LASNET_MASKER_CELLS(T, 512); break;                                                \
+    default: LASNET_MASKER_CELLS(T, 1024); break;                                                \
+  }
+  // Threads per cell: enough to hold the cell in registers, and more while the chip would not have eight waves per
+  // CU and a thread still has at least two pieces.
+  CellPieces cp{};
+  cp.pc = vec ? (int)(x.c * esz / 16) : 1;
+  cp.pr = S * cp.pc;
+  const long long np = (long long)S * cp.pr;
+  int tpc = 64;
+  while (tpc < 1024 && (np > (long long)tpc * kCellPieces || ((long long)P * tpc < 64 * 2048 && np >= 4 * tpc))) tpc *= 2;
+  const bool cells = vec && np <= (long long)tpc * kCellPieces;
+  if (cells) {
+    cp.np = (int)np;
+    cp.m_pr = cp.pr > 1 ? (unsigned)((0x100000000ull + cp.pr - 1) / cp.pr) : 0;
+    cp.m_pc = cp.pc > 1 ? (unsigned)((0x100000000ull + cp.pc - 1) / cp.pc) : 0;
+  }
   if (P == 0) {
     // empty batch: nothing to pool; the compaction below still writes count = 0
-  } else if (hoist && (S == 1 || S == 2 || S == 4 || S == 8)) {
+  } else if (vec && (size_t)S * x.c * esz == 4096 && (S == 1 || S == 2 || S == 4 || S == 8)) {
     if (x.dtype == LASNET_BF16) {
       if (S == 1) LASNET_MASKER_ROWS(uint16_t, 1, 1);      // pixel-level cells (7x7x2048): a cell is one row
       else if (S == 2) LASNET_MASKER_ROWS(uint16_t, 2, 1); // one row per wave: 0.9 us faster than two at stage 3
@@ -344,24 +404,29 @@ hipError_t launch_masker(const lasnet_tensor& x, const float* Wm, float bm, int 
       else if (S == 4) LASNET_MASKER_ROWS(float, 2);
       else LASNET_MASKER_ROWS(float, 4);
     }
+  } else if (cells) {
+    if (x.dtype == LASNET_BF16) { LASNET_MASKER_CELLS_ANY(uint16_t) } else { LASNET_MASKER_CELLS_ANY(float) }
   } else if (x.dtype == LASNET_BF16) {
-    if (hoist) LASNET_MASKER_LAUNCH(uint16_t, true, true);
-    else if (vec) LASNET_MASKER_LAUNCH(uint16_t, true, false);
-    else LASNET_MASKER_LAUNCH(uint16_t, false, false);
+    if (vec) LASNET_MASKER_LAUNCH(uint16_t, true);
+    else LASNET_MASKER_LAUNCH(uint16_t, false);
   } else {
-    if (hoist) LASNET_MASKER_LAUNCH(float, true, true);
-    else if (vec) LASNET_MASKER_LAUNCH(float, true, false);
-    else LASNET_MASKER_LAUNCH(float, false, false);
+    if (vec) LASNET_MASKER_LAUNCH(float, true);
+    else LASNET_MASKER_LAUNCH(float, false);
   }
+#undef LASNET_MASKER_CELLS_ANY
+#undef LASNET_MASKER_CELLS
 #undef LASNET_MASKER_LAUNCH
 #undef LASNET_MASKER_ROWS
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
   if (count) {
-    if (((uintptr_t)mask % 8) == 0)
-      hipLaunchKernelGGL(compact_kernel<8>, dim3(1), dim3(kCompactThreads), 0, st, mask, P, idx, count);
+    int run = (P + kCompactBlocks - 1) / kCompactBlocks;
+    run = run > 0 ? (run + kCompactRound - 1) / kCompactRound * kCompactRound : kCompactRound;
+    const dim3 cgrid(P > 0 ? (P + run - 1) / run : 1);
+    if (((uintptr_t)mask % 16) == 0)
+      hipLaunchKernelGGL(compact_kernel<true>, cgrid, dim3(kCompactThreads), 0, st, mask, P, run, idx, count);
     else
-      hipLaunchKernelGGL(compact_kernel<1>, dim3(1), dim3(kCompactThreads), 0, st, mask, P, idx, count);
+      hipLaunchKernelGGL(compact_kernel<false>, cgrid, dim3(kCompactThreads), 0, st, mask, P, run, idx, count);
     e = hipGetLastError();
   }
   return e;
