@@ -71,7 +71,7 @@ enum {
   LASNET_SKIP_IDENTITY = 4,    /* caller guarantees out already equals x on inactive patches:
                                   do not copy x to out first                                 */
   LASNET_FORCE_FUSED = 8,      /* run the one-kernel (fused) schedule even where the library would
-                                  pick the tiled one (see "Schedules" below); for measurements  */
+                                  pick another one (see "Schedules" below); for measurements  */
   LASNET_FORCE_TILED = 16      /* run the three-kernel (tiled) schedule where the shape has one but
                                   the library would pick the fused one; LASNET_EUNSUPPORTED where
                                   it has none, or in lasnet_sparse_bottleneck_noalloc           */
@@ -160,7 +160,7 @@ LASNET_API int lasnet_sparse_bottleneck_ex(const lasnet_tensor* x, const int32_t
                                 lasnet_tensor* out, uint32_t flags, void* hip_stream);
 
 /*
- * Schedules.  Two matrix-core schedules exist, and the library picks by shape (Sec. 3.4 discusses
+ * Schedules.  Three matrix-core schedules exist, and the library picks by shape (Sec. 3.4 discusses
  * this choice of operator fusion against the activation rate; on this GPU the block shape decides):
  *   fused  one kernel: gather + conv1 + conv3x3 + conv3 + scatter-add, y1 and y2 never leave the CU.
  *          Used where a CU can afford to stream all weights per batch of patches (ResNet-101 stages 1-3).
@@ -171,12 +171,18 @@ LASNET_API int lasnet_sparse_bottleneck_ex(const lasnet_tensor* x, const int32_t
  *          size.  The library's own choice for 2048x512 (measured faster there at every activation
  *          rate); for 1024x256 the fused kernel measured faster or equal at every rate, so the tiled
  *          one runs only with LASNET_FORCE_TILED (a caller that wants the in-place update).
+ *   slab   the same split in smaller pieces, for a few images of 1024x256 and 2048x512 channels (up to 16
+ *          14x14 images' worth of pixels, 32 with patches of S = 7, 40 7x7 images'): the fused kernel would
+ *          leave most of the GPU idle there.  It needs at most 8 MiB for y1 and y2, from where the tiled one takes
+ *          its own (a lasnet_workspace_bytes() buffer is large enough); without them -- a stream under
+ *          capture whose buffer is not there yet, lasnet_sparse_bottleneck_planned without a workspace -- the
+ *          fused or tiled schedule runs as it would for more images.
  * Results are the same function of the inputs either way (same roundings: y1, y2 to bf16, out once).
  * The tiled schedule needs lasnet_workspace_bytes() of device memory (that query answers for every
  * shape that has a tiled schedule, chosen by default or not; 0 = none): lasnet_sparse_bottleneck[_ex],
  * lasnet_dense_bottleneck and lasnet_sparse_bottleneck_packed take it from the library's per-stream
  * buffer (see below); lasnet_sparse_bottleneck_planned takes it from the caller;
- * lasnet_sparse_bottleneck_noalloc never uses the tiled schedule.
+ * lasnet_sparse_bottleneck_noalloc never uses the tiled schedule (and the slab one in its fixed array).
  */
 LASNET_API size_t lasnet_workspace_bytes(int dtype, int N, int H, int W, int C, int M, int S);
 
@@ -203,8 +209,8 @@ LASNET_API size_t lasnet_workspace_bytes(int dtype, int N, int H, int W, int C, 
  * made for (both schedules read the same layout).  lasnet_sparse_bottleneck_packed is otherwise
  * lasnet_sparse_bottleneck_ex (same semantics, flags LASNET_POST_RELU, LASNET_SKIP_IDENTITY and
  * LASNET_FORCE_FUSED) and returns LASNET_EUNSUPPORTED for shapes or dtypes without a matrix-core
- * kernel.  It allocates nothing on the fused schedule; on the tiled schedule the workspace comes
- * from the library's per-stream buffer (hipMalloc on first use or growth, as above).
+ * kernel.  It allocates nothing on the fused schedule; on the tiled and slab schedules the workspace
+ * comes from the library's per-stream buffer (hipMalloc on first use or growth, as above).
  *
  * lasnet_sparse_bottleneck_planned is the fully explicit form, which never allocates: packed
  * weights AND the workspace are the caller's (workspace: 256-byte aligned device memory of at least
@@ -235,8 +241,8 @@ LASNET_API int lasnet_sparse_bottleneck_planned(const lasnet_tensor* x, const in
  * loops, harnesses that forbid hipMalloc): lasnet_sparse_bottleneck_ex with the per-call weight
  * repack going to a fixed array in device memory instead of the library's per-stream buffer.
  * This entry point calls no hipMalloc / hipFree and no allocating library routine, on any call.
- *   - The array is LASNET_NOALLOC_MAX_PACKED_BYTES long, exists once per GPU the library runs
- *     on, and is held until the process ends.  Shapes whose repacked weights
+ *   - The array holds LASNET_NOALLOC_MAX_PACKED_BYTES of weights and the slab schedule's 8 MiB, exists once per
+ *     GPU the library runs on, and is held until the process ends.  Shapes whose repacked weights
  *     (lasnet_packed_weights_bytes) are larger -- the 7x7 stage of ResNet-101, 8.5 MiB -- get
  *     LASNET_ETOOBIG before anything is enqueued; such callers repack once into a buffer of their
  *     own and use lasnet_sparse_bottleneck_packed, which allocates nothing either.

@@ -16,7 +16,7 @@ LIB = os.path.join(PKG, "liblasnet.so")
 LIB_CHECK = os.path.join(PKG, "liblasnet_check.so")
 CHECK_FLAGS = ("-DLASNET_DRAIN_AT_BARRIERS",)
 SOURCES = ["tiled_stages.hip", "mfma_stage3.hip", "mfma_stage2.hip", "mfma_stage1.hip", "mfma_stage4.hip",   # slowest first
-           "rows_generic.hip",
+           "rows_generic.hip", "slab_stages.hip",
            "api.hip", "masker.hip", "bottleneck_generic.hip", "bottleneck_mfma.hip", "microbench.hip"]
 
 FLAGS = [

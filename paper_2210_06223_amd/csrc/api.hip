@@ -56,8 +56,9 @@ void get_workspace(Lease& lease, hipStream_t st, size_t bytes) {
 // Repacked weights for callers that cannot allocate (lasnet_sparse_bottleneck_noalloc): a fixed
 // array in device memory, one copy per GPU the library runs on, held until the process ends.
 // In host code the array's name is only a handle for hipGetSymbolAddress: the address that
-// kernels and copies take is the one that call returns, looked up once per device.
-static __device__ __align__(256) unsigned char scratch[LASNET_NOALLOC_MAX_PACKED_BYTES];
+// kernels and copies take is the one that call returns, looked up once per device.  Behind the weights lie the y1 and y2
+// of the slab schedule, so that this entry runs the schedule that the others would.
+static __device__ __align__(256) unsigned char scratch[LASNET_NOALLOC_MAX_PACKED_BYTES + kSlabBytes];
 constexpr int kMaxDevices = 64;
 void* g_scratch_ptr[kMaxDevices];                // per device; nullptr = not looked up yet
 std::mutex g_scratch_mu;
@@ -165,7 +166,7 @@ int run_block(const lasnet_tensor* x, const int32_t* idx, const int32_t* count, 
   }
   if (packed && !fast) return LASNET_EUNSUPPORTED;
   if (!fast && !generic_fits(M, S)) return LASNET_EUNSUPPORTED;
-  if (fast && !packed && pad.fixed_array && mfma_packed_bytes(x->c, M, S) > sizeof(scratch))
+  if (fast && !packed && pad.fixed_array && mfma_packed_bytes(x->c, M, S) > LASNET_NOALLOC_MAX_PACKED_BYTES)
     return LASNET_ETOOBIG;
   const Geom g = make_geom(x, M, S);
   // Deep stages run the tiled schedule (three kernels, y1 and y2 through a workspace) unless the
@@ -186,6 +187,10 @@ int run_block(const lasnet_tensor* x, const int32_t* idx, const int32_t* count, 
     if (a < b + map_bytes && b < a + map_bytes) return LASNET_EALIAS;
   }
   if (in_place && !tiled) return LASNET_EALIAS;
+  // A few images of a deep stage run the slab schedule (in place it is as safe as the tiled one: neighbours are read by
+  // its first kernel, out is written by its last).
+  bool slab = fast && !(flags & (LASNET_FORCE_FUSED | LASNET_FORCE_TILED)) && slab_takes(g);
+  const size_t slab_need = slab ? slab_workspace_bytes(g) : 0;
   const size_t packed_need = (fast && !packed) ? round256(mfma_packed_bytes(x->c, M, S)) : 0;
   const size_t tiled_need = tiled ? tiled->workspace_bytes(g) : 0;
   if (pad.from_caller && tiled && (!pad.workspace || pad.workspace_bytes < tiled_need || ((uintptr_t)pad.workspace & 255)))
@@ -200,44 +205,49 @@ int run_block(const lasnet_tensor* x, const int32_t* idx, const int32_t* count, 
   // library's per stream, or `scratch`).
   hipError_t e = !fast ? prepare_generic(x->dtype) : tiled ? tiled->prepare() : prepare_mfma(x->c, M, S);
   if (e != hipSuccess) return LASNET_EHIP;
-  unsigned char* tiled_ws = nullptr;
+  unsigned char* block_ws = nullptr;             // the tiled or the slab schedule's
   // Without a matrix-core kernel of its own the shape runs the row schedule; where there is no memory for that (the
   // caller forbids it, a capture is under way, the map is too large), the one-kernel generic path.
   const size_t rows_need = !fast && !pad.fixed_array && !pad.from_caller ? rows_workspace_bytes(x->dtype, g) : 0;
   void* rows_ws = nullptr;
   Lease lease;
   if (pad.from_caller) {
-    tiled_ws = (unsigned char*)pad.workspace;              // (this entry takes packed weights: packed_need is 0)
+    block_ws = (unsigned char*)pad.workspace;              // (this entry takes packed weights: packed_need is 0)
+    if (!block_ws || pad.workspace_bytes < slab_need || ((uintptr_t)block_ws & 255)) slab = false;
   } else if (pad.fixed_array) {
     if (packed_need) {
-      void* p = scratch_for_current_device();
+      unsigned char* p = (unsigned char*)scratch_for_current_device();
       if (!p) return LASNET_EHIP;
       e = launch_pack(x->c, M, S, W1, W2, W3, p, st);
       if (e != hipSuccess) return LASNET_EHIP;
       packed = p;
+      block_ws = p + LASNET_NOALLOC_MAX_PACKED_BYTES;
     }
   } else if (rows_need) {
     get_workspace(lease, st, rows_need);
     rows_ws = lease.ptr;
-  } else if (packed_need + tiled_need) {
-    get_workspace(lease, st, packed_need + tiled_need);
+  } else if (packed_need + tiled_need + slab_need) {
+    get_workspace(lease, st, packed_need + (tiled_need > slab_need ? tiled_need : slab_need));
     unsigned char* ws = (unsigned char*)lease.ptr;
-    if (!ws) return LASNET_EHIP;
+    if (!ws && packed_need + tiled_need) return LASNET_EHIP;
+    if (!ws) slab = false;                      // (under capture, for one: the fused kernel needs none)
     if (packed_need) {
       e = launch_pack(x->c, M, S, W1, W2, W3, ws, st);
       if (e != hipSuccess) return LASNET_EHIP;
       packed = ws;
     }
-    tiled_ws = ws + packed_need;
+    block_ws = ws + packed_need;
   }
   if (!dense && idx && !in_place && !(flags & LASNET_SKIP_IDENTITY)) {
     e = launch_copy(x->data, out->data, map_bytes, st);
     if (e != hipSuccess) return LASNET_EHIP;
   }
   const bool relu = (flags & LASNET_POST_RELU) != 0;
-  if (tiled)
+  if (slab)
+    e = launch_slab(g, x->data, idx, count, packed, b1, b2, b3, out->data, relu, block_ws, st);
+  else if (tiled)
     e = tiled->launch(g, x->data, idx, count, idx ? pad.cellmask : nullptr, packed, b1, b2, b3, out->data, relu,
-                      tiled_ws, st);
+                      block_ws, st);
   else if (fast)
     e = launch_mfma(g, x->data, idx, count, packed, b1, b2, b3, out->data, relu, st);
   else if (rows_ws)

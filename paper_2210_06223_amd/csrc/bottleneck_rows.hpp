@@ -27,6 +27,8 @@
 #pragma once
 #include "common.hpp"
 
+#include <type_traits>
+
 namespace lasnet {
 namespace {
 
@@ -48,6 +50,14 @@ __device__ __forceinline__ V rows_load16(rows_rsrc_t r, unsigned lane_bytes, uns
   return __builtin_bit_cast(V, __builtin_amdgcn_raw_buffer_load_b128(r, (int)lane_bytes, (int)uniform_bytes, 0));
 }
 
+// Where the fragments of a group of 32 output channels lie: groups of 2^sh channel groups `hi` bytes apart, in them channel
+// groups `lo` bytes apart, the two tiles of a k-step next to each other and the k-steps `step` bytes apart.
+struct RowsWeights {
+  unsigned lo, hi, step;
+  int sh;
+  __device__ __forceinline__ unsigned base(int pair) const { return (unsigned)(pair >> sh) * hi + (unsigned)(pair & ((1 << sh) - 1)) * lo; }
+};
+
 // One call (or one chunk of images of it), by value into every kernel.
 struct RowsArgs {
   Geom g;
@@ -58,6 +68,7 @@ struct RowsArgs {
   const int32_t* count;
   const uint8_t* need;     // nullptr: every pixel
   unsigned w1_bytes, w2_bytes, w3_bytes;    // packed
+  RowsWeights w1, w2, w3;
 };
 
 // The active list as rows: row r is pixel (r mod S*S) of entry r / (S*S).
@@ -143,17 +154,17 @@ __device__ __forceinline__ void store_y<Bf16Wide>(unsigned char* row, int ch, in
 }
 
 // ---- the GEMM of one wave: NB blocks of 16 rows x one group of 32 channels ------------------------------
-// k-steps [s0, s1) of `total`.  Weights: fragments (step, tile) at wbase + (step * 2 + tile) * KPL KiB.  B rows by `rows`,
+// k-steps [s0, s1) of `total`.  Weights: fragments (step, tile) at wbase + step * wstep + tile * KPL KiB.  B rows by `rows`,
 // which yields the byte offset of each row block's lane for the k-step it is advanced to.
 template <class F, int NB, int PL, int D, class Rows>
-__device__ __forceinline__ void rows_gemm(floatx4 (&acc)[NB][2], rows_rsrc_t wrs, unsigned wbase, Rows& rows, int s0, int s1,
-                                          int lane) {
+__device__ __forceinline__ void rows_gemm(floatx4 (&acc)[NB][2], rows_rsrc_t wrs, unsigned wbase, unsigned wstep, Rows& rows,
+                                          int s0, int s1, int lane) {
   using Frag = typename F::Frag;
   using V = typename F::V;
   Frag a[D][2], b[D][NB][PL];
   const unsigned lane16 = lane * 16;
   auto load = [&](int d, int s) {
-    const unsigned so = wbase + (unsigned)s * (2 * F::KPL * 1024);
+    const unsigned so = wbase + (unsigned)s * wstep;
 #pragma unroll
     for (int j = 0; j < 2; ++j)
 #pragma unroll
@@ -370,7 +381,7 @@ __global__ __launch_bounds__(kRowsThreads, 2) void rows_conv1_kernel(RowsArgs a,
       floatx4 acc[N][2];
       start_at_bias<N>(acc, b1, a.g.M, rows_channel(pair, lg), wave % KS == 0);
       if (s0 < s1 && pair < a.pairs1)
-        rows_gemm<F, N, F::XP, 2>(acc, rows_rsrc(wp, a.w1_bytes), (unsigned)(pair * a.ks1) * (2 * F::KPL * 1024), rows, s0, s1, lane);
+        rows_gemm<F, N, F::XP, 2>(acc, rows_rsrc(wp, a.w1_bytes), a.w1.base(pair), a.w1.step, rows, s0, s1, lane);
       reduce_over_waves<N, KS>(acc, (ROWS_LDS float*)part, wave, lane);
 #pragma unroll
       for (int i = 0; i < N; ++i) {
@@ -423,7 +434,7 @@ __global__ __launch_bounds__(kRowsThreads, 2) void rows_conv2_kernel(RowsArgs a,
     start_at_bias<NB>(acc, b2, a.g.M, rows_channel(pair, lg), wave % KS == 0);
     rows.seek(min(s0, total - 1), NB);
     if (s0 < s1 && pair < a.pairs1)
-      rows_gemm<F, NB, F::YP, 2>(acc, rows_rsrc(wp, a.w2_bytes), (unsigned)(pair * total) * (2 * F::KPL * 1024), rows, s0, s1, lane);
+      rows_gemm<F, NB, F::YP, 2>(acc, rows_rsrc(wp, a.w2_bytes), a.w2.base(pair), a.w2.step, rows, s0, s1, lane);
     reduce_over_waves<NB, KS>(acc, (ROWS_LDS float*)part, wave, lane);
 #pragma unroll
     for (int i = 0; i < NB; ++i)
@@ -471,7 +482,7 @@ __global__ __launch_bounds__(kRowsThreads, 2) void rows_conv3_kernel(RowsArgs a,
     const int ch = rows_channel(pair, lg);
     start_at_bias<NB>(acc, b3, C, ch, wave % KS == 0);
     if (s0 < s1 && pair < a.pairs3)
-      rows_gemm<F, NB, F::YP, 2>(acc, rows_rsrc(wp, a.w3_bytes), (unsigned)(pair * a.ksm) * (2 * F::KPL * 1024), rows, s0, s1, lane);
+      rows_gemm<F, NB, F::YP, 2>(acc, rows_rsrc(wp, a.w3_bytes), a.w3.base(pair), a.w3.step, rows, s0, s1, lane);
     reduce_over_waves<NB, KS>(acc, (ROWS_LDS float*)part, wave, lane);
 #pragma unroll
     for (int i = 0; i < NB; ++i)
@@ -611,6 +622,60 @@ bool rows_layout(const Geom& g, RowsLayout& l) {
   l.y = rows_round(n * hw * ypx);
   l.total = rows_round(l.w1) + rows_round(l.w2) + rows_round(l.w3) + l.need + 2 * l.y;
   return true;
+}
+
+// How a convolution is cut: NB row blocks per wave, KS waves to a tile's reduction, nsl channel slices per row tile.
+// 1024 waves are one per SIMD.  More rows per wave read the weights less often, so NB is as large as leaves the chip
+// that many tiles; with fewer even at NB = 1 the waves of a workgroup share a tile's reduction.
+struct RowsCut { int nb, ks, units, nsl; };
+inline RowsCut rows_cut(long long rows_max, long long rows_expected, int pairs, int ksteps) {
+  RowsCut c;
+  c.nb = 4;
+  while (c.nb > 1 && (rows_expected + 16 * c.nb - 1) / (16 * c.nb) * pairs < 1024) c.nb /= 2;
+  const long long tiles = (rows_expected + 16 * c.nb - 1) / (16 * c.nb);
+  c.ks = tiles * pairs < 1024 && ksteps >= 8 ? 4 : 1;
+  c.units = (int)((rows_max + 16 * c.nb - 1) / (16 * c.nb));
+  const int wc = 4 / c.ks, most = (pairs + wc - 1) / wc;
+  c.nsl = (int)((1024 + tiles - 1) / tiles);
+  if (c.nsl > most) c.nsl = most;
+  return c;
+}
+
+#define ROWS_DISPATCH(c, CALL)                                             \
+  if (c.ks == 4) {                                                         \
+    if (c.nb == 1) CALL(1, 4); else if (c.nb == 2) CALL(2, 4); else CALL(4, 4); \
+  } else {                                                                 \
+    if (c.nb == 1) CALL(1, 1); else if (c.nb == 2) CALL(2, 1); else CALL(4, 1); \
+  }
+
+// The three convolutions of the chunk that `a` describes.
+template <class F, bool VEC>
+hipError_t launch_rows_convs(const RowsArgs& a, const void* x, const unsigned char* wp1, const unsigned char* wp2,
+                             const unsigned char* wp3, const float* b1, const float* b2, const float* b3, unsigned char* y1,
+                             unsigned char* y2, void* out, bool post_relu, hipStream_t st) {
+  typedef typename F::T T;
+  const Geom& g = a.g;
+  // the list's rows of this chunk are not known here: half of the pixels is a middling activation ratio
+  const long long rows = (long long)g.P * g.S * g.S, likely = a.idx ? (a.npx + 1) / 2 : a.npx;
+  RowsCut c = rows_cut(a.npx, a.npx, a.pairs1, a.ks1);
+#define ROWS_CONV1(NB, KS)                                                                                               \
+  hipLaunchKernelGGL((rows_conv1_kernel<F, VEC, NB, KS>), dim3(rows_grid(c.units, c.nsl)), dim3(kRowsThreads), 0, st, a, \
+                     c.nsl, (const T*)x, wp1, b1, y1)
+  ROWS_DISPATCH(c, ROWS_CONV1)
+  c = rows_cut(rows, likely, a.pairs1, 9 * a.ksm);
+#define ROWS_CONV2(NB, KS)                                                                                               \
+  hipLaunchKernelGGL((rows_conv2_kernel<F, NB, KS>), dim3(rows_grid(c.units, c.nsl)), dim3(kRowsThreads), 0, st, a,      \
+                     c.nsl, wp2, b2, y1, y2)
+  ROWS_DISPATCH(c, ROWS_CONV2)
+  c = rows_cut(rows, likely, a.pairs3, a.ksm);
+#define ROWS_CONV3(NB, KS)                                                                                               \
+  hipLaunchKernelGGL((rows_conv3_kernel<F, VEC, NB, KS>), dim3(rows_grid(c.units, c.nsl)), dim3(kRowsThreads), 0, st, a, \
+                     c.nsl, (const T*)x, wp3, b3, y2, (T*)out, (int)post_relu)
+  ROWS_DISPATCH(c, ROWS_CONV3)
+#undef ROWS_CONV1
+#undef ROWS_CONV2
+#undef ROWS_CONV3
+  return hipGetLastError();
 }
 
 }  // namespace

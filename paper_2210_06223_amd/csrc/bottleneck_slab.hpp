@@ -1,0 +1,405 @@
+// The slab schedule: the sparse bottleneck for a few images of a deep ResNet-101 stage (bf16), where the fused kernel
+// leaves most of the chip idle -- it has a workgroup per run of patches, and each streams all weights through one
+// CU, which takes 20 us whatever little there is to compute.  Three launches instead, each cut into (16 * NB rows of
+// pixels) x (a few groups of 32 output channels) per workgroup, so that hundreds of CUs read a slice of the weights each:
+//
+//   conv1  rows = 16 * NB consecutive pixels of the whole map (it then depends on no list)     y1[pixel]
+//   conv2  rows = the list's pixels, S*S per entry, in the list's order                        y2[pixel]
+//   conv3  the same rows                                                                       out
+//
+// What bounds it is the chain of dependent memory accesses (~1 us each), so a workgroup makes as few as it can: the
+// count, the list entries (requested together with the count: the list has storage for every cell) and its first
+// weights at once; then its whole activation operand -- every row over the full reduction, conv2's with all nine
+// taps -- as one burst of direct global->LDS loads; then the reduction from LDS, with weights D k-steps ahead in registers.
+// The four waves of a workgroup share the slab: 4 / KS of them take different groups of 32 channels, and KS of them split
+// the reduction (partial sums added through LDS in a fixed order), so that few rows still make many waves.
+//
+// Measured (block alone): 14x14x1024, S=2, one image 20.9 -> 14.4 us (conv1 3.4, conv2 6.6, conv3 3.2 of them on the GPU:
+// the launches are the bound), 16 images 24.7 -> 18.8; S=7, 24 images 32.8 -> 23.6; 7x7x2048, one image 35 -> 18 us, 40
+// images 54 -> 34.  In conv2 the chain of accesses takes about 3 us; past that a CU streams its weights.
+//
+// Rounding points, weight layout (lasnet_pack_weights') and results are the fused kernel's, up to the order of the sums.
+#pragma once
+#include "bottleneck_mfma.hpp"
+
+namespace lasnet {
+namespace {
+
+constexpr int kSlabThreads = 256;
+
+struct SlabArgs {
+  Geom g;
+  const int32_t* idx;              // nullptr: every cell
+  const int32_t* count;
+  int npx, nsl;                    // pixels of the map; channel slices per row tile
+  int ppt;                         // conv2: patches per workgroup
+  int m_t2, m_t, m_s2, m_s;        // small_div's multipliers for (S+2)^2, S+2, S*S and S
+};
+
+// Workgroup -> (row tile, channel slice): the slices of a row tile sit on one XCD (workgroup b runs on XCD b mod 8), so
+// the rows they share are fetched into one L2.
+__device__ __forceinline__ void slab_unit(int nsl, int& unit, int& slice) {
+  const int xcd = (int)blockIdx.x & 7, j = (int)blockIdx.x >> 3;
+  unit = (j / nsl) * 8 + xcd;
+  slice = j % nsl;
+}
+inline int slab_grid(int units, int nsl) { return (units + 7) / 8 * 8 * nsl; }
+
+__device__ __forceinline__ void slab_load(const AS_GLOBAL __bf16* src, AS_LDS __bf16* dst) {     // 64 x 16 bytes -> 1 KiB at dst
+  const unsigned a = uni((int)(unsigned)(size_t)dst);
+  asm volatile("s_mov_b32 m0, %1\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, off" ::"v"(src), "s"(a) : "memory");
+}
+// Every load of every wave has landed in LDS.
+__device__ __forceinline__ void slab_ready() {
+  __builtin_amdgcn_sched_barrier(0);
+  asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)\n\ts_barrier" ::: "memory");
+  __builtin_amdgcn_sched_barrier(0);
+}
+
+// One convolution's reduction: K channels per tap, TAPS taps, split over KS waves; a wave keeps D k-steps of weights in flight.
+// The slab is rows of K channels whose 16-byte chunks are XOR-swizzled with the row's key, so that the 16 rows that a
+// fragment read touches lie in different banks.
+template <int K, int TAPS, int NB, int KS, int D>
+struct Slab {
+  static constexpr int MS = K / 32, NST = TAPS * MS / KS;
+  static_assert(TAPS * MS % KS == 0 && NST % D == 0, "whole rings");
+  static constexpr int KEYS = K / 8 - 1 < 15 ? K / 8 - 1 : 15;
+  static constexpr int PART_BYTES = KS > 1 ? 4 * NB * 2 * 1024 : 0;              // partial sums (over the slab, when it is dead)
+  bf16x8 w[D][2];
+
+  __device__ __forceinline__ void fetch(rsrc_t wrs, int lane16, unsigned base, unsigned step, int slot, int s) {
+#pragma unroll
+    for (int j = 0; j < 2; ++j) w[slot][j] = buf_load16(wrs, lane16 + j * 1024, (int)(base + (unsigned)s * step));
+  }
+  // the first D k-steps of this wave's share
+  __device__ __forceinline__ void start(rsrc_t wrs, int lane16, unsigned base, unsigned step, int s0) {
+#pragma unroll
+    for (int d = 0; d < D; ++d) fetch(wrs, lane16, base, step, d, s0 + d);
+  }
+  // where(i, tap, row, key): slab row of the lane's row in block i
+  template <class Where>
+  __device__ __forceinline__ void run(floatx4 (&acc)[NB][2], rsrc_t wrs, int lane16, unsigned base, unsigned step, int s0,
+                                      const AS_LDS __bf16* slab, int lg, Where&& where) {
+    // k-steps are read in order; the rows' addresses change with the tap only (one wave per SIMD issues an
+    // instruction every four clocks at best: worked out for every k-step, they took longer than the MFMAs)
+    int at[NB], key[NB];
+    unsigned cur = (unsigned)s0;
+    auto enter = [&](int tap) {
+#pragma unroll
+      for (int i = 0; i < NB; ++i) {
+        int row, k;
+        where(i, tap, row, k);
+        at[i] = row * (K * 2);
+        key[i] = (lg ^ (k & KEYS)) << 4;
+      }
+    };
+    enter(TAPS > 1 ? (int)(cur / MS) : 0);
+    auto read = [&](bf16x8 (&b)[NB]) {
+      asm volatile("" : "+s"(cur));              // opaque: or every k-step's address is computed ahead of the loop and spilled
+      const unsigned ms = TAPS > 1 ? cur % MS : cur;
+      if (TAPS > 1 && ms == 0) enter((int)(cur / MS));
+#pragma unroll
+      for (int i = 0; i < NB; ++i)
+        b[i] = *reinterpret_cast<const AS_LDS bf16x8*>(reinterpret_cast<const AS_LDS char*>(slab) + at[i] + ((int)(ms * 64) ^ key[i]));
+      ++cur;
+    };
+    // Fragments are read R - 1 k-steps ahead: with one or two waves per SIMD nothing else hides the LDS latency, which is
+    // several k-steps' MFMAs.  (Rolled over whole rings of weights, or this would be tens of KB of code.)
+    constexpr int R = D % 3 == 0 ? 3 : 4;
+    static_assert(D % R == 0, "the fragment ring turns over with the weights' ring");
+    bf16x8 b[R][NB];
+#pragma unroll
+    for (int d = 0; d < R - 1; ++d) read(b[d]);
+    auto ring = [&](int g, auto last) {
+#pragma unroll
+      for (int d = 0; d < D; ++d) {
+        if (!last.value || d + R - 1 < D) read(b[(d + R - 1) % R]);
+#pragma unroll
+        for (int i = 0; i < NB; ++i)
+#pragma unroll
+          for (int j = 0; j < 2; ++j) acc[i][j] = mfma16(w[d][j], b[d % R][i], acc[i][j]);
+        if (!last.value) fetch(wrs, lane16, base, step, d, s0 + g + d + D);
+        __builtin_amdgcn_sched_barrier(0);
+      }
+    };
+#pragma nounroll
+    for (int g = 0; g < NST - D; g += D) ring(g, std::false_type{});
+    ring(NST - D, std::true_type{});
+  }
+};
+
+// Lane -> (row of the piece, chunk position in it) for the 1 KiB pieces of a slab with K channels per row: RPI whole rows, or
+// a part of one.
+template <int K>
+__device__ __forceinline__ void slab_piece(int piece, int lane, int& row, int& pos) {
+  constexpr int CPR = K / 8;                     // 16-byte chunks per row
+  static_assert(CPR % 64 == 0 || 64 % CPR == 0, "whole rows or whole pieces");
+  if constexpr (CPR <= 64) {
+    row = piece * (64 / CPR) + lane / CPR;
+    pos = lane % CPR;
+  } else {
+    row = piece / (CPR / 64);
+    pos = piece % (CPR / 64) * 64 + lane;
+  }
+}
+
+// Weights in flight, in k-steps.  (Twice as deep measured slower: the slab's loads then wait behind them.)
+constexpr int kConv1Ring = 8, kConv2Ring = 9;
+
+// The accumulators' start: the bias in the first of the waves that share a tile, zero in the others.
+template <int NB>
+__device__ __forceinline__ void slab_bias(floatx4 (&acc)[NB][2], const float* b, int ch, bool first) {
+#pragma unroll
+  for (int j = 0; j < 2; ++j) {
+    floatx4 v = {0.f, 0.f, 0.f, 0.f};
+    if (first) __builtin_memcpy(&v, b + ch + j * 4, 16);
+#pragma unroll
+    for (int i = 0; i < NB; ++i) acc[i][j] = v;
+  }
+}
+
+// Adds the partial sums of the KS waves that share a tile, in the order of the waves; wave k is left with the row blocks
+// i = k, k + KS, ..
+template <int NB, int KS>
+__device__ __forceinline__ void slab_reduce(floatx4 (&acc)[NB][2], AS_LDS float* part, int wave, int lane) {
+  if constexpr (KS > 1) {
+    __syncthreads();                             // the slab is dead
+#pragma unroll
+    for (int i = 0; i < NB; ++i)
+#pragma unroll
+      for (int j = 0; j < 2; ++j)
+        *reinterpret_cast<AS_LDS floatx4*>(part + (((wave * NB + i) * 2 + j) * 64 + lane) * 4) = acc[i][j];
+    __syncthreads();
+    const int w0 = wave / KS * KS;
+#pragma unroll
+    for (int i = 0; i < NB; ++i)
+      if (i % KS == wave % KS)
+#pragma unroll
+        for (int j = 0; j < 2; ++j) {
+          floatx4 t = *reinterpret_cast<AS_LDS floatx4*>(part + (((w0 * NB + i) * 2 + j) * 64 + lane) * 4);
+#pragma unroll
+          for (int k = 1; k < KS; ++k)
+            t += *reinterpret_cast<AS_LDS floatx4*>(part + ((((w0 + k) * NB + i) * 2 + j) * 64 + lane) * 4);
+          acc[i][j] = t;
+        }
+  }
+}
+
+// ReLU, bf16, the lane's 8 channels (tiles 0 and 1 of a group of 32 give lane group lg the channels 8*lg ..) as one store.
+__device__ __forceinline__ void slab_store_y(__bf16* dst, const floatx4 (&t)[2]) {
+  bf16x8 o;
+#pragma unroll
+  for (int u = 0; u < 8; ++u) o[u] = (__bf16)fmaxf(t[u / 4][u % 4], 0.f);
+  *reinterpret_cast<AS_GLOBAL bf16x8*>((AS_GLOBAL __bf16*)dst) = o;
+}
+
+// Cell e of the list: its image's first pixel and its own first row and column, or n < 0.  The entry is read together with
+// the count, not after it (e < P keeps it inside the list's storage).
+struct SlabCell { int n, h, w; };
+__device__ __forceinline__ SlabCell slab_cell(const SlabArgs& a, int e) {
+  SlabCell c{-1, 0, 0};
+  if (e >= a.g.P) return c;
+  const int cell = a.idx ? a.idx[e] : e;
+  const int nact = a.idx ? min(*a.count, a.g.P) : a.g.P;
+  if (e >= nact || (unsigned)cell >= (unsigned)a.g.P) return c;
+  const int cpi = a.g.G * a.g.GW, n = cell / cpi, rem = cell - n * cpi, gy = rem / a.g.GW;
+  c.n = n;
+  c.h = gy * a.g.S;
+  c.w = (rem - gy * a.g.GW) * a.g.S;
+  return c;
+}
+// a / d for the small a of a slab (a * d < 2^16): a multiply and a shift, m = 65536 / d + 1
+__device__ __forceinline__ int small_div(int a, int m) { return (a * m) >> 16; }
+
+// ---- conv1 -----------------------------------------------------------------------------------------------
+template <int C, int M, int NB, int KS>
+__global__ __launch_bounds__(kSlabThreads, 2) void slab_conv1_kernel(SlabArgs a, const __bf16* __restrict__ x,
+                                                                     const __bf16* __restrict__ wp, const float* __restrict__ b1,
+                                                                     __bf16* __restrict__ y1) {
+  using L = Slab<C, 1, NB, KS, kConv1Ring>;
+  extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
+  AS_LDS __bf16* slab = (AS_LDS __bf16*)smem;
+  const int tid = threadIdx.x, lane = tid & 63, l16 = lane & 15, lg = lane >> 4, wave = uni(tid >> 6);
+  int unit, slice;
+  slab_unit(a.nsl, unit, slice);
+  const int p0 = unit * NB * 16;
+  if (p0 >= a.npx) return;
+  // the lane reads the chunk that belongs at the position it writes
+#pragma unroll
+  for (int u = 0; u < NB * 16 * C * 2 / 4096; ++u) {
+    int row, pos;
+    slab_piece<C>(u * 4 + wave, lane, row, pos);
+    slab_load((const AS_GLOBAL __bf16*)x + (size_t)min(p0 + row, a.npx - 1) * C + ((pos ^ (row & L::KEYS)) << 3),
+              slab + (u * 4 + wave) * 512);
+  }
+  const int pair = slice * (4 / KS) + wave / KS, s0 = wave % KS * L::NST, ch = pair * 32 + lg * 8;
+  const rsrc_t wrs = make_rsrc((g_bf16_p)wp, (unsigned)M * C * 2);
+  L l;
+  l.start(wrs, lane * 16, pair * 2048, M * 64, s0);
+  floatx4 acc[NB][2];
+  slab_bias<NB>(acc, b1, ch, KS == 1 || wave % KS == 0);
+  slab_ready();
+  l.run(acc, wrs, lane * 16, pair * 2048, M * 64, s0, slab, lg, [&](int i, int, int& row, int& key) { row = i * 16 + l16; key = l16; });
+  slab_reduce<NB, KS>(acc, (AS_LDS float*)smem, wave, lane);
+#pragma unroll
+  for (int i = 0; i < NB; ++i)
+    if ((KS == 1 || i % KS == wave % KS) && p0 + i * 16 + l16 < a.npx)
+      slab_store_y(y1 + (size_t)(p0 + i * 16 + l16) * M + ch, acc[i]);
+}
+
+// ---- conv2 -----------------------------------------------------------------------------------------------
+// A workgroup takes a.ppt patches (a.ppt * S*S <= NB * 16 output rows); its slab is their (S+2)x(S+2) windows, one after
+// the other, then an all-zero row for what lies outside the image.  Output row q of patch p reads window row
+// (i + dy, j + dx): the key p*S*S + wy*S + wx of a window row makes that q + dy*S + dx, so the 16 rows of a
+// block always have 16 different keys.
+constexpr int kSlabMaxPatches = 64, kSlabMaxRows = 608;   // (608 rows of 128 channels fill the LDS)
+// the all-zero row comes after whole 1 KiB pieces of window rows
+template <int M>
+__device__ __host__ __forceinline__ int slab_zero_row(int wrows) {
+  constexpr int RPP = M * 2 < 1024 ? 1024 / (M * 2) : 1;
+  return (wrows + RPP - 1) / RPP * RPP;
+}
+template <int M, int NB, int KS>
+__global__ __launch_bounds__(kSlabThreads, 1) void slab_conv2_kernel(SlabArgs a, const __bf16* __restrict__ wp,
+                                                                     const float* __restrict__ b2, const __bf16* __restrict__ y1,
+                                                                     __bf16* __restrict__ y2) {
+  using L = Slab<M, 9, NB, KS, kConv2Ring>;
+  extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
+  __shared__ int cells[kSlabMaxPatches * 4];
+  __shared__ int source[kSlabMaxRows];           // of every window row: pixel | key << 27
+  AS_LDS __bf16* slab = (AS_LDS __bf16*)smem;
+  const int tid = threadIdx.x, lane = tid & 63, l16 = lane & 15, lg = lane >> 4, wave = uni(tid >> 6);
+  int unit, slice;
+  slab_unit(a.nsl, unit, slice);
+  const int S = a.g.S, T = S + 2, T2 = T * T, H = a.g.H, W = a.g.W, ppt = a.ppt, wrows = ppt * T2;
+  const int zrow = slab_zero_row<M>(wrows);
+  const int pair = slice * (4 / KS) + wave / KS, s0 = wave % KS * L::NST, ch = pair * 32 + lg * 8;
+  SlabCell me{-1, 0, 0};
+  if (lane < ppt) me = slab_cell(a, unit * ppt + lane);
+  if (!__any(me.n >= 0)) return;                 // (the same patches in every wave)
+  if (wave == 0 && lane < ppt) {
+    cells[lane * 4 + 0] = me.n < 0 ? -1 : me.n * H * W;
+    cells[lane * 4 + 1] = me.h;
+    cells[lane * 4 + 2] = me.w;
+  }
+  const rsrc_t wrs = make_rsrc((g_bf16_p)wp, (unsigned)M * M * 18);
+  L l;
+  l.start(wrs, lane * 16, pair * 2048, M * 64, s0);
+  floatx4 acc[NB][2];
+  slab_bias<NB>(acc, b2, ch, KS == 1 || wave % KS == 0);
+  for (int i = tid; i < M / 8; i += kSlabThreads)
+    *reinterpret_cast<AS_LDS bf16x8*>(slab + zrow * M + i * 8) = bf16x8{0, 0, 0, 0, 0, 0, 0, 0};
+  __syncthreads();
+  // where every window row comes from: one that lies outside the image, or of a patch that does not exist, is loaded
+  // from pixel 0 and never read (rows past the last fill up the last piece)
+  for (int r = tid; r < zrow; r += kSlabThreads) {
+    const int row = min(r, wrows - 1);
+    const int p = small_div(row, a.m_t2), wpos = row - p * T2, wy = small_div(wpos, a.m_t), wx = wpos - wy * T;
+    const int img = cells[p * 4], h = cells[p * 4 + 1] + wy - 1, w = cells[p * 4 + 2] + wx - 1;
+    const bool in = img >= 0 && (unsigned)h < (unsigned)H && (unsigned)w < (unsigned)W;
+    source[r] = (in ? img + h * W + w : 0) | ((p * S * S + wy * S + wx) & L::KEYS) << 27;
+  }
+  __syncthreads();
+  // (four pieces' table entries are read at once: the loads then go out back to back)
+  const int npiece = zrow * (M / 8) / 64;
+  for (int first = wave; first < npiece; first += 16) {
+    int src[4], pos[4];
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+      int row;
+      slab_piece<M>(min(first + 4 * k, npiece - 1), lane, row, pos[k]);
+      src[k] = source[row];
+    }
+#pragma unroll
+    for (int k = 0; k < 4; ++k)
+      if (first + 4 * k < npiece)
+        slab_load((const AS_GLOBAL __bf16*)y1 + (size_t)(src[k] & 0x7ffffff) * M + ((pos[k] ^ (int)((unsigned)src[k] >> 27)) << 3),
+                  slab + (first + 4 * k) * 512);
+  }
+  int px[NB], ok[NB], row0[NB];
+#pragma unroll
+  for (int i = 0; i < NB; ++i) {
+    const int q = i * 16 + l16, p = small_div(q, a.m_s2), r = q - p * S * S, iy = small_div(r, a.m_s), ix = r - iy * S;
+    const int img = p < ppt ? cells[p * 4] : -1;
+    px[i] = -1;
+    ok[i] = 0;
+    row0[i] = p * T2 + iy * T + ix;
+    if (img >= 0) {
+      const int h = cells[p * 4 + 1] + iy, w = cells[p * 4 + 2] + ix;
+      px[i] = img + h * W + w;
+#pragma unroll
+      for (int tap = 0; tap < 9; ++tap)
+        ok[i] |= (unsigned)(h + tap / 3 - 1) < (unsigned)H && (unsigned)(w + tap % 3 - 1) < (unsigned)W ? 1 << tap : 0;
+    }
+  }
+  slab_ready();
+  l.run(acc, wrs, lane * 16, pair * 2048, M * 64, s0, slab, lg, [&](int i, int tap, int& row, int& key) {
+    const int dy = tap / 3, dx = tap - dy * 3;
+    const bool in = (ok[i] >> tap) & 1;
+    row = in ? row0[i] + dy * T + dx : zrow;
+    key = i * 16 + l16 + dy * S + dx;
+  });
+  slab_reduce<NB, KS>(acc, (AS_LDS float*)smem, wave, lane);
+#pragma unroll
+  for (int i = 0; i < NB; ++i)
+    if ((KS == 1 || i % KS == wave % KS) && px[i] >= 0) slab_store_y(y2 + (size_t)px[i] * M + ch, acc[i]);
+}
+
+// ---- conv3 + residual ------------------------------------------------------------------------------------
+// Rows are the list's pixels, S*S per entry.  (In place, out == x, is safe: a lane reads and writes the same elements.)
+template <int C, int M, int NB>
+__global__ __launch_bounds__(kSlabThreads, 2) void slab_conv3_kernel(SlabArgs a, const __bf16* x, const __bf16* __restrict__ wp,
+                                                                     const float* __restrict__ b3, const __bf16* __restrict__ y2,
+                                                                     __bf16* out, int post_relu) {
+  using L = Slab<M, 1, NB, 1, (M / 32 < 8 ? M / 32 : 8)>;
+  extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
+  __shared__ int rowpx[NB * 16];
+  AS_LDS __bf16* slab = (AS_LDS __bf16*)smem;
+  const int tid = threadIdx.x, lane = tid & 63, l16 = lane & 15, lg = lane >> 4, wave = uni(tid >> 6);
+  int unit, slice;
+  slab_unit(a.nsl, unit, slice);
+  const int S = a.g.S, pair = slice * 4 + wave, ch = pair * 32 + lg * 8;
+  int mine = -1;
+  if (lane < NB * 16) {
+    const int r = unit * NB * 16 + lane, e = r / (S * S), q = r - e * S * S, iy = q / S;
+    const SlabCell c = slab_cell(a, e);
+    if (c.n >= 0) mine = (c.n * a.g.H + c.h + iy) * a.g.W + c.w + q - iy * S;
+  }
+  if (!__any(mine >= 0)) return;
+  if (wave == 0 && lane < NB * 16) rowpx[lane] = mine;
+  // packed in passes of four tiles: two groups of 32 channels
+  const rsrc_t wrs = make_rsrc((g_bf16_p)wp, (unsigned)M * C * 2);
+  const unsigned wbase = (unsigned)(pair >> 1) * (M / 32) * 4096 + (pair & 1) * 2048;
+  L l;
+  l.start(wrs, lane * 16, wbase, 4096, 0);
+  floatx4 acc[NB][2];
+  slab_bias<NB>(acc, b3, ch, true);
+  __syncthreads();
+#pragma unroll
+  for (int u = 0; u < NB * 16 * M * 2 / 4096; ++u) {
+    int row, pos;
+    slab_piece<M>(u * 4 + wave, lane, row, pos);
+    slab_load((const AS_GLOBAL __bf16*)y2 + (size_t)max(rowpx[row], 0) * M + ((pos ^ (row & L::KEYS)) << 3), slab + (u * 4 + wave) * 512);
+  }
+  int px[NB];
+  bf16x8 res[NB];
+#pragma unroll
+  for (int i = 0; i < NB; ++i) {
+    px[i] = rowpx[i * 16 + l16];
+    res[i] = *reinterpret_cast<const AS_GLOBAL bf16x8*>((const AS_GLOBAL __bf16*)x + (size_t)max(px[i], 0) * C + ch);
+  }
+  slab_ready();
+  l.run(acc, wrs, lane * 16, wbase, 4096, 0, slab, lg, [&](int i, int, int& row, int& key) { row = i * 16 + l16; key = l16; });
+  const float floor_ = post_relu ? 0.f : -__builtin_inff();
+#pragma unroll
+  for (int i = 0; i < NB; ++i)
+    if (px[i] >= 0) {
+      bf16x8 o;
+#pragma unroll
+      for (int u = 0; u < 8; ++u) o[u] = (__bf16)fmaxf((float)res[i][u] + acc[i][u / 4][u % 4], floor_);
+      *reinterpret_cast<AS_GLOBAL bf16x8*>((AS_GLOBAL __bf16*)out + (size_t)px[i] * C + ch) = o;
+    }
+}
+
+}  // namespace
+}  // namespace lasnet

@@ -47,6 +47,15 @@ size_t rows_workspace_bytes(int dtype, const Geom& g);
 hipError_t launch_rows(int dtype, const Geom& g, const void* x, const int32_t* idx, const int32_t* count,
                        const BlockWeights& w, void* out, bool post_relu, void* workspace, hipStream_t st);
 
+// The slab schedule (bottleneck_slab.hpp): three launches spread over the chip for a few images of a deep stage.  It reads
+// the same packed weights as the fused and tiled kernels; workspace: 256-byte aligned.
+constexpr size_t kSlabBytes = (size_t)8 << 20;      // most that slab_workspace_bytes() asks for where slab_takes()
+bool slab_takes(const Geom& g);
+size_t slab_workspace_bytes(const Geom& g);
+hipError_t launch_slab(const Geom& g, const void* x, const int32_t* idx, const int32_t* count, const void* packed,
+                       const float* b1, const float* b2, const float* b3, void* out, bool post_relu, void* workspace,
+                       hipStream_t st);
+
 // One matrix-core instantiation: its shape and its two launchers.
 struct MfmaVariant {
   int C, M, S;

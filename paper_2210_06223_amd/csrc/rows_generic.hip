@@ -1,34 +1,8 @@
 // The row schedule for every shape and type without a matrix-core kernel of its own: fp32, and bf16 at any width.
 #include "bottleneck_rows.hpp"
 
-#include <type_traits>
-
 namespace lasnet {
 namespace {
-
-// How a convolution is cut: NB row blocks per wave, KS waves to a tile's reduction, nsl channel slices per row tile.
-// 1024 waves are one per SIMD.  More rows per wave read the weights less often, so NB is as large as leaves the chip
-// that many tiles; with fewer even at NB = 1 the waves of a workgroup share a tile's reduction.
-struct RowsCut { int nb, ks, units, nsl; };
-RowsCut rows_cut(long long rows_max, long long rows_expected, int pairs, int ksteps) {
-  RowsCut c;
-  c.nb = 4;
-  while (c.nb > 1 && (rows_expected + 16 * c.nb - 1) / (16 * c.nb) * pairs < 1024) c.nb /= 2;
-  const long long tiles = (rows_expected + 16 * c.nb - 1) / (16 * c.nb);
-  c.ks = tiles * pairs < 1024 && ksteps >= 8 ? 4 : 1;
-  c.units = (int)((rows_max + 16 * c.nb - 1) / (16 * c.nb));
-  const int wc = 4 / c.ks, most = (pairs + wc - 1) / wc;
-  c.nsl = (int)((1024 + tiles - 1) / tiles);
-  if (c.nsl > most) c.nsl = most;
-  return c;
-}
-
-#define ROWS_DISPATCH(c, CALL)                                             \
-  if (c.ks == 4) {                                                         \
-    if (c.nb == 1) CALL(1, 4); else if (c.nb == 2) CALL(2, 4); else CALL(4, 4); \
-  } else {                                                                 \
-    if (c.nb == 1) CALL(1, 1); else if (c.nb == 2) CALL(2, 1); else CALL(4, 1); \
-  }
 
 template <class F, bool VEC>
 hipError_t run_rows(const Geom& g, const void* x, const int32_t* idx, const int32_t* count, const BlockWeights& w, void* out,
@@ -49,6 +23,10 @@ hipError_t run_rows(const Geom& g, const void* x, const int32_t* idx, const int3
   a.idx = idx;
   a.count = count;
   a.need = idx ? need : nullptr;
+  constexpr unsigned kStep = 2 * F::KPL * 1024;
+  a.w1 = RowsWeights{a.ks1 * kStep, 0, kStep, 30};
+  a.w2 = RowsWeights{9 * a.ksm * kStep, 0, kStep, 30};
+  a.w3 = RowsWeights{a.ksm * kStep, 0, kStep, 30};
   a.w1_bytes = (unsigned)l.w1;
   a.w2_bytes = (unsigned)l.w2;
   a.w3_bytes = (unsigned)l.w3;
@@ -63,24 +41,8 @@ hipError_t run_rows(const Geom& g, const void* x, const int32_t* idx, const int3
     if (pack_blocks + need_blocks > 0)
       hipLaunchKernelGGL(rows_plan_kernel<F>, dim3(pack_blocks + need_blocks), dim3(kRowsThreads), 0, st, a, pack_blocks,
                          (const T*)w.W1, (const T*)w.W2, (const T*)w.W3, wp1, need);
-    // the list's rows of this chunk are not known here: half of the pixels is a middling activation ratio
-    const long long rows = (long long)g.P * g.S * g.S, likely = idx ? (a.npx + 1) / 2 : a.npx;
-    RowsCut c = rows_cut(a.npx, a.npx, a.pairs1, a.ks1);
-#define ROWS_CONV1(NB, KS)                                                                                               \
-  hipLaunchKernelGGL((rows_conv1_kernel<F, VEC, NB, KS>), dim3(rows_grid(c.units, c.nsl)), dim3(kRowsThreads), 0, st, a, \
-                     c.nsl, (const T*)x, wp1, w.b1, y1)
-    ROWS_DISPATCH(c, ROWS_CONV1)
-    c = rows_cut(rows, likely, a.pairs1, 9 * a.ksm);
-#define ROWS_CONV2(NB, KS)                                                                                               \
-  hipLaunchKernelGGL((rows_conv2_kernel<F, NB, KS>), dim3(rows_grid(c.units, c.nsl)), dim3(kRowsThreads), 0, st, a,      \
-                     c.nsl, wp2, w.b2, y1, y2)
-    ROWS_DISPATCH(c, ROWS_CONV2)
-    c = rows_cut(rows, likely, a.pairs3, a.ksm);
-#define ROWS_CONV3(NB, KS)                                                                                               \
-  hipLaunchKernelGGL((rows_conv3_kernel<F, VEC, NB, KS>), dim3(rows_grid(c.units, c.nsl)), dim3(kRowsThreads), 0, st, a, \
-                     c.nsl, (const T*)x, wp3, w.b3, y2, (T*)out, (int)post_relu)
-    ROWS_DISPATCH(c, ROWS_CONV3)
-    if (hipError_t e = hipGetLastError(); e != hipSuccess) return e;
+    if (hipError_t e = launch_rows_convs<F, VEC>(a, x, wp1, wp2, wp3, w.b1, w.b2, w.b3, y1, y2, out, post_relu, st); e != hipSuccess)
+      return e;
   }
   return hipSuccess;
 }
