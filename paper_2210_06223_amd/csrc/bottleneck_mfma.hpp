@@ -48,7 +48,7 @@ constexpr int pow2_at_least(int v) { int p = 1; while (p < v) p *= 2; return p; 
 // wave grid of conv i.  RD2/RD3: k-steps of weights a wave keeps in flight in conv2/conv3.
 // NB3: channel tiles per conv3 pass.
 template <int C_, int M_, int S_, int PPW_, int R1MAX_, int NW_, int KC_, int NSTG_, int WR1_,
-          int WC1_, int WR2_, int WC2_, int RD2_, int WR3_, int WC3_, int NB3_, int RD3_>
+          int WC1_, int WR2_, int WC2_, int RD2_, int WR3_, int WC3_, int NB3_, int RD3_, bool Y1X_ = false>
 struct Cfg {
   static constexpr int C = C_, M = M_, S = S_, PPW = PPW_, NW = NW_, KC = KC_, NSTG = NSTG_;
   static constexpr int NT = NW * 64;
@@ -60,7 +60,7 @@ struct Cfg {
   static constexpr int WR3 = WR3_, WC3 = WC3_, NBT3 = C / 16 / WC3, NB3 = NB3_, RD3 = RD3_;
   static constexpr int R2 = PPW * S * S;
   static constexpr int R2B = roundup(cdiv(R2, 16), cmax(WR2, WR3)), R2P = R2B * 16;
-  static constexpr int NB3ROWS = 4 * WR3;              // row blocks conv3 takes at a time
+  static constexpr int NB3ROWS = (Y1X_ ? 2 : 4) * WR3;  // row blocks conv3 takes at a time (it holds their accumulators and residuals)
   // LDS rows have power-of-two pitch and their 16-byte chunks are XOR-swizzled (see swz()):
   // measured on gfx950, ds_read_b128 then runs at ~6 clk per wave against ~9 with a padded pitch.
   static constexpr int LDX = KC, LDY = M;
@@ -70,7 +70,7 @@ struct Cfg {
   static constexpr int LDY2 = LDY, YMASK2 = YMASK;     // pitch / key bits of the y2 rows conv2 writes
   // the packed weight buffers: bytes from one k-step's fragments to the next, and sizes
   static constexpr int WD = 2;                         // conv1's weight ring, in chunks
-  static constexpr bool Y1_IN_XS = false;              // y1s is a region of its own
+  static constexpr bool Y1_IN_XS = Y1X_;               // y1 takes the place of the x stages when conv1 has read them
   static constexpr bool ACTS_BARRIER = false;          // conv2 / conv3 find their LDS inputs complete on entry
   static constexpr bool Y1_TO_GLOBAL = false, Y2_TO_GLOBAL = false;   // conv1 / conv2 results stay in LDS
   static constexpr int W_KSTEP_BYTES = M * 64;
@@ -87,11 +87,12 @@ struct Cfg {
   static constexpr int OFF_BIAS = (OFF_CELL + PPW * 4 + 15) / 16 * 16;   // float[M | M | C]: b1, b2, b3
   static constexpr int OFF_Y1 = OFF_BIAS + (2 * M + C) * 4;
   static constexpr int Y1_BYTES = (R1MAX + 1) * LDY * 2;
-  static constexpr int OFF_XS = OFF_Y1 + Y1_BYTES;
+  static constexpr int OFF_XS = Y1_IN_XS ? OFF_Y1 : OFF_Y1 + Y1_BYTES;
   static constexpr int STAGE_ELEMS = R1MAX * LDX;
   static constexpr int XS_BYTES = NSTG * STAGE_ELEMS * 2 + 1024;  // + 1 KiB that padding loads land in
   static constexpr int Y2_BYTES = R2P * LDY * 2;
-  static constexpr int LDS_BYTES = OFF_XS + cmax(XS_BYTES, Y2_BYTES);
+  static constexpr int OFF_Y2 = Y1_IN_XS ? OFF_XS + Y1_BYTES : OFF_XS;              // xs is dead once conv1 is done
+  static constexpr int LDS_BYTES = cmax(OFF_XS + XS_BYTES, OFF_Y2 + Y2_BYTES);
   static constexpr size_t PACKED_ELEMS = (size_t)M * C * 2 + 9 * (size_t)M * M;
   static_assert(R1MAX % 16 == 0 && R1MAX >= WW && R1MAX < 32767, "y1 rows");
   static_assert(R1B % WR1 == 0, "conv1 row blocks split evenly over the wave rows");
@@ -823,7 +824,7 @@ __global__ __launch_bounds__(K::NT, K::WAVES_PER_SIMD) void fused_bneck_kernel(
   float* b3s = b2s + K::M;
   __bf16* y1s = reinterpret_cast<__bf16*>(smem + K::OFF_Y1);
   __bf16* xs = reinterpret_cast<__bf16*>(smem + K::OFF_XS);
-  __bf16* y2s = xs;                                        // xs is dead once conv1 is done
+  __bf16* y2s = reinterpret_cast<__bf16*>(smem + K::OFF_Y2);
 
   constexpr int S = K::S, T = K::T, WW = K::WW;
   const int tid = threadIdx.x;
@@ -853,9 +854,11 @@ __global__ __launch_bounds__(K::NT, K::WAVES_PER_SIMD) void fused_bneck_kernel(
   const int tb = xb + jx * len0 + min(jx, extra);
   const int te = tb + len0 + (jx < extra ? 1 : 0);
 
-  // the all-zero y1 row
-  for (int i = tid; i < K::LDY / 8; i += K::NT)
-    *reinterpret_cast<uint4*>(y1s + K::ZROW * K::LDY + i * 8) = uint4{0, 0, 0, 0};
+  const auto zero_row = [&] {                              // the all-zero y1 row
+    for (int i = tid; i < K::LDY / 8; i += K::NT)
+      *reinterpret_cast<uint4*>(y1s + K::ZROW * K::LDY + i * 8) = uint4{0, 0, 0, 0};
+  };
+  if constexpr (!K::Y1_IN_XS) zero_row();
   // the biases go to LDS: requested here, stored once the first batch's cell ids (requested next)
   // have been waited for anyway
   constexpr int NBV = cdiv(2 * K::M + K::C, K::NT);
@@ -961,6 +964,7 @@ __global__ __launch_bounds__(K::NT, K::WAVES_PER_SIMD) void fused_bneck_kernel(
       conv1_phase<K, decltype(nb)::value * K::WR1>((g_bf16_p)x, (g_bf16_p)W1, (l_f32_cp)b1s, (l_i32_cp)rowpix,
                                                    (l_bf16_p)xs, (l_bf16_p)y1s, opaque(tid), wave, tables);
     });
+    if constexpr (K::Y1_IN_XS) zero_row();                 // (the x stages have been over it)
     __syncthreads();
     constexpr int WR23 = K::WR2 > K::WR3 ? K::WR2 : K::WR3;
     // conv2 and conv3 share one dispatch on the block count: conv3's first residual is requested at the
@@ -1063,7 +1067,8 @@ hipError_t launch_one(const Geom& g, const void* x, const int32_t* idx, const in
                       void* out, bool post_relu, hipStream_t st) {
   auto k = fused_bneck_kernel<K>;
   if (hipError_t e = prepare_one<K>(); e != hipSuccess) return e;
-  const int slots = device_cu_count() * ((160 * 1024) / K::LDS_BYTES);
+  // the list is cut for two workgroups per CU also where three fit (tiles for three: 5 % slower at 56x56x256)
+  const int fit = (160 * 1024) / K::LDS_BYTES, slots = device_cu_count() * (fit > 2 ? 2 : fit);
   int grid = (g.P + K::PPW - 1) / K::PPW;
   grid = (grid + slots - 1) / slots * slots;
   if (grid > g.P) grid = g.P;

@@ -5,13 +5,16 @@
 namespace lasnet {
 namespace {
 //             C     M   S PPW R1MAX NW KC NSTG conv1  conv2 RD2  conv3 NB3 RD3
-// Two 4-wave workgroups per CU (see stage 2); x is only 4 chunks of 64 channels deep, so all of a
-// batch's x is requested at once (NSTG = 4).
+// What bounds the block is latency: a batch's x is 4 chunks of 64 channels, its weights 137 KB, its MFMAs 2 us of the 13
+// that it takes.  So y1 takes the place of the x stages when conv1 has read them and conv3 takes the rows in groups of
+// two blocks, which lets three 4-wave workgroups run on a CU (<= 53 KB of LDS, 168 registers) instead of two.
+// Block alone, us, two -> three: S=4, batch 64, r=0.5 45.4 -> 37.8; S=2 60.2 -> 48.0; S=1, batch 32 52.7 -> 40.9; S=7 47.0 ->
+// 38.7; S=4, batch 256, r=0.4 in one region per image 149.8 -> 129.2.
 using K_s1 = Cfg<256, 64, 8, 1, 112, 4, 64, 4, 1, 4, 1, 4, 6, 1, 4, 4, 2>;       // S=8
-using K_s1s4 = Cfg<256, 64, 4, 4, 112, 4, 64, 4, 1, 4, 1, 4, 6, 1, 4, 4, 2>;     // S=4 (the block of Table 1)
-using K_s1s7 = Cfg<256, 64, 7, 1, 96, 4, 64, 4, 1, 4, 1, 4, 6, 1, 4, 4, 2>;      // S=7 (dense tile)
-using K_s1s2 = Cfg<256, 64, 2, 8, 112, 4, 64, 4, 1, 4, 1, 4, 6, 1, 4, 4, 2>;     // S=2
-using K_s1s1 = Cfg<256, 64, 1, 16, 112, 4, 64, 4, 1, 4, 1, 4, 6, 1, 4, 4, 2>;    // S=1 (pixel level)
+using K_s1s4 = Cfg<256, 64, 4, 4, 112, 4, 64, 3, 1, 4, 1, 4, 6, 1, 4, 4, 2, true>;     // S=4 (the block of Table 1)
+using K_s1s7 = Cfg<256, 64, 7, 1, 96, 4, 64, 3, 1, 4, 1, 4, 6, 1, 4, 4, 2, true>;      // S=7 (dense tile)
+using K_s1s2 = Cfg<256, 64, 2, 8, 112, 4, 64, 3, 1, 4, 1, 4, 6, 1, 4, 4, 2, true>;     // S=2
+using K_s1s1 = Cfg<256, 64, 1, 16, 112, 4, 64, 3, 1, 4, 1, 4, 6, 1, 4, 4, 2, true>;    // S=1 (pixel level)
 }  // namespace
 
 // S=8 runs on the streaming, weight-stationary kernel; it reads the buffer that K_s1's packing
