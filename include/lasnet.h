@@ -174,9 +174,10 @@ LASNET_API int lasnet_sparse_bottleneck_ex(const lasnet_tensor* x, const int32_t
  *   slab   the same split in smaller pieces, for a few images of 1024x256 and 2048x512 channels (up to 16
  *          14x14 images' worth of pixels, 32 with patches of S = 7, 40 7x7 images'): the fused kernel would
  *          leave most of the GPU idle there.  It needs at most 8 MiB for y1 and y2, from where the tiled one takes
- *          its own (a lasnet_workspace_bytes() buffer is large enough); without them -- a stream under
- *          capture whose buffer is not there yet, lasnet_sparse_bottleneck_planned without a workspace -- the
- *          fused or tiled schedule runs as it would for more images.
+ *          its own (a lasnet_workspace_bytes() buffer is large enough); without them --
+ *          lasnet_sparse_bottleneck_planned without a workspace, and 1024x256 under capture except in
+ *          lasnet_sparse_bottleneck_planned and _noalloc, because a graph may be replayed beside later calls on
+ *          the stream whose buffer it would use -- the fused or tiled schedule runs as it would for more images.
  * Results are the same function of the inputs either way (same roundings: y1, y2 to bf16, out once).
  * The tiled schedule needs lasnet_workspace_bytes() of device memory (that query answers for every
  * shape that has a tiled schedule, chosen by default or not; 0 = none): lasnet_sparse_bottleneck[_ex],
@@ -197,8 +198,8 @@ LASNET_API size_t lasnet_workspace_bytes(int dtype, int N, int H, int W, int C, 
  * least twice as large, so what is left behind never exceeds what is in use); all are kept until
  * the process ends.  So those entry points cannot be stream-captured before the stream's buffer has its
  * final size.  Shapes and types without a matrix-core kernel of their own (all of fp32) keep y1 and y2 there as
- * well, at most 256 MiB of them at a time; where that memory cannot be had (under capture, for one)
- * they run a slower kernel that needs none.
+ * well, at most 256 MiB of them at a time; where that memory cannot be had, and under capture, they run a
+ * slower kernel that needs none.
  * Weights of an inference model do not change, so a caller can instead
  * repack once, like it folded BN once (Sec. 3.4), and pass the result to
  * lasnet_sparse_bottleneck_packed, which allocates nothing:

@@ -24,6 +24,14 @@ std::map<std::tuple<int, hipStream_t, std::thread::id>, Workspace> g_ws;
 
 struct Lease { std::unique_lock<std::mutex> lock; void* ptr = nullptr; };
 
+// (also where the runtime will not say: it does not while another stream's capture forbids work on the null stream)
+bool capturing(hipStream_t st) {
+  hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
+  if (hipStreamIsCapturing(st, &cap) == hipSuccess) return cap != hipStreamCaptureStatusNone;
+  (void)hipGetLastError();
+  return true;
+}
+
 // lease.ptr stays nullptr where the memory cannot be had: the device is full, or the buffer would have to grow
 // while the stream is being captured.
 void get_workspace(Lease& lease, hipStream_t st, size_t bytes) {
@@ -34,13 +42,9 @@ void get_workspace(Lease& lease, hipStream_t st, size_t bytes) {
     std::lock_guard<std::mutex> lock(g_ws_mu);
     w = &g_ws[std::make_tuple(dev, st, st == hipStreamPerThread ? std::this_thread::get_id() : std::thread::id())];
   }
-  lease.lock = std::unique_lock<std::mutex>(w->mu);
+  if (!lease.lock.owns_lock()) lease.lock = std::unique_lock<std::mutex>(w->mu);
   if (w->cap < bytes) {
-    hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
-    if (hipStreamIsCapturing(st, &cap) != hipSuccess || cap != hipStreamCaptureStatusNone) {
-      (void)hipGetLastError();
-      return;
-    }
+    if (capturing(st)) return;
     if (bytes < 2 * w->cap) bytes = 2 * w->cap;
     void* p = nullptr;
     if (hipMalloc(&p, bytes) != hipSuccess) {
@@ -190,7 +194,6 @@ int run_block(const lasnet_tensor* x, const int32_t* idx, const int32_t* count, 
   // A few images of a deep stage run the slab schedule (in place it is as safe as the tiled one: neighbours are read by
   // its first kernel, out is written by its last).
   bool slab = fast && !(flags & (LASNET_FORCE_FUSED | LASNET_FORCE_TILED)) && slab_takes(g);
-  const size_t slab_need = slab ? slab_workspace_bytes(g) : 0;
   const size_t packed_need = (fast && !packed) ? round256(mfma_packed_bytes(x->c, M, S)) : 0;
   const size_t tiled_need = tiled ? tiled->workspace_bytes(g) : 0;
   if (pad.from_caller && tiled && (!pad.workspace || pad.workspace_bytes < tiled_need || ((uintptr_t)pad.workspace & 255)))
@@ -200,6 +203,12 @@ int run_block(const lasnet_tensor* x, const int32_t* idx, const int32_t* count, 
 
   const BlockWeights w{W1, b1, W2, b2, W3, b3};
   hipStream_t st = (hipStream_t)stream;
+  // A captured graph may be replayed on any stream, beside this one's later calls: what would take the library's buffer
+  // only to be faster leaves it alone there and records the kernels that need none.
+  const bool own_memory = pad.from_caller || pad.fixed_array;
+  const bool may_lease = own_memory || tiled || (fast && !slab) || !capturing(st);
+  if (!may_lease) slab = false;
+  const size_t slab_need = slab ? slab_workspace_bytes(g) : 0;
   // Everything that can fail on the host comes before the first launch: kernel attributes, then the
   // memory for the repacked weights and the tiled schedule's intermediates (the caller's, the
   // library's per stream, or `scratch`).
@@ -208,7 +217,7 @@ int run_block(const lasnet_tensor* x, const int32_t* idx, const int32_t* count, 
   unsigned char* block_ws = nullptr;             // the tiled or the slab schedule's
   // Without a matrix-core kernel of its own the shape runs the row schedule; where there is no memory for that (the
   // caller forbids it, a capture is under way, the map is too large), the one-kernel generic path.
-  const size_t rows_need = !fast && !pad.fixed_array && !pad.from_caller ? rows_workspace_bytes(x->dtype, g) : 0;
+  const size_t rows_need = !fast && !own_memory && may_lease ? rows_workspace_bytes(x->dtype, g) : 0;
   void* rows_ws = nullptr;
   Lease lease;
   if (pad.from_caller) {
@@ -228,9 +237,12 @@ int run_block(const lasnet_tensor* x, const int32_t* idx, const int32_t* count, 
     rows_ws = lease.ptr;
   } else if (packed_need + tiled_need + slab_need) {
     get_workspace(lease, st, packed_need + (tiled_need > slab_need ? tiled_need : slab_need));
+    if (!lease.ptr && slab) {                    // (the device is full: what the other schedule needs may still be there)
+      slab = false;
+      if (packed_need + tiled_need) get_workspace(lease, st, packed_need + tiled_need);
+    }
     unsigned char* ws = (unsigned char*)lease.ptr;
     if (!ws && packed_need + tiled_need) return LASNET_EHIP;
-    if (!ws) slab = false;                      // (under capture, for one: the fused kernel needs none)
     if (packed_need) {
       e = launch_pack(x->c, M, S, W1, W2, W3, ws, st);
       if (e != hipSuccess) return LASNET_EHIP;

@@ -53,9 +53,10 @@ def test_chunks_of_images_match_single_images():
         assert np.array_equal(U.bits(got[n:n + 1]), U.bits(want)), n
 
 
-def test_capture_on_a_stream_without_workspace():
-    """Under capture nothing is allocated: the one-kernel path is recorded instead (its fp32 sums run in another order,
-    K <= 9 * 24 terms of 6e-8 each)."""
+@pytest.mark.parametrize("warm", [False, True])
+def test_capture_uses_no_workspace(warm):
+    """Under capture nothing is allocated, and a buffer that the stream has is left to its later calls: the one-kernel path is
+    recorded instead (its fp32 sums run in another order, K <= 9 * 24 terms of 6e-8 each), which is the noalloc entry's."""
     cfg = synth.BlockConfig("captured", 2, 8, 8, 48, 24, 4, "f32", 0.5, 72)
     d = U.dev_inputs(synth.make_block_inputs(cfg, want_f64=False))
     w = U.weights(d)
@@ -63,8 +64,14 @@ def test_capture_on_a_stream_without_workspace():
     idx, count = U.list_tensor(il, cfg.P), torch.tensor([len(il)], dtype=torch.int32, device="cuda")
     want = _call(d["x"], idx, count, cfg.S, w)
     out = torch.empty_like(d["x"])
-    graph = torch.cuda.CUDAGraph()
-    with torch.cuda.graph(graph, stream=torch.cuda.Stream()):
+    same = B.lasnet_sparse_bottleneck_noalloc(d["x"], idx, count, cfg.S, *w, out=torch.empty_like(d["x"]))
+    side, graph = torch.cuda.Stream(), torch.cuda.CUDAGraph()
+    torch.cuda.synchronize()
+    if warm:
+        with torch.cuda.stream(side):
+            B.lasnet_sparse_bottleneck(d["x"], idx, count, cfg.S, *w, out=out)
+        torch.cuda.synchronize()
+    with torch.cuda.graph(graph, stream=side):
         B.lasnet_sparse_bottleneck(d["x"], idx, count, cfg.S, *w, out=out)
     for _ in range(3):
         out.fill_(777.0)
@@ -72,3 +79,4 @@ def test_capture_on_a_stream_without_workspace():
         torch.cuda.synchronize()
         err = (out - want).abs().max().item()
         assert err <= 2e-5 * want.abs().max().item(), err
+        assert np.array_equal(U.bits(out), U.bits(same))

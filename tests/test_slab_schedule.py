@@ -52,8 +52,11 @@ def test_slab_matches_the_other_schedules(name, N, S, r):
     assert rel <= 2.0 ** -8, rel
 
 
-def test_captured_before_and_after_the_workspace_exists():
-    """A stream whose workspace does not exist yet records the fused kernel, one that has it the slab launches; both replay."""
+@pytest.mark.parametrize("raw", [False, True], ids=["packed", "raw"])
+def test_capture_leaves_the_library_buffer_alone(raw):
+    """A graph may be replayed on any stream, beside later calls on the one it was captured on, so the fused kernel is recorded
+    whether or not the stream has a buffer that the slab launches fit in.  (Raw weights are repacked into that buffer: there
+    it is as large as a call that ran the fused kernel made it, which has to be enough.)"""
     cfg = _cfg("stage3_b128", N=2, name="s3_captured")
     d = U.dev_inputs(synth.make_block_inputs(cfg, want_f64=False))
     il = synth.make_index_list(cfg.N, cfg.G, cfg.GW, 0.5, seed=3)
@@ -62,16 +65,20 @@ def test_captured_before_and_after_the_workspace_exists():
     side = torch.cuda.Stream()
 
     def call(out, flags=0):
-        B.lasnet_sparse_bottleneck_packed(d["x"], idx, count, cfg.S, cfg.M, packed, d["b1"], d["b2"], d["b3"], out=out, flags=flags)
+        if raw:
+            B.lasnet_sparse_bottleneck(d["x"], idx, count, cfg.S, *U.weights(d), out=out, flags=flags)
+        else:
+            B.lasnet_sparse_bottleneck_packed(d["x"], idx, count, cfg.S, cfg.M, packed, d["b1"], d["b2"], d["b3"], out=out, flags=flags)
 
-    torch.cuda.synchronize()
-    for flags in (B.LASNET_FORCE_FUSED, 0):
-        want, out = torch.empty_like(d["x"]), torch.empty_like(d["x"])
-        if flags == 0:
-            with torch.cuda.stream(side):
-                call(torch.empty_like(d["x"]))
-        call(want, flags)
+    want = torch.empty_like(d["x"])
+    call(want, B.LASNET_FORCE_FUSED)
+    for warm in ((B.LASNET_FORCE_FUSED, 0) if raw else (None, 0)):
+        out = torch.empty_like(d["x"])
         torch.cuda.synchronize()
+        if warm is not None:
+            with torch.cuda.stream(side):
+                call(torch.empty_like(d["x"]), warm)
+            torch.cuda.synchronize()
         graph = torch.cuda.CUDAGraph()
         with torch.cuda.graph(graph, stream=side):
             call(out)
@@ -79,4 +86,4 @@ def test_captured_before_and_after_the_workspace_exists():
             out.fill_(777.0)
             graph.replay()
             torch.cuda.synchronize()
-            assert np.array_equal(U.bits(out), U.bits(want)), flags
+            assert np.array_equal(U.bits(out), U.bits(want)), warm
