@@ -62,6 +62,29 @@ def window_pixels(cells: Iterable[Tuple[int, int, int]], S: int, H: int, W: int)
     return out
 
 
+def fused_runs(nact: int, P: int, PPW: int, slots: int) -> List[Tuple[int, int]]:
+    """Per workgroup of fused_bneck_kernel, in launch order, its run of the list (first entry, one past the last)."""
+    nt = -(-nact // PPW)
+    nt = -(-nt // slots) * slots
+    grid = -(-P // PPW)
+    grid = min(-(-grid // slots) * slots, P)
+    nt = min(nt, grid, nact)
+    out = []
+    for b in range(nt):
+        q = b // slots * slots                                  # the round: its part of the list, the last part first
+        nr, hi = min(slots, nt - q), nact - q * nact // nt
+        lo = nact - (q + nr) * nact // nt
+        xcd, jx = (b - q) & 7, (b - q) >> 3
+        first = xcd * (nr >> 3) + min(xcd, nr & 7)
+        runs = (nr >> 3) + (1 if xcd < (nr & 7) else 0)
+        xb, xe = lo + first * (hi - lo) // nr, lo + (first + runs) * (hi - lo) // nr
+        len0 = (xe - xb) // runs
+        extra = (xe - xb) - len0 * runs
+        tb = xb + jx * len0 + min(jx, extra)
+        out.append((tb, tb + len0 + (1 if jx < extra else 0)))
+    return out
+
+
 def simulate_fused(idx: np.ndarray, N: int, H: int, W: int, C: int, M: int, S: int) -> List[List[Tuple[int, int]]]:
     """How fused_bneck_kernel cuts the list: per workgroup (in launch order) its batches as
     (conv1 blocks, conv2/conv3 blocks)."""
@@ -72,23 +95,10 @@ def simulate_fused(idx: np.ndarray, N: int, H: int, W: int, C: int, M: int, S: i
     nact = len(idx)
     if nact == 0:
         return []
-    nt = -(-nact // PPW)
-    nt = -(-nt // slots) * slots
-    grid = -(-(N * G * GW) // PPW)
-    grid = min(-(-grid // slots) * slots, N * G * GW)
-    nt = min(nt, grid, nact)
     n, gy, gx = _cells(idx, G, GW)
     cells = list(zip(n.tolist(), gy.tolist(), gx.tolist()))
     wgs = []
-    for b in range(nt):
-        xcd, jx = b & 7, b >> 3
-        first = xcd * (nt >> 3) + min(xcd, nt & 7)
-        runs = (nt >> 3) + (1 if xcd < (nt & 7) else 0)
-        xb, xe = first * nact // nt, (first + runs) * nact // nt
-        len0 = (xe - xb) // runs
-        extra = (xe - xb) - len0 * runs
-        tb = xb + jx * len0 + min(jx, extra)
-        te = tb + len0 + (1 if jx < extra else 0)
+    for tb, te in fused_runs(nact, N * G * GW, PPW, slots):
         batches = []
         e0 = tb
         while e0 < te:

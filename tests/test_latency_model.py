@@ -26,6 +26,15 @@ def test_replay_of_the_fused_kernels_work_split():
     assert LM.simulate_fused(np.zeros(0, np.int32), cfg.N, cfg.H, cfg.W, cfg.C, cfg.M, cfg.S) == []
 
 
+def test_runs_of_several_rounds_cover_the_list_once():
+    """Whatever the remainders, and with no run that needs a second batch."""
+    for nact, P, PPW, slots in ((50176, 50176, 4, 512), (20071, 50176, 4, 512), (513, 600, 1, 512), (1025, 1027, 1, 512), (8193, 9000, 16, 512),
+                                (6271, 6272, 16, 256), (4099, 6272, 4, 256), (511, 6272, 4, 512), (7, 49, 32, 256), (1, 1, 4, 512)):
+        spans = LM.fused_runs(nact, P, PPW, slots)
+        assert sorted(i for a, b in spans for i in range(a, b)) == list(range(nact)), (nact, P)
+        assert max(b - a for a, b in spans) <= PPW and min(b - a for a, b in spans) >= 1, (nact, P)
+
+
 def test_window_pixels_counts():
     assert len(LM.window_pixels([(0, 0, 0)], 2, 14, 14)) == 9          # corner patch: 3 x 3 in the image
     assert len(LM.window_pixels([(0, 3, 3)], 2, 14, 14)) == 16         # interior: 4 x 4
