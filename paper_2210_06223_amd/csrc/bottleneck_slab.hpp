@@ -11,21 +11,21 @@
 // count, the list entries (requested together with the count: the list has storage for every cell) and its first
 // weights at once; then its whole activation operand -- every row over the full reduction, conv2's with all nine
 // taps -- as one burst of direct global->LDS loads; then the reduction from LDS, with weights D k-steps ahead in registers.
-// The four waves of a workgroup share the slab: 4 / KS of them take different groups of 32 channels, and KS of them split
-// the reduction (partial sums added through LDS in a fixed order), so that few rows still make many waves.
+// The waves of a workgroup (NW) share the slab and take TJ tiles of 16 channels each: four waves with a group of 32 channels
+// (TJ = 2) where there are many rows, four or two with half a group each where there are few.  A wave sums over the whole
+// reduction, in the order of the fused and the tiled kernels: splitting it over the waves gave other bits than theirs (a relative
+// 2.6e-4 of the output, from roundings of y1 and y2 that flip).
 //
-// Measured (block alone): 14x14x1024, S=2, one image 20.9 -> 14.4 us (conv1 3.4, conv2 6.6, conv3 3.2 of them on the GPU:
-// the launches are the bound), 16 images 24.7 -> 18.8; S=7, 24 images 32.8 -> 23.6; 7x7x2048, one image 35 -> 18 us, 40
-// images 54 -> 34.  In conv2 the chain of accesses takes about 3 us; past that a CU streams its weights.
+// Measured (the block's three launches on the GPU, against the schedule that ran before): 14x14x1024, S=2, one image 20.9 -> 10.6 us,
+// 16 images 23.9 -> 17.4; S=7, 24 images 32.4 -> 24.4; 7x7x2048, one image 34 -> 20.5 us, 40 images 55 -> 33.  In conv2 the chain
+// of accesses takes about 3 us; past that a CU streams its weights.
 //
-// Rounding points, weight layout (lasnet_pack_weights') and results are the fused kernel's, up to the order of the sums.
+// Rounding points, order of the sums, weight layout (lasnet_pack_weights') and results are the fused kernel's, bit for bit.
 #pragma once
 #include "bottleneck_mfma.hpp"
 
 namespace lasnet {
 namespace {
-
-constexpr int kSlabThreads = 256;
 
 struct SlabArgs {
   Geom g;
@@ -56,71 +56,80 @@ __device__ __forceinline__ void slab_ready() {
   __builtin_amdgcn_sched_barrier(0);
 }
 
-// One convolution's reduction: K channels per tap, TAPS taps, split over KS waves; a wave keeps D k-steps of weights in flight.
+// One convolution's reduction: K channels per tap, TAPS taps, TJ tiles of output channels; D k-steps of weights in flight.
 // The slab is rows of K channels whose 16-byte chunks are XOR-swizzled with the row's key, so that the 16 rows that a
 // fragment read touches lie in different banks.
-template <int K, int TAPS, int NB, int KS, int D>
+template <int K, int TAPS, int NB, int TJ, int D>
 struct Slab {
-  static constexpr int MS = K / 32, NST = TAPS * MS / KS;
-  static_assert(TAPS * MS % KS == 0 && NST % D == 0, "whole rings");
+  static constexpr int MS = K / 32, NST = TAPS * MS;
+  static_assert(NST % D == 0, "whole rings");
   static constexpr int KEYS = K / 8 - 1 < 15 ? K / 8 - 1 : 15;
-  static constexpr int PART_BYTES = KS > 1 ? 4 * NB * 2 * 1024 : 0;              // partial sums (over the slab, when it is dead)
-  bf16x8 w[D][2];
+  bf16x8 w[D][TJ];
 
   __device__ __forceinline__ void fetch(rsrc_t wrs, int lane16, unsigned base, unsigned step, int slot, int s) {
 #pragma unroll
-    for (int j = 0; j < 2; ++j) w[slot][j] = buf_load16(wrs, lane16 + j * 1024, (int)(base + (unsigned)s * step));
+    for (int j = 0; j < TJ; ++j) w[slot][j] = buf_load16(wrs, lane16 + j * 1024, (int)(base + (unsigned)s * step));
   }
-  // the first D k-steps of this wave's share
-  __device__ __forceinline__ void start(rsrc_t wrs, int lane16, unsigned base, unsigned step, int s0) {
+  // the first D k-steps
+  __device__ __forceinline__ void start(rsrc_t wrs, int lane16, unsigned base, unsigned step) {
 #pragma unroll
-    for (int d = 0; d < D; ++d) fetch(wrs, lane16, base, step, d, s0 + d);
+    for (int d = 0; d < D; ++d) fetch(wrs, lane16, base, step, d, d);
   }
   // where(i, tap, row, key): slab row of the lane's row in block i
   template <class Where>
-  __device__ __forceinline__ void run(floatx4 (&acc)[NB][2], rsrc_t wrs, int lane16, unsigned base, unsigned step, int s0,
+  __device__ __forceinline__ void run(floatx4 (&acc)[NB][TJ], rsrc_t wrs, int lane16, unsigned base, unsigned step,
                                       const AS_LDS __bf16* slab, int lg, Where&& where) {
-    // k-steps are read in order; the rows' addresses change with the tap only (one wave per SIMD issues an
-    // instruction every four clocks at best: worked out for every k-step, they took longer than the MFMAs)
-    int at[NB], key[NB];
-    unsigned cur = (unsigned)s0;
-    auto enter = [&](int tap) {
+    // One wave per SIMD issues an instruction every four clocks at best, and a k-step has as few as one MFMA of 16, so it may
+    // hold little else: the swizzle flips bits 4 .. 7 of a chunk's byte offset, so four addresses per row (k-steps 0 .. 3 of
+    // a tap) serve the others through the immediate offset.  (With the address worked out for every k-step, a k-step took 85 to
+    // 100 clocks: 14x14x1024, S=2, one image 13.1 us; so 10.4.)
+    const AS_LDS char* at[NB][4];
+    int tap = 0;
+    auto enter = [&] {
 #pragma unroll
       for (int i = 0; i < NB; ++i) {
         int row, k;
         where(i, tap, row, k);
-        at[i] = row * (K * 2);
-        key[i] = (lg ^ (k & KEYS)) << 4;
+#pragma unroll
+        for (int m = 0; m < 4; ++m)
+          at[i][m] = reinterpret_cast<const AS_LDS char*>(slab) + row * (K * 2) + ((m * 64) ^ ((lg ^ (k & KEYS)) << 4));
       }
     };
-    enter(TAPS > 1 ? (int)(cur / MS) : 0);
-    auto read = [&](bf16x8 (&b)[NB]) {
-      asm volatile("" : "+s"(cur));              // opaque: or every k-step's address is computed ahead of the loop and spilled
-      const unsigned ms = TAPS > 1 ? cur % MS : cur;
-      if (TAPS > 1 && ms == 0) enter((int)(cur / MS));
+    enter();
+    // k-step s of the ring (s >= D: of the next one)
+    static_assert(TAPS == 1 || D % MS == 0, "a tap begins at the same places of every ring");
+    auto read = [&](bf16x8 (&b)[NB], int s) {
+      if (TAPS > 1 && s > 0 && s % MS == 0) {
+        ++tap;
+        enter();
+      }
+      const int ms = TAPS > 1 ? s % MS : s;
 #pragma unroll
-      for (int i = 0; i < NB; ++i)
-        b[i] = *reinterpret_cast<const AS_LDS bf16x8*>(reinterpret_cast<const AS_LDS char*>(slab) + at[i] + ((int)(ms * 64) ^ key[i]));
-      ++cur;
+      for (int i = 0; i < NB; ++i) b[i] = *reinterpret_cast<const AS_LDS bf16x8*>(at[i][ms & 3] + (ms >> 2) * 256);
     };
     // Fragments are read R - 1 k-steps ahead: with one or two waves per SIMD nothing else hides the LDS latency, which is
     // several k-steps' MFMAs.  (Rolled over whole rings of weights, or this would be tens of KB of code.)
-    constexpr int R = D % 3 == 0 ? 3 : 4;
+    constexpr int R = NB * TJ <= 2 ? 8 : 4;
     static_assert(D % R == 0, "the fragment ring turns over with the weights' ring");
     bf16x8 b[R][NB];
 #pragma unroll
-    for (int d = 0; d < R - 1; ++d) read(b[d]);
+    for (int d = 0; d < R - 1; ++d) read(b[d], d);
     auto ring = [&](int g, auto last) {
 #pragma unroll
       for (int d = 0; d < D; ++d) {
-        if (!last.value || d + R - 1 < D) read(b[(d + R - 1) % R]);
+        if (!last.value || d + R - 1 < D) read(b[(d + R - 1) % R], d + R - 1);
 #pragma unroll
         for (int i = 0; i < NB; ++i)
 #pragma unroll
-          for (int j = 0; j < 2; ++j) acc[i][j] = mfma16(w[d][j], b[d % R][i], acc[i][j]);
-        if (!last.value) fetch(wrs, lane16, base, step, d, s0 + g + d + D);
+          for (int j = 0; j < TJ; ++j) acc[i][j] = mfma16(w[d][j], b[d % R][i], acc[i][j]);
+        if (!last.value) fetch(wrs, lane16, base, step, d, g + d + D);
         __builtin_amdgcn_sched_barrier(0);
       }
+      if (TAPS == 1)
+#pragma unroll
+        for (int i = 0; i < NB; ++i)
+#pragma unroll
+          for (int m = 0; m < 4; ++m) at[i][m] += D * 64;
     };
 #pragma nounroll
     for (int g = 0; g < NST - D; g += D) ring(g, std::false_type{});
@@ -143,54 +152,44 @@ __device__ __forceinline__ void slab_piece(int piece, int lane, int& row, int& p
   }
 }
 
-// Weights in flight, in k-steps.  (Twice as deep measured slower: the slab's loads then wait behind them.)
-constexpr int kConv1Ring = 8, kConv2Ring = 9;
+// Weights in flight, in k-steps of TJ tiles: conv2's in whole taps.  (About twice as deep measured the same.)
+constexpr int conv1_ring(int tj) { return 16 / tj; }
+constexpr int conv2_ring(int m, int tj) { return m == 512 ? 16 : tj == 2 ? 8 : 24; }
 
-// The accumulators' start: the bias in the first of the waves that share a tile, zero in the others.
-template <int NB>
-__device__ __forceinline__ void slab_bias(floatx4 (&acc)[NB][2], const float* b, int ch, bool first) {
+// Which group of 32 channels a wave works on, and the first of its tiles there.
+template <int NW, int TJ>
+struct SlabWave {
+  static constexpr int WPP = 2 / TJ, PAIRS = NW / WPP;     // waves per group; groups per workgroup
+  static_assert(NW % WPP == 0, "whole groups");
+  int pair, ch;                                            // group; first channel of the lane's
+  unsigned tile;                                           // byte offset of the wave's first tile in a k-step
+  __device__ __forceinline__ SlabWave(int slice, int wave, int lg) {
+    pair = slice * PAIRS + wave / WPP;
+    tile = (unsigned)(wave % WPP) * 1024;
+    ch = pair * 32 + lg * 8 + wave % WPP * 4;
+  }
+};
+
+// The accumulators' start: the bias.
+template <int NB, int TJ>
+__device__ __forceinline__ void slab_bias(floatx4 (&acc)[NB][TJ], const float* b, int ch) {
 #pragma unroll
-  for (int j = 0; j < 2; ++j) {
-    floatx4 v = {0.f, 0.f, 0.f, 0.f};
-    if (first) __builtin_memcpy(&v, b + ch + j * 4, 16);
+  for (int j = 0; j < TJ; ++j) {
+    floatx4 v;
+    __builtin_memcpy(&v, b + ch + j * 4, 16);
 #pragma unroll
     for (int i = 0; i < NB; ++i) acc[i][j] = v;
   }
 }
 
-// Adds the partial sums of the KS waves that share a tile, in the order of the waves; wave k is left with the row blocks
-// i = k, k + KS, ..
-template <int NB, int KS>
-__device__ __forceinline__ void slab_reduce(floatx4 (&acc)[NB][2], AS_LDS float* part, int wave, int lane) {
-  if constexpr (KS > 1) {
-    __syncthreads();                             // the slab is dead
+// ReLU, bf16, the lane's 4 * TJ channels (tiles 0 and 1 of a group of 32 give lane group lg the channels 8*lg ..) as one store.
+template <int TJ>
+__device__ __forceinline__ void slab_store_y(__bf16* dst, const floatx4 (&t)[TJ]) {
+  typedef __bf16 V __attribute__((ext_vector_type(4 * TJ)));
+  V o;
 #pragma unroll
-    for (int i = 0; i < NB; ++i)
-#pragma unroll
-      for (int j = 0; j < 2; ++j)
-        *reinterpret_cast<AS_LDS floatx4*>(part + (((wave * NB + i) * 2 + j) * 64 + lane) * 4) = acc[i][j];
-    __syncthreads();
-    const int w0 = wave / KS * KS;
-#pragma unroll
-    for (int i = 0; i < NB; ++i)
-      if (i % KS == wave % KS)
-#pragma unroll
-        for (int j = 0; j < 2; ++j) {
-          floatx4 t = *reinterpret_cast<AS_LDS floatx4*>(part + (((w0 * NB + i) * 2 + j) * 64 + lane) * 4);
-#pragma unroll
-          for (int k = 1; k < KS; ++k)
-            t += *reinterpret_cast<AS_LDS floatx4*>(part + ((((w0 + k) * NB + i) * 2 + j) * 64 + lane) * 4);
-          acc[i][j] = t;
-        }
-  }
-}
-
-// ReLU, bf16, the lane's 8 channels (tiles 0 and 1 of a group of 32 give lane group lg the channels 8*lg ..) as one store.
-__device__ __forceinline__ void slab_store_y(__bf16* dst, const floatx4 (&t)[2]) {
-  bf16x8 o;
-#pragma unroll
-  for (int u = 0; u < 8; ++u) o[u] = (__bf16)fmaxf(t[u / 4][u % 4], 0.f);
-  *reinterpret_cast<AS_GLOBAL bf16x8*>((AS_GLOBAL __bf16*)dst) = o;
+  for (int u = 0; u < 4 * TJ; ++u) o[u] = (__bf16)fmaxf(t[u / 4][u % 4], 0.f);
+  *reinterpret_cast<AS_GLOBAL V*>((AS_GLOBAL __bf16*)dst) = o;
 }
 
 // Cell e of the list: its image's first pixel and its own first row and column, or n < 0.  The entry is read together with
@@ -212,11 +211,11 @@ __device__ __forceinline__ SlabCell slab_cell(const SlabArgs& a, int e) {
 __device__ __forceinline__ int small_div(int a, int m) { return (a * m) >> 16; }
 
 // ---- conv1 -----------------------------------------------------------------------------------------------
-template <int C, int M, int NB, int KS>
-__global__ __launch_bounds__(kSlabThreads, 2) void slab_conv1_kernel(SlabArgs a, const __bf16* __restrict__ x,
+template <int C, int M, int NB, int NW, int TJ>
+__global__ __launch_bounds__(NW * 64, NW / 2) void slab_conv1_kernel(SlabArgs a, const __bf16* __restrict__ x,
                                                                      const __bf16* __restrict__ wp, const float* __restrict__ b1,
                                                                      __bf16* __restrict__ y1) {
-  using L = Slab<C, 1, NB, KS, kConv1Ring>;
+  using L = Slab<C, 1, NB, TJ, conv1_ring(TJ)>;
   extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
   AS_LDS __bf16* slab = (AS_LDS __bf16*)smem;
   const int tid = threadIdx.x, lane = tid & 63, l16 = lane & 15, lg = lane >> 4, wave = uni(tid >> 6);
@@ -226,25 +225,24 @@ __global__ __launch_bounds__(kSlabThreads, 2) void slab_conv1_kernel(SlabArgs a,
   if (p0 >= a.npx) return;
   // the lane reads the chunk that belongs at the position it writes
 #pragma unroll
-  for (int u = 0; u < NB * 16 * C * 2 / 4096; ++u) {
+  for (int u = 0; u < NB * 32 * C / 1024 / NW; ++u) {
     int row, pos;
-    slab_piece<C>(u * 4 + wave, lane, row, pos);
+    slab_piece<C>(u * NW + wave, lane, row, pos);
     slab_load((const AS_GLOBAL __bf16*)x + (size_t)min(p0 + row, a.npx - 1) * C + ((pos ^ (row & L::KEYS)) << 3),
-              slab + (u * 4 + wave) * 512);
+              slab + (u * NW + wave) * 512);
   }
-  const int pair = slice * (4 / KS) + wave / KS, s0 = wave % KS * L::NST, ch = pair * 32 + lg * 8;
+  const SlabWave<NW, TJ> me(slice, wave, lg);
   const rsrc_t wrs = make_rsrc((g_bf16_p)wp, (unsigned)M * C * 2);
+  const unsigned wbase = me.pair * 2048 + me.tile;
   L l;
-  l.start(wrs, lane * 16, pair * 2048, M * 64, s0);
-  floatx4 acc[NB][2];
-  slab_bias<NB>(acc, b1, ch, KS == 1 || wave % KS == 0);
+  l.start(wrs, lane * 16, wbase, M * 64);
+  floatx4 acc[NB][TJ];
+  slab_bias<NB, TJ>(acc, b1, me.ch);
   slab_ready();
-  l.run(acc, wrs, lane * 16, pair * 2048, M * 64, s0, slab, lg, [&](int i, int, int& row, int& key) { row = i * 16 + l16; key = l16; });
-  slab_reduce<NB, KS>(acc, (AS_LDS float*)smem, wave, lane);
+  l.run(acc, wrs, lane * 16, wbase, M * 64, slab, lg, [&](int i, int, int& row, int& key) { row = i * 16 + l16; key = l16; });
 #pragma unroll
   for (int i = 0; i < NB; ++i)
-    if ((KS == 1 || i % KS == wave % KS) && p0 + i * 16 + l16 < a.npx)
-      slab_store_y(y1 + (size_t)(p0 + i * 16 + l16) * M + ch, acc[i]);
+    if (p0 + i * 16 + l16 < a.npx) slab_store_y<TJ>(y1 + (size_t)(p0 + i * 16 + l16) * M + me.ch, acc[i]);
 }
 
 // ---- conv2 -----------------------------------------------------------------------------------------------
@@ -259,11 +257,11 @@ __device__ __host__ __forceinline__ int slab_zero_row(int wrows) {
   constexpr int RPP = M * 2 < 1024 ? 1024 / (M * 2) : 1;
   return (wrows + RPP - 1) / RPP * RPP;
 }
-template <int M, int NB, int KS>
-__global__ __launch_bounds__(kSlabThreads, 1) void slab_conv2_kernel(SlabArgs a, const __bf16* __restrict__ wp,
+template <int M, int NB, int NW, int TJ>
+__global__ __launch_bounds__(NW * 64, 1) void slab_conv2_kernel(SlabArgs a, const __bf16* __restrict__ wp,
                                                                      const float* __restrict__ b2, const __bf16* __restrict__ y1,
                                                                      __bf16* __restrict__ y2) {
-  using L = Slab<M, 9, NB, KS, kConv2Ring>;
+  using L = Slab<M, 9, NB, TJ, conv2_ring(M, TJ)>;
   extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
   __shared__ int cells[kSlabMaxPatches * 4];
   __shared__ int source[kSlabMaxRows];           // of every window row: pixel | key << 27
@@ -273,7 +271,7 @@ __global__ __launch_bounds__(kSlabThreads, 1) void slab_conv2_kernel(SlabArgs a,
   slab_unit(a.nsl, unit, slice);
   const int S = a.g.S, T = S + 2, T2 = T * T, H = a.g.H, W = a.g.W, ppt = a.ppt, wrows = ppt * T2;
   const int zrow = slab_zero_row<M>(wrows);
-  const int pair = slice * (4 / KS) + wave / KS, s0 = wave % KS * L::NST, ch = pair * 32 + lg * 8;
+  const SlabWave<NW, TJ> mine(slice, wave, lg);
   SlabCell me{-1, 0, 0};
   if (lane < ppt) me = slab_cell(a, unit * ppt + lane);
   if (!__any(me.n >= 0)) return;                 // (the same patches in every wave)
@@ -283,16 +281,17 @@ __global__ __launch_bounds__(kSlabThreads, 1) void slab_conv2_kernel(SlabArgs a,
     cells[lane * 4 + 2] = me.w;
   }
   const rsrc_t wrs = make_rsrc((g_bf16_p)wp, (unsigned)M * M * 18);
+  const unsigned wbase = mine.pair * 2048 + mine.tile;
   L l;
-  l.start(wrs, lane * 16, pair * 2048, M * 64, s0);
-  floatx4 acc[NB][2];
-  slab_bias<NB>(acc, b2, ch, KS == 1 || wave % KS == 0);
-  for (int i = tid; i < M / 8; i += kSlabThreads)
+  l.start(wrs, lane * 16, wbase, M * 64);
+  floatx4 acc[NB][TJ];
+  slab_bias<NB, TJ>(acc, b2, mine.ch);
+  for (int i = tid; i < M / 8; i += NW * 64)
     *reinterpret_cast<AS_LDS bf16x8*>(slab + zrow * M + i * 8) = bf16x8{0, 0, 0, 0, 0, 0, 0, 0};
   __syncthreads();
   // where every window row comes from: one that lies outside the image, or of a patch that does not exist, is loaded
   // from pixel 0 and never read (rows past the last fill up the last piece)
-  for (int r = tid; r < zrow; r += kSlabThreads) {
+  for (int r = tid; r < zrow; r += NW * 64) {
     const int row = min(r, wrows - 1);
     const int p = small_div(row, a.m_t2), wpos = row - p * T2, wy = small_div(wpos, a.m_t), wx = wpos - wy * T;
     const int img = cells[p * 4], h = cells[p * 4 + 1] + wy - 1, w = cells[p * 4 + 2] + wx - 1;
@@ -302,19 +301,19 @@ __global__ __launch_bounds__(kSlabThreads, 1) void slab_conv2_kernel(SlabArgs a,
   __syncthreads();
   // (four pieces' table entries are read at once: the loads then go out back to back)
   const int npiece = zrow * (M / 8) / 64;
-  for (int first = wave; first < npiece; first += 16) {
+  for (int first = wave; first < npiece; first += 4 * NW) {
     int src[4], pos[4];
 #pragma unroll
     for (int k = 0; k < 4; ++k) {
       int row;
-      slab_piece<M>(min(first + 4 * k, npiece - 1), lane, row, pos[k]);
+      slab_piece<M>(min(first + NW * k, npiece - 1), lane, row, pos[k]);
       src[k] = source[row];
     }
 #pragma unroll
     for (int k = 0; k < 4; ++k)
-      if (first + 4 * k < npiece)
+      if (first + NW * k < npiece)
         slab_load((const AS_GLOBAL __bf16*)y1 + (size_t)(src[k] & 0x7ffffff) * M + ((pos[k] ^ (int)((unsigned)src[k] >> 27)) << 3),
-                  slab + (first + 4 * k) * 512);
+                  slab + (first + NW * k) * 512);
   }
   int px[NB], ok[NB], row0[NB];
 #pragma unroll
@@ -333,25 +332,24 @@ __global__ __launch_bounds__(kSlabThreads, 1) void slab_conv2_kernel(SlabArgs a,
     }
   }
   slab_ready();
-  l.run(acc, wrs, lane * 16, pair * 2048, M * 64, s0, slab, lg, [&](int i, int tap, int& row, int& key) {
+  l.run(acc, wrs, lane * 16, wbase, M * 64, slab, lg, [&](int i, int tap, int& row, int& key) {
     const int dy = tap / 3, dx = tap - dy * 3;
     const bool in = (ok[i] >> tap) & 1;
     row = in ? row0[i] + dy * T + dx : zrow;
     key = i * 16 + l16 + dy * S + dx;
   });
-  slab_reduce<NB, KS>(acc, (AS_LDS float*)smem, wave, lane);
 #pragma unroll
   for (int i = 0; i < NB; ++i)
-    if ((KS == 1 || i % KS == wave % KS) && px[i] >= 0) slab_store_y(y2 + (size_t)px[i] * M + ch, acc[i]);
+    if (px[i] >= 0) slab_store_y<TJ>(y2 + (size_t)px[i] * M + mine.ch, acc[i]);
 }
 
 // ---- conv3 + residual ------------------------------------------------------------------------------------
 // Rows are the list's pixels, S*S per entry.  (In place, out == x, is safe: a lane reads and writes the same elements.)
 template <int C, int M, int NB>
-__global__ __launch_bounds__(kSlabThreads, 2) void slab_conv3_kernel(SlabArgs a, const __bf16* x, const __bf16* __restrict__ wp,
+__global__ __launch_bounds__(256, 2) void slab_conv3_kernel(SlabArgs a, const __bf16* x, const __bf16* __restrict__ wp,
                                                                      const float* __restrict__ b3, const __bf16* __restrict__ y2,
                                                                      __bf16* out, int post_relu) {
-  using L = Slab<M, 1, NB, 1, (M / 32 < 8 ? M / 32 : 8)>;
+  using L = Slab<M, 1, NB, 2, 8>;
   extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
   __shared__ int rowpx[NB * 16];
   AS_LDS __bf16* slab = (AS_LDS __bf16*)smem;
@@ -371,9 +369,9 @@ __global__ __launch_bounds__(kSlabThreads, 2) void slab_conv3_kernel(SlabArgs a,
   const rsrc_t wrs = make_rsrc((g_bf16_p)wp, (unsigned)M * C * 2);
   const unsigned wbase = (unsigned)(pair >> 1) * (M / 32) * 4096 + (pair & 1) * 2048;
   L l;
-  l.start(wrs, lane * 16, wbase, 4096, 0);
+  l.start(wrs, lane * 16, wbase, 4096);
   floatx4 acc[NB][2];
-  slab_bias<NB>(acc, b3, ch, true);
+  slab_bias<NB, 2>(acc, b3, ch);
   __syncthreads();
 #pragma unroll
   for (int u = 0; u < NB * 16 * M * 2 / 4096; ++u) {
@@ -389,7 +387,7 @@ __global__ __launch_bounds__(kSlabThreads, 2) void slab_conv3_kernel(SlabArgs a,
     res[i] = *reinterpret_cast<const AS_GLOBAL bf16x8*>((const AS_GLOBAL __bf16*)x + (size_t)max(px[i], 0) * C + ch);
   }
   slab_ready();
-  l.run(acc, wrs, lane * 16, wbase, 4096, 0, slab, lg, [&](int i, int, int& row, int& key) { row = i * 16 + l16; key = l16; });
+  l.run(acc, wrs, lane * 16, wbase, 4096, slab, lg, [&](int i, int, int& row, int& key) { row = i * 16 + l16; key = l16; });
   const float floor_ = post_relu ? 0.f : -__builtin_inff();
 #pragma unroll
   for (int i = 0; i < NB; ++i)
