@@ -142,7 +142,7 @@ size_t slab_workspace_bytes(const Geom& g) { return 2 * round256((size_t)g.N * g
 bool slab_takes(const Geom& g) {
   const long long px = (long long)g.N * g.H * g.W;
   if (g.S * g.S > 64) return false;              // (a patch is at most four blocks of rows)
-  if (g.C == 1024 && g.M == 256) return px <= (g.S >= 7 ? 32 * 196 : 16 * 196);
+  if (g.C == 1024 && g.M == 256) return px <= (g.S >= 7 ? 32 * 196 : g.S > 1 ? 16 * 196 : 10 * 196);
   if (g.C == 2048 && g.M == 512) return px <= 40 * 49;
   return false;
 }

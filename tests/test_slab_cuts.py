@@ -66,3 +66,11 @@ def test_slab_bits_are_those_of_the_other_schedules(shape, listed, cuts):
                                               flags=flags | B.LASNET_POST_RELU)
             outs.append(U.bits(out))
         assert np.array_equal(outs[0], outs[1]), r
+
+
+def test_where_the_slab_schedule_ends():
+    """(Host only.)  The largest batch of each shape that takes it, and one image more."""
+    ends = [((14, 14, 1024, 256, 1), 10), ((14, 14, 1024, 256, 2), 16), ((14, 14, 1024, 256, 7), 32), ((7, 7, 2048, 512, 1), 40)]
+    got = H.run("result = [[['slab' in k for k in kernels(call('packed', BF16, n + e, *a, flags=4)[1])] for e in (0, 1)] for a, n in %r]" % ends)
+    for (shape, _), (last, beyond) in zip(ends, got):
+        assert all(last) and len(last) == 3 and not any(beyond), shape
