@@ -194,8 +194,9 @@ LASNET_API size_t lasnet_workspace_bytes(int dtype, int N, int H, int W, int C, 
  * tensors and repack them on every call, on the caller's stream, into device memory the
  * library owns: one buffer per device and stream, allocated with hipMalloc (the only call of
  * these entry points that may block) on first use and again when a shape needs a larger one --
- * the smaller buffer is then kept, not freed, because enqueued work may still read it (the new one is at
- * least twice as large, so what is left behind never exceeds what is in use); all are kept until
+ * the smaller buffer is then kept, not freed, because enqueued work may still read it (the new one is twice
+ * as large, so what is left behind does not exceed what is in use -- or, on a device without room for that, as
+ * large as the call needs); all are kept until
  * the process ends.  So those entry points cannot be stream-captured before the stream's buffer has its
  * final size.  Shapes and types without a matrix-core kernel of their own (all of fp32) keep y1 and y2 there as
  * well, at most 256 MiB of them at a time; where that memory cannot be had, and under capture, they run a

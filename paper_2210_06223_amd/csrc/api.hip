@@ -16,7 +16,8 @@ namespace {
 // while its lease holds the buffer's lock, so two threads that call on one stream do not interleave theirs.
 // A buffer that turns out too small is not freed (work already enqueued, or a captured graph, may still use it): one
 // of at least twice its size takes its place and the old one is kept until the process ends, so what a stream has
-// left behind is never more than what it holds.
+// left behind is never more than what it holds.  (Only where the device has no room for twice the size, the new one is as
+// large as the call needs.)
 struct Workspace { std::mutex mu; void* ptr = nullptr; size_t cap = 0; };
 std::mutex g_ws_mu;
 // (hipStreamPerThread names another stream in every thread: there the thread is part of the key)
@@ -45,14 +46,20 @@ void get_workspace(Lease& lease, hipStream_t st, size_t bytes) {
   if (!lease.lock.owns_lock()) lease.lock = std::unique_lock<std::mutex>(w->mu);
   if (w->cap < bytes) {
     if (capturing(st)) return;
-    if (bytes < 2 * w->cap) bytes = 2 * w->cap;
+    size_t cap = bytes < 2 * w->cap ? 2 * w->cap : bytes;
     void* p = nullptr;
-    if (hipMalloc(&p, bytes) != hipSuccess) {
+    hipError_t e = hipMalloc(&p, cap);
+    if (e != hipSuccess && cap > bytes) {        // no room for twice the size: what the call needs
+      (void)hipGetLastError();
+      cap = bytes;
+      e = hipMalloc(&p, cap);
+    }
+    if (e != hipSuccess) {
       (void)hipGetLastError();
       return;
     }
     w->ptr = p;                                  // the previous buffer, if any, stays allocated
-    w->cap = bytes;
+    w->cap = cap;
   }
   lease.ptr = w->ptr;
 }

@@ -1,0 +1,40 @@
+"""What a block call does on the host when the device's memory or an attribute is refused (no GPU: a recording HIP runtime)."""
+from tests import _fake_hip as H
+
+
+def test_a_buffer_that_cannot_double_grows_to_what_the_call_needs():
+    """A stream's buffer grows to at least twice its size, but a device that has room for the call's need alone must serve the
+    call (raw weights and the tiled schedule have no other memory; fp32 would fall to the scalar kernel)."""
+    r = H.run("""
+a = (F32, 1, 56, 56, 256, 64, 4)                   # row schedule
+b = (F32, 1, 64, 64, 256, 64, 4)
+first = [e for e in call('ex', *a, stream=16)[1] if e[0] == 'malloc']
+need = [e for e in call('ex', *b, stream=32)[1] if e[0] == 'malloc']
+tight = int(need[0][1])
+st, ev = call('ex', *b, stream=16, limit=tight)
+st2, ev2 = call('ex', *b, stream=16)
+st3, ev3 = call('ex', BF16, 128, 7, 7, 2048, 512, 1, flags=16, stream=48)
+big = [int(e[1]) for e in ev3 if e[0] == 'malloc'][0]
+st4, ev4 = call('ex', BF16, 150, 7, 7, 2048, 512, 1, flags=16, stream=64)
+big4 = [int(e[1]) for e in ev4 if e[0] == 'malloc'][0]
+st5, ev5 = call('ex', BF16, 150, 7, 7, 2048, 512, 1, flags=16, stream=48, limit=big4)
+result = [first, tight, [st, ev], [st2, ev2], big, big4, [st5, ev5]]
+""")
+    first, tight, (st, ev), (st2, ev2), big, big4, (st5, ev5) = r
+    assert int(first[0][1]) < tight < 2 * int(first[0][1])
+    assert st == 0 and [e[1:] for e in ev if e[0] == "malloc"] == [[str(2 * int(first[0][1])), "1"], [str(tight), "0"]]
+    assert any("rows_conv2" in e[1] for e in ev)
+    assert st2 == 0 and not [e for e in ev2 if e[0] == "malloc"]              # the buffer has that size now
+    assert big < big4 < 2 * big
+    assert st5 == 0 and [e[1:] for e in ev5 if e[0] == "malloc"] == [[str(2 * big), "1"], [str(big4), "0"]]
+
+
+def test_no_memory_at_all():
+    """fp32 then runs the kernel that needs none; a call whose weights have to be repacked is refused with nothing enqueued."""
+    (st, ev), (st2, ev2) = H.run("""
+result = [call('ex', F32, 1, 56, 56, 256, 64, 4, stream=16, limit=1024), call('ex', BF16, 2, 14, 14, 1024, 256, 2, stream=16, limit=1024)]
+""")
+    assert st == 0 and [H.kernel_name(e[1]) for e in ev if e[0] == "launch"][-1] == "bneck_generic_kernel"
+    assert st2 == -5 and not [e for e in ev2 if e[0] in ("launch", "copy")]
+
+
