@@ -216,10 +216,12 @@ int run_block(const lasnet_tensor* x, const int32_t* idx, const int32_t* count, 
   const bool may_lease = own_memory || tiled || (fast && !slab) || !capturing(st);
   if (!may_lease) slab = false;
   const size_t slab_need = slab ? slab_workspace_bytes(g) : 0;
+  if (pad.from_caller && (!pad.workspace || pad.workspace_bytes < slab_need || ((uintptr_t)pad.workspace & 255))) slab = false;
   // Everything that can fail on the host comes before the first launch: kernel attributes, then the
   // memory for the repacked weights and the tiled schedule's intermediates (the caller's, the
   // library's per stream, or `scratch`).
   hipError_t e = !fast ? prepare_generic(x->dtype) : tiled ? tiled->prepare() : prepare_mfma(x->c, M, S);
+  if (e == hipSuccess && slab) e = prepare_slab(g, idx);     // (beside the others': where its memory cannot be had, they run)
   if (e != hipSuccess) return LASNET_EHIP;
   unsigned char* block_ws = nullptr;             // the tiled or the slab schedule's
   // Without a matrix-core kernel of its own the shape runs the row schedule; where there is no memory for that (the
@@ -229,7 +231,6 @@ int run_block(const lasnet_tensor* x, const int32_t* idx, const int32_t* count, 
   Lease lease;
   if (pad.from_caller) {
     block_ws = (unsigned char*)pad.workspace;              // (this entry takes packed weights: packed_need is 0)
-    if (!block_ws || pad.workspace_bytes < slab_need || ((uintptr_t)block_ws & 255)) slab = false;
   } else if (pad.fixed_array) {
     if (packed_need) {
       unsigned char* p = (unsigned char*)scratch_for_current_device();

@@ -52,6 +52,7 @@ hipError_t launch_rows(int dtype, const Geom& g, const void* x, const int32_t* i
 constexpr size_t kSlabBytes = (size_t)8 << 20;      // most that slab_workspace_bytes() asks for where slab_takes()
 bool slab_takes(const Geom& g);
 size_t slab_workspace_bytes(const Geom& g);
+hipError_t prepare_slab(const Geom& g, const int32_t* idx);      // the attributes of the kernels that launch_slab will run
 hipError_t launch_slab(const Geom& g, const void* x, const int32_t* idx, const int32_t* count, const void* packed,
                        const float* b1, const float* b2, const float* b3, void* out, bool post_relu, void* workspace,
                        hipStream_t st);

@@ -30,12 +30,14 @@ struct Conv1 {
   static constexpr int pairs = SlabWave<NW, TJ>::PAIRS, slices = M / 32 / pairs;
   static int tiles(const SlabArgs& a) { return (a.npx + NB * 16 - 1) / (NB * 16); }
   static double cost(const SlabArgs& a) { return cut_cost(tiles(a), slices, NW, NB * 32 * C, NB * 32.0 * C + pairs * 64.0 * C, C / 32, NB * TJ); }
-  static hipError_t run(SlabArgs a, const void* x, const __bf16* wp, const float* b1, __bf16* y1, hipStream_t st) {
+  static constexpr int lds = NB * 32 * C;
+  static_assert(lds <= kSlabLds, "LDS");
+  static constexpr auto k = slab_conv1_kernel<C, M, NB, NW, TJ>;
+  static hipError_t prepare() {
     static std::atomic<unsigned long long> done;
-    auto k = slab_conv1_kernel<C, M, NB, NW, TJ>;
-    constexpr int lds = NB * 32 * C;
-    static_assert(lds <= kSlabLds, "LDS");
-    if (hipError_t e = allow_dynamic_lds((const void*)k, lds, done); e != hipSuccess) return e;
+    return allow_dynamic_lds((const void*)k, lds, done);
+  }
+  static hipError_t run(SlabArgs a, const void* x, const __bf16* wp, const float* b1, __bf16* y1, hipStream_t st) {
     a.nsl = slices;
     hipLaunchKernelGGL(k, dim3(slab_grid(tiles(a), slices)), dim3(NW * 64), lds, st, a, (const __bf16*)x, wp, b1, y1);
     return hipGetLastError();
@@ -57,10 +59,12 @@ struct Conv2 {
       return cut_cost(tiles(a, patches), slices, NW, lds(a), lds(a) + pairs * 64.0 * 9 * M, 9 * M / 32, NB * TJ);
     });
   }
-  static hipError_t run(SlabArgs a, const __bf16* wp, const float* b2, const __bf16* y1, __bf16* y2, hipStream_t st) {
+  static constexpr auto k = slab_conv2_kernel<M, NB, NW, TJ>;
+  static hipError_t prepare() {
     static std::atomic<unsigned long long> done;
-    auto k = slab_conv2_kernel<M, NB, NW, TJ>;
-    if (hipError_t e = allow_dynamic_lds((const void*)k, kSlabLds, done); e != hipSuccess) return e;
+    return allow_dynamic_lds((const void*)k, kSlabLds, done);
+  }
+  static hipError_t run(SlabArgs a, const __bf16* wp, const float* b2, const __bf16* y1, __bf16* y2, hipStream_t st) {
     a.nsl = slices;
     a.ppt = ppt(a);
     hipLaunchKernelGGL(k, dim3(slab_grid(tiles(a, a.g.P), slices)), dim3(NW * 64), lds(a), st, a, wp, b2, y1, y2);
@@ -77,12 +81,14 @@ struct Conv3 {
       return cut_cost(tiles(rows), slices, 4, NB * 32 * M, NB * 32.0 * M + 256.0 * M + NB * 16 * 512.0, M / 32, NB * 2);
     });
   }
+  static constexpr int lds = NB * 32 * M;
+  static constexpr auto k = slab_conv3_kernel<C, M, NB>;
+  static hipError_t prepare() {
+    static std::atomic<unsigned long long> done;
+    return allow_dynamic_lds((const void*)k, lds, done);
+  }
   static hipError_t run(SlabArgs a, const void* x, const __bf16* wp, const float* b3, const __bf16* y2, void* out, bool post_relu,
                         hipStream_t st) {
-    static std::atomic<unsigned long long> done;
-    auto k = slab_conv3_kernel<C, M, NB>;
-    constexpr int lds = NB * 32 * M;
-    if (hipError_t e = allow_dynamic_lds((const void*)k, lds, done); e != hipSuccess) return e;
     a.nsl = slices;
     hipLaunchKernelGGL(k, dim3(slab_grid(tiles(a.npx), slices)), dim3(256), lds, st, a, (const __bf16*)x, wp, b3, y2,
                        (__bf16*)out, (int)post_relu);
@@ -90,37 +96,65 @@ struct Conv3 {
   }
 };
 
-// Runs the cheapest of Cs.
-template <class... Cs, class... Args>
-hipError_t cheapest(const SlabArgs& a, Args... args) {
-  double best = 1e30;
-  hipError_t (*run)(SlabArgs, Args...) = nullptr;
-  ((Cs::cost(a) < best ? (void)(best = Cs::cost(a), run = &Cs::run) : (void)0), ...);
-  return run ? run(a, args...) : hipErrorInvalidValue;
-}
+// The ways to cut one convolution: prepare() and run() take the cheapest.
+template <class... Cs>
+struct Cuts {
+  static hipError_t prepare(const SlabArgs& a) {
+    hipError_t (*p)() = pick<hipError_t (*)()>(a, &Cs::prepare...);
+    return p ? p() : hipErrorInvalidValue;
+  }
+  template <class... Args>
+  static hipError_t run(const SlabArgs& a, Args... args) {
+    auto r = pick<hipError_t (*)(SlabArgs, Args...)>(a, &Cs::run...);
+    return r ? r(a, args...) : hipErrorInvalidValue;
+  }
+
+ private:
+  template <class Fn, class... Fns>
+  static Fn pick(const SlabArgs& a, Fns... fns) {
+    double best = 1e30;
+    Fn f = nullptr;
+    ((Cs::cost(a) < best ? (void)(best = Cs::cost(a), f = fns) : (void)0), ...);
+    return f;
+  }
+};
 
 // The cuts of a stage: those that some map in slab_takes' range is cheapest with.
 template <int C, int M>
-hipError_t run_conv1(const SlabArgs& a, const void* x, const __bf16* wp, const float* b1, __bf16* y1, hipStream_t st) {
-  return cheapest<Conv1<C, M, 1, 2, 1>, Conv1<C, M, 2, 2, 1>, Conv1<C, M, 2, 4, 1>, Conv1<C, M, 2, 4, 2>>(a, x, wp, b1, y1, st);
-}
-template <int M>
-hipError_t run_conv2(const SlabArgs& a, const __bf16* wp, const float* b2, const __bf16* y1, __bf16* y2, hipStream_t st) {
-  if constexpr (M == 512)      // (S = 1: the windows of 32 pixels exceed the LDS)
-    return cheapest<Conv2<M, 1, 2, 1>, Conv2<M, 1, 4, 1>, Conv2<M, 1, 4, 2>>(a, wp, b2, y1, y2, st);
-  else
-    return cheapest<Conv2<M, 1, 2, 1>, Conv2<M, 2, 2, 1>, Conv2<M, 2, 4, 1>, Conv2<M, 4, 2, 1>, Conv2<M, 4, 4, 1>, Conv2<M, 4, 4, 2>>(
-        a, wp, b2, y1, y2, st);
-}
-template <int C, int M>
-hipError_t launch(const SlabArgs& a, const void* x, const __bf16* wp, const float* b1, const float* b2, const float* b3,
-                  __bf16* y1, __bf16* y2, void* out, bool relu, hipStream_t st) {
-  const __bf16 *w2 = wp + (size_t)M * C, *w3 = w2 + (size_t)9 * M * M;
-  hipError_t e = run_conv1<C, M>(a, x, wp, b1, y1, st);
-  if (e != hipSuccess) return e;
-  e = run_conv2<M>(a, w2, b2, (const __bf16*)y1, y2, st);
-  if (e != hipSuccess) return e;
-  return cheapest<Conv3<C, M, 1>, Conv3<C, M, 2>, Conv3<C, M, 4>>(a, x, w3, b3, (const __bf16*)y2, out, relu, st);
+struct Stage {
+  typedef Cuts<Conv1<C, M, 1, 2, 1>, Conv1<C, M, 2, 2, 1>, Conv1<C, M, 2, 4, 1>, Conv1<C, M, 2, 4, 2>> Cuts1;
+  typedef Cuts<Conv3<C, M, 1>, Conv3<C, M, 2>, Conv3<C, M, 4>> Cuts3;
+  // (512, S = 1: the windows of 32 pixels exceed the LDS)
+  typedef std::conditional_t<M == 512, Cuts<Conv2<M, 1, 2, 1>, Conv2<M, 1, 4, 1>, Conv2<M, 1, 4, 2>>,
+                             Cuts<Conv2<M, 1, 2, 1>, Conv2<M, 2, 2, 1>, Conv2<M, 2, 4, 1>, Conv2<M, 4, 2, 1>, Conv2<M, 4, 4, 1>,
+                                  Conv2<M, 4, 4, 2>>> Cuts2;
+
+  static hipError_t prepare(const SlabArgs& a) {
+    hipError_t e = Cuts1::prepare(a);
+    if (e == hipSuccess) e = Cuts2::prepare(a);
+    return e == hipSuccess ? Cuts3::prepare(a) : e;
+  }
+  static hipError_t launch(const SlabArgs& a, const void* x, const __bf16* wp, const float* b1, const float* b2, const float* b3,
+                           __bf16* y1, __bf16* y2, void* out, bool relu, hipStream_t st) {
+    const __bf16 *w2 = wp + (size_t)M * C, *w3 = w2 + (size_t)9 * M * M;
+    hipError_t e = Cuts1::run(a, x, wp, b1, y1, st);
+    if (e == hipSuccess) e = Cuts2::run(a, w2, b2, (const __bf16*)y1, y2, st);
+    return e == hipSuccess ? Cuts3::run(a, x, w3, b3, (const __bf16*)y2, out, relu, st) : e;
+  }
+};
+
+SlabArgs slab_args(const Geom& g, const int32_t* idx, const int32_t* count) {
+  SlabArgs a;
+  a.g = g;
+  a.idx = idx;
+  a.count = count;
+  a.npx = g.N * g.H * g.W;
+  a.nsl = a.ppt = 0;
+  a.m_t2 = small_div_magic((g.S + 2) * (g.S + 2));
+  a.m_t = small_div_magic(g.S + 2);
+  a.m_s2 = small_div_magic(g.S * g.S);
+  a.m_s = small_div_magic(g.S);
+  return a;
 }
 
 }  // namespace
@@ -147,23 +181,19 @@ bool slab_takes(const Geom& g) {
   return false;
 }
 
+hipError_t prepare_slab(const Geom& g, const int32_t* idx) {
+  const SlabArgs a = slab_args(g, idx, nullptr);
+  return g.M == 256 ? Stage<1024, 256>::prepare(a) : Stage<2048, 512>::prepare(a);
+}
+
 hipError_t launch_slab(const Geom& g, const void* x, const int32_t* idx, const int32_t* count, const void* packed,
                        const float* b1, const float* b2, const float* b3, void* out, bool post_relu, void* workspace,
                        hipStream_t st) {
-  SlabArgs a;
-  a.g = g;
-  a.idx = idx;
-  a.count = count;
-  a.npx = g.N * g.H * g.W;
-  a.nsl = a.ppt = 0;
-  a.m_t2 = small_div_magic((g.S + 2) * (g.S + 2));
-  a.m_t = small_div_magic(g.S + 2);
-  a.m_s2 = small_div_magic(g.S * g.S);
-  a.m_s = small_div_magic(g.S);
+  const SlabArgs a = slab_args(g, idx, count);
   __bf16* y1 = (__bf16*)workspace;
   __bf16* y2 = (__bf16*)((unsigned char*)workspace + round256((size_t)a.npx * g.M * 2));
-  if (g.M == 256) return launch<1024, 256>(a, x, (const __bf16*)packed, b1, b2, b3, y1, y2, out, post_relu, st);
-  return launch<2048, 512>(a, x, (const __bf16*)packed, b1, b2, b3, y1, y2, out, post_relu, st);
+  if (g.M == 256) return Stage<1024, 256>::launch(a, x, (const __bf16*)packed, b1, b2, b3, y1, y2, out, post_relu, st);
+  return Stage<2048, 512>::launch(a, x, (const __bf16*)packed, b1, b2, b3, y1, y2, out, post_relu, st);
 }
 
 }  // namespace lasnet

@@ -38,3 +38,8 @@ result = [call('ex', F32, 1, 56, 56, 256, 64, 4, stream=16, limit=1024), call('e
     assert st2 == -5 and not [e for e in ev2 if e[0] in ("launch", "copy")]
 
 
+def test_a_call_that_fails_has_enqueued_nothing():
+    """The slab kernels' attributes are set with the others, before the repack, the copy and the first convolution."""
+    st, ev = H.run("result = call('ex', BF16, 2, 14, 14, 1024, 256, 2, attr_fail=1)")
+    assert st == -5
+    assert not [e for e in ev if e[0] in ("launch", "copy")], ev
