@@ -3,6 +3,8 @@
 // list (App. B.1 (2)).  HBM-bound: reads x once, 16 bytes per lane per load.
 #include "common.hpp"
 
+#include <type_traits>
+
 namespace lasnet {
 namespace {
 
@@ -273,52 +275,63 @@ __global__ __launch_bounds__(TPC < kMaskerThreads ? kMaskerThreads : TPC) void m
 }
 
 // Ordered stream compaction.  A workgroup takes a run of consecutive cells and counts the set bytes of all cells
-// before it by itself (16 per load and thread: the mask is a few KB to a few hundred, in L2), so that no
-// workgroup waits for another; within its run a shuffle scan and the four wave totals give every cell its
+// before it by itself (16 per load and thread, four loads in flight: the mask is a few KB to a few hundred, in L2), so that no
+// workgroup waits for another; within its run a shuffle scan and the wave totals give every cell its
 // place.  Integer work only: the list is the ascending sequence of active cell ids whatever the timing.
-// One 1024-thread workgroup for the whole mask took 2.4 us for 49 cells, 4.8 for 6272 and 13.6 for 50176; this 2.1, 3.8
-// and 5.6.
-constexpr int kCompactThreads = 256;
-constexpr int kCompactRound = kCompactThreads * 4;      // cells a workgroup places per round: four bytes per thread
+// What bounds it is the chain of loads, barriers and shuffles, so up to 1024 cells four waves place them in one round (1.8 us;
+// one 1024-thread workgroup for every mask took 2.2), beyond that workgroups of 16 waves take runs of 8192: one such
+// workgroup for 6272 cells 2.8 us, as before (in runs of 1024 it was 3.4), 12544 cells 4.1 -> 3.4, 50176 cells 10.4 -> 4.0.
 constexpr int kCompactBlocks = 64;                      // most workgroups: bounds the bytes counted again (32 * P)
+struct CompactSmall { static constexpr int NT = 256, CELLS = 4, ROUND = NT * CELLS; };      // CELLS: of a thread, per round
+struct CompactLarge { static constexpr int NT = 1024, CELLS = 8, ROUND = NT * CELLS; };
 
-template <bool ALIGNED>
-__global__ __launch_bounds__(kCompactThreads) void compact_kernel(
+template <class K, bool ALIGNED>
+__global__ __launch_bounds__(K::NT) void compact_kernel(
     const uint8_t* __restrict__ mask, int P, int run, int32_t* __restrict__ idx, int32_t* __restrict__ count) {
-  __shared__ int wave_tot[kCompactThreads / 64];
+  constexpr int NW = K::NT / 64;
+  __shared__ int wave_tot[NW];
   const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
-  const int start = blockIdx.x * run, end = min(start + run, P);     // (run is a multiple of kCompactRound)
-  auto four = [&](int i0) {                    // the bytes of cells i0 .. i0 + 3 (zeros past the end), the masker's 0 / 1
-    if (ALIGNED && i0 + 4 <= end) return *reinterpret_cast<const unsigned*>(mask + i0);
-    unsigned v = 0;
+  const int start = blockIdx.x * run, end = min(start + run, P);     // (run is a multiple of K::ROUND)
+  auto bytes = [&](int i0) {                   // of cells i0 .. i0 + CELLS - 1 (zeros past the end), the masker's 0 / 1
+    typedef std::conditional_t<K::CELLS == 8, unsigned long long, unsigned> V;
+    if (ALIGNED && i0 + K::CELLS <= end) return (unsigned long long)*reinterpret_cast<const V*>(mask + i0);
+    unsigned long long v = 0;
 #pragma unroll
-    for (int b = 0; b < 4; ++b)
-      if (i0 + b < end) v |= (unsigned)mask[i0 + b] << (8 * b);
+    for (int b = 0; b < K::CELLS; ++b)
+      if (i0 + b < end) v |= (unsigned long long)mask[i0 + b] << (8 * b);
     return v;
   };
-  unsigned next = four(start + tid * 4);       // requested before the long count
-  int mine = 0;
-  if constexpr (ALIGNED) {
-    for (int i = tid * 16; i < start; i += kCompactThreads * 16) {
-      const uint4 q = *reinterpret_cast<const uint4*>(mask + i);
-      mine += __popc(q.x) + __popc(q.y) + __popc(q.z) + __popc(q.w);
-    }
-  } else {
-    for (int i = tid; i < start; i += kCompactThreads) mine += mask[i];
-  }
-#pragma unroll
-  for (int o = 32; o > 0; o >>= 1) mine += __shfl_xor(mine, o, 64);
-  if (lane == 0) wave_tot[wv] = mine;
-  __syncthreads();
+  unsigned long long next = bytes(start + tid * K::CELLS);       // requested before the long count
   int base = 0;                                // identical in every thread
+  if (start > 0) {
+    int mine = 0;
+    if constexpr (ALIGNED) {
+      for (int i = tid * 16; i < start; i += 4 * K::NT * 16) {
+        uint4 q[4];
 #pragma unroll
-  for (int k = 0; k < kCompactThreads / 64; ++k) base += wave_tot[k];
-  __syncthreads();
-  for (int r0 = start; r0 < end; r0 += kCompactRound) {
-    const int i0 = r0 + tid * 4;
-    const unsigned on = next;
-    if (r0 + kCompactRound < end) next = four(i0 + kCompactRound);
-    const int c = __popc(on);
+        for (int u = 0; u < 4; ++u) {
+          const int j = i + u * K::NT * 16;
+          q[u] = j < start ? *reinterpret_cast<const uint4*>(mask + j) : uint4{0, 0, 0, 0};
+        }
+#pragma unroll
+        for (int u = 0; u < 4; ++u) mine += __popc(q[u].x) + __popc(q[u].y) + __popc(q[u].z) + __popc(q[u].w);
+      }
+    } else {
+      for (int i = tid; i < start; i += K::NT) mine += mask[i];
+    }
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) mine += __shfl_xor(mine, o, 64);
+    if (lane == 0) wave_tot[wv] = mine;
+    __syncthreads();
+#pragma unroll
+    for (int k = 0; k < NW; ++k) base += wave_tot[k];
+    __syncthreads();
+  }
+  for (int r0 = start; r0 < end; r0 += K::ROUND) {
+    const int i0 = r0 + tid * K::CELLS;
+    const unsigned long long on = next;
+    if (r0 + K::ROUND < end) next = bytes(i0 + K::ROUND);
+    const int c = __popcll(on);
     int incl = c;                              // inclusive scan over the wave
 #pragma unroll
     for (int o = 1; o < 64; o <<= 1) {
@@ -329,14 +342,14 @@ __global__ __launch_bounds__(kCompactThreads) void compact_kernel(
     __syncthreads();
     int before = 0, total = 0;
 #pragma unroll
-    for (int k = 0; k < kCompactThreads / 64; ++k) {
+    for (int k = 0; k < NW; ++k) {
       const int t = wave_tot[k];
       before += (k < wv) ? t : 0;
       total += t;
     }
     int pos = base + before + incl - c;
 #pragma unroll
-    for (int b = 0; b < 4; ++b)
+    for (int b = 0; b < K::CELLS; ++b)
       if ((on >> (8 * b)) & 1u) idx[pos++] = i0 + b;
     base += total;
     __syncthreads();                           // wave_tot is rewritten next round
@@ -420,13 +433,19 @@ hipError_t launch_masker(const lasnet_tensor& x, const float* Wm, float bm, int 
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
   if (count) {
+    const bool small = P <= CompactSmall::ROUND;
+    const int round = small ? CompactSmall::ROUND : CompactLarge::ROUND;
     int run = (P + kCompactBlocks - 1) / kCompactBlocks;
-    run = run > 0 ? (run + kCompactRound - 1) / kCompactRound * kCompactRound : kCompactRound;
+    run = run > 0 ? (run + round - 1) / round * round : round;
     const dim3 cgrid(P > 0 ? (P + run - 1) / run : 1);
-    if (((uintptr_t)mask % 16) == 0)
-      hipLaunchKernelGGL(compact_kernel<true>, cgrid, dim3(kCompactThreads), 0, st, mask, P, run, idx, count);
-    else
-      hipLaunchKernelGGL(compact_kernel<false>, cgrid, dim3(kCompactThreads), 0, st, mask, P, run, idx, count);
+#define LASNET_COMPACT(K, ALIGNED) \
+  hipLaunchKernelGGL((compact_kernel<K, ALIGNED>), cgrid, dim3(K::NT), 0, st, mask, P, run, idx, count)
+    if (((uintptr_t)mask % 16) == 0) {
+      if (small) LASNET_COMPACT(CompactSmall, true); else LASNET_COMPACT(CompactLarge, true);
+    } else {
+      if (small) LASNET_COMPACT(CompactSmall, false); else LASNET_COMPACT(CompactLarge, false);
+    }
+#undef LASNET_COMPACT
     e = hipGetLastError();
   }
   return e;
