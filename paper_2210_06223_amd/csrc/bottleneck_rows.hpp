@@ -518,11 +518,15 @@ __global__ __launch_bounds__(kRowsThreads, 2) void rows_conv3_kernel(RowsArgs a,
 
 // ---- plan ------------------------------------------------------------------------------------------------
 constexpr int kNeedPixels = 16384;                // pixels whose bytes one workgroup of the plan makes (in LDS)
+// Every such workgroup scans the whole list, which is a launch less than clearing the bytes and scattering into them
+// (1.3 us at a few hundred cells) but grows with pixels times cells: to this many cells of the map.  (64 images of
+// 224x224x16, S=1, a list of 1.6 M entries: fp32 12.3 ms by scans, 1.9 ms scattered; bf16 14.9 and 1.8.  3136 cells: 29 and 21 us.)
+constexpr int kScanCells = 1024;
 
 // Blocks [0, pack_blocks): the weight fragments, one 8-element lane share per thread.  The others: the need
-// bytes of kNeedPixels pixels each, by a scan of the list (it may be in any order).
+// bytes of kNeedPixels pixels each, by a scan of the list (it may be in any order), or cleared for rows_need_kernel.
 template <class F>
-__global__ __launch_bounds__(kRowsThreads) void rows_plan_kernel(RowsArgs a, int pack_blocks, const typename F::T* __restrict__ W1,
+__global__ __launch_bounds__(kRowsThreads) void rows_plan_kernel(RowsArgs a, int pack_blocks, int scan, const typename F::T* __restrict__ W1,
                                                                  const typename F::T* __restrict__ W2,
                                                                  const typename F::T* __restrict__ W3,
                                                                  unsigned char* __restrict__ wp, uint8_t* __restrict__ need) {
@@ -575,7 +579,7 @@ __global__ __launch_bounds__(kRowsThreads) void rows_plan_kernel(RowsArgs a, int
   const int q0 = ((int)blockIdx.x - pack_blocks) * kNeedPixels, nq = min(kNeedPixels, a.npx - q0);
   for (int i = tid; i < kNeedPixels / 16; i += kRowsThreads) reinterpret_cast<uint4*>(flag)[i] = uint4{0, 0, 0, 0};
   __syncthreads();
-  const int nact = rows_uni(min(*a.count, a.g.P)), S = a.g.S, H = a.g.H, W = a.g.W, cpi = a.g.G * a.g.GW;
+  const int nact = scan ? rows_uni(min(*a.count, a.g.P)) : 0, S = a.g.S, H = a.g.H, W = a.g.W, cpi = a.g.G * a.g.GW;
   for (int e = tid; e < nact; e += kRowsThreads) {
     const int cell = a.idx[e];
     if ((unsigned)cell >= (unsigned)a.g.P) continue;
@@ -590,6 +594,23 @@ __global__ __launch_bounds__(kRowsThreads) void rows_plan_kernel(RowsArgs a, int
   __syncthreads();
   // (need has room for whole workgroups' pixels)
   for (int i = tid; i * 16 < nq; i += kRowsThreads) reinterpret_cast<uint4*>(need + q0)[i] = reinterpret_cast<uint4*>(flag)[i];
+}
+
+// The need bytes of a chunk (cleared by the plan) from a long list: one thread per row of an entry's window.
+__global__ __launch_bounds__(kRowsThreads) void rows_need_kernel(RowsArgs a, uint8_t* __restrict__ need) {
+  const int S = a.g.S, H = a.g.H, W = a.g.W, cpi = a.g.G * a.g.GW;
+  const unsigned T = S + 2;
+  const long long n = (long long)rows_uni(min(*a.count, a.g.P)) * T;
+  for (long long i = (long long)blockIdx.x * kRowsThreads + threadIdx.x; i < n; i += (long long)gridDim.x * kRowsThreads) {
+    const int e = (int)(i / T), cell = a.idx[e];
+    if ((unsigned)cell >= (unsigned)a.g.P) continue;
+    const int img = cell / cpi, rem = cell - img * cpi, gy = rem / a.g.GW, gx = rem - gy * a.g.GW;
+    const int h = gy * S - 1 + (int)(i - (long long)e * T);
+    if ((unsigned)h >= (unsigned)H) continue;
+    const int w0 = max(gx * S - 1, 0), w1 = min(gx * S + S, W - 1), row = (img * H + h) * W - a.px0;
+    for (int w = w0; w <= w1; ++w)
+      if ((unsigned)(row + w) < (unsigned)a.npx) need[row + w] = 1;
+  }
 }
 
 // ---- host ------------------------------------------------------------------------------------------------

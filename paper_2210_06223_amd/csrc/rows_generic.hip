@@ -40,7 +40,11 @@ hipError_t run_rows(const Geom& g, const void* x, const int32_t* idx, const int3
     const int need_blocks = idx ? (a.npx + kNeedPixels - 1) / kNeedPixels : 0;
     if (pack_blocks + need_blocks > 0)
       hipLaunchKernelGGL(rows_plan_kernel<F>, dim3(pack_blocks + need_blocks), dim3(kRowsThreads), 0, st, a, pack_blocks,
-                         (const T*)w.W1, (const T*)w.W2, (const T*)w.W3, wp1, need);
+                         (int)(g.P <= kScanCells), (const T*)w.W1, (const T*)w.W2, (const T*)w.W3, wp1, need);
+    if (idx && g.P > kScanCells) {
+      const long long blocks = ((long long)g.P * (g.S + 2) + kRowsThreads - 1) / kRowsThreads;
+      hipLaunchKernelGGL(rows_need_kernel, dim3((unsigned)(blocks < 4096 ? blocks : 4096)), dim3(kRowsThreads), 0, st, a, need);
+    }
     if (hipError_t e = launch_rows_convs<F, VEC>(a, x, wp1, wp2, wp3, w.b1, w.b2, w.b3, y1, y2, out, post_relu, st); e != hipSuccess)
       return e;
   }
