@@ -327,7 +327,7 @@ __device__ __forceinline__ void rows_unit(int nsl, int& unit, int& slice) {
   unit = (j / nsl) * 8 + xcd;
   slice = j % nsl;
 }
-inline int rows_grid(int units, int nsl) { return (units + 7) / 8 * 8 * nsl; }
+inline long long rows_grid(long long units, int nsl) { return (units + 7) / 8 * 8 * nsl; }
 
 // Calls f(integral_constant<n>) for the run-time n in [1, HI] (2 and 3 blocks share an instantiation of 4's size class).
 template <int HI, class Fn>
@@ -624,27 +624,6 @@ struct RowsLayout {
 };
 inline size_t rows_round(size_t v) { return (v + 255) / 256 * 256; }
 
-// false: even one image does not fit (or exceeds the 32-bit offsets of the loads).
-template <class F>
-bool rows_layout(const Geom& g, RowsLayout& l) {
-  const size_t pairs1 = (g.M + 31) / 32, pairs3 = (g.C + 31) / 32, ks1 = pairs3, ksm = pairs1;
-  const size_t hw = (size_t)g.H * g.W, ypx = y_pitch<F>((int)ksm), xpx = (size_t)g.C * F::ES;
-  l.w1 = pairs1 * ks1 * 2 * F::KPL * 1024;
-  l.w2 = pairs1 * 9 * ksm * 2 * F::KPL * 1024;
-  l.w3 = pairs3 * ksm * 2 * F::KPL * 1024;
-  const size_t lim = (size_t)1 << 31;            // every descriptor stays below kOutOfRange
-  if (hw * 2 * ypx > kRowsYBytes || hw * xpx >= lim || l.w1 >= lim || l.w2 >= lim || l.w3 >= lim) return false;
-  size_t n = kRowsYBytes / (hw * 2 * ypx), nx = (lim - 1) / (hw * xpx);
-  if (n > nx) n = nx;
-  if (n > (size_t)g.N) n = (size_t)g.N;
-  if (n == 0) return false;
-  l.images = (int)n;
-  l.need = (n * hw + kNeedPixels - 1) / kNeedPixels * kNeedPixels;
-  l.y = rows_round(n * hw * ypx);
-  l.total = rows_round(l.w1) + rows_round(l.w2) + rows_round(l.w3) + l.need + 2 * l.y;
-  return true;
-}
-
 // How a convolution is cut: NB row blocks per wave, KS waves to a tile's reduction, nsl channel slices per row tile.
 // 1024 waves are one per SIMD.  More rows per wave read the weights less often, so NB is as large as leaves the chip
 // that many tiles; with fewer even at NB = 1 the waves of a workgroup share a tile's reduction.
@@ -662,6 +641,32 @@ inline RowsCut rows_cut(long long rows_max, long long rows_expected, int pairs, 
   return c;
 }
 
+// false: even one image does not fit (or exceeds the 32-bit offsets of the loads), or a launch would have 2^32 threads.
+template <class F>
+bool rows_layout(const Geom& g, RowsLayout& l) {
+  const size_t pairs1 = (g.M + 31) / 32, pairs3 = (g.C + 31) / 32, ks1 = pairs3, ksm = pairs1;
+  const size_t hw = (size_t)g.H * g.W, ypx = y_pitch<F>((int)ksm), xpx = (size_t)g.C * F::ES;
+  l.w1 = pairs1 * ks1 * 2 * F::KPL * 1024;
+  l.w2 = pairs1 * 9 * ksm * 2 * F::KPL * 1024;
+  l.w3 = pairs3 * ksm * 2 * F::KPL * 1024;
+  const size_t lim = (size_t)1 << 31;            // every descriptor stays below kOutOfRange
+  if (hw * 2 * ypx > kRowsYBytes || hw * xpx >= lim || l.w1 >= lim || l.w2 >= lim || l.w3 >= lim) return false;
+  size_t n = kRowsYBytes / (hw * 2 * ypx), nx = (lim - 1) / (hw * xpx);
+  if (n > nx) n = nx;
+  if (n > (size_t)g.N) n = (size_t)g.N;
+  if (n == 0) return false;
+  l.images = (int)n;
+  const long long all = (long long)g.P * g.S * g.S, chunk = (long long)(n * hw);
+  for (const RowsCut& c : {rows_cut(chunk, chunk, (int)pairs1, (int)ks1), rows_cut(all, (chunk + 1) / 2, (int)pairs1, 9 * (int)ksm),
+                           rows_cut(all, chunk, (int)pairs1, 9 * (int)ksm), rows_cut(all, (chunk + 1) / 2, (int)pairs3, (int)ksm),
+                           rows_cut(all, chunk, (int)pairs3, (int)ksm)})
+    if (rows_grid(c.units, c.nsl) * kRowsThreads >= 1ll << 32) return false;
+  l.need = (n * hw + kNeedPixels - 1) / kNeedPixels * kNeedPixels;
+  l.y = rows_round(n * hw * ypx);
+  l.total = rows_round(l.w1) + rows_round(l.w2) + rows_round(l.w3) + l.need + 2 * l.y;
+  return true;
+}
+
 #define ROWS_DISPATCH(c, CALL)                                             \
   if (c.ks == 4) {                                                         \
     if (c.nb == 1) CALL(1, 4); else if (c.nb == 2) CALL(2, 4); else CALL(4, 4); \
@@ -671,26 +676,27 @@ inline RowsCut rows_cut(long long rows_max, long long rows_expected, int pairs, 
 
 // The three convolutions of the chunk that `a` describes.
 template <class F, bool VEC>
-hipError_t launch_rows_convs(const RowsArgs& a, const void* x, const unsigned char* wp1, const unsigned char* wp2,
+hipError_t launch_rows_convs(const RowsArgs& a, int chunk, const void* x, const unsigned char* wp1, const unsigned char* wp2,
                              const unsigned char* wp3, const float* b1, const float* b2, const float* b3, unsigned char* y1,
                              unsigned char* y2, void* out, bool post_relu, hipStream_t st) {
   typedef typename F::T T;
   const Geom& g = a.g;
   // the list's rows of this chunk are not known here: half of the pixels is a middling activation ratio
-  const long long rows = (long long)g.P * g.S * g.S, likely = a.idx ? (a.npx + 1) / 2 : a.npx;
-  RowsCut c = rows_cut(a.npx, a.npx, a.pairs1, a.ks1);
+  // (and every chunk is cut like the full one, which rows_layout has checked)
+  const long long rows = (long long)g.P * g.S * g.S, likely = a.idx ? (chunk + 1) / 2 : chunk;
+  RowsCut c = rows_cut(a.npx, chunk, a.pairs1, a.ks1);
 #define ROWS_CONV1(NB, KS)                                                                                               \
-  hipLaunchKernelGGL((rows_conv1_kernel<F, VEC, NB, KS>), dim3(rows_grid(c.units, c.nsl)), dim3(kRowsThreads), 0, st, a, \
+  hipLaunchKernelGGL((rows_conv1_kernel<F, VEC, NB, KS>), dim3((unsigned)rows_grid(c.units, c.nsl)), dim3(kRowsThreads), 0, st, a, \
                      c.nsl, (const T*)x, wp1, b1, y1)
   ROWS_DISPATCH(c, ROWS_CONV1)
   c = rows_cut(rows, likely, a.pairs1, 9 * a.ksm);
 #define ROWS_CONV2(NB, KS)                                                                                               \
-  hipLaunchKernelGGL((rows_conv2_kernel<F, NB, KS>), dim3(rows_grid(c.units, c.nsl)), dim3(kRowsThreads), 0, st, a,      \
+  hipLaunchKernelGGL((rows_conv2_kernel<F, NB, KS>), dim3((unsigned)rows_grid(c.units, c.nsl)), dim3(kRowsThreads), 0, st, a,      \
                      c.nsl, wp2, b2, y1, y2)
   ROWS_DISPATCH(c, ROWS_CONV2)
   c = rows_cut(rows, likely, a.pairs3, a.ksm);
 #define ROWS_CONV3(NB, KS)                                                                                               \
-  hipLaunchKernelGGL((rows_conv3_kernel<F, VEC, NB, KS>), dim3(rows_grid(c.units, c.nsl)), dim3(kRowsThreads), 0, st, a, \
+  hipLaunchKernelGGL((rows_conv3_kernel<F, VEC, NB, KS>), dim3((unsigned)rows_grid(c.units, c.nsl)), dim3(kRowsThreads), 0, st, a, \
                      c.nsl, (const T*)x, wp3, b3, y2, (T*)out, (int)post_relu)
   ROWS_DISPATCH(c, ROWS_CONV3)
 #undef ROWS_CONV1

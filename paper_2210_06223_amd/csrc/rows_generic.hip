@@ -45,7 +45,7 @@ hipError_t run_rows(const Geom& g, const void* x, const int32_t* idx, const int3
       const long long blocks = ((long long)g.P * (g.S + 2) + kRowsThreads - 1) / kRowsThreads;
       hipLaunchKernelGGL(rows_need_kernel, dim3((unsigned)(blocks < 4096 ? blocks : 4096)), dim3(kRowsThreads), 0, st, a, need);
     }
-    if (hipError_t e = launch_rows_convs<F, VEC>(a, x, wp1, wp2, wp3, w.b1, w.b2, w.b3, y1, y2, out, post_relu, st); e != hipSuccess)
+    if (hipError_t e = launch_rows_convs<F, VEC>(a, l.images * hw, x, wp1, wp2, wp3, w.b1, w.b2, w.b3, y1, y2, out, post_relu, st); e != hipSuccess)
       return e;
   }
   return hipSuccess;

@@ -43,3 +43,16 @@ def test_a_call_that_fails_has_enqueued_nothing():
     st, ev = H.run("result = call('ex', BF16, 2, 14, 14, 1024, 256, 2, attr_fail=1)")
     assert st == -5
     assert not [e for e in ev if e[0] in ("launch", "copy")], ev
+
+
+def test_no_launch_beyond_the_limit_of_threads():
+    """fp32 maps of 1.1e9 pixels: a launch of 2^32 threads is an error, so the scalar kernel (whose grid is bounded) runs."""
+    r = H.run("""
+result = []
+for N, h, w, C, M, S in ((1100, 1000, 1000, 4, 12, 1), (2000, 1000, 1000, 1, 8, 10), (1000, 1000, 1000, 4, 12, 1), (90000, 64, 32, 8, 2000, 1)):
+    st, ev = call('ex', F32, N, h, w, C, M, S, flags=4)
+    result.append([st, [[e[1], int(e[2]) * int(e[3])] for e in ev if e[0] == 'launch']])
+""")
+    for (st, launches), scalar in zip(r, (True, True, False, True)):
+        assert st == 0 and launches and all(n < 1 << 32 for _, n in launches), launches
+        assert (H.kernel_name(launches[0][0]) == "bneck_generic_kernel") == scalar
