@@ -224,8 +224,8 @@ int run_block(const lasnet_tensor* x, const int32_t* idx, const int32_t* count, 
   if (e == hipSuccess && slab) e = prepare_slab(g, idx);     // (beside the others': where its memory cannot be had, they run)
   if (e != hipSuccess) return LASNET_EHIP;
   unsigned char* block_ws = nullptr;             // the tiled or the slab schedule's
-  // Without a matrix-core kernel of its own the shape runs the row schedule; where there is no memory for that (the
-  // caller forbids it, a capture is under way, the map is too large), the one-kernel generic path.
+  // Without a matrix-core kernel of its own the shape runs the row schedule; where that is slower (little to do) or
+  // there is no memory for it (the caller forbids it, a capture is under way, the map is too large), the one-kernel generic path.
   const size_t rows_need = !fast && !own_memory && may_lease ? rows_workspace_bytes(x->dtype, g) : 0;
   void* rows_ws = nullptr;
   Lease lease;

@@ -42,7 +42,7 @@ hipError_t launch_generic(int dtype, const Geom& g, const void* x, const int32_t
                           hipStream_t st);
 
 // The row schedule (bottleneck_rows.hpp): the same function as launch_generic on the matrix cores, through a workspace
-// (256-byte aligned, rows_workspace_bytes(); 0: the map is beyond what its loads address).
+// (256-byte aligned, rows_workspace_bytes(); 0: launch_generic is faster, or the map is beyond what its loads address).
 size_t rows_workspace_bytes(int dtype, const Geom& g);
 hipError_t launch_rows(int dtype, const Geom& g, const void* x, const int32_t* idx, const int32_t* count,
                        const BlockWeights& w, void* out, bool post_relu, void* workspace, hipStream_t st);
