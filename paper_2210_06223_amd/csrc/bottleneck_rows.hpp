@@ -667,12 +667,9 @@ bool rows_layout(const Geom& g, RowsLayout& l) {
   return true;
 }
 
-#define ROWS_DISPATCH(c, CALL)                                             \
-  if (c.ks == 4) {                                                         \
-    if (c.nb == 1) CALL(1, 4); else if (c.nb == 2) CALL(2, 4); else CALL(4, 4); \
-  } else {                                                                 \
-    if (c.nb == 1) CALL(1, 1); else if (c.nb == 2) CALL(2, 1); else CALL(4, 1); \
-  }
+// (several waves to a tile only with one row block: with more there are tiles enough)
+#define ROWS_DISPATCH(c, CALL) \
+  if (c.ks == 4) CALL(1, 4); else if (c.nb == 1) CALL(1, 1); else if (c.nb == 2) CALL(2, 1); else CALL(4, 1);
 
 // The three convolutions of the chunk that `a` describes.
 template <class F, bool VEC>
