@@ -141,12 +141,16 @@ template <>
 __device__ __forceinline__ void store_y<Bf16Wide>(unsigned char* row, int ch, int ksm, const float (&v)[8]) {
   bf16x8 t[3];
 #pragma unroll
-  for (int i = 0; i < 8; ++i) {                  // v = t0 + t1 + t2: each term takes the next 8 significant bits
+  for (int i = 0; i < 8; ++i) {                  // v = t0 + t1 + t2, v >= 0: each term takes the next 8 significant bits
+    // Truncated, so that no term is negative, and no term of a v > 0 is zero (the smallest normal number stands in, 30
+    // decimal places below what fp32 resolves of ordinary values): an infinite weight then gives an infinity, as it
+    // does with v itself, and not the NaN of 0 * inf or of inf - inf.
     float r = v[i];
 #pragma unroll
     for (int k = 0; k < 3; ++k) {
-      t[k][i] = (__bf16)r;
-      r = __builtin_isfinite((float)t[k][i]) ? r - (float)t[k][i] : 0.f;   // (an infinite y stays one)
+      const float top = __uint_as_float(__float_as_uint(r) & 0xffff0000u);
+      t[k][i] = (__bf16)(k > 0 && v[i] > 0.f ? fmaxf(top, 0x1p-126f) : top);
+      r = __builtin_isfinite(r) ? r - top : 0.f;            // (an infinite y stays one)
     }
   }
 #pragma unroll
