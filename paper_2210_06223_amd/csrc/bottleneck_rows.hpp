@@ -73,7 +73,7 @@ struct RowsArgs {
 
 // The active list as rows: row r is pixel (r mod S*S) of entry r / (S*S).
 __device__ __forceinline__ int rows_active(const RowsArgs& a) {
-  return rows_uni(a.idx ? min(*a.count, a.g.P) : a.g.P) * (a.g.S * a.g.S);
+  return rows_uni(a.idx ? max(min(*a.count, a.g.P), 0) : a.g.P) * (a.g.S * a.g.S);     // (P * S * S < 2^31)
 }
 // Its pixel, or -1: past the end of the list, not a cell of the map, or not of this chunk.
 struct RowPixel { int px, h, w; };

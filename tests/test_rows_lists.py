@@ -1,8 +1,11 @@
 """The row schedule's map of needed pixels from long lists: scattered entry by entry, against scanned by the plan."""
 import pytest
+import torch
 
+from paper_2210_06223_amd import binding as B
 from paper_2210_06223_amd import synth
 from tests import _fake_hip as H
+from tests import _util as U
 from tests.test_gpu_parity import _run_case
 
 CASES = [
@@ -28,3 +31,16 @@ def test_long_lists(cfg):
     _run_case(cfg, k=int(round(cfg.r * cfg.P)))
     _run_case(cfg, k=cfg.P)
     _run_case(cfg, k=0)
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("S,count", [(2, -10**9), (2, -1), (3, -2**31), (5, -(2**31) // 25 - 7)])
+def test_a_negative_count_is_an_empty_list(dtype, S, count):
+    """Also one that, times S * S, wraps to a positive number of rows in 32 bits (-10**9 * 4 = 294967296 there)."""
+    cfg = synth.BlockConfig("negative", 1, 6 * S, 4 * S, 64, 40, S, dtype, 0.5, 115)
+    d = U.dev_inputs(synth.make_block_inputs(cfg, want_f64=False))
+    idx = torch.arange(cfg.P, dtype=torch.int32, device="cuda")
+    out = torch.full_like(d["x"], 777.0)
+    B.lasnet_sparse_bottleneck(d["x"], idx, torch.tensor([count], dtype=torch.int32, device="cuda"), S, *U.weights(d), out=out)
+    assert (U.bits(out) == U.bits(d["x"])).all()
