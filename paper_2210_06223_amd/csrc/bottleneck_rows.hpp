@@ -50,13 +50,9 @@ __device__ __forceinline__ V rows_load16(rows_rsrc_t r, unsigned lane_bytes, uns
   return __builtin_bit_cast(V, __builtin_amdgcn_raw_buffer_load_b128(r, (int)lane_bytes, (int)uniform_bytes, 0));
 }
 
-// Where the fragments of a group of 32 output channels lie: groups of 2^sh channel groups `hi` bytes apart, in them channel
-// groups `lo` bytes apart, the two tiles of a k-step next to each other and the k-steps `step` bytes apart.
-struct RowsWeights {
-  unsigned lo, hi, step;
-  int sh;
-  __device__ __forceinline__ unsigned base(int pair) const { return (unsigned)(pair >> sh) * hi + (unsigned)(pair & ((1 << sh) - 1)) * lo; }
-};
+// Where the fragments of the groups of 32 output channels lie: `group` bytes apart, the two tiles of a k-step next to each
+// other and the k-steps `step` bytes apart.
+struct RowsWeights { unsigned group, step; };
 
 // One call (or one chunk of images of it), by value into every kernel.
 struct RowsArgs {
@@ -324,15 +320,6 @@ __device__ __forceinline__ void reduce_over_waves(floatx4 (&acc)[NB][2], ROWS_LD
   }
 }
 
-// Workgroup -> (row tile, channel slice): the slices of a row tile sit on one XCD (workgroup b runs on XCD b mod 8), so
-// the rows they share are fetched into one L2.
-__device__ __forceinline__ void rows_unit(int nsl, int& unit, int& slice) {
-  const int xcd = (int)blockIdx.x & 7, j = (int)blockIdx.x >> 3;
-  unit = (j / nsl) * 8 + xcd;
-  slice = j % nsl;
-}
-inline long long rows_grid(long long units, int nsl) { return (units + 7) / 8 * 8 * nsl; }
-
 // Calls f(integral_constant<n>) for the run-time n in [1, HI] (2 and 3 blocks share an instantiation of 4's size class).
 template <int HI, class Fn>
 __device__ __forceinline__ void rows_blocks(int n, Fn&& f) {
@@ -354,9 +341,8 @@ __global__ __launch_bounds__(kRowsThreads, 2) void rows_conv1_kernel(RowsArgs a,
   __shared__ __attribute__((aligned(16))) float part[KS > 1 ? 4 * NB * 2 * 64 * 4 : 4];
   const int tid = threadIdx.x, lane = tid & 63, l16 = lane & 15, lg = lane >> 4, wave = rows_uni(tid >> 6);
   int unit, slice;
-  rows_unit(nsl, unit, slice);
+  if (!unit_and_slice((a.npx + NB * 16 - 1) / (NB * 16), nsl, unit, slice)) return;
   const int p0 = unit * NB * 16;
-  if (p0 >= a.npx) return;
   // the needed pixels of this run, ascending
   static_assert(NB * 16 <= 64, "one ballot");
   const bool on = lane < NB * 16 && p0 + lane < a.npx && (!a.need || a.need[p0 + lane] != 0);
@@ -385,7 +371,7 @@ __global__ __launch_bounds__(kRowsThreads, 2) void rows_conv1_kernel(RowsArgs a,
       floatx4 acc[N][2];
       start_at_bias<N>(acc, b1, a.g.M, rows_channel(pair, lg), wave % KS == 0);
       if (s0 < s1 && pair < a.pairs1)
-        rows_gemm<F, N, F::XP, 2>(acc, rows_rsrc(wp, a.w1_bytes), a.w1.base(pair), a.w1.step, rows, s0, s1, lane);
+        rows_gemm<F, N, F::XP, 2>(acc, rows_rsrc(wp, a.w1_bytes), pair * a.w1.group, a.w1.step, rows, s0, s1, lane);
       reduce_over_waves<N, KS>(acc, (ROWS_LDS float*)part, wave, lane);
 #pragma unroll
       for (int i = 0; i < N; ++i) {
@@ -410,9 +396,9 @@ __global__ __launch_bounds__(kRowsThreads, 2) void rows_conv2_kernel(RowsArgs a,
   __shared__ __attribute__((aligned(16))) float part[KS > 1 ? 4 * NB * 2 * 64 * 4 : 4];
   const int tid = threadIdx.x, lane = tid & 63, l16 = lane & 15, lg = lane >> 4, wave = rows_uni(tid >> 6);
   int unit, slice;
-  rows_unit(nsl, unit, slice);
-  const int nrows = rows_active(a), r0 = unit * NB * 16;
-  if (r0 >= nrows) return;
+  const int nrows = rows_active(a);
+  if (!unit_and_slice((nrows + NB * 16 - 1) / (NB * 16), nsl, unit, slice)) return;
+  const int r0 = unit * NB * 16;
   YRows<true> rows;
   const unsigned pitch = y_pitch<F>(a.ksm);
   bool any = false;
@@ -438,7 +424,7 @@ __global__ __launch_bounds__(kRowsThreads, 2) void rows_conv2_kernel(RowsArgs a,
     start_at_bias<NB>(acc, b2, a.g.M, rows_channel(pair, lg), wave % KS == 0);
     rows.seek(min(s0, total - 1), NB);
     if (s0 < s1 && pair < a.pairs1)
-      rows_gemm<F, NB, F::YP, 2>(acc, rows_rsrc(wp, a.w2_bytes), a.w2.base(pair), a.w2.step, rows, s0, s1, lane);
+      rows_gemm<F, NB, F::YP, 2>(acc, rows_rsrc(wp, a.w2_bytes), pair * a.w2.group, a.w2.step, rows, s0, s1, lane);
     reduce_over_waves<NB, KS>(acc, (ROWS_LDS float*)part, wave, lane);
 #pragma unroll
     for (int i = 0; i < NB; ++i)
@@ -462,9 +448,9 @@ __global__ __launch_bounds__(kRowsThreads, 2) void rows_conv3_kernel(RowsArgs a,
   typedef typename F::T T;
   const int tid = threadIdx.x, lane = tid & 63, l16 = lane & 15, lg = lane >> 4, wave = rows_uni(tid >> 6);
   int unit, slice;
-  rows_unit(nsl, unit, slice);
-  const int nrows = rows_active(a), r0 = unit * NB * 16;
-  if (r0 >= nrows) return;
+  const int nrows = rows_active(a);
+  if (!unit_and_slice((nrows + NB * 16 - 1) / (NB * 16), nsl, unit, slice)) return;
+  const int r0 = unit * NB * 16;
   YRows<false> rows;
   const unsigned pitch = y_pitch<F>(a.ksm);
   int px[NB];
@@ -486,7 +472,7 @@ __global__ __launch_bounds__(kRowsThreads, 2) void rows_conv3_kernel(RowsArgs a,
     const int ch = rows_channel(pair, lg);
     start_at_bias<NB>(acc, b3, C, ch, wave % KS == 0);
     if (s0 < s1 && pair < a.pairs3)
-      rows_gemm<F, NB, F::YP, 2>(acc, rows_rsrc(wp, a.w3_bytes), a.w3.base(pair), a.w3.step, rows, s0, s1, lane);
+      rows_gemm<F, NB, F::YP, 2>(acc, rows_rsrc(wp, a.w3_bytes), pair * a.w3.group, a.w3.step, rows, s0, s1, lane);
     reduce_over_waves<NB, KS>(acc, (ROWS_LDS float*)part, wave, lane);
 #pragma unroll
     for (int i = 0; i < NB; ++i)
@@ -664,7 +650,7 @@ bool rows_layout(const Geom& g, RowsLayout& l) {
   for (const RowsCut& c : {rows_cut(chunk, chunk, (int)pairs1, (int)ks1), rows_cut(all, (chunk + 1) / 2, (int)pairs1, 9 * (int)ksm),
                            rows_cut(all, chunk, (int)pairs1, 9 * (int)ksm), rows_cut(all, (chunk + 1) / 2, (int)pairs3, (int)ksm),
                            rows_cut(all, chunk, (int)pairs3, (int)ksm)})
-    if (rows_grid(c.units, c.nsl) * kRowsThreads >= 1ll << 32) return false;
+    if (sliced_grid(c.units, c.nsl) * kRowsThreads >= 1ll << 32) return false;
   l.need = (n * hw + kNeedPixels - 1) / kNeedPixels * kNeedPixels;
   l.y = rows_round(n * hw * ypx);
   l.total = rows_round(l.w1) + rows_round(l.w2) + rows_round(l.w3) + l.need + 2 * l.y;
@@ -687,17 +673,17 @@ hipError_t launch_rows_convs(const RowsArgs& a, int chunk, const void* x, const 
   const long long rows = (long long)g.P * g.S * g.S, likely = a.idx ? (chunk + 1) / 2 : chunk;
   RowsCut c = rows_cut(a.npx, chunk, a.pairs1, a.ks1);
 #define ROWS_CONV1(NB, KS)                                                                                               \
-  hipLaunchKernelGGL((rows_conv1_kernel<F, VEC, NB, KS>), dim3((unsigned)rows_grid(c.units, c.nsl)), dim3(kRowsThreads), 0, st, a, \
+  hipLaunchKernelGGL((rows_conv1_kernel<F, VEC, NB, KS>), dim3((unsigned)sliced_grid(c.units, c.nsl)), dim3(kRowsThreads), 0, st, a, \
                      c.nsl, (const T*)x, wp1, b1, y1)
   ROWS_DISPATCH(c, ROWS_CONV1)
   c = rows_cut(rows, likely, a.pairs1, 9 * a.ksm);
 #define ROWS_CONV2(NB, KS)                                                                                               \
-  hipLaunchKernelGGL((rows_conv2_kernel<F, NB, KS>), dim3((unsigned)rows_grid(c.units, c.nsl)), dim3(kRowsThreads), 0, st, a,      \
+  hipLaunchKernelGGL((rows_conv2_kernel<F, NB, KS>), dim3((unsigned)sliced_grid(c.units, c.nsl)), dim3(kRowsThreads), 0, st, a,      \
                      c.nsl, wp2, b2, y1, y2)
   ROWS_DISPATCH(c, ROWS_CONV2)
   c = rows_cut(rows, likely, a.pairs3, a.ksm);
 #define ROWS_CONV3(NB, KS)                                                                                               \
-  hipLaunchKernelGGL((rows_conv3_kernel<F, VEC, NB, KS>), dim3((unsigned)rows_grid(c.units, c.nsl)), dim3(kRowsThreads), 0, st, a, \
+  hipLaunchKernelGGL((rows_conv3_kernel<F, VEC, NB, KS>), dim3((unsigned)sliced_grid(c.units, c.nsl)), dim3(kRowsThreads), 0, st, a, \
                      c.nsl, (const T*)x, wp3, b3, y2, (T*)out, (int)post_relu)
   ROWS_DISPATCH(c, ROWS_CONV3)
 #undef ROWS_CONV1

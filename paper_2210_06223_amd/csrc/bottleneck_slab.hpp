@@ -36,15 +36,6 @@ struct SlabArgs {
   int m_t2, m_t, m_s2, m_s;        // small_div's multipliers for (S+2)^2, S+2, S*S and S
 };
 
-// Workgroup -> (row tile, channel slice): the slices of a row tile sit on one XCD (workgroup b runs on XCD b mod 8), so
-// the rows they share are fetched into one L2.
-__device__ __forceinline__ void slab_unit(int nsl, int& unit, int& slice) {
-  const int xcd = (int)blockIdx.x & 7, j = (int)blockIdx.x >> 3;
-  unit = (j / nsl) * 8 + xcd;
-  slice = j % nsl;
-}
-inline int slab_grid(int units, int nsl) { return (units + 7) / 8 * 8 * nsl; }
-
 __device__ __forceinline__ void slab_load(const AS_GLOBAL __bf16* src, AS_LDS __bf16* dst) {     // 64 x 16 bytes -> 1 KiB at dst
   const unsigned a = uni((int)(unsigned)(size_t)dst);
   asm volatile("s_mov_b32 m0, %1\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, off" ::"v"(src), "s"(a) : "memory");
@@ -220,9 +211,8 @@ __global__ __launch_bounds__(NW * 64, NW / 2) void slab_conv1_kernel(SlabArgs a,
   AS_LDS __bf16* slab = (AS_LDS __bf16*)smem;
   const int tid = threadIdx.x, lane = tid & 63, l16 = lane & 15, lg = lane >> 4, wave = uni(tid >> 6);
   int unit, slice;
-  slab_unit(a.nsl, unit, slice);
+  if (!unit_and_slice((a.npx + NB * 16 - 1) / (NB * 16), a.nsl, unit, slice)) return;
   const int p0 = unit * NB * 16;
-  if (p0 >= a.npx) return;
   // the lane reads the chunk that belongs at the position it writes
 #pragma unroll
   for (int u = 0; u < NB * 32 * C / 1024 / NW; ++u) {
@@ -250,7 +240,7 @@ __global__ __launch_bounds__(NW * 64, NW / 2) void slab_conv1_kernel(SlabArgs a,
 // the other, then an all-zero row for what lies outside the image.  Output row q of patch p reads window row
 // (i + dy, j + dx): the key p*S*S + wy*S + wx of a window row makes that q + dy*S + dx, so the 16 rows of a
 // block always have 16 different keys.
-constexpr int kSlabMaxPatches = 64, kSlabMaxRows = 608;   // (608 rows of 128 channels fill the LDS)
+constexpr int kSlabMaxPatches = 64, kSlabMaxRows = 304;   // (304 rows of 256 channels, the zero row among them, are 152 KB)
 // the all-zero row comes after whole 1 KiB pieces of window rows
 template <int M>
 __device__ __host__ __forceinline__ int slab_zero_row(int wrows) {
@@ -268,7 +258,7 @@ __global__ __launch_bounds__(NW * 64, 1) void slab_conv2_kernel(SlabArgs a, cons
   AS_LDS __bf16* slab = (AS_LDS __bf16*)smem;
   const int tid = threadIdx.x, lane = tid & 63, l16 = lane & 15, lg = lane >> 4, wave = uni(tid >> 6);
   int unit, slice;
-  slab_unit(a.nsl, unit, slice);
+  unit_and_slice(0, a.nsl, unit, slice);       // (a unit past the last has no entries)
   const int S = a.g.S, T = S + 2, T2 = T * T, H = a.g.H, W = a.g.W, ppt = a.ppt, wrows = ppt * T2;
   const int zrow = slab_zero_row<M>(wrows);
   const SlabWave<NW, TJ> mine(slice, wave, lg);
@@ -355,7 +345,7 @@ __global__ __launch_bounds__(256, 2) void slab_conv3_kernel(SlabArgs a, const __
   AS_LDS __bf16* slab = (AS_LDS __bf16*)smem;
   const int tid = threadIdx.x, lane = tid & 63, l16 = lane & 15, lg = lane >> 4, wave = uni(tid >> 6);
   int unit, slice;
-  slab_unit(a.nsl, unit, slice);
+  unit_and_slice(0, a.nsl, unit, slice);       // (a unit past the last has no entries)
   const int S = a.g.S, pair = slice * 4 + wave, ch = pair * 32 + lg * 8;
   int mine = -1;
   if (lane < NB * 16) {

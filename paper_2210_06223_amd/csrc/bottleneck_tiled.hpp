@@ -135,17 +135,6 @@ __device__ __forceinline__ int cell_of(const GroupPixel& q, int h, int w, const 
   return q.li * tg.cpi + mdiv(h, tg.m_s) * g.GW + mdiv(w, tg.m_s);
 }
 
-// Workgroup b -> (unit, slice): the NSL slices of a unit are consecutive workgroups of ONE XCD
-// (workgroups are dealt round-robin to the 8 XCDs, each with its own L2), so what the slices share
-// -- the unit's activations -- is fetched into one L2 once.
-__device__ __forceinline__ bool unit_and_slice(int nunits, int nsl, int& unit, int& slice) {
-  const int xcd = (int)blockIdx.x & 7, j = (int)blockIdx.x >> 3;
-  unit = (j / nsl) * 8 + xcd;
-  slice = j % nsl;
-  return unit < nunits;
-}
-inline int tiled_grid(int nunits, int nsl) { return (nunits + 7) / 8 * 8 * nsl; }
-
 // The byte mask of one group's cells -> LDS, in two steps so that a kernel can put its long prefetches
 // between them: a wave's loads complete in issue order, so whatever is requested BEFORE these small
 // loads delays them, and whatever is requested after them (and before the wait) flies along.
@@ -522,14 +511,14 @@ hipError_t launch_tiled(const Geom& g, const void* x, const int32_t* idx, const 
   const __bf16* p3 = p2 + 9 * (size_t)TC::M * TC::M;
   const bool all = idx == nullptr;
   const uint8_t* mask_src = all ? nullptr : (cellmask ? cellmask : mask_ws);
-  hipLaunchKernelGGL(tiled_conv1_kernel<TC>, dim3(tiled_grid(tg.ngroups * tg.nt1, TC::NSL1)), dim3(256),
+  hipLaunchKernelGGL(tiled_conv1_kernel<TC>, dim3((unsigned)sliced_grid(tg.ngroups * tg.nt1, TC::NSL1)), dim3(256),
                      TC::K1::LDS_BYTES, st, g, tg, (const __bf16*)x, idx, count, all ? nullptr : cellmask,
                      (all || cellmask) ? nullptr : mask_ws, p1, b1, y1g);
   if (hipError_t e = hipGetLastError(); e != hipSuccess) return e;
-  hipLaunchKernelGGL(tiled_conv2_kernel<TC>, dim3(tiled_grid(tg.ngroups, TC::NSL2)), dim3(256), TC::K2::LDS_BYTES, st,
+  hipLaunchKernelGGL(tiled_conv2_kernel<TC>, dim3((unsigned)sliced_grid(tg.ngroups, TC::NSL2)), dim3(256), TC::K2::LDS_BYTES, st,
                      g, tg, mask_src, (int)all, p2, b2, (const __bf16*)y1g, y2g);
   if (hipError_t e = hipGetLastError(); e != hipSuccess) return e;
-  hipLaunchKernelGGL(tiled_conv3_kernel<TC>, dim3(tiled_grid(tg.ngroups, TC::NSL3)), dim3(256), TC::K3::LDS_BYTES, st,
+  hipLaunchKernelGGL(tiled_conv3_kernel<TC>, dim3((unsigned)sliced_grid(tg.ngroups, TC::NSL3)), dim3(256), TC::K3::LDS_BYTES, st,
                      g, tg, mask_src, (int)all, (const __bf16*)x, p3, b3, (const __bf16*)y2g, (__bf16*)out,
                      (int)post_relu);
   return hipGetLastError();

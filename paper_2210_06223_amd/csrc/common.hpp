@@ -27,6 +27,17 @@ struct BlockWeights {
   const void* W3; const float* b3;
 };
 
+// Workgroup b -> (unit, slice) of a launch of sliced_grid(): the nsl slices of a unit are consecutive workgroups of ONE XCD
+// (workgroups are dealt round-robin to the 8 XCDs, each with its own L2), so what the slices share -- the unit's
+// activations -- is fetched into one L2 once.  false: no such unit (the grid is rounded up).
+__device__ __forceinline__ bool unit_and_slice(int nunits, int nsl, int& unit, int& slice) {
+  const int xcd = (int)blockIdx.x & 7, j = (int)blockIdx.x >> 3;
+  unit = (j / nsl) * 8 + xcd;
+  slice = j % nsl;
+  return unit < nunits;
+}
+inline long long sliced_grid(long long nunits, int nsl) { return (nunits + 7) / 8 * 8 * nsl; }
+
 // ---- launchers (each returns a hipError_t from the launch, never synchronises) ----
 hipError_t launch_masker(const lasnet_tensor& x, const float* Wm, float bm, int S, float thr,
                          uint8_t* mask, int32_t* idx, int32_t* count, double* logits,

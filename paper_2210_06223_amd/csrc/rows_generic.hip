@@ -24,9 +24,9 @@ hipError_t run_rows(const Geom& g, const void* x, const int32_t* idx, const int3
   a.count = count;
   a.need = idx ? need : nullptr;
   constexpr unsigned kStep = 2 * F::KPL * 1024;
-  a.w1 = RowsWeights{a.ks1 * kStep, 0, kStep, 30};
-  a.w2 = RowsWeights{9 * a.ksm * kStep, 0, kStep, 30};
-  a.w3 = RowsWeights{a.ksm * kStep, 0, kStep, 30};
+  a.w1 = RowsWeights{a.ks1 * kStep, kStep};
+  a.w2 = RowsWeights{9 * a.ksm * kStep, kStep};
+  a.w3 = RowsWeights{a.ksm * kStep, kStep};
   a.w1_bytes = (unsigned)l.w1;
   a.w2_bytes = (unsigned)l.w2;
   a.w3_bytes = (unsigned)l.w3;

@@ -39,7 +39,7 @@ struct Conv1 {
   }
   static hipError_t run(SlabArgs a, const void* x, const __bf16* wp, const float* b1, __bf16* y1, hipStream_t st) {
     a.nsl = slices;
-    hipLaunchKernelGGL(k, dim3(slab_grid(tiles(a), slices)), dim3(NW * 64), lds, st, a, (const __bf16*)x, wp, b1, y1);
+    hipLaunchKernelGGL(k, dim3((unsigned)sliced_grid(tiles(a), slices)), dim3(NW * 64), lds, st, a, (const __bf16*)x, wp, b1, y1);
     return hipGetLastError();
   }
 };
@@ -67,7 +67,7 @@ struct Conv2 {
   static hipError_t run(SlabArgs a, const __bf16* wp, const float* b2, const __bf16* y1, __bf16* y2, hipStream_t st) {
     a.nsl = slices;
     a.ppt = ppt(a);
-    hipLaunchKernelGGL(k, dim3(slab_grid(tiles(a, a.g.P), slices)), dim3(NW * 64), lds(a), st, a, wp, b2, y1, y2);
+    hipLaunchKernelGGL(k, dim3((unsigned)sliced_grid(tiles(a, a.g.P), slices)), dim3(NW * 64), lds(a), st, a, wp, b2, y1, y2);
     return hipGetLastError();
   }
 };
@@ -90,7 +90,7 @@ struct Conv3 {
   static hipError_t run(SlabArgs a, const void* x, const __bf16* wp, const float* b3, const __bf16* y2, void* out, bool post_relu,
                         hipStream_t st) {
     a.nsl = slices;
-    hipLaunchKernelGGL(k, dim3(slab_grid(tiles(a.npx), slices)), dim3(256), lds, st, a, (const __bf16*)x, wp, b3, y2,
+    hipLaunchKernelGGL(k, dim3((unsigned)sliced_grid(tiles(a.npx), slices)), dim3(256), lds, st, a, (const __bf16*)x, wp, b3, y2,
                        (__bf16*)out, (int)post_relu);
     return hipGetLastError();
   }
