@@ -172,13 +172,15 @@ LASNET_API int lasnet_sparse_bottleneck_ex(const lasnet_tensor* x, const int32_t
  *          rate); for 1024x256 the fused kernel measured faster or equal at every rate, so the tiled
  *          one runs only with LASNET_FORCE_TILED (a caller that wants the in-place update).
  *   slab   the same split in smaller pieces, for a few images of 1024x256 and 2048x512 channels (up to 16
- *          14x14 images' worth of pixels, 32 with patches of S = 7, 40 7x7 images'): the fused kernel would
- *          leave most of the GPU idle there.  It needs at most 8 MiB for y1 and y2, from where the tiled one takes
- *          its own (a lasnet_workspace_bytes() buffer is large enough); without them --
+ *          14x14 images' worth of pixels, 10 with patches of S = 1, 32 with S = 7, 40 7x7 images'): the fused
+ *          kernel would leave most of the GPU idle there.  It needs at most 8 MiB for y1 and y2, from where the tiled one
+ *          takes its own: 4*N*H*W*M + 512 bytes.  (A lasnet_workspace_bytes() buffer is as large as that; where an image has
+ *          too many pixels for the tiled schedule that query answers 0, and lasnet_sparse_bottleneck_planned still runs the
+ *          slab schedule in a workspace of that size.)  Without the memory --
  *          lasnet_sparse_bottleneck_planned without a workspace, and 1024x256 under capture except in
  *          lasnet_sparse_bottleneck_planned and _noalloc, because a graph may be replayed beside later calls on
  *          the stream whose buffer it would use -- the fused or tiled schedule runs as it would for more images.
- * Results are the same function of the inputs either way (same roundings: y1, y2 to bf16, out once).
+ * Results are the same bits whichever runs (same roundings: y1, y2 to bf16, out once; same order of every sum).
  * The tiled schedule needs lasnet_workspace_bytes() of device memory (that query answers for every
  * shape that has a tiled schedule, chosen by default or not; 0 = none): lasnet_sparse_bottleneck[_ex],
  * lasnet_dense_bottleneck and lasnet_sparse_bottleneck_packed take it from the library's per-stream
@@ -198,8 +200,8 @@ LASNET_API size_t lasnet_workspace_bytes(int dtype, int N, int H, int W, int C, 
  * as large, so what is left behind does not exceed what is in use -- or, on a device without room for that, as
  * large as the call needs); all are kept until
  * the process ends.  So those entry points cannot be stream-captured before the stream's buffer has its
- * final size.  Shapes and types without a matrix-core kernel of their own (all of fp32) keep y1 and y2 there as
- * well, at most 256 MiB of them at a time; where that memory cannot be had, and under capture, they run a
+ * final size.  Shapes and types without a matrix-core kernel of their own (all of fp32), unless there is little to do,
+ * keep y1 and y2 there as well, at most 256 MiB of them at a time; where that memory cannot be had, and under capture, they run a
  * slower kernel that needs none.
  * Weights of an inference model do not change, so a caller can instead
  * repack once, like it folded BN once (Sec. 3.4), and pass the result to

@@ -11,7 +11,7 @@ using namespace lasnet;
 namespace {
 
 // Device memory the library owns: one buffer per (device, stream) for what a call needs beyond its arguments
-// (repacked weights, the intermediates of the tiled and the row schedule).  Work on one stream is ordered, so calls on
+// (repacked weights, the intermediates of the tiled, the slab and the row schedule).  Work on one stream is ordered, so calls on
 // the same stream may share it; calls on different streams get different buffers.  The launches of one call go out
 // while its lease holds the buffer's lock, so two threads that call on one stream do not interleave theirs.
 // A buffer that turns out too small is not freed (work already enqueued, or a captured graph, may still use it): one

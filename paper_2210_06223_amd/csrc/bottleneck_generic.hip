@@ -4,9 +4,9 @@
 // gather fused into the dynamic convolution), keep y1 and y2 in LDS as fp32, add the
 // residual and write the S x S result in place of the patch (scatter fused with the add).
 // Shapes without a matrix-core kernel (and all of fp32) run the row schedule (bottleneck_rows.hpp); this kernel
-// is what they run where that may have no workspace: lasnet_sparse_bottleneck_noalloc, a stream that is being
-// captured before its buffer exists, maps beyond the row schedule's 32-bit offsets.  fp32 accumulation, no
-// intermediate rounding, as there.
+// is what they run where that is slower (little to do: scalar_is_faster()) or may have no workspace:
+// lasnet_sparse_bottleneck_noalloc, any stream that is being captured, maps beyond the row schedule's 32-bit offsets.
+// fp32 accumulation, no intermediate rounding, as there.
 #include "common.hpp"
 
 namespace lasnet {

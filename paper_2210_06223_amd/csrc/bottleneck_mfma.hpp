@@ -849,7 +849,7 @@ __global__ __launch_bounds__(K::NT, K::WAVES_PER_SIMD) void fused_bneck_kernel(
   // Where the launch takes several rounds, each round has a contiguous part of the list and the LAST part goes first:
   // the masker has just gone through the map from its first image to its last, and the Infinity Cache still holds its end.
   // (One sweep for the whole launch -> this, call sequences: 56x56x256, S=4, batch 256, a map of 411 MB: 251.0 -> 241.6 us;
-  // 28x28x512, S=4, batch 128: 78.1 -> 77.2; launches of one round are cut as before.)
+  // 28x28x512, S=4, batch 128, a map of 103 MB: no difference beyond the noise; launches of one round are cut as before.)
   int lo = 0, hi = nact, nr = nt, b = (int)blockIdx.x;         // the round's part of the list, its workgroups, this one of them
   if (nt > tile_slots) {
     const int q = b / tile_slots * tile_slots;

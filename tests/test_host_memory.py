@@ -56,3 +56,23 @@ for N, h, w, C, M, S in ((1100, 1000, 1000, 4, 12, 1), (2000, 1000, 1000, 1, 8, 
     for (st, launches), scalar in zip(r, (True, True, False, True)):
         assert st == 0 and launches and all(n < 1 << 32 for _, n in launches), launches
         assert (H.kernel_name(launches[0][0]) == "bneck_generic_kernel") == scalar
+
+
+def test_planned_workspace_for_the_slab_schedule():
+    """What the header says a caller has to bring: 4*N*H*W*M + 512 bytes, also for maps that the tiled schedule does not take (the
+    query answers 0 there, and without a workspace the fused kernel runs); never more than the query's answer where it has one."""
+    shapes = [(1, 25, 42, 2048, 512, 1), (1, 50, 60, 1024, 256, 2), (2, 14, 14, 1024, 256, 2), (3, 7, 7, 2048, 512, 1), (1, 1, 1, 2048, 512, 1)]
+    r = H.run("""
+result = []
+for N, h, w, C, M, S in %r:
+    q, need = L.lasnet_workspace_bytes(BF16, N, h, w, C, M, S), 4 * N * h * w * M + 512
+    runs = [[st, kernels(ev), [e for e in ev if e[0] == 'malloc']] for st, ev in
+            (call('planned', BF16, N, h, w, C, M, S, flags=4, ws=b, capturing=c) for b in ((need, 0) if q == 0 else (q,)) for c in (0, 1))]
+    result.append([q, need, runs])
+""" % shapes)
+    for shape, (q, need, runs) in zip(shapes, r):
+        assert q == 0 or q + 512 >= need
+        assert (q == 0) == (shape[1] * shape[2] > (196 if shape[3] == 1024 else 49))
+        for i, (st, names, mallocs) in enumerate(runs):
+            assert st == 0 and not mallocs
+            assert all(("slab" if i < 2 else "fused") in n for n in names), (shape, names)
