@@ -361,15 +361,22 @@ def main():
             pix_need |= pad[:, dy:dy + cfg.H, dx:dx + cfg.W]
     w_bytes = (2 * cfg.C * cfg.M + 9 * cfg.M * cfg.M) * esize
     alg_bytes = (int(pix_need.sum()) + int(pix_act.sum())) * cfg.C * esize + w_bytes
-    tiled = fast and ws_bytes > 0 and args.schedule != "fused" and (args.schedule == "tiled" or (cfg.C, cfg.M) == (2048, 512))
-    # The tiled schedule's own minimum adds what its three kernels hand on through memory: y1 of every needed
-    # pixel and y2 of every active pixel written once and read once, and the residual read again by the third.
+    from paper_2210_06223_amd import latency_model as LM
+    schedule = "generic" if not fast else args.schedule if forced else LM.schedule_of(cfg.N, cfg.H, cfg.W, cfg.C, cfg.M, S)
+    if schedule == "fused" and (cfg.C, cfg.M, S) == (256, 64, 8):
+        schedule = "stream"
+    # The tiled and the slab schedule's own minimum adds what their three kernels hand on through memory: y1 of every needed
+    # pixel (slab: of every pixel) and y2 of every active pixel written once and read once, and the residual read again by
+    # the third.
     alg_bytes_path = alg_bytes
-    if tiled:
-        alg_bytes += (2 * int(pix_need.sum()) + 2 * int(pix_act.sum())) * cfg.M * esize + int(pix_act.sum()) * cfg.C * esize
+    if schedule in ("tiled", "slab"):
+        pix_conv1 = int(pix_need.sum()) if schedule == "tiled" else pix_need.size
+        alg_bytes += (pix_conv1 - int(pix_need.sum())) * cfg.C * esize
+        alg_bytes += (2 * pix_conv1 + 2 * int(pix_act.sum())) * cfg.M * esize + int(pix_act.sum()) * cfg.C * esize
     achieved_gbs = alg_bytes / fused_s / 1e9
-    schedule = "generic" if not fast else "tiled" if tiled else "stream" if (cfg.C, cfg.M, S) == (256, 64, 8) else "fused"
-    kernel_name = {"generic": "rows_conv1_kernel + rows_conv2_kernel + rows_conv3_kernel", "stream": "stream_bneck_kernel", "fused": "fused_bneck_kernel",
+    kernel_name = {"generic": "rows_conv1_kernel + rows_conv2_kernel + rows_conv3_kernel (little work: bneck_generic_kernel)",
+                   "stream": "stream_bneck_kernel", "fused": "fused_bneck_kernel",
+                   "slab": "slab_conv1_kernel + slab_conv2_kernel + slab_conv3_kernel (one block = three launches)",
                    "tiled": "tiled_conv1_kernel + tiled_conv2_kernel + tiled_conv3_kernel (one block = three launches; "
                             "per-kernel durations: profiles/)"}[schedule]
     # the bound is whichever ideal time is longer: active FLOPs at the MFMA peak or these bytes at the HBM peak

@@ -17,6 +17,8 @@ to measured latency-against-ratio sweeps (profiles/ratio_sweeps_mi355x.txt):
                               Workgroups fill the chip's slots in launch order; latency = t0 + makespan.
   tiled schedule              three launches; latency = F + g1 * max blocks of a conv1 tile
                                   + g2 * max over image groups of (blocks + p per pass) of conv2/conv3.
+  slab schedule               three launches cut to fill the chip; latency = t0 + px * pixels of the map (conv1)
+                                  + rows * active pixels (conv2, conv3); profiles/slab_sweep_mi355x.txt.
 
 It is a model of THIS implementation (it predicts what the library will take, e.g. to choose S or a
 schedule), not of the hardware in general.  Nothing in the product path calls it.
@@ -126,8 +128,18 @@ def _makespan(times: Sequence[float], slots: int) -> float:
     return max(heap)
 
 
+def schedule_of(N: int, H: int, W: int, C: int, M: int, S: int) -> str:
+    """The schedule that the library picks for a bf16 shape with a matrix-core kernel (given a workspace, not under capture)."""
+    px = N * H * W
+    if (C, M) == (1024, 256) and px <= (32 if S >= 7 else 16 if S > 1 else 10) * 196 or (C, M) == (2048, 512) and px <= 40 * 49:
+        return "slab"
+    return "tiled" if (C, M) == (2048, 512) and H * W <= 49 else "fused"
+
+
 def features(idx: np.ndarray, N: int, H: int, W: int, C: int, M: int, S: int, schedule: str) -> dict:
     """The integer quantities the coefficients multiply."""
+    if schedule == "slab":
+        return dict(px=N * H * W, rows=len(idx) * S * S)
     if schedule == "tiled":
         p = TILED[(C, M)]
         G, GW = H // S, W // S
@@ -169,6 +181,8 @@ def features(idx: np.ndarray, N: int, H: int, W: int, C: int, M: int, S: int, sc
 
 
 def _predict(f: dict, k: Dict[str, float], schedule: str, kind: str) -> float:
+    if schedule == "slab":
+        return k["t0"] + k["px"] * f["px"] + k["rows"] * f["rows"]
     if schedule == "tiled":
         if not f["any"]:
             return k["F"]
@@ -189,8 +203,8 @@ def predict_us(idx: np.ndarray, N: int, H: int, W: int, C: int, M: int, S: int, 
     """Predicted latency of the block (prepacked weights, no identity pass-through) in microseconds."""
     coeffs = COEFFS if coeffs is None else coeffs
     if schedule == "auto":
-        schedule = "tiled" if (C, M) == (2048, 512) else "fused"
-    kind = "tiled" if schedule == "tiled" else FUSED[(C, M, S)]["kind"]
+        schedule = schedule_of(N, H, W, C, M, S)
+    kind = schedule if schedule in ("tiled", "slab") else FUSED[(C, M, S)]["kind"]
     k = coeffs[key_of(C, M, S, schedule)]
     return _predict(features(np.asarray(idx), N, H, W, C, M, S, schedule), k, schedule, kind)
 
@@ -205,11 +219,11 @@ def fit(points: List[dict]) -> Dict[str, Dict[str, float]]:
         groups.setdefault(key_of(p["C"], p["M"], p["S"], p["schedule"]), []).append(p)
     for key, pts in groups.items():
         sch = pts[0]["schedule"]
-        kind = "tiled" if sch == "tiled" else FUSED[(pts[0]["C"], pts[0]["M"], pts[0]["S"])]["kind"]
+        kind = sch if sch in ("tiled", "slab") else FUSED[(pts[0]["C"], pts[0]["M"], pts[0]["S"])]["kind"]
         feats = [features(np.asarray(p["idx"]), p["N"], p["H"], p["W"], p["C"], p["M"], p["S"], sch) for p in pts]
         y = np.array([p["ms"] * 1e3 for p in pts])
-        names = ["F", "g1", "g2", "p"] if sch == "tiled" else ["t0", "c"] if kind == "stream" else ["t0", "w0", "a", "b", "c"]
-        if sch != "tiled" and kind == "fused" and FUSED[(pts[0]["C"], pts[0]["M"], pts[0]["S"])]["PPW"] * pts[0]["S"] ** 2 > 64:
+        names = {"tiled": ["F", "g1", "g2", "p"], "slab": ["t0", "px", "rows"], "stream": ["t0", "c"]}.get(kind, ["t0", "w0", "a", "b", "c"])
+        if kind == "fused" and FUSED[(pts[0]["C"], pts[0]["M"], pts[0]["S"])]["PPW"] * pts[0]["S"] ** 2 > 64:
             names.append("d")
         x0 = np.full(len(names), 1.0)
 

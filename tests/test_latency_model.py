@@ -65,3 +65,25 @@ def test_predicted_latency_does_not_fall_when_more_is_active():
         t = LM.predict_us(il, cfg.N, cfg.H, cfg.W, cfg.C, cfg.M, cfg.S, "tiled")
         assert t >= prev - 1e-9
         prev = t
+
+
+def test_slab_predictions_against_the_stored_sweep_and_the_librarys_own_choice():
+    """Host side of the library by a recording HIP runtime: the schedule that schedule_of names is the one that runs."""
+    from tests import _fake_hip as H
+    worst, n = 0.0, 0
+    for line in open(os.path.join(ROOT, "profiles", "slab_sweep_mi355x.txt")):
+        if line.startswith("#"):
+            continue
+        v = line.split()
+        shape = tuple(map(int, v[:6]))
+        il = np.arange(int(v[7]))
+        assert LM.schedule_of(*shape) == "slab"
+        pred = LM.predict_us(il, *shape, "auto")
+        assert abs(pred - float(v[9])) < 0.06
+        worst, n = max(worst, abs(pred / float(v[8]) - 1)), n + 1
+    assert n > 100 and worst < 0.2, worst
+    shapes = [(N, h, w, C, M, S) for C, M, S, hw in ((1024, 256, 1, 14), (1024, 256, 2, 14), (1024, 256, 7, 14), (2048, 512, 1, 7), (512, 128, 4, 28))
+              for N in (1, 10, 11, 16, 17, 32, 33, 40, 41, 128) for h, w in ((hw, hw), (hw, 3 * hw))]
+    got = H.run("result = [kernels(call('packed', BF16, *a, flags=4)[1])[-1] for a in %r]" % shapes)
+    for shape, name in zip(shapes, got):
+        assert H.kernel_name(name).split("_")[0] == LM.schedule_of(*shape), shape
