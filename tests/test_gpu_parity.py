@@ -243,7 +243,7 @@ def test_mfma_extremes_and_flags(cfg, k):
     _run_case(cfg, k=cfg.P)                                    # ratio 1: every patch active
     _run_case(cfg, k=1)
     _run_case(cfg, k=k, flags=B.LASNET_POST_RELU)
-    _run_case(cfg, k=k, flags=B.LASNET_FORCE_GENERIC)          # scalar kernel on the same shape
+    _run_case(cfg, k=k, flags=B.LASNET_FORCE_GENERIC)          # the row schedule on the same shape
     if _tiled(cfg):
         for forced in (B.LASNET_FORCE_FUSED, B.LASNET_FORCE_TILED):
             for kk in (0, cfg.P, 1):
@@ -589,8 +589,9 @@ def test_planned_entry_with_callers_workspace_and_mask(cfg):
                          ids=lambda v: getattr(v, "name", str(v)))
 def test_in_place_update_on_the_tiled_schedule(cfg, flags):
     """out == x: the tiled schedule updates the active patches in place (its last kernel touches only
-    their own elements, after the kernel that reads neighbours); same bits as out of place, and the
-    oracle's result.  The fused schedule refuses."""
+    their own elements, after the kernel that reads neighbours), and so does the slab schedule, which
+    the unforced case of a few images runs; same bits as out of place, and the oracle's result.  The
+    fused schedule refuses."""
     inp = synth.make_block_inputs(cfg)
     d = U.dev_inputs(inp)
     il = synth.make_index_list(cfg.N, cfg.G, cfg.GW, 0.5, seed=cfg.seed + 3)

@@ -19,7 +19,7 @@ CASES = [
     synth.BlockConfig("c40_m33_s4_bf16", 2, 8, 12, 40, 33, 4, "bf16", 0.5, 64),        # a second group of one channel
     synth.BlockConfig("c64_m32_s1_f32", 2, 9, 7, 64, 32, 1, "f32", 0.2, 65),           # whole steps and groups
     synth.BlockConfig("c264_m96_s5_bf16", 1, 15, 20, 264, 96, 5, "bf16", 0.6, 66),     # reduction over four waves
-    synth.BlockConfig("c64_m16_s8_f32", 6, 40, 40, 64, 16, 8, "f32", 0.5, 67),         # enough rows for 32-row tiles
+    synth.BlockConfig("c64_m16_s8_f32", 6, 40, 40, 64, 16, 8, "f32", 0.5, 67),         # many row tiles; patches of 64 pixels
 ]
 
 
