@@ -19,6 +19,8 @@ to measured latency-against-ratio sweeps (profiles/ratio_sweeps_mi355x.txt):
                                   + g2 * max over image groups of (blocks + p per pass) of conv2/conv3.
   slab schedule               three launches cut to fill the chip; latency = t0 + px * pixels of the map (conv1)
                                   + rows * active pixels (conv2, conv3); profiles/slab_sweep_mi355x.txt.
+                              (Time on the GPU: a caller that launches block after block from Python waits
+                              for its own launches at a few images, about 15 us each.)
 
 It is a model of THIS implementation (it predicts what the library will take, e.g. to choose S or a
 schedule), not of the hardware in general.  Nothing in the product path calls it.
