@@ -73,7 +73,7 @@ struct Slab {
     // One wave per SIMD issues an instruction every four clocks at best, and a k-step has as few as one MFMA of 16, so it may
     // hold little else: the swizzle flips bits 4 .. 7 of a chunk's byte offset, so four addresses per row (k-steps 0 .. 3 of
     // a tap) serve the others through the immediate offset.  (With the address worked out for every k-step, a k-step took 85 to
-    // 100 clocks: 14x14x1024, S=2, one image 13.1 us; so 10.4.)
+    // 100 clocks: 14x14x1024, S=2, one image 13.1 us; so 10.6.)
     const AS_LDS char* at[NB][4];
     int tap = 0;
     auto enter = [&] {

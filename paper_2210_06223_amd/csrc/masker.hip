@@ -281,6 +281,8 @@ __global__ __launch_bounds__(TPC < kMaskerThreads ? kMaskerThreads : TPC) void m
 // What bounds it is the chain of loads, barriers and shuffles, so up to 1024 cells four waves place them in one round (1.8 us;
 // one 1024-thread workgroup for every mask took 2.2), beyond that workgroups of 16 waves take runs of 8192: one such
 // workgroup for 6272 cells 2.8 us, as before (in runs of 1024 it was 3.4), 12544 cells 4.1 -> 3.4, 50176 cells 10.4 -> 4.0.
+// (Compactions of one small map after the other.  Behind the masker of a large map 3136 to 6272 cells take 3.9 to 4.9 us
+// with any of these: the mask is then fetched from farther away.)
 constexpr int kCompactBlocks = 64;                      // most workgroups: bounds the bytes counted again (32 * P)
 struct CompactSmall { static constexpr int NT = 256, CELLS = 4, ROUND = NT * CELLS; };      // CELLS: of a thread, per round
 struct CompactLarge { static constexpr int NT = 1024, CELLS = 8, ROUND = NT * CELLS; };
