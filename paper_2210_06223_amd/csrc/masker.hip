@@ -3,8 +3,6 @@
 // list (App. B.1 (2)).  HBM-bound: reads x once, 16 bytes per lane per load.
 #include "common.hpp"
 
-#include <type_traits>
-
 namespace lasnet {
 namespace {
 
@@ -278,48 +276,49 @@ __global__ __launch_bounds__(TPC < kMaskerThreads ? kMaskerThreads : TPC) void m
 // before it by itself (16 per load and thread, four loads in flight: the mask is a few KB to a few hundred, in L2), so that no
 // workgroup waits for another; within its run a shuffle scan and the wave totals give every cell its
 // place.  Integer work only: the list is the ascending sequence of active cell ids whatever the timing.
-// What bounds it is the chain of loads, barriers and shuffles, so up to 1024 cells four waves place them in one round (1.8 us;
-// one 1024-thread workgroup for every mask took 2.2), beyond that workgroups of 16 waves take runs of 8192: one such
-// workgroup for 6272 cells 2.8 us, as before (in runs of 1024 it was 3.4), 12544 cells 4.1 -> 3.4, 50176 cells 10.4 -> 4.0.
-// (Compactions of one small map after the other.  Behind the masker of a large map 3136 to 6272 cells take 3.9 to 4.9 us
-// with any of these: the mask is then fetched from farther away.)
+// What bounds it is the chain of loads, barriers and shuffles, and the wait for a place: behind the masker of a large map a
+// workgroup of four waves starts on the first CU that has room, one of 16 waves does not.  masker_ex, runs of 1024 cells
+// by 4 waves against one 16-wave workgroup (8192 cells a round): 56x56x256, S=8, 64 images (3136 cells) 20.8 / 22.0 us;
+// 28x28x512, S=4, 128 images (6272) 21.2 / 23.2; 14x14x1024, S=1, 64 images (12544) 12.3 / 14.2.  The kernel's own duration does not
+// show it (6272 cells on an idle GPU: 3.2 / 2.8).
+constexpr int kCompactThreads = 256;
+constexpr int kCompactCells = 4;                        // of a thread, per round
+constexpr int kCompactRound = kCompactThreads * kCompactCells;
 constexpr int kCompactBlocks = 64;                      // most workgroups: bounds the bytes counted again (32 * P)
-struct CompactSmall { static constexpr int NT = 256, CELLS = 4, ROUND = NT * CELLS; };      // CELLS: of a thread, per round
-struct CompactLarge { static constexpr int NT = 1024, CELLS = 8, ROUND = NT * CELLS; };
 
-template <class K, bool ALIGNED>
-__global__ __launch_bounds__(K::NT) void compact_kernel(
+template <bool ALIGNED>
+__global__ __launch_bounds__(kCompactThreads) void compact_kernel(
     const uint8_t* __restrict__ mask, int P, int run, int32_t* __restrict__ idx, int32_t* __restrict__ count) {
-  constexpr int NW = K::NT / 64;
+  constexpr int NW = kCompactThreads / 64;
   __shared__ int wave_tot[NW];
   const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
-  const int start = blockIdx.x * run, end = min(start + run, P);     // (run is a multiple of K::ROUND)
+  const int start = blockIdx.x * run, end = min(start + run, P);     // (run is a multiple of kCompactRound)
   auto bytes = [&](int i0) {                   // of cells i0 .. i0 + CELLS - 1 (zeros past the end), the masker's 0 / 1
-    typedef std::conditional_t<K::CELLS == 8, unsigned long long, unsigned> V;
-    if (ALIGNED && i0 + K::CELLS <= end) return (unsigned long long)*reinterpret_cast<const V*>(mask + i0);
-    unsigned long long v = 0;
+    static_assert(kCompactCells == 4, "one 32-bit load");
+    if (ALIGNED && i0 + kCompactCells <= end) return *reinterpret_cast<const unsigned*>(mask + i0);
+    unsigned v = 0;
 #pragma unroll
-    for (int b = 0; b < K::CELLS; ++b)
-      if (i0 + b < end) v |= (unsigned long long)mask[i0 + b] << (8 * b);
+    for (int b = 0; b < kCompactCells; ++b)
+      if (i0 + b < end) v |= (unsigned)mask[i0 + b] << (8 * b);
     return v;
   };
-  unsigned long long next = bytes(start + tid * K::CELLS);       // requested before the long count
+  unsigned next = bytes(start + tid * kCompactCells);       // requested before the long count
   int base = 0;                                // identical in every thread
   if (start > 0) {
     int mine = 0;
     if constexpr (ALIGNED) {
-      for (int i = tid * 16; i < start; i += 4 * K::NT * 16) {
+      for (int i = tid * 16; i < start; i += 4 * kCompactThreads * 16) {
         uint4 q[4];
 #pragma unroll
         for (int u = 0; u < 4; ++u) {
-          const int j = i + u * K::NT * 16;
+          const int j = i + u * kCompactThreads * 16;
           q[u] = j < start ? *reinterpret_cast<const uint4*>(mask + j) : uint4{0, 0, 0, 0};
         }
 #pragma unroll
         for (int u = 0; u < 4; ++u) mine += __popc(q[u].x) + __popc(q[u].y) + __popc(q[u].z) + __popc(q[u].w);
       }
     } else {
-      for (int i = tid; i < start; i += K::NT) mine += mask[i];
+      for (int i = tid; i < start; i += kCompactThreads) mine += mask[i];
     }
 #pragma unroll
     for (int o = 32; o > 0; o >>= 1) mine += __shfl_xor(mine, o, 64);
@@ -329,11 +328,11 @@ __global__ __launch_bounds__(K::NT) void compact_kernel(
     for (int k = 0; k < NW; ++k) base += wave_tot[k];
     __syncthreads();
   }
-  for (int r0 = start; r0 < end; r0 += K::ROUND) {
-    const int i0 = r0 + tid * K::CELLS;
-    const unsigned long long on = next;
-    if (r0 + K::ROUND < end) next = bytes(i0 + K::ROUND);
-    const int c = __popcll(on);
+  for (int r0 = start; r0 < end; r0 += kCompactRound) {
+    const int i0 = r0 + tid * kCompactCells;
+    const unsigned on = next;
+    if (r0 + kCompactRound < end) next = bytes(i0 + kCompactRound);
+    const int c = __popc(on);
     int incl = c;                              // inclusive scan over the wave
 #pragma unroll
     for (int o = 1; o < 64; o <<= 1) {
@@ -351,7 +350,7 @@ __global__ __launch_bounds__(K::NT) void compact_kernel(
     }
     int pos = base + before + incl - c;
 #pragma unroll
-    for (int b = 0; b < K::CELLS; ++b)
+    for (int b = 0; b < kCompactCells; ++b)
       if ((on >> (8 * b)) & 1u) idx[pos++] = i0 + b;
     base += total;
     __syncthreads();                           // wave_tot is rewritten next round
@@ -435,19 +434,13 @@ hipError_t launch_masker(const lasnet_tensor& x, const float* Wm, float bm, int 
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
   if (count) {
-    const bool small = P <= CompactSmall::ROUND;
-    const int round = small ? CompactSmall::ROUND : CompactLarge::ROUND;
     int run = (P + kCompactBlocks - 1) / kCompactBlocks;
-    run = run > 0 ? (run + round - 1) / round * round : round;
+    run = run > 0 ? (run + kCompactRound - 1) / kCompactRound * kCompactRound : kCompactRound;
     const dim3 cgrid(P > 0 ? (P + run - 1) / run : 1);
-#define LASNET_COMPACT(K, ALIGNED) \
-  hipLaunchKernelGGL((compact_kernel<K, ALIGNED>), cgrid, dim3(K::NT), 0, st, mask, P, run, idx, count)
-    if (((uintptr_t)mask % 16) == 0) {
-      if (small) LASNET_COMPACT(CompactSmall, true); else LASNET_COMPACT(CompactLarge, true);
-    } else {
-      if (small) LASNET_COMPACT(CompactSmall, false); else LASNET_COMPACT(CompactLarge, false);
-    }
-#undef LASNET_COMPACT
+    if (((uintptr_t)mask % 16) == 0)
+      hipLaunchKernelGGL(compact_kernel<true>, cgrid, dim3(kCompactThreads), 0, st, mask, P, run, idx, count);
+    else
+      hipLaunchKernelGGL(compact_kernel<false>, cgrid, dim3(kCompactThreads), 0, st, mask, P, run, idx, count);
     e = hipGetLastError();
   }
   return e;
