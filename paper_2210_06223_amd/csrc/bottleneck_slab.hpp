@@ -17,7 +17,7 @@
 // 2.6e-4 of the output, from roundings of y1 and y2 that flip).
 //
 // Measured (the block's three launches on the GPU, against the schedule that ran before): 14x14x1024, S=2, one image 20.9 -> 10.6 us,
-// 16 images 23.9 -> 17.4; S=7, 24 images 32.4 -> 24.4; 7x7x2048, one image 34 -> 20.5 us, 40 images 55 -> 33.  In conv2 the chain
+// 16 images 23.9 -> 17.4; S=7, 24 images 32.4 -> 24.4; 7x7x2048, one image 34 -> 19.3 us, 40 images 55 -> 33.  In conv2 the chain
 // of accesses takes about 3 us; past that a CU streams its weights.
 //
 // Rounding points, order of the sums, weight layout (lasnet_pack_weights') and results are the fused kernel's, bit for bit.
@@ -143,9 +143,10 @@ __device__ __forceinline__ void slab_piece(int piece, int lane, int& row, int& p
   }
 }
 
-// Weights in flight, in k-steps of TJ tiles: conv2's in whole taps.  (About twice as deep measured the same.)
-constexpr int conv1_ring(int tj) { return 16 / tj; }
-constexpr int conv2_ring(int m, int tj) { return m == 512 ? 16 : tj == 2 ? 8 : 24; }
+// Weights in flight, in k-steps of TJ tiles: conv2's in whole taps.  2048x512, whose weights exceed an XCD's L2, has three
+// times as many where a wave takes one tile (one image: 20.5 -> 19.3 us); at 1024x256 more measured the same or slower.
+constexpr int conv1_ring(int c, int tj) { return tj == 2 ? 8 : c == 2048 ? 32 : 16; }
+constexpr int conv2_ring(int m, int tj) { return m == 512 ? (tj == 2 ? 16 : 48) : tj == 2 ? 8 : 24; }
 
 // Which group of 32 channels a wave works on, and the first of its tiles there.
 template <int NW, int TJ>
@@ -206,7 +207,7 @@ template <int C, int M, int NB, int NW, int TJ>
 __global__ __launch_bounds__(NW * 64, NW / 2) void slab_conv1_kernel(SlabArgs a, const __bf16* __restrict__ x,
                                                                      const __bf16* __restrict__ wp, const float* __restrict__ b1,
                                                                      __bf16* __restrict__ y1) {
-  using L = Slab<C, 1, NB, TJ, conv1_ring(TJ)>;
+  using L = Slab<C, 1, NB, TJ, conv1_ring(C, TJ)>;
   extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
   AS_LDS __bf16* slab = (AS_LDS __bf16*)smem;
   const int tid = threadIdx.x, lane = tid & 63, l16 = lane & 15, lg = lane >> 4, wave = uni(tid >> 6);

@@ -169,7 +169,7 @@ size_t slab_workspace_bytes(const Geom& g) { return 2 * round256((size_t)g.N * g
 //               S=7   N=1 30.4 / 31.1 / 31.1, 14.0 / 14.3 / 14.4              N=32 32.6 / 34.3 / 34.4, 25.1 / 33.3 / 33.9
 //               dense N=1 31.1, slab 14.2                                     N=32 34.1, 33.5
 //   50x60x1024, S=2   N=1 23.6 / 24.1 / 23.5, 17.2 / 22.6 / 22.7
-//   7x7x2048, S=1     N=1 tiled 34.4 / 38.3 / 44.0, slab 20.5 / 20.9 / 21.4   N=40 54.7 / 63.2 / 67.5, 33.3 / 48.2 / 49.1
+//   7x7x2048, S=1     N=1 tiled 34.4 / 38.3 / 44.0, slab 19.3 / 19.7 / 19.9   N=40 54.7 / 63.2 / 67.5, 33.3 / 48.2 / 49.1
 //   25x42x2048, S=1   N=1 fused 119 / 120 / 123, slab 30.3 / 31.9 / 45.2
 // (with S = 1 a workgroup's windows take the most LDS, so its rounds are full first; the fused kernel's larger tiles of S = 7 leave
 // it fewer workgroups, so its end of the range is farther out.)
