@@ -42,6 +42,9 @@ constexpr int cmax(int a, int b) { return a > b ? a : b; }
 constexpr int roundup(int a, int b) { return cdiv(a, b) * b; }
 constexpr int pow2_at_least(int v) { int p = 1; while (p < v) p *= 2; return p; }
 
+// A window position's entry: row of y1 | the row's swizzle key << kRowBits.
+constexpr int kRowBits = 10;
+
 // C, M, S: block shape.  PPW: patches per batch (max).  R1MAX: rows of y1 kept in LDS (unique
 // window pixels of a batch; a batch is cut short if it would need more).  NSTG: LDS stages of
 // the x stream (KC channels each; x chunks are in flight NSTG-1 chunks ahead).  WRi x WCi:
@@ -78,13 +81,13 @@ struct Cfg {
   static constexpr int HT = pow2_at_least(cmax(2 * R1MAX, PPW * (S + 2) * (S + 2) + 1));  // hash table slots
   // LDS map (bytes)
   static constexpr int OFF_HKEY = 0;                            // int  [HT]     pixel+1 or 0
-  static constexpr int OFF_HVAL = OFF_HKEY + HT * 4;            // short[HT]     row of that pixel
-  static constexpr int OFF_WINROW = OFF_HVAL + HT * 2;          // short[PPW*WW] row of each window position
+  static constexpr int OFF_HVAL = OFF_HKEY + HT * 4;            // short[HT]     row of that pixel and its key
+  static constexpr int OFF_WINROW = OFF_HVAL + HT * 2;          // short[PPW*WW] row of each window position and its key
   static constexpr int OFF_ROWPIX = (OFF_WINROW + PPW * WW * 2 + 15) / 16 * 16;  // int[R1MAX]
   static constexpr int OFF_PIXQ = OFF_ROWPIX + R1MAX * 4;       // int  [R2P]
   static constexpr int OFF_MISC = OFF_PIXQ + R2P * 4;           // int  [4]
-  static constexpr int OFF_CELL = OFF_MISC + 16;                // int  [PPW]    cell ids of the batch
-  static constexpr int OFF_BIAS = (OFF_CELL + PPW * 4 + 15) / 16 * 16;   // float[M | M | C]: b1, b2, b3
+  static constexpr int OFF_ROWKEY = OFF_MISC + 16;              // uint8[R1MAX]  swizzle key of each row
+  static constexpr int OFF_BIAS = (OFF_ROWKEY + R1MAX + 15) / 16 * 16;   // float[M | M | C]: b1, b2, b3
   static constexpr int OFF_Y1 = OFF_BIAS + (2 * M + C) * 4;
   static constexpr int Y1_BYTES = (R1MAX + 1) * LDY * 2;
   static constexpr int OFF_XS = Y1_IN_XS ? OFF_Y1 : OFF_Y1 + Y1_BYTES;
@@ -94,7 +97,7 @@ struct Cfg {
   static constexpr int OFF_Y2 = Y1_IN_XS ? OFF_XS + Y1_BYTES : OFF_XS;              // xs is dead once conv1 is done
   static constexpr int LDS_BYTES = cmax(OFF_XS + XS_BYTES, OFF_Y2 + Y2_BYTES);
   static constexpr size_t PACKED_ELEMS = (size_t)M * C * 2 + 9 * (size_t)M * M;
-  static_assert(R1MAX % 16 == 0 && R1MAX >= WW && R1MAX < 32767, "y1 rows");
+  static_assert(R1MAX % 16 == 0 && R1MAX >= WW && R1MAX < (1 << kRowBits), "y1 rows");
   static_assert(R1B % WR1 == 0, "conv1 row blocks split evenly over the wave rows");
   static_assert(HT > PPW * WW, "the hash table always keeps an empty slot, so probing ends");
   static_assert(WR1 * WC1 == NW && WR2 * WC2 == NW && WR3 * WC3 == NW, "wave grid");
@@ -134,6 +137,7 @@ typedef AS_LDS __bf16* l_bf16_p;
 typedef const AS_LDS __bf16* l_bf16_cp;
 typedef const AS_LDS int* l_i32_cp;
 typedef const AS_LDS short* l_i16_cp;
+typedef const AS_LDS unsigned char* l_u8_cp;
 typedef const AS_LDS float* l_f32_cp;
 
 // Element offset of 16-byte chunk `chunk` in an LDS row of pitch `ld` elements whose chunks
@@ -175,6 +179,16 @@ __host__ __device__ inline int lane_channel(int base, int nb, int j, int lg, int
 // Channel whose weights sit in A-operand row i (0..15) of tile j.
 __host__ __device__ inline int arow_channel(int base, int nb, int j, int i) {
   return lane_channel(base, nb, j, i >> 2, i & 3);
+}
+
+// Swizzle key of a pixel's y1 row, linear in its coordinates, so that a tap moves the keys of all rows of a block alike and 16 rows
+// with different keys keep them.  A block of 16 output pixels is a patch or a part of one where S >= 4, consecutive pixels
+// (mostly) where S = 1, and where S = 2 four patches, which lie side by side in an ascending list of a dense mask.
+// A fragment read is 9.6 clocks of the CU's LDS then, 12.3 with keys that are as good as random (the row's number, as
+// rows were numbered by the hash table): the static block at 14x14x1024, batch 128 (S=7), conv2 57.7k -> 48.5k clocks, 72 -> 61.5 us.
+template <int S>
+__device__ __forceinline__ int swizzle_key(int pix, int h, int w) {
+  return S == 1 ? pix : S == 2 ? h + 2 * w : S * h + w;
 }
 
 __device__ inline unsigned hash_pix(int pix) { return ((unsigned)pix * 2654435761u) >> 12; }
@@ -309,14 +323,15 @@ __device__ __forceinline__ void conv1_ring_fill(Conv1Ring<K>& ring, g_bf16_p W1,
 // What conv1 runs between requesting its first chunks and waiting for them, when the caller has nothing to put there.
 struct Nothing { __device__ __forceinline__ void operator()() const {} };
 
-// HOISTED: `ring` arrives filled by conv1_ring_fill.  yg / nrows: with K::Y1_TO_GLOBAL the result rows
-// go straight to memory, row r < nrows to yg + rowpix[r] * K::YG_PITCH (+ channel).  `meanwhile` runs after
+// HOISTED: `ring` arrives filled by conv1_ring_fill.  nrows (> 0): entries of rowpix; the rows up to NB1*16 beyond them
+// repeat the last.  The result goes to y1s with the swizzle keys rowkey[], or with K::Y1_TO_GLOBAL straight to memory, row
+// r < nrows to yg + rowpix[r] * K::YG_PITCH (+ channel).  `meanwhile` runs after
 // the first chunks of x and weights have been requested and before the first of them is waited for: work
 // that needs no global memory hides behind that latency (it must not touch xs or y1s).
 template <class K, int NB1, bool HOISTED, class Meanwhile = Nothing>
 __device__ LASNET_PHASE_INLINE void conv1_core(Conv1Ring<K>& ring, g_bf16_p x, g_bf16_p W1, l_f32_cp b1s,
-                                               l_i32_cp rowpix, l_bf16_p xs, l_bf16_p y1s, int tid, int wave,
-                                               AS_GLOBAL __bf16* yg = nullptr, int nrows = 0,
+                                               l_i32_cp rowpix, int nrows, l_u8_cp rowkey, l_bf16_p xs, l_bf16_p y1s,
+                                               int tid, int wave, AS_GLOBAL __bf16* yg = nullptr,
                                                Meanwhile meanwhile = Meanwhile{}) {
   constexpr int C = K::C, NBW = K::NBW1, KS = K::KC / 32, NCH = C / K::KC;
   constexpr int RB = cdiv(NB1, K::WR1);                   // row blocks of this wave (last may be padding)
@@ -346,7 +361,7 @@ __device__ LASNET_PHASE_INLINE void conv1_core(Conv1Ring<K>& ring, g_bf16_p x, g
     const int grp = wave + u * K::NW;
     if (grp < NGRP) {
       const int row = grp * 8 + (lane >> 3), pc = lane & 7;
-      xsrc[u] = x + (size_t)rowpix[row] * C + ((pc ^ (row & 7)) << 3);
+      xsrc[u] = x + (size_t)rowpix[min(row, nrows - 1)] * C + ((pc ^ (row & 7)) << 3);
       xdst[u] = grp * 8 * K::LDX;
     } else {                                              // padding load: keeps the per-chunk count uniform
       xsrc[u] = x + (size_t)rowpix[0] * C + ((lane & 7) << 3);
@@ -447,7 +462,7 @@ __device__ LASNET_PHASE_INLINE void conv1_core(Conv1Ring<K>& ring, g_bf16_p x, g
   // epilogue: ReLU, round to bf16; 8 channels (one 16-byte chunk) per LDS store where NBW allows
 #pragma unroll
   for (int i = 0; i < RB; ++i) {
-    const int row = (wr + K::WR1 * i) * 16 + l16;
+    const int row = (wr + K::WR1 * i) * 16 + l16, key = K::Y1_TO_GLOBAL ? 0 : rowkey[row];
     bf16x4 o[NBW];
 #pragma unroll
     for (int j = 0; j < NBW; ++j)
@@ -464,23 +479,23 @@ __device__ LASNET_PHASE_INLINE void conv1_core(Conv1Ring<K>& ring, g_bf16_p x, g
     } else if constexpr (NBW % 2 == 0) {
 #pragma unroll
       for (int j = 0; j < NBW; j += 2)
-        *reinterpret_cast<AS_LDS bf16x8*>(y1s + swz(row, K::LDY, lane_channel(chb, NBW, j, lg, 0) >> 3, row, K::YMASK)) = join8(o[j], o[j + 1]);
+        *reinterpret_cast<AS_LDS bf16x8*>(y1s + swz(row, K::LDY, lane_channel(chb, NBW, j, lg, 0) >> 3, key, K::YMASK)) = join8(o[j], o[j + 1]);
     } else {
 #pragma unroll
       for (int j = 0; j < NBW; ++j) {
         const int c = lane_channel(chb, NBW, j, lg, 0);
-        *reinterpret_cast<AS_LDS bf16x4*>(y1s + swz(row, K::LDY, c >> 3, row, K::YMASK) + (c & 7)) = o[j];
+        *reinterpret_cast<AS_LDS bf16x4*>(y1s + swz(row, K::LDY, c >> 3, key, K::YMASK) + (c & 7)) = o[j];
       }
     }
   }
 }
 
 template <class K, int NB1, class Meanwhile = Nothing>
-__device__ LASNET_PHASE_INLINE void conv1_phase(g_bf16_p x, g_bf16_p W1, l_f32_cp b1s, l_i32_cp rowpix,
-                                                l_bf16_p xs, l_bf16_p y1s, int tid, int wave,
+__device__ LASNET_PHASE_INLINE void conv1_phase(g_bf16_p x, g_bf16_p W1, l_f32_cp b1s, l_i32_cp rowpix, int nrows,
+                                                l_u8_cp rowkey, l_bf16_p xs, l_bf16_p y1s, int tid, int wave,
                                                 Meanwhile meanwhile = Meanwhile{}) {
   Conv1Ring<K> ring;
-  conv1_core<K, NB1, false>(ring, x, W1, b1s, rowpix, xs, y1s, tid, wave, nullptr, 0, meanwhile);
+  conv1_core<K, NB1, false>(ring, x, W1, b1s, rowpix, nrows, rowkey, xs, y1s, tid, wave, nullptr, meanwhile);
 }
 
 // ---- phase 2: conv3x3 as an implicit GEMM over the 9 taps, y1 rows from LDS ---------------
@@ -556,11 +571,13 @@ __device__ LASNET_PHASE_INLINE void conv2_core(Conv2Ring<K>& ring, g_bf16_p W2, 
   };
   int brow[RB];
   FragRow fr[RB];
-  lookup(brow, 0);
+  auto enter = [&] {                                       // the tap that brow was looked up for
 #pragma unroll
-  for (int i = 0; i < RB; ++i) fr[i] = frag_row(brow[i], K::LDY, lg, brow[i], K::YMASK);
-  // B fragments one k-step ahead of the MFMAs (bcur/bnxt); the row lookup of the next tap
-  // happens while the last k-step of the current one is computed.
+    for (int i = 0; i < RB; ++i) fr[i] = frag_row(brow[i] & ((1 << kRowBits) - 1), K::LDY, lg, brow[i] >> kRowBits, K::YMASK);
+  };
+  lookup(brow, 0);
+  enter();
+  // B fragments one k-step ahead of the MFMAs (bcur/bnxt), the row lookups of a tap one more.
   bf16x8 bcur[RB], bnxt[RB];
 #pragma unroll
   for (int i = 0; i < RB; ++i) bcur[i] = frag_read(y1s, fr[i], 0);
@@ -573,13 +590,11 @@ __device__ LASNET_PHASE_INLINE void conv2_core(Conv2Ring<K>& ring, g_bf16_p W2, 
       const int t = t0 + tt;
       const int msn = (t + 1) % MS;                        // k-step inside the tap of step t+1
       if (t + 1 < NSTEP) {
-        if (msn == 0) {
-          lookup(brow, (t + 1) / MS);
-#pragma unroll
-          for (int i = 0; i < RB; ++i) fr[i] = frag_row(brow[i], K::LDY, lg, brow[i], K::YMASK);
-        }
+        if (msn == 0) enter();
 #pragma unroll
         for (int i = 0; i < RB; ++i) bnxt[i] = frag_read(y1s, fr[i], msn);
+        // (looked up a k-step before it is entered: the fragment reads wait for it)
+        if (msn == MS - 1 && t + 2 < NSTEP) lookup(brow, (t + 2) / MS);
       }
 #pragma unroll
       for (int i = 0; i < RB; ++i)
@@ -804,9 +819,11 @@ __device__ LASNET_PHASE_INLINE void conv3_core(Conv3Ring<K>& ring, g_bf16_p x, g
   }
 }
 
+struct FusedDivs { Div31 cpi, gw, slots; };                // cells per image, cells per row of cells, tile_slots
+
 template <class K>
 __global__ __launch_bounds__(K::NT, K::WAVES_PER_SIMD) void fused_bneck_kernel(
-    Geom g, int tile_slots, const __bf16* __restrict__ x, const int32_t* __restrict__ idx,
+    Geom g, FusedDivs dv, int tile_slots, const __bf16* __restrict__ x, const int32_t* __restrict__ idx,
     const int32_t* __restrict__ count, const __bf16* __restrict__ W1,
     const float* __restrict__ b1, const __bf16* __restrict__ W2, const float* __restrict__ b2,
     const __bf16* __restrict__ W3, const float* __restrict__ b3, __bf16* __restrict__ out,
@@ -818,7 +835,7 @@ __global__ __launch_bounds__(K::NT, K::WAVES_PER_SIMD) void fused_bneck_kernel(
   int* rowpix = reinterpret_cast<int*>(smem + K::OFF_ROWPIX);
   int* pixq = reinterpret_cast<int*>(smem + K::OFF_PIXQ);
   int* misc = reinterpret_cast<int*>(smem + K::OFF_MISC);      // [0] = number of unique rows
-  int* cellq = reinterpret_cast<int*>(smem + K::OFF_CELL);
+  unsigned char* rowkey = smem + K::OFF_ROWKEY;
   float* b1s = reinterpret_cast<float*>(smem + K::OFF_BIAS);
   float* b2s = b1s + K::M;
   float* b3s = b2s + K::M;
@@ -830,6 +847,24 @@ __global__ __launch_bounds__(K::NT, K::WAVES_PER_SIMD) void fused_bneck_kernel(
   const int tid = threadIdx.x;
   const int wave = uni(tid >> 6);
 
+  // Before the count is waited for: the biases are requested (they go to LDS once the first batch's entries, requested
+  // later, have arrived) and the hash table is cleared.
+  constexpr int NBV = cdiv(2 * K::M + K::C, K::NT);
+  float bv[NBV];
+#pragma unroll
+  for (int u = 0; u < NBV; ++u) {
+    const int i = tid + u * K::NT;
+    bv[u] = i < K::M ? b1[i] : i < 2 * K::M ? b2[i - K::M] : i < 2 * K::M + K::C ? b3[i - 2 * K::M] : 0.f;
+  }
+  const auto clear = [&] {
+    for (int i = tid; i < K::HT / 4; i += K::NT) reinterpret_cast<int4*>(hkey)[i] = int4{0, 0, 0, 0};
+    if (tid == 0) {
+      misc[0] = 0;
+      rowpix[0] = 0;                                       // (stays if every entry of the batch is invalid)
+    }
+  };
+  clear();
+
   // ---- which entries of the index list are this workgroup's ------------------------------
   // The list is cut into `nt` near-equal runs, nt = the number of PPW-sized tiles rounded up
   // to a multiple of `tile_slots` (workgroups the chip holds at once), so that every round
@@ -837,7 +872,7 @@ __global__ __launch_bounds__(K::NT, K::WAVES_PER_SIMD) void fused_bneck_kernel(
   const int nact = uni(idx ? min(*count, g.P) : g.P);
   if (nact <= 0) return;
   int nt = (nact + K::PPW - 1) / K::PPW;
-  nt = (nt + tile_slots - 1) / tile_slots * tile_slots;
+  nt = div31_by(nt + tile_slots - 1, dv.slots) * tile_slots;
   nt = min(min(nt, (int)gridDim.x), nact);
   if ((int)blockIdx.x >= nt) return;                       // uniform over the workgroup
   // Workgroup b runs on XCD b % 8 (round-robin dispatch), and each XCD has its own L2.  Runs
@@ -850,78 +885,83 @@ __global__ __launch_bounds__(K::NT, K::WAVES_PER_SIMD) void fused_bneck_kernel(
   // the masker has just gone through the map from its first image to its last, and the Infinity Cache still holds its end.
   // (One sweep for the whole launch -> this, call sequences: 56x56x256, S=4, batch 256, a map of 411 MB: 251.0 -> 241.6 us;
   // 28x28x512, S=4, batch 128, a map of 103 MB: no difference beyond the noise; launches of one round are cut as before.)
-  int lo = 0, hi = nact, nr = nt, b = (int)blockIdx.x;         // the round's part of the list, its workgroups, this one of them
+  // Run t of the whole list has q entries, the first `rem` runs one more.
+  const int q = (int)((unsigned)nact / (unsigned)nt), rem = nact - q * nt;
+  int b = (int)blockIdx.x, lo = 0, nr = nt, longer = rem;      // the round's part of the list, its runs, how many have q + 1
   if (nt > tile_slots) {
-    const int q = b / tile_slots * tile_slots;
-    nr = min(tile_slots, nt - q);
-    b -= q;
-    hi = nact - (int)((long long)q * nact / nt);
-    lo = nact - (int)((long long)(q + nr) * nact / nt);
+    const int r0 = div31_by(b, dv.slots) * tile_slots;     // rounds before this one took the last r0 runs
+    nr = min(tile_slots, nt - r0);
+    b -= r0;
+    const int t0 = nt - r0 - nr;
+    lo = t0 * q + min(t0, rem);
+    longer = min(t0 + nr, rem) - min(t0, rem);
   }
-  const int nl = hi - lo, xcd = b & 7, jx = b >> 3;
-  const int first = xcd * (nr >> 3) + min(xcd, nr & 7);        // jx < runs of this XCD because b < nr
-  const int runs = (nr >> 3) + (xcd < (nr & 7) ? 1 : 0);
-  const int xb = lo + (int)(((long long)first * nl) / nr), xe = lo + (int)(((long long)(first + runs) * nl) / nr);
-  const int len0 = (xe - xb) / runs, extra = (xe - xb) - len0 * runs;
-  const int tb = xb + jx * len0 + min(jx, extra);
-  const int te = tb + len0 + (jx < extra ? 1 : 0);
+  const int xcd = b & 7, jx = b >> 3;                      // jx < runs of this XCD because b < nr
+  const int first = xcd * (nr >> 3) + min(xcd, nr & 7);    // runs of the XCDs before it, and how many of them are longer ones
+  const int first_longer = xcd * (longer >> 3) + min(xcd, longer & 7), extra = (longer >> 3) + (xcd < (longer & 7) ? 1 : 0);
+  const int tb = lo + (first + jx) * q + first_longer + min(jx, extra);
+  const int te = tb + q + (jx < extra ? 1 : 0);
 
   const auto zero_row = [&] {                              // the all-zero y1 row
     for (int i = tid; i < K::LDY / 8; i += K::NT)
       *reinterpret_cast<uint4*>(y1s + K::ZROW * K::LDY + i * 8) = uint4{0, 0, 0, 0};
   };
   if constexpr (!K::Y1_IN_XS) zero_row();
-  // the biases go to LDS: requested here, stored once the first batch's cell ids (requested next)
-  // have been waited for anyway
-  constexpr int NBV = cdiv(2 * K::M + K::C, K::NT);
-  float bv[NBV];
-#pragma unroll
-  for (int u = 0; u < NBV; ++u) {
-    const int i = tid + u * K::NT;
-    bv[u] = i < K::M ? b1[i] : i < 2 * K::M ? b2[i - K::M] : i < 2 * K::M + K::C ? b3[i - 2 * K::M] : 0.f;
-  }
 
   for (int e0 = tb; e0 < te;) {
     // ---------------------------------------------------------------- phase 0
+    // Every in-image window pixel claims a hash slot; the thread that gets it first gives the pixel its row.  A thread keeps the
+    // slots of its window positions (NU of them) for the tables below.  What a batch waits for here is its chain of
+    // dependent steps -- count, entries, claims, barrier -- so there is one pass and one barrier, and cells are decoded with
+    // multiplications.  (A pass to claim, one to number the rows and one to look them up, with divisions: 10.2k clocks to conv1
+    // and 6.1k more to its first chunk at 14x14x1024, S=2, batch 128; so 4.7k and 4.2k.  The block 46.6 -> 42.9 us, of one
+    // region per image at 28x28x512, S=4, batch 128, 51.5 -> 48.8, at 56x56x256, S=4, batch 256 136 -> 130.)
+    constexpr int NU = cdiv(K::PPW * WW, K::NT);
     int npb = min(te - e0, K::PPW);                        // patches in this batch
     int U;                                                 // unique window pixels = y1 rows
-    // the batch's cell ids: one round of global loads, every later step reads them from LDS
-    for (int i = tid; i < npb; i += K::NT) cellq[i] = idx ? idx[e0 + i] : e0 + i;
+    int cells[NU], slots[NU];
+#pragma unroll
+    for (int u = 0; u < NU; ++u) {
+      const int t = tid + u * K::NT;
+      cells[u] = t < npb * WW ? (idx ? idx[e0 + t / WW] : e0 + t / WW) : -1;
+    }
     if (e0 == tb) {
 #pragma unroll
       for (int u = 0; u < NBV; ++u)
         if (tid + u * K::NT < 2 * K::M + K::C) b1s[tid + u * K::NT] = bv[u];   // b1 | b2 | b3 are contiguous
     }
     for (;;) {
-      for (int i = tid; i < K::HT; i += K::NT) hkey[i] = 0;
-      if (tid == 0) misc[0] = 0;
-      __syncthreads();
-      // (a) every in-image window pixel claims a hash slot
-      for (int t = tid; t < npb * WW; t += K::NT) {
-        const int slot = t / WW, wp = t - slot * WW;
-        const int cell = cellq[slot];
-        const int n = cell / (g.G * g.GW), rem = cell - n * (g.G * g.GW);
-        const int gy = rem / g.GW, gx = rem - gy * g.GW;
-        const int h = gy * S + wp / T - 1, w = gx * S + wp % T - 1;
-        // (a list entry that is not a cell of this map claims nothing and stores nothing)
-        if ((unsigned)cell < (unsigned)g.P && h >= 0 && h < g.H && w >= 0 && w < g.W) {
-          const int key = (n * g.H + h) * g.W + w + 1;
-          unsigned s = hash_pix(key) & (K::HT - 1);
-          for (;;) {
-            const int old = atomicCAS(&hkey[s], 0, key);
-            if (old == 0 || old == key) break;
-            s = (s + 1) & (K::HT - 1);
+      __syncthreads();                                     // the hash table is clear
+#pragma unroll
+      for (int u = 0; u < NU; ++u) {
+        const int t = tid + u * K::NT, slot = t / WW, wp = t - slot * WW, wy = wp / T, wx = wp - wy * T;
+        slots[u] = -1;
+        if (t < npb * WW) {
+          // (a list entry that is not a cell of this map claims nothing and stores nothing)
+          const bool valid = (unsigned)cells[u] < (unsigned)g.P;
+          const int cell = valid ? cells[u] : 0;
+          const int n = div31_by(cell, dv.cpi), rest = cell - n * (g.G * g.GW), gy = div31_by(rest, dv.gw);
+          const int h = gy * S + wy - 1, w = (rest - gy * g.GW) * S + wx - 1;
+          const int pix = (n * g.H + h) * g.W + w;
+          if (wy >= 1 && wy <= S && wx >= 1 && wx <= S) pixq[slot * (S * S) + (wy - 1) * S + wx - 1] = valid ? pix : -1;
+          if (valid && (unsigned)h < (unsigned)g.H && (unsigned)w < (unsigned)g.W) {
+            unsigned s = hash_pix(pix + 1) & (K::HT - 1);
+            for (;;) {
+              const int old = atomicCAS(&hkey[s], 0, pix + 1);
+              if (old == 0) {
+                const int row = atomicAdd(&misc[0], 1), key = swizzle_key<S>(pix, h, w) & K::YMASK;
+                hval[s] = (short)(row | key << kRowBits);
+                if (row < K::R1MAX) {
+                  rowpix[row] = pix;
+                  rowkey[row] = (unsigned char)key;
+                }
+                break;
+              }
+              if (old == pix + 1) break;
+              s = (s + 1) & (K::HT - 1);
+            }
+            slots[u] = (int)s;
           }
-        }
-      }
-      __syncthreads();
-      // (b) occupied slots take row numbers
-      for (int i = tid; i < K::HT; i += K::NT) {
-        const int key = hkey[i];
-        if (key != 0) {
-          const int row = atomicAdd(&misc[0], 1);
-          hval[i] = (short)row;
-          if (row < K::R1MAX) rowpix[row] = key - 1;
         }
       }
       __syncthreads();
@@ -931,50 +971,26 @@ __global__ __launch_bounds__(K::NT, K::WAVES_PER_SIMD) void fused_bneck_kernel(
       // one patch always fits)
       npb = max(1, min(npb - 1, npb * K::R1MAX / U));
       __syncthreads();
+      clear();
     }
     const int nblk1 = max(1, (U + 15) >> 4);              // (U = 0 only if every entry of the batch was invalid)
     const int nq = npb * S * S, nblk2 = (nq + 15) >> 4;
-    // rows up to the block count conv1 really runs (rounded up to its wave rows) must name
-    // a valid pixel: their x is loaded and convolved, the result is never used
-    const int pad_pix = U > 0 ? rowpix[0] : 0;
-    for (int r = U + tid; r < (nblk1 + K::WR1 - 1) / K::WR1 * K::WR1 * 16; r += K::NT) rowpix[r] = pad_pix;
-    __syncthreads();
-    // (c) row of every window position; pixel of every output row.  Only conv2 and conv3 need these, so
+    // Row of every window position; no pixel for the output rows past the last.  Only conv2 and conv3 need these, so
     // they are built inside conv1, between the request for its first chunks of x and the wait for them.
     const auto tables = [&] {
-      for (int t = tid; t < npb * WW; t += K::NT) {
-        const int slot = t / WW, wp = t - slot * WW;
-        const int cell = cellq[slot];
-        const int n = cell / (g.G * g.GW), rem = cell - n * (g.G * g.GW);
-        const int gy = rem / g.GW, gx = rem - gy * g.GW;
-        const int h = gy * S + wp / T - 1, w = gx * S + wp % T - 1;
-        int row = K::ZROW;
-        if ((unsigned)cell < (unsigned)g.P && h >= 0 && h < g.H && w >= 0 && w < g.W) {
-          const int key = (n * g.H + h) * g.W + w + 1;
-          unsigned s = hash_pix(key) & (K::HT - 1);
-          while (hkey[s] != key) s = (s + 1) & (K::HT - 1);
-          row = hval[s];
-        }
-        winrow[t] = (short)row;
+#pragma unroll
+      for (int u = 0; u < NU; ++u) {
+        const int t = tid + u * K::NT;
+        if (t < npb * WW) winrow[t] = slots[u] >= 0 ? hval[slots[u]] : (short)K::ZROW;
       }
-      for (int q = tid; q < K::R2P; q += K::NT) {
-        int pix = -1;
-        if (q < nq) {
-          const int slot = q / (S * S), r = q - slot * (S * S);
-          const int cell = cellq[slot];
-          const int n = cell / (g.G * g.GW), rem = cell - n * (g.G * g.GW);
-          const int gy = rem / g.GW, gx = rem - gy * g.GW;
-          if ((unsigned)cell < (unsigned)g.P) pix = (n * g.H + gy * S + r / S) * g.W + gx * S + r % S;
-        }
-        pixq[q] = pix;
-      }
+      for (int r = nq + tid; r < K::R2P; r += K::NT) pixq[r] = -1;
     };
 
     // Row blocks are dealt to the wave rows round-robin (wave row wr takes blocks wr, wr+WR,
     // ...); the count is rounded up to a multiple of WR, the extra blocks compute unused rows.
     dispatch_count<1, K::R1B / K::WR1>((nblk1 + K::WR1 - 1) / K::WR1, [&](auto nb) {
       conv1_phase<K, decltype(nb)::value * K::WR1>((g_bf16_p)x, (g_bf16_p)W1, (l_f32_cp)b1s, (l_i32_cp)rowpix,
-                                                   (l_bf16_p)xs, (l_bf16_p)y1s, opaque(tid), wave, tables);
+                                                   max(U, 1), (l_u8_cp)rowkey, (l_bf16_p)xs, (l_bf16_p)y1s, opaque(tid), wave, tables);
     });
     if constexpr (K::Y1_IN_XS) zero_row();                 // (the x stages have been over it)
     __syncthreads();
@@ -1009,7 +1025,10 @@ __global__ __launch_bounds__(K::NT, K::WAVES_PER_SIMD) void fused_bneck_kernel(
       }
     });
     e0 += npb;
-    if (e0 < te) __syncthreads();                          // LDS is reused by the next batch
+    if (e0 < te) {
+      __syncthreads();                                     // LDS is reused by the next batch
+      clear();
+    }
   }
 }
 
@@ -1087,7 +1106,8 @@ hipError_t launch_one(const Geom& g, const void* x, const int32_t* idx, const in
   const __bf16* p1 = (const __bf16*)packed;
   const __bf16* p2 = p1 + (size_t)K::M * K::C;
   const __bf16* p3 = p2 + 9 * (size_t)K::M * K::M;
-  hipLaunchKernelGGL(k, dim3(grid), dim3(K::NT), K::LDS_BYTES, st, g, slots, (const __bf16*)x, idx,
+  const FusedDivs dv{div31((unsigned)(g.G * g.GW)), div31((unsigned)g.GW), div31((unsigned)slots)};
+  hipLaunchKernelGGL(k, dim3(grid), dim3(K::NT), K::LDS_BYTES, st, g, dv, slots, (const __bf16*)x, idx,
                      count, p1, b1, p2, b2, p3, b3, (__bf16*)out, (int)post_relu);
   return hipGetLastError();
 }

@@ -73,6 +73,7 @@ struct TiledCfg {
     static constexpr bool ACTS_BARRIER = true, Y2_TO_GLOBAL = true;        // y2 rows go straight to memory
     static constexpr int YG_PITCH = M;
     static constexpr int ZROW = GPXMAX;                                    // the all-zero y1 row
+    static_assert(GPXMAX < (1 << kRowBits), "winrow's entries");
     static constexpr int LDY = M, YMASK = 15, LDY2 = TC2, YMASK2 = 15;
     static constexpr int W_KSTEP_BYTES = M * 64;
     static constexpr unsigned W2_BYTES = 9 * M * M * 2;
@@ -306,13 +307,10 @@ __global__ __launch_bounds__(256, 1) void tiled_conv1_kernel(
   if (U == 0) return;                                      // uniform: nothing near this tile is active
   if (pos >= 0) rowpix[pos] = img0 * tg.hw + p;
   __syncthreads();
-  const int nblk = (U + 15) >> 4;
-  for (int r = U + tid; r < nblk * 16; r += 256) rowpix[r] = rowpix[0];   // padding rows: loaded, computed, not stored
-  __syncthreads();
 
-  dispatch_count<1, kTiledRows / 16>(nblk, [&](auto nb) {
-    conv1_core<K, decltype(nb)::value, true>(ring, (g_bf16_p)x, W1s, (l_f32_cp)b1s, (l_i32_cp)rowpix, (l_bf16_p)xs,
-                                             (l_bf16_p)xs, tid, wave, (AS_GLOBAL __bf16*)y1g + slice * TC::TC1, U);
+  dispatch_count<1, kTiledRows / 16>((U + 15) >> 4, [&](auto nb) {
+    conv1_core<K, decltype(nb)::value, true>(ring, (g_bf16_p)x, W1s, (l_f32_cp)b1s, (l_i32_cp)rowpix, U, nullptr, (l_bf16_p)xs,
+                                             (l_bf16_p)xs, tid, wave, (AS_GLOBAL __bf16*)y1g + slice * TC::TC1);
   });
 }
 
@@ -371,7 +369,7 @@ __global__ __launch_bounds__(256, 1) void tiled_conv2_kernel(
     const int e = plist[qq], ph = e >> 16, pw = (e >> 8) & 255, pl = e & 255;
     const int dy = tap / 3 - 1, dx = tap - (tap / 3) * 3 - 1;
     winrow[t] = ((unsigned)(ph + dy) < (unsigned)g.H && (unsigned)(pw + dx) < (unsigned)g.W)
-                    ? (short)(pl + dy * g.W + dx) : (short)K::ZROW;
+                    ? (short)((pl + dy * g.W + dx) | ((pl + dy * g.W + dx) & K::YMASK) << kRowBits) : (short)K::ZROW;
   }
   // (no barrier here: conv2_core has one on entry)
 

@@ -27,6 +27,17 @@ struct BlockWeights {
   const void* W3; const float* b3;
 };
 
+// n / d for 0 <= n < 2^31 by a multiplication: floor(n * m / 2^(31 + l)) with l = ceil(log2 d) and m = floor(2^(31 + l) / d) + 1, which
+// exceeds 2^(31 + l) / d by at most 2^l / d of itself, too little to matter below 2^31 (d = 1 has no such m: m = 0).
+struct Div31 { unsigned m, s; };
+inline Div31 div31(unsigned d) {
+  if (d <= 1) return Div31{0, 0};
+  unsigned l = 1;
+  while ((1ull << l) < d) ++l;
+  return Div31{(unsigned)((1ull << (31 + l)) / d + 1), l - 1};
+}
+__device__ __forceinline__ int div31_by(int n, Div31 d) { return d.m ? (int)(__umulhi((unsigned)n, d.m) >> d.s) : n; }
+
 // Workgroup b -> (unit, slice) of a launch of sliced_grid(): the nsl slices of a unit are consecutive workgroups of ONE XCD
 // (workgroups are dealt round-robin to the 8 XCDs, each with its own L2), so what the slices share -- the unit's
 // activations -- is fetched into one L2 once.  false: no such unit (the grid is rounded up).

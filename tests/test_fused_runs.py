@@ -1,0 +1,55 @@
+"""How the fused kernel cuts the list into runs and decodes its cells: every cut gives every listed patch the same bits."""
+import numpy as np
+import pytest
+import torch
+
+from oracle import lasnet_oracle as O
+from paper_2210_06223_amd import binding as B
+from paper_2210_06223_amd import synth
+from tests import _util as U
+
+pytestmark = pytest.mark.gpu
+
+# Lists of one entry, of a few more and less than the chip's workgroups, of several rounds with runs of two lengths, and of
+# patches apart from each other (a batch that exceeds the y1 rows is cut and runs again).  Maps with one column or one row of
+# cells (a divisor of one) and with sides that are no powers of two.
+CASES = [
+    (6, 56, 56, 256, 64, 2, (1, 255, 511, 513, 4095, 4097, 4600)),
+    (3, 12, 84, 256, 64, 4, (1, 9, 63, 180)),
+    (40, 8, 2, 512, 128, 2, (3, 100, 159)),
+    (7, 3, 33, 512, 128, 1, (17, 300, 693)),
+    (2, 14, 63, 512, 128, 7, (1, 20, 36)),
+    (41, 2, 46, 1024, 256, 2, (7, 256, 257, 900)),
+    (5, 45, 3, 1024, 256, 1, (64, 600)),
+]
+
+
+@pytest.mark.parametrize("N,H,W,C,M,S,counts", CASES, ids=lambda v: "-".join(map(str, v)) if isinstance(v, tuple) else str(v))
+def test_every_cut_gives_the_same_bits(N, H, W, C, M, S, counts):
+    cfg = synth.BlockConfig("runs", N, H, W, C, M, S, "bf16", 1.0, 55)
+    inp = synth.make_block_inputs(cfg)
+    d = U.dev_inputs(inp)
+    full = torch.empty_like(d["x"])
+    B.lasnet_sparse_bottleneck(d["x"], None, None, S, *U.weights(d), out=full, flags=B.LASNET_FORCE_FUSED)
+    few = [0, N - 1]
+    f = inp.f64
+    ref = O.dense_bottleneck(f["x"][few], f["W1"], f["b1"], f["W2"], f["b2"], f["W3"], f["b3"])
+    U.assert_block_close(full[few], ref, d["x"][few], np.ones((len(few), H, W)), "bf16", "full")
+    want, untouched = U.bits(full), U.bits(torch.tensor(777.0, dtype=torch.bfloat16))
+    packed = B.lasnet_pack_weights(S, d["W1"], d["W2"], d["W3"])
+    rng = np.random.default_rng(5)
+    for count in counts:
+        for order in ("ascending", "shuffled"):
+            cells = rng.permutation(cfg.P)[:count].astype(np.int32)
+            if order == "ascending":
+                cells.sort()
+            idx, cnt = U.list_tensor(cells, cfg.P), torch.tensor([count], dtype=torch.int32, device="cuda")
+            out = torch.full_like(d["x"], 777.0)
+            B.lasnet_sparse_bottleneck_packed(d["x"], idx, cnt, S, M, packed, d["b1"], d["b2"], d["b3"], out=out,
+                                              flags=B.LASNET_FORCE_FUSED | B.LASNET_SKIP_IDENTITY)
+            mask = np.zeros(cfg.P, bool)
+            mask[cells] = True
+            up = mask.reshape(N, H // S, W // S).repeat(S, 1).repeat(S, 2)
+            got = U.bits(out)
+            assert np.array_equal(got[up], want[up]), (count, order)
+            assert (got[~up] == untouched).all(), (count, order)
