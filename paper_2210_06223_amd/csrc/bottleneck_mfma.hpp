@@ -88,13 +88,14 @@ struct Cfg {
   static constexpr int OFF_MISC = OFF_PIXQ + R2P * 4;           // int  [4]
   static constexpr int OFF_ROWKEY = OFF_MISC + 16;              // uint8[R1MAX]  swizzle key of each row
   static constexpr int OFF_BIAS = (OFF_ROWKEY + R1MAX + 15) / 16 * 16;   // float[M | M | C]: b1, b2, b3
-  static constexpr int OFF_Y1 = OFF_BIAS + (2 * M + C) * 4;
+  static constexpr int OFF_Y1 = roundup(OFF_BIAS + (2 * M + C) * 4, LDY * 2);   // (rows at multiples of their size: frag_row)
   static constexpr int Y1_BYTES = (R1MAX + 1) * LDY * 2;
   static constexpr int OFF_XS = Y1_IN_XS ? OFF_Y1 : OFF_Y1 + Y1_BYTES;
   static constexpr int STAGE_ELEMS = R1MAX * LDX;
   static constexpr int XS_BYTES = NSTG * STAGE_ELEMS * 2 + 1024;  // + 1 KiB that padding loads land in
   static constexpr int Y2_BYTES = R2P * LDY * 2;
   static constexpr int OFF_Y2 = Y1_IN_XS ? OFF_XS + Y1_BYTES : OFF_XS;              // xs is dead once conv1 is done
+  static_assert(OFF_Y2 % (LDY * 2) == 0, "rows at multiples of their size");
   static constexpr int LDS_BYTES = cmax(OFF_XS + XS_BYTES, OFF_Y2 + Y2_BYTES);
   static constexpr size_t PACKED_ELEMS = (size_t)M * C * 2 + 9 * (size_t)M * M;
   static_assert(R1MAX % 16 == 0 && R1MAX >= WW && R1MAX < (1 << kRowBits), "y1 rows");
@@ -104,12 +105,11 @@ struct Cfg {
   static_assert(M % (16 * WC1) == 0 && M % (16 * WC2) == 0 && C % (16 * WC3) == 0, "channel split");
   static_assert(NBT3 % NB3 == 0 && NB3 % 2 == 0, "conv3 passes; 16-byte epilogue pieces");
   static_assert(C % (2 * KC) == 0 && KC == 64 && M % 32 == 0, "k steps");
-  // x stream: chunk c lives in stage c % NSTG.  XD chunks are requested ahead of the one being
-  // consumed: all of them when they all fit, else one less than there are stages (a stage is
-  // refilled right after the barrier that follows its last read).
+  // x stream: chunk c lives in stage c % NSTG.  XD chunks are requested ahead of the one being multiplied, as many as there
+  // are stages: a chunk's fragments have all been read when its multiplication begins.
   static constexpr int NCH = C / KC;
-  static constexpr int XD = NCH <= NSTG ? NCH : NSTG - 1;
-  static_assert(NSTG >= 3 && XD >= 2, "x stream depth");
+  static constexpr int XD = NCH <= NSTG ? NCH : NSTG;
+  static_assert(NSTG >= 3 && NCH >= 2, "x stream depth");
   static_assert(LDY % 64 == 0 && (LDY & (LDY - 1)) == 0, "y rows: power-of-two pitch, whole swizzle groups");
   static_assert((9 * MS) % RD2 == 0 && MS % RD3 == 0, "weight rings");
   static_assert(LDS_BYTES <= 160 * 1024, "LDS");
@@ -148,20 +148,20 @@ __device__ inline int swz(int row, int ld, int chunk, int key, int mask = 15) {
 
 // The same address for the B-fragment reads of the k-loops, split so that the part that changes
 // with the k-step is a compile-time constant: chunk = 4*s + lg never carries, so
-// (4*s + lg) ^ key = (4*s) ^ (lg ^ key), and in bytes the fragment of k-step s sits at
-//   row_bytes + ((64*s) ^ key_bytes),   key_bytes = (lg ^ (key & mask)) << 4.
-// One xor-add per read and two registers per row, instead of one register per (row, k-step).
-struct FragRow { int row_bytes, key_bytes; };
-__device__ __forceinline__ FragRow frag_row(int row, int ld, int lg, int key, int mask = 15) {
-  return FragRow{row * ld * 2, (lg ^ (key & mask)) << 4};
+// (4*s + lg) ^ key = (4*s) ^ (lg ^ key), and where rows begin at multiples of their size, a power of two (the kernels align their y1 and
+// y2), the fragment of k-step s sits at frag_row() ^ (64*s): one register per row and one instruction per read.  (A k-step is 8 to 14 MFMAs
+// of 16 clocks, and what else a wave issues takes 4 clocks each.  Two registers and four instructions per read, and the lookups of rows
+// past a batch's last under masks -> this, call sequences: 14x14x1024, S=2, batch 128 61.0 -> 59.4 us; 56x56x256, S=4, batch 256
+// 238.8 -> 235.8; 7x7x2048, batch 128 64.5 -> 62.5.)
+__device__ __forceinline__ int frag_row(const AS_LDS __bf16* base, int row, int ld, int lg, int key, int mask = 15) {
+  return (int)(unsigned)(size_t)base + row * ld * 2 + ((lg ^ (key & mask)) << 4);
 }
-__device__ __forceinline__ bf16x8 frag_read(const AS_LDS __bf16* base, FragRow r, int s) {
-  int key = r.key_bytes;
-  // opaque to the optimiser: otherwise (64*s) ^ key is computed for every s ahead of the loop,
-  // kept in registers across the whole phase, and some of them end up spilled
-  asm volatile("" : "+v"(key));
-  return *reinterpret_cast<const AS_LDS bf16x8*>(reinterpret_cast<const AS_LDS char*>(base) + r.row_bytes +
-                                                 ((64 * s) ^ key));
+__device__ __forceinline__ bf16x8 frag_read(int row, int s) {
+  // (asm: otherwise the address is computed for every s ahead of the loop, kept in registers across the whole phase, and
+  // some of them end up spilled)
+  unsigned a;
+  asm volatile("v_xor_b32 %0, %1, %2" : "=v"(a) : "n"(64 * s), "v"(row));
+  return *(const AS_LDS bf16x8*)(size_t)a;
 }
 
 // Which output channel a lane holds.  In the 16x16 result of an MFMA, lane group lg (= lane / 16)
@@ -246,16 +246,16 @@ __device__ __forceinline__ void barrier_keep_vm_n(int n) {
 //   prologue   c = 0, 1, ..:  W(c) if c < WD,  X(c) if c < XD
 //   chunk ch   (barrier, matrix work, and between the MFMAs)  W(ch + WD),  then  X(ch + XD)
 // (with the ring filled ahead of the phase -- HOISTED -- the prologue is W(0..WD-1) and then X(0..XD-1)).
-// W(c) = the NWL weight fragments of chunk c, X(c) = the NXL x loads of chunk c.  The barrier
-// that opens chunk ch needs W(ch) and X(ch) complete; this is the number of operations issued
-// after the younger of the two, which may stay in flight.
+// W(c) = the NWL weight fragments of chunk c, X(c) = the NXL x loads of chunk c.  The barrier that opens chunk ch (-1: the
+// one before the first fragments are read) needs X(ch + 1) complete; this is the number of operations issued
+// after it, which may stay in flight.  (The weights come back to registers: the compiler waits for those.)
 constexpr int conv1_keep_in_flight(int ch, int nch, int wd, int xd, int nwl, int nxl, bool w_first = false) {
-  int after_w = -1, after_x = -1;          // operations issued up to and including W(ch) / X(ch)
+  int after_x = -1;                        // operations issued up to and including X(ch + 1)
   int total = 0;
   auto issue = [&](bool is_w, int c, int n) {
     if (c >= nch) return;
     total += n;
-    if (c == ch) { if (is_w) after_w = total; else after_x = total; }
+    if (!is_w && c == ch + 1) after_x = total;
   };
   if (w_first) {                           // the ring was filled before the phase: all of W(0..wd-1), then the x chunks
     for (int c = 0; c < wd; ++c) issue(true, c, nwl);
@@ -267,8 +267,7 @@ constexpr int conv1_keep_in_flight(int ch, int nch, int wd, int xd, int nwl, int
     }
   }
   for (int c = 0; c < ch; ++c) { issue(true, c + wd, nwl); issue(false, c + xd, nxl); }
-  const int last = after_w > after_x ? after_w : after_x;
-  return total - last;
+  return total - after_x;
 }
 
 // A lane's 4*NB consecutive channels leave as 16-byte pieces (8 channels = one swizzle chunk).
@@ -394,13 +393,10 @@ __device__ LASNET_PHASE_INLINE void conv1_core(Conv1Ring<K>& ring, g_bf16_p x, g
     for (int j = 0; j < NBW; ++j)
       w[slot][j] = buf_load16(wrs, lane16 + j * 1024, wbase + kstep * K::W_KSTEP_BYTES);
   };
-  int boff[RB][KS];                                       // LDS offsets of this lane's B fragments
+  // LDS offsets of this lane's B fragments: a row block is 16 rows on, a whole number of swizzle periods
+  int boff[KS];
 #pragma unroll
-  for (int i = 0; i < RB; ++i) {
-    const int row = (wr + K::WR1 * i) * 16 + l16;
-#pragma unroll
-    for (int s = 0; s < KS; ++s) boff[i][s] = swz(row, K::LDX, s * 4 + lg, row, K::XMASK);
-  }
+  for (int s = 0; s < KS; ++s) boff[s] = swz(wr * 16 + l16, K::LDX, s * 4 + lg, l16, K::XMASK);
 
   // prologue of the stream (see conv1_keep_in_flight for the order)
   constexpr int XD = K::XD;
@@ -420,42 +416,43 @@ __device__ LASNET_PHASE_INLINE void conv1_core(Conv1Ring<K>& ring, g_bf16_p x, g
   meanwhile();
   __builtin_amdgcn_sched_barrier(0);
 
-  // B fragments are read one k-step ahead of the MFMAs that use them (bcur/bnxt), so a
-  // wave's LDS latency hides behind its own matrix work.
-  bf16x8 bcur[RB], bnxt[RB];
+  // B fragments are read a chunk ahead of the MFMAs that use them, each into the registers that its predecessor has just
+  // left: chunk ch+1 must have landed when chunk ch is multiplied, and chunk ch's stage is free.
+  bf16x8 b[KS][RB];
+  auto read = [&](int ch, int s, int i) {
+    b[s][i] = *reinterpret_cast<const AS_LDS bf16x8*>(xs + boff[s] + ((ch % K::NSTG) * K::STAGE_ELEMS + K::WR1 * i * 16 * K::LDX));
+  };
+  barrier_keep_vm_n(conv1_keep_in_flight(-1, NCH, WD, XD, NWL, NXL, HOISTED));
+  __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+  for (int s = 0; s < KS; ++s)
+#pragma unroll
+    for (int i = 0; i < RB; ++i) read(0, s, i);
+  __builtin_amdgcn_sched_barrier(0);
   // fully unrolled: with a back edge the compiler's own waits for the weight registers fall
   // back to vmcnt(0), which would drain the x stream every other chunk
 #pragma unroll
   for (int ch = 0; ch < NCH; ++ch) {
-    {
-      const int cc = ch % WD;                              // ring slot group of this chunk (constant after unrolling)
+    const int cc = ch % WD;                                // ring slot group of this chunk (constant after unrolling)
+    if (ch + 1 < NCH) {
       barrier_keep_vm_n(conv1_keep_in_flight(ch, NCH, WD, XD, NWL, NXL, HOISTED));
       __builtin_amdgcn_sched_barrier(0);
-      l_bf16_cp xb = xs + (ch % K::NSTG) * K::STAGE_ELEMS;
+    }
 #pragma unroll
-      for (int i = 0; i < RB; ++i) bcur[i] = *reinterpret_cast<const AS_LDS bf16x8*>(xb + boff[i][0]);
+    for (int s = 0; s < KS; ++s) {
 #pragma unroll
-      for (int s = 0; s < KS; ++s) {
-        if (s + 1 < KS) {
+      for (int i = 0; i < RB; ++i) {
 #pragma unroll
-          for (int i = 0; i < RB; ++i) bnxt[i] = *reinterpret_cast<const AS_LDS bf16x8*>(xb + boff[i][s + 1]);
-        }
-#pragma unroll
-        for (int i = 0; i < RB; ++i)
-#pragma unroll
-          for (int j = 0; j < NBW; ++j) acc[i][j] = mfma16(w[cc * KS + s][j], bcur[i], acc[i][j]);
-        if (ch + WD < NCH) wload(cc * KS + s, (ch + WD) * KS + s);
+        for (int j = 0; j < NBW; ++j) acc[i][j] = mfma16(w[cc * KS + s][j], b[s][i], acc[i][j]);
+        if (ch + 1 < NCH) read(ch + 1, s, i);
         __builtin_amdgcn_sched_barrier(0);
-        if (s + 1 < KS) {
-#pragma unroll
-          for (int i = 0; i < RB; ++i) bcur[i] = bnxt[i];
-        }
       }
-      // the stage of chunk ch+XD was last read during chunk ch-1, which every wave has left
-      // (barrier above)
-      if (ch + XD < NCH) issue_x(ch + XD);
+      if (ch + WD < NCH) wload(cc * KS + s, (ch + WD) * KS + s);
       __builtin_amdgcn_sched_barrier(0);
     }
+    // (every wave has read the stage's chunk, ch: barrier above)
+    if (ch + XD < NCH) issue_x(ch + XD);
+    __builtin_amdgcn_sched_barrier(0);
   }
   // (y1s may lie inside the x stages: every wave must have read its last chunk first)
   if constexpr (K::Y1_IN_XS) __syncthreads();
@@ -538,12 +535,9 @@ __device__ LASNET_PHASE_INLINE void conv2_core(Conv2Ring<K>& ring, g_bf16_p W2, 
   int wpos[RB];                                            // window position of tap (0,0)
 #pragma unroll
   for (int i = 0; i < RB; ++i) {
-    const int q = (wr + K::WR2 * i) * 16 + l16;
-    wpos[i] = -1;
-    if (q < nq) {
-      const int slot = q / (S * S), r = q - slot * (S * S);
-      wpos[i] = slot * WW + (r / S) * T + r % S;
-    }
+    const int q = min((wr + K::WR2 * i) * 16 + l16, nq - 1);      // (rows past the last repeat it, unused)
+    const int slot = q / (S * S), r = q - slot * (S * S);
+    wpos[i] = slot * WW + (r / S) * T + r % S;
   }
   const rsrc_t wrs = make_rsrc(W2, K::W2_BYTES);
   const int wbase = (wc * NBW) * 1024;                     // bytes, wave-uniform
@@ -567,43 +561,41 @@ __device__ LASNET_PHASE_INLINE void conv2_core(Conv2Ring<K>& ring, g_bf16_p W2, 
   auto lookup = [&](int (&br)[RB], int tap) {
     const int toff = (tap / 3) * T + tap % 3;
 #pragma unroll
-    for (int i = 0; i < RB; ++i) br[i] = wpos[i] >= 0 ? winrow[wpos[i] + toff] : K::ZROW;
+    for (int i = 0; i < RB; ++i) br[i] = winrow[wpos[i] + toff];
   };
   int brow[RB];
-  FragRow fr[RB];
+  int fr[RB];
   auto enter = [&] {                                       // the tap that brow was looked up for
 #pragma unroll
-    for (int i = 0; i < RB; ++i) fr[i] = frag_row(brow[i] & ((1 << kRowBits) - 1), K::LDY, lg, brow[i] >> kRowBits, K::YMASK);
+    for (int i = 0; i < RB; ++i) fr[i] = frag_row(y1s, brow[i] & ((1 << kRowBits) - 1), K::LDY, lg, brow[i] >> kRowBits, K::YMASK);
   };
   lookup(brow, 0);
   enter();
-  // B fragments one k-step ahead of the MFMAs (bcur/bnxt), the row lookups of a tap one more.
-  bf16x8 bcur[RB], bnxt[RB];
+  // B fragments one k-step ahead, each into the registers that the MFMAs have just read (two k-steps ahead measured the same); a
+  // tap's row lookups one more.
+  static_assert(MS >= 2, "the lookups");
+  bf16x8 b[RB];
 #pragma unroll
-  for (int i = 0; i < RB; ++i) bcur[i] = frag_read(y1s, fr[i], 0);
+  for (int i = 0; i < RB; ++i) b[i] = frag_read(fr[i], 0);
+  __builtin_amdgcn_sched_barrier(0);
   // fully unrolled (as in conv1): across a back edge the compiler's waits for the weight ring
   // degrade towards vmcnt(0) and the ring stops hiding any latency
 #pragma unroll
   for (int t0 = 0; t0 < NSTEP; t0 += RD) {
 #pragma unroll
     for (int tt = 0; tt < RD; ++tt) {
-      const int t = t0 + tt;
-      const int msn = (t + 1) % MS;                        // k-step inside the tap of step t+1
-      if (t + 1 < NSTEP) {
-        if (msn == 0) enter();
+      const int t = t0 + tt, tn = t + 1;                   // the k-step multiplied, the one read
+      if (tn < NSTEP && tn % MS == 0) enter();
 #pragma unroll
-        for (int i = 0; i < RB; ++i) bnxt[i] = frag_read(y1s, fr[i], msn);
-        // (looked up a k-step before it is entered: the fragment reads wait for it)
-        if (msn == MS - 1 && t + 2 < NSTEP) lookup(brow, (t + 2) / MS);
+      for (int i = 0; i < RB; ++i) {
+#pragma unroll
+        for (int j = 0; j < NBW; ++j) acc[i][j] = mfma16(w[tt][j], b[i], acc[i][j]);
+        if (tn < NSTEP) b[i] = frag_read(fr[i], tn % MS);
+        __builtin_amdgcn_sched_barrier(0);
       }
-#pragma unroll
-      for (int i = 0; i < RB; ++i)
-#pragma unroll
-        for (int j = 0; j < NBW; ++j) acc[i][j] = mfma16(w[tt][j], bcur[i], acc[i][j]);
+      if (tn + 1 < NSTEP && (tn + 1) % MS == 0) lookup(brow, (tn + 1) / MS);
       if (HOISTED || t + RD < NSTEP) wload(tt, (t + RD) % NSTEP);
       __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-      for (int i = 0; i < RB; ++i) bcur[i] = bnxt[i];
     }
   }
 #pragma unroll
@@ -691,11 +683,11 @@ __device__ LASNET_PHASE_INLINE void conv3_core(Conv3Ring<K>& ring, g_bf16_p x, g
   const int wr = wave / K::WC3, wc = wc0 + wave % K::WC3;
   const float floor_ = post_relu ? 0.f : -__builtin_inff();   // ReLU after the add, or nothing
   int pq[RB];
-  FragRow fr[RB];
+  int fr[RB];
 #pragma unroll
   for (int i = 0; i < RB; ++i) {
     const int bq = (wr + K::WR3 * i) * 16 + l16;
-    fr[i] = frag_row(bq, K::LDY, lg, bq, K::YMASK);
+    fr[i] = frag_row(y2s, bq, K::LDY, lg, bq, K::YMASK);
   }
   // this wave's weight stream is contiguous over (pass, k-step, tile)
   const rsrc_t wrs = make_rsrc(W3, K::W3_BYTES);
@@ -739,6 +731,10 @@ __device__ LASNET_PHASE_INLINE void conv3_core(Conv3Ring<K>& ring, g_bf16_p x, g
   } else {
     rload(0);
   }
+  bf16x8 b[RB];                                            // as in conv2 (they run on into the next pass: the same rows)
+#pragma unroll
+  for (int i = 0; i < RB; ++i) b[i] = frag_read(fr[i], 0);
+  __builtin_amdgcn_sched_barrier(0);
   // fully unrolled, like conv1 and conv2: the weight ring runs on across the passes
 #pragma unroll
   for (int pass = 0; pass < NPASS; ++pass) {
@@ -750,27 +746,20 @@ __device__ LASNET_PHASE_INLINE void conv3_core(Conv3Ring<K>& ring, g_bf16_p x, g
 #pragma unroll
       for (int i = 0; i < RB; ++i) acc[i][j] = bias;
     }
-    bf16x8 bcur[RB], bnxt[RB];
-#pragma unroll
-    for (int i = 0; i < RB; ++i) bcur[i] = frag_read(y2s, fr[i], 0);
 #pragma unroll
     for (int s = 0; s < MS; ++s) {
-      if (s + 1 < MS) {
+      const int t = pass * MS + s;
 #pragma unroll
-        for (int i = 0; i < RB; ++i) bnxt[i] = frag_read(y2s, fr[i], s + 1);
+      for (int i = 0; i < RB; ++i) {
+#pragma unroll
+        for (int j = 0; j < NB; ++j) acc[i][j] = mfma16(w[s % RD][j], b[i], acc[i][j]);
+        if (t + 1 < NSTEP) b[i] = frag_read(fr[i], (s + 1) % MS);
+        __builtin_amdgcn_sched_barrier(0);
       }
-#pragma unroll
-      for (int i = 0; i < RB; ++i)
-#pragma unroll
-        for (int j = 0; j < NB; ++j) acc[i][j] = mfma16(w[s % RD][j], bcur[i], acc[i][j]);
       // refill with the step RD ahead (the stream runs on into the next pass; past its end the
       // last step is re-read, unused)
-      wload(s % RD, HOISTED ? (pass * MS + s + RD) % NSTEP : min(pass * MS + s + RD, NSTEP - 1));
+      wload(s % RD, HOISTED ? (t + RD) % NSTEP : min(t + RD, NSTEP - 1));
       __builtin_amdgcn_sched_barrier(0);
-      if (s + 1 < MS) {
-#pragma unroll
-        for (int i = 0; i < RB; ++i) bcur[i] = bnxt[i];
-      }
     }
     if (pass + 1 < NPASS) rload(pass + 1);
 #pragma unroll
@@ -828,7 +817,7 @@ __global__ __launch_bounds__(K::NT, K::WAVES_PER_SIMD) void fused_bneck_kernel(
     const float* __restrict__ b1, const __bf16* __restrict__ W2, const float* __restrict__ b2,
     const __bf16* __restrict__ W3, const float* __restrict__ b3, __bf16* __restrict__ out,
     int post_relu) {
-  extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
+  extern __shared__ __attribute__((aligned(1024))) unsigned char smem[];
   int* hkey = reinterpret_cast<int*>(smem + K::OFF_HKEY);
   short* hval = reinterpret_cast<short*>(smem + K::OFF_HVAL);
   short* winrow = reinterpret_cast<short*>(smem + K::OFF_WINROW);

@@ -78,7 +78,7 @@ __global__ __launch_bounds__(K::NT, 1) void stream_bneck_kernel(
     const int32_t* __restrict__ count, const __bf16* __restrict__ W1p, const float* __restrict__ b1,
     const __bf16* __restrict__ W2p, const float* __restrict__ b2, const __bf16* __restrict__ W3p,
     const float* __restrict__ b3, __bf16* __restrict__ out) {
-  extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
+  extern __shared__ __attribute__((aligned(1024))) unsigned char smem[];
   constexpr int C = K::C, M = K::M, S = K::S, T = K::T, WW = K::WW;
   AS_LDS char* lds = (AS_LDS char*)smem;
   AS_LDS char* xs = lds + K::OFF_XS;
@@ -209,7 +209,7 @@ __global__ __launch_bounds__(K::NT, 1) void stream_bneck_kernel(
     // ------------------------------------------------------------------ conv1
     {
       floatx4 acc[K::RB1][K::MT];
-      FragRow fr[K::RB1];
+      int fr[K::RB1];
 #pragma unroll
       for (int i = 0; i < K::RB1; ++i) {
         // the accumulators start at the bias: the first MFMA takes it as its C operand
@@ -219,7 +219,7 @@ __global__ __launch_bounds__(K::NT, 1) void stream_bneck_kernel(
         // a wave row's last block may not exist (R1B not a multiple of WR): it recomputes the
         // last real one, and its result is dropped
         const int row = min(wr + K::WR * i, K::R1B - 1) * 16 + l16;
-        fr[i] = frag_row(row, C, lg, row, 15);
+        fr[i] = frag_row((const AS_LDS __bf16*)xc, row, C, lg, row, 15);
       }
       // B fragments are read PF k-steps ahead of the MFMAs that use them: with one wave per SIMD
       // nothing else hides the LDS latency (deeper than 1 measured the same)
@@ -228,13 +228,13 @@ __global__ __launch_bounds__(K::NT, 1) void stream_bneck_kernel(
 #pragma unroll
       for (int s0 = 0; s0 < PF; ++s0)
 #pragma unroll
-        for (int i = 0; i < K::RB1; ++i) bq[s0][i] = frag_read((const AS_LDS __bf16*)xc, fr[i], s0);
+        for (int i = 0; i < K::RB1; ++i) bq[s0][i] = frag_read(fr[i], s0);
 #pragma unroll
       for (int ks = 0; ks < K::KS1; ++ks) {
         if (ks + PF < K::KS1) {
 #pragma unroll
           for (int i = 0; i < K::RB1; ++i)
-            bq[(ks + PF) % (PF + 1)][i] = frag_read((const AS_LDS __bf16*)xc, fr[i], ks + PF);
+            bq[(ks + PF) % (PF + 1)][i] = frag_read(fr[i], ks + PF);
         }
 #pragma unroll
         for (int i = 0; i < K::RB1; ++i)

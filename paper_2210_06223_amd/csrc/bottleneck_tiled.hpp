@@ -53,7 +53,7 @@ struct TiledCfg {
     static constexpr int WR1 = 1, WC1 = 4, NBW1 = TC1 / 16 / WC1;
     static constexpr int R1MAX = kTiledRows;
     static constexpr int LDX = KC, XMASK = KC / 8 - 1, STAGE_ELEMS = R1MAX * LDX;
-    static constexpr int NCH = C / KC, XD = NCH <= NSTG ? NCH : NSTG - 1;
+    static constexpr int NCH = C / KC, XD = NCH <= NSTG ? NCH : NSTG;
     static constexpr int LDY = TC1, YMASK = LDY / 8 - 1 < 15 ? LDY / 8 - 1 : 15;
     static constexpr int W_KSTEP_BYTES = M * 64;
     static constexpr unsigned W1_BYTES = M * C * 2;
@@ -259,7 +259,7 @@ __global__ __launch_bounds__(256, 1) void tiled_conv1_kernel(
     const int32_t* __restrict__ count, const uint8_t* __restrict__ mask_in, uint8_t* __restrict__ mask_ws,
     const __bf16* __restrict__ W1p, const float* __restrict__ b1, __bf16* __restrict__ y1g) {
   using K = typename TC::K1;
-  extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
+  extern __shared__ __attribute__((aligned(1024))) unsigned char smem[];
   int unit, slice;
   if (!unit_and_slice(tg.ngroups * tg.nt1, TC::NSL1, unit, slice)) return;
   const int tid = threadIdx.x, wave = uni(tid >> 6);
@@ -321,7 +321,7 @@ __global__ __launch_bounds__(256, 1) void tiled_conv2_kernel(
     const __bf16* __restrict__ W2p, const float* __restrict__ b2, const __bf16* __restrict__ y1g,
     __bf16* __restrict__ y2g) {
   using K = typename TC::K2;
-  extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
+  extern __shared__ __attribute__((aligned(1024))) unsigned char smem[];
   int group, slice;
   if (!unit_and_slice(tg.ngroups, TC::NSL2, group, slice)) return;
   const int tid = threadIdx.x, wave = uni(tid >> 6), lane = tid & 63;
@@ -392,7 +392,7 @@ __global__ __launch_bounds__(256, 1) void tiled_conv3_kernel(
     const __bf16* __restrict__ W3p, const float* __restrict__ b3, const __bf16* __restrict__ y2g,
     __bf16* out, int post_relu) {                          // out may be x: a lane reads and writes the same elements
   using K = typename TC::K3;
-  extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
+  extern __shared__ __attribute__((aligned(1024))) unsigned char smem[];
   int group, slice;
   if (!unit_and_slice(tg.ngroups, TC::NSL3, group, slice)) return;
   const int tid = threadIdx.x, wave = uni(tid >> 6), lane = tid & 63;
