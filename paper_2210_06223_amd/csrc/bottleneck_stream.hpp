@@ -10,15 +10,15 @@
 // feeds two (conv1, conv2) or eight (conv3) MFMAs; 272 registers per lane hold the wave's weights.
 // Per patch:
 //
-//   top      the (S+2)x(S+2) window of the NEXT patch is requested global -> LDS (the other half
-//            of a double buffer), so HBM works while this patch is computed; nothing else in the
+//   top      the (S+2)x(S+2) window of this patch has landed in LDS (one half of a double buffer); nothing else in the
 //            loop loads from global memory (weights in registers, biases and patch origins in LDS,
-//            the residual is the window's own interior), so the only wait for memory is one
-//            per patch, a whole patch after the request
+//            the residual is the window's own interior), so this is the only wait for memory
 //   conv1    y1 = ReLU(W1 x + b1) on the 100 window positions; positions outside the image
-//            get y1 = 0 (the 3x3 pads conv1's output)                     -> LDS, row = wy*16 + wx
+//            get y1 = 0 (the 3x3 pads conv1's output)                     -> LDS, row = wy*16 + wx;
+//            the residual -> registers; then the window after the next is requested into the place of this one, so HBM
+//            works for most of two patches on each
 //   conv2    3x3 from LDS, rows addressed arithmetically (no lookup table) -> y2 in LDS
-//   conv3    + b3 + residual from the x window in LDS, one rounding, whole-line streaming stores
+//   conv3    + b3 + residual, one rounding, whole-line streaming stores
 //
 // The pixel of every window position of a patch (or -1 outside the image) is tabulated in LDS two
 // patches ahead, off the critical path, from the patch origins decoded once at the start.
@@ -49,6 +49,7 @@ struct StreamCfg {
   static constexpr int MAXQ = 64;                           // list entries one workgroup takes
   static constexpr int XGRP = R1 / 2;                       // 1 KiB pieces (two x rows) of a window
   static constexpr int NXL = XGRP / NW;                     // x loads per wave per patch
+  static constexpr int NST = RB2 * G3 * 2;                  // stores per wave per patch
   static constexpr int OFF_XS = 0, XS_BYTES = 2 * R1 * XROW;
   static constexpr int OFF_Y1 = OFF_XS + XS_BYTES, Y1_BYTES = Y1ROWS * YROW;
   static constexpr int OFF_Y2 = OFF_Y1 + Y1_BYTES, Y2_BYTES = Q * YROW;
@@ -64,6 +65,7 @@ struct StreamCfg {
   static_assert(XGRP % NW == 0, "every wave requests the same number of window pieces");
   static_assert(NW * 2 * 2048 <= Y1_BYTES, "conv3's transpose areas (two per wave) sit in the y1 rows");
   static_assert(LDS_BYTES <= 160 * 1024, "LDS");
+  static_assert(NXL + NST < 64, "vmcnt");
 };
 
 // Swizzle keys of the 128-byte y rows (8 chunks of 16 bytes; even and odd rows sit in different
@@ -72,9 +74,11 @@ struct StreamCfg {
 __device__ __forceinline__ int y1_key(int row) { return ((row >> 1) & 3) | ((row >> 2) & 4); }
 __device__ __forceinline__ int y2_key(int row) { return (row >> 1) & 7; }
 
+constexpr int kNoCell = -(1 << 20);              // window origin of an entry that is no cell of the map
+
 template <class K, bool POST_RELU>
 __global__ __launch_bounds__(K::NT, 1) void stream_bneck_kernel(
-    Geom g, const __bf16* __restrict__ x, const int32_t* __restrict__ idx,
+    Geom g, Div31 cpi, Div31 gw, const __bf16* __restrict__ x, const int32_t* __restrict__ idx,
     const int32_t* __restrict__ count, const __bf16* __restrict__ W1p, const float* __restrict__ b1,
     const __bf16* __restrict__ W2p, const float* __restrict__ b2, const __bf16* __restrict__ W3p,
     const float* __restrict__ b3, __bf16* __restrict__ out) {
@@ -95,33 +99,7 @@ __global__ __launch_bounds__(K::NT, 1) void stream_bneck_kernel(
   const int tid = threadIdx.x, lane = tid & 63, l16 = lane & 15, lg = lane >> 4;
   const int wave = uni(tid >> 6), wr = wave / K::WC, wc = wave % K::WC;
 
-  // ---- this workgroup's run of the list (XCD k takes a contiguous eighth of the runs) ------
-  const int nact = uni(idx ? min(*count, g.P) : g.P);
-  if (nact <= 0) return;
-  const int nt = min((int)gridDim.x, nact);
-  if ((int)blockIdx.x >= nt) return;
-  const int xcd = (int)blockIdx.x & 7, jx = (int)blockIdx.x >> 3;
-  const int run = xcd * (nt >> 3) + min(xcd, nt & 7) + jx;
-  const int tb = (int)(((long long)run * nact) / nt);
-  const int npat = (int)(((long long)(run + 1) * nact) / nt) - tb;   // <= MAXQ by the grid size
-
-  for (int i = tid; i < npat; i += K::NT) {
-    const int cell = idx ? idx[tb + i] : tb + i;
-    const int n = cell / (g.G * g.GW), rem = cell - n * (g.G * g.GW);
-    const int gy = rem / g.GW, gx = rem - gy * g.GW;
-    int h0 = gy * S - 1, w0 = gx * S - 1, base = (n * g.H + h0) * g.W + w0;
-    if ((unsigned)cell >= (unsigned)g.P) {                   // not a cell of this map: a window that lies
-      h0 = w0 = -(1 << 20);                                  // wholly outside the image (nothing is stored
-      base = -(g.W + 1);                                     // for it; its loads read pixel 0)
-    }
-    hdr[i * 4 + 0] = base;
-    hdr[i * 4 + 1] = h0;
-    hdr[i * 4 + 2] = w0;
-  }
-  for (int i = tid; i < M; i += K::NT) { b1s[i] = b1[i]; b2s[i] = b2[i]; }
-  for (int i = tid; i < C; i += K::NT) b3s[i] = b3[i];
-
-  // ---- all weights of this wave -> registers (A fragments), once ---------------------------
+  // ---- all weights of this wave -> registers (A fragments), once: requested before anything is waited for ----
   bf16x8 w1[K::KS1][K::MT], w2[9 * K::KS2][K::MT], w3[K::KS2][K::G3][K::NT3];
   {
     const AS_GLOBAL bf16x8* p1 = (const AS_GLOBAL bf16x8*)W1p + lane;
@@ -143,6 +121,37 @@ __global__ __launch_bounds__(K::NT, 1) void stream_bneck_kernel(
         for (int j = 0; j < K::NT3; ++j)
           w3[ks][gg][j] = p3[(((wc * K::G3 + gg) * K::KS2 + ks) * K::NT3 + j) * 64];
   }
+  __builtin_amdgcn_sched_barrier(0);
+
+  // ---- this workgroup's run of the list (XCD k takes a contiguous eighth of the runs) ------
+  const int nact = uni(idx ? min(*count, g.P) : g.P);
+  if (nact <= 0) return;
+  const int nt = min((int)gridDim.x, nact);
+  if ((int)blockIdx.x >= nt) return;
+  const int xcd = (int)blockIdx.x & 7, jx = (int)blockIdx.x >> 3;
+  const int run = xcd * (nt >> 3) + min(xcd, nt & 7) + jx;
+  const int len = (int)((unsigned)nact / (unsigned)nt), longer = nact - len * nt;   // the first `longer` runs have one entry more
+  const int tb = run * len + min(run, longer);
+  const int npat = len + (run < longer ? 1 : 0);           // <= MAXQ by the grid size
+
+  for (int i = tid; i < npat; i += K::NT) {
+    const int entry = idx ? idx[tb + i] : tb + i;
+    const bool valid = (unsigned)entry < (unsigned)g.P;
+    const int cell = valid ? entry : 0;
+    const int n = div31_by(cell, cpi), rem = cell - n * (g.G * g.GW);
+    const int gy = div31_by(rem, gw), gx = rem - gy * g.GW;
+    int h0 = gy * S - 1, w0 = gx * S - 1, base = (n * g.H + h0) * g.W + w0;
+    if (!valid) {                                            // not a cell of this map: a window that lies
+      h0 = w0 = kNoCell;                                     // wholly outside the image (nothing is stored
+      base = -(g.W + 1);                                     // for it; its loads read pixel 0)
+    }
+    hdr[i * 4 + 0] = base;
+    hdr[i * 4 + 1] = h0;
+    hdr[i * 4 + 2] = w0;
+  }
+  for (int i = tid; i < M; i += K::NT) { b1s[i] = b1[i]; b2s[i] = b2[i]; }
+  for (int i = tid; i < C; i += K::NT) b3s[i] = b3[i];
+
   // W2 and W3 live in the accumulation registers (an MFMA reads its A operand from either half of
   // the register file; other instructions only from the first 256, which stay free for W1, the
   // accumulators and the epilogues).  Without this the compiler parks them there anyway, as spills,
@@ -171,40 +180,47 @@ __global__ __launch_bounds__(K::NT, 1) void stream_bneck_kernel(
       pixs[(p % 3) * (2 * K::R1) + K::R1 + tid] = in ? px : base + g.W + 1;
     }
   };
-  // request the x window of entry p: a wave instruction fills two 512-byte rows (chunks swizzled
-  // with the row's low 4 bits).  Byte offsets from x fit 32 bits (the launcher checks).
-  auto issue_x = [&](int p) {
+  // request parts [u0, u1) of this wave's share of the x window of entry p: a wave instruction fills two 512-byte rows (chunks
+  // swizzled with the row's low 4 bits).  Byte offsets from x fit 32 bits (the launcher checks).
+  auto issue_x = [&](int p, int u0, int u1) {
     AS_LDS const int* pl = pixs + (p % 3) * (2 * K::R1) + K::R1 + wave * 2 + (lane >> 5);
+    const unsigned lds0 = uni((int)(unsigned)(size_t)(xs + (p & 1) * (K::R1 * K::XROW) + wave * 1024));
     int px[K::NXL];
 #pragma unroll
-    for (int u = 0; u < K::NXL; ++u) px[u] = pl[u * K::NW * 2];
-    const unsigned lds0 = uni((int)(unsigned)(size_t)(xs + (p & 1) * (K::R1 * K::XROW) + wave * 1024));
+    for (int u = u0; u < u1; ++u) px[u] = pl[u * K::NW * 2];
 #pragma unroll
-    for (int u = 0; u < K::NXL; ++u) {
-      {
-        // row = (wave + 4u)*2 + (lane >> 5): its low 4 bits are those of wave*2 + (lane >> 5) + 8u
-        const int key = (wave * 2 + (lane >> 5) + 8 * (u & 1)) & 15;
-        const unsigned off = ((unsigned)px[u] << 9) + ((((lane & 31) ^ key)) << 4);
-        asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, %1" ::"v"(off), "s"(x),
-                     "s"(lds0 + u * K::NW * 1024)
-                     : "memory");
-      }
+    for (int u = u0; u < u1; ++u) {
+      // row = (wave + 4u)*2 + (lane >> 5): its low 4 bits are those of wave*2 + (lane >> 5) + 8u
+      const int key = (wave * 2 + (lane >> 5) + 8 * (u & 1)) & 15;
+      const unsigned off = ((unsigned)px[u] << 9) + ((((lane & 31) ^ key)) << 4);
+      asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, %1" ::"v"(off), "s"(x),
+                   "s"(lds0 + u * K::NW * 1024)
+                   : "memory");
     }
   };
 
   decode(0);
   if (npat > 1) decode(1);
   __syncthreads();
-  issue_x(0);
+  issue_x(0, 0, K::NXL);
 
   for (int p = 0; p < npat; ++p) {
     AS_LDS const char* xc = xs + (p & 1) * (K::R1 * K::XROW);
     AS_LDS const int* pix = pixs + (p % 3) * (2 * K::R1);
-    // The window of entry p has landed (requested a whole patch ago), the previous patch's stores
-    // are done and every wave has left the previous patch.  (Letting those stores stay in flight
-    // here measured the same.)
-    barrier_keep_vm<0>();
-    if (p + 1 < npat) issue_x(p + 1);
+    // Every wave has left the previous patch, and the window of entry p has landed.  A wave's memory operations complete in
+    // order; those it has issued since that request are the next window's (NXL) and the previous patch's stores (NST),
+    // and before the latter the stores of the patch before.
+    // (The second window is requested when the first has landed: all workgroups begin together, and with two each they would
+    // wait for twice the bytes before they compute.)
+    if (p == 0) {
+      barrier_keep_vm<0>();
+      if (npat > 1) issue_x(1, 0, K::NXL);
+    } else if (p + 1 < npat) {
+      barrier_keep_vm<K::NXL + K::NST>();
+    } else {
+      barrier_keep_vm<K::NST>();
+    }
+    if (p + 2 < npat) decode(p + 2);                       // read after the next barrier
 
     // ------------------------------------------------------------------ conv1
     {
@@ -259,8 +275,25 @@ __global__ __launch_bounds__(K::NT, 1) void stream_bneck_kernel(
         }
       }
     }
-    barrier_keep_vm<63>();                                 // LDS only: the next window stays in flight
-    if (p + 2 < npat) decode(p + 2);                       // read after the next patch's first barrier
+    // The residual (the window's own interior) is taken along in registers: with it the window has been read, and the one after
+    // the next is requested into its place.  So one window and two thirds are in flight, and a patch waits for none (with one,
+    // 1 us each).  56x56x256, batch 64, r=0.4: with the weights requested before the list is read, and the list cut and decoded without
+    // divisions (19.7k -> 10.6k clocks to the first window), the block 30.8 -> 28.6 us.  What is left of a patch's 9.0k
+    // clocks is LDS reads and the instructions of one wave per SIMD: its MFMAs take 2.7k.
+    bf16x8 res[K::RB2][K::G3][2];
+#pragma unroll
+    for (int i = 0; i < K::RB2; ++i) {
+      const int q = (wr + K::WR * i) * 16 + l16;
+      const int wp = (q / S + 1) * T + q % S + 1;          // the pixel's own window position
+#pragma unroll
+      for (int gg = 0; gg < K::G3; ++gg)
+#pragma unroll
+        for (int t = 0; t < 2; ++t) {
+          const int c8 = (wc * K::G3 + gg) * 64 + t * 32 + lg * 8;   // 8 consecutive channels (tiles 2t, 2t+1)
+          res[i][gg][t] = *reinterpret_cast<AS_LDS const bf16x8*>(xc + wp * K::XROW + (((c8 >> 3) ^ (wp & 15)) << 4));
+        }
+    }
+    barrier_keep_vm<63>();                                 // LDS only
 
     // ------------------------------------------------------------------ conv2
     {
@@ -299,6 +332,10 @@ __global__ __launch_bounds__(K::NT, 1) void stream_bneck_kernel(
             for (int tt = 0; tt < K::MT; ++tt)
               acc[i][tt] = mfma16(w2[tap * K::KS2 + ks][tt], bcur[i][ks], acc[i][tt]);
         __builtin_amdgcn_sched_barrier(0);
+        // (in parts, between the taps: all at once, the requests fill the memory pipeline and the wave stands for 1200 clocks)
+        constexpr int PER = cdiv(K::NXL, 9);
+        if (p + 2 < npat) issue_x(p + 2, min(tap * PER, K::NXL), min((tap + 1) * PER, K::NXL));
+        __builtin_amdgcn_sched_barrier(0);
         if (tap + 1 < 9) {
 #pragma unroll
           for (int i = 0; i < K::RB2; ++i)
@@ -323,20 +360,6 @@ __global__ __launch_bounds__(K::NT, 1) void stream_bneck_kernel(
 
     // ------------------------------------------------------------------ conv3 + residual + store
     {
-      // the residual (the window's own interior) is read ahead of the MFMAs
-      bf16x8 res[K::RB2][K::G3][2];
-#pragma unroll
-      for (int i = 0; i < K::RB2; ++i) {
-        const int q = (wr + K::WR * i) * 16 + l16;
-        const int wp = (q / S + 1) * T + q % S + 1;        // the pixel's own window position
-#pragma unroll
-        for (int gg = 0; gg < K::G3; ++gg)
-#pragma unroll
-          for (int t = 0; t < 2; ++t) {
-            const int c8 = (wc * K::G3 + gg) * 64 + t * 32 + lg * 8;   // 8 consecutive channels (tiles 2t, 2t+1)
-            res[i][gg][t] = *reinterpret_cast<AS_LDS const bf16x8*>(xc + wp * K::XROW + (((c8 >> 3) ^ (wp & 15)) << 4));
-          }
-      }
       floatx4 acc[K::RB2][K::G3][K::NT3];
 #pragma unroll
       for (int i = 0; i < K::RB2; ++i)
@@ -364,6 +387,7 @@ __global__ __launch_bounds__(K::NT, 1) void stream_bneck_kernel(
       // written, then read back and stored, together.
       AS_LDS char* tr = y1s + wave * 4096;
       const int c8l = lane & 7;
+      const bool stores = uni(hdr[p * 4 + 1]) > kNoCell;   // (all or none: own pixels are inside the image)
 #pragma unroll
       for (int i = 0; i < K::RB2; ++i) {
 #pragma unroll
@@ -391,12 +415,14 @@ __global__ __launch_bounds__(K::NT, 1) void stream_bneck_kernel(
             const int pr = half * 8 + (lane >> 3);
             const bf16x8 v = *reinterpret_cast<AS_LDS const bf16x8*>(tr + gg * 2048 + pr * 128 + ((c8l ^ (pr & 7)) << 4));
             const int qq = (wr + K::WR * i) * 16 + pr;
-            const int px = pix[(qq / S + 1) * T + qq % S + 1];   // own pixels are inside the image, unless the entry was invalid
-            if (px >= 0)
+            const int px = pix[(qq / S + 1) * T + qq % S + 1];
+            if (stores)
               __builtin_nontemporal_store(v, reinterpret_cast<AS_GLOBAL bf16x8*>((AS_GLOBAL __bf16*)out + (size_t)px * C + chb + c8l * 8));
           }
         }
       }
+      // (the count at the top takes the stores for granted; where there are none nothing is left in flight)
+      if (!stores) asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
     }
   }
 }
@@ -429,7 +455,8 @@ hipError_t launch_stream(const Geom& g, const void* x, const int32_t* idx, const
   const __bf16* p1 = (const __bf16*)packed;
   const __bf16* p2 = p1 + (size_t)K::M * K::C;
   const __bf16* p3 = p2 + 9 * (size_t)K::M * K::M;
-  hipLaunchKernelGGL(k, dim3(grid), dim3(K::NT), K::LDS_BYTES, st, g, (const __bf16*)x, idx, count, p1, b1,
+  hipLaunchKernelGGL(k, dim3(grid), dim3(K::NT), K::LDS_BYTES, st, g, div31((unsigned)(g.G * g.GW)),
+                     div31((unsigned)g.GW), (const __bf16*)x, idx, count, p1, b1,
                      p2, b2, p3, b3, (__bf16*)out);
   return hipGetLastError();
 }

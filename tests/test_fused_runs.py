@@ -1,4 +1,4 @@
-"""How the fused kernel cuts the list into runs and decodes its cells: every cut gives every listed patch the same bits."""
+"""How the fused and the streaming kernel cut the list into runs and decode its cells: every cut gives every listed patch the same bits."""
 import numpy as np
 import pytest
 import torch
@@ -21,6 +21,7 @@ CASES = [
     (2, 14, 63, 512, 128, 7, (1, 20, 36)),
     (41, 2, 46, 1024, 256, 2, (7, 256, 257, 900)),
     (5, 45, 3, 1024, 256, 1, (64, 600)),
+    (17, 56, 56, 256, 64, 8, (1, 255, 257, 700, 833)),      # (the streaming kernel: runs of one, two and four patches)
 ]
 
 
@@ -39,11 +40,15 @@ def test_every_cut_gives_the_same_bits(N, H, W, C, M, S, counts):
     packed = B.lasnet_pack_weights(S, d["W1"], d["W2"], d["W3"])
     rng = np.random.default_rng(5)
     for count in counts:
-        for order in ("ascending", "shuffled"):
+        for order in ("ascending", "shuffled", "with invalid entries"):
             cells = rng.permutation(cfg.P)[:count].astype(np.int32)
             if order == "ascending":
                 cells.sort()
-            idx, cnt = U.list_tensor(cells, cfg.P), torch.tensor([count], dtype=torch.int32, device="cuda")
+            entries = cells
+            if order == "with invalid entries":              # (the last of a run too)
+                cells = cells[:count - count // 3]
+                entries = rng.permutation(np.concatenate([cells, rng.choice([-1, cfg.P, -(1 << 31), 1 << 30], count // 3)])).astype(np.int32)
+            idx, cnt = U.list_tensor(entries, cfg.P), torch.tensor([count], dtype=torch.int32, device="cuda")
             out = torch.full_like(d["x"], 777.0)
             B.lasnet_sparse_bottleneck_packed(d["x"], idx, cnt, S, M, packed, d["b1"], d["b2"], d["b3"], out=out,
                                               flags=B.LASNET_FORCE_FUSED | B.LASNET_SKIP_IDENTITY)
