@@ -258,7 +258,8 @@ int run_block(const lasnet_tensor* x, const int32_t* idx, const int32_t* count, 
     }
     block_ws = ws + packed_need;
   }
-  if (!dense && idx && !in_place && !(flags & LASNET_SKIP_IDENTITY)) {
+  const bool copy = !dense && idx && !in_place && !(flags & LASNET_SKIP_IDENTITY);
+  if (copy && !rows_ws) {
     e = launch_copy(x->data, out->data, map_bytes, st);
     if (e != hipSuccess) return LASNET_EHIP;
   }
@@ -271,7 +272,7 @@ int run_block(const lasnet_tensor* x, const int32_t* idx, const int32_t* count, 
   else if (fast)
     e = launch_mfma(g, x->data, idx, count, packed, b1, b2, b3, out->data, relu, st);
   else if (rows_ws)
-    e = launch_rows(x->dtype, g, x->data, idx, count, w, out->data, relu, rows_ws, st);
+    e = launch_rows(x->dtype, g, x->data, idx, count, w, out->data, relu, copy, rows_ws, st);
   else
     e = launch_generic(x->dtype, g, x->data, idx, count, w, out->data, relu, st);
   return e == hipSuccess ? LASNET_OK : LASNET_EHIP;

@@ -63,8 +63,10 @@ struct RowsArgs {
   const int32_t* idx;      // nullptr: every cell
   const int32_t* count;
   const uint8_t* need;     // nullptr: every pixel
-  unsigned w1_bytes, w2_bytes, w3_bytes;    // packed
-  RowsWeights w1, w2, w3;
+  unsigned w1_bytes, w2_bytes, w3_bytes;    // as they lie in memory: packed, or in a direct call the caller's
+  RowsWeights w1, w2, w3;                   // (packed)
+  Div31 cpi, gw, s2, s;    // cells per image and per row of cells, S*S, S
+  int conv_blocks;         // conv1 in a direct call: workgroups that are the convolution's; the others copy x to out
 };
 
 // The active list as rows: row r is pixel (r mod S*S) of entry r / (S*S).
@@ -76,12 +78,13 @@ struct RowPixel { int px, h, w; };
 __device__ __forceinline__ RowPixel row_pixel(const RowsArgs& a, int r, int nrows) {
   RowPixel p{-1, 0, 0};
   if (r >= nrows) return p;
-  const int S = a.g.S, s2 = S * S, e = r / s2, q = r - e * s2;
+  const int S = a.g.S, e = div31_by(r, a.s2), q = r - e * (S * S);
   const int cell = a.idx ? a.idx[e] : e;
   if ((unsigned)cell >= (unsigned)a.g.P) return p;
-  const int cpi = a.g.G * a.g.GW, n = cell / cpi, rem = cell - n * cpi, gy = rem / a.g.GW, gx = rem - gy * a.g.GW;
-  p.h = gy * S + q / S;
-  p.w = gx * S + q % S;
+  const int n = div31_by(cell, a.cpi), rem = cell - n * (a.g.G * a.g.GW), gy = div31_by(rem, a.gw), gx = rem - gy * a.g.GW;
+  const int qy = div31_by(q, a.s);
+  p.h = gy * S + qy;
+  p.w = gx * S + q - qy * S;
   const int px = (n * a.g.H + p.h) * a.g.W + p.w;
   if (px >= a.px0 && px < a.px0 + a.npx) p.px = px;
   return p;
@@ -153,22 +156,78 @@ __device__ __forceinline__ void store_y<Bf16Wide>(unsigned char* row, int ch, in
   for (int k = 0; k < 3; ++k) *reinterpret_cast<bf16x8*>(row + (k * ksm * 32 + ch) * 2) = t[k];
 }
 
-// ---- the GEMM of one wave: NB blocks of 16 rows x one group of 32 channels ------------------------------
-// k-steps [s0, s1) of `total`.  Weights: fragments (step, tile) at wbase + step * wstep + tile * KPL KiB.  B rows by `rows`,
-// which yields the byte offset of each row block's lane for the k-step it is advanced to.
-template <class F, int NB, int PL, int D, class Rows>
-__device__ __forceinline__ void rows_gemm(floatx4 (&acc)[NB][2], rows_rsrc_t wrs, unsigned wbase, unsigned wstep, Rows& rows,
-                                          int s0, int s1, int lane) {
-  using Frag = typename F::Frag;
-  using V = typename F::V;
-  Frag a[D][2], b[D][NB][PL];
-  const unsigned lane16 = lane * 16;
-  auto load = [&](int d, int s) {
-    const unsigned so = wbase + (unsigned)s * wstep;
+// ---- weights ------------------------------------------------------------------------------------------
+// One group of 32 output channels (`pair`) of a convolution with nch of them, K channels in per tap and kpt k-steps per tap.
+// Packed by the plan: the fragments of a k-step are consecutive KiB.
+struct plan_weights {
+  static constexpr bool direct = false;
+  rows_rsrc_t rs;
+  unsigned lane16, base, step;
+  template <class F>
+  __device__ __forceinline__ void open(const unsigned char* wp, unsigned bytes, RowsWeights w, int pair, int, int, int, int, int lane) {
+    rs = rows_rsrc(wp, bytes);
+    lane16 = lane * 16;
+    base = pair * w.group;
+    step = w.step;
+  }
+  template <class F>
+  __device__ __forceinline__ void load(typename F::Frag (&a)[2], int s) {
+    const unsigned so = base + (unsigned)s * step;
 #pragma unroll
     for (int j = 0; j < 2; ++j)
 #pragma unroll
-      for (int h = 0; h < F::KPL; ++h) a[d][j].v[h] = rows_load16<V>(wrs, lane16 + (j * F::KPL + h) * 1024, so);
+      for (int h = 0; h < F::KPL; ++h) a[j].v[h] = rows_load16<typename F::V>(rs, lane16 + (j * F::KPL + h) * 1024, so);
+  }
+};
+// The caller's, [nch][taps][K]: a lane reads its 16-byte pieces of its channel's row, zeros past the last channel and past K.
+struct call_weights {
+  static constexpr bool direct = true;
+  rows_rsrc_t rs;
+  unsigned off[2];
+  int K, kpt, lg, at, in_tap, tap;         // (k-steps are asked for in order, as by YRows)
+  template <class F>
+  __device__ __forceinline__ void open(const unsigned char* wp, unsigned bytes, RowsWeights, int pair, int nch, int k, int ksteps, int s0,
+                                       int lane) {
+    rs = rows_rsrc(wp, bytes);
+    K = k;
+    kpt = ksteps;
+    lg = lane >> 4;
+    const unsigned pitch = bytes / (unsigned)nch;
+    const int ch = pair * 32 + ((lane & 15) >> 2) * 8 + (lane & 3);
+#pragma unroll
+    for (int j = 0; j < 2; ++j) off[j] = ch + j * 4 < nch ? (unsigned)(ch + j * 4) * pitch : kOutOfRange;
+    at = s0;
+    tap = s0 / kpt;
+    in_tap = s0 - tap * kpt;
+  }
+  template <class F>
+  __device__ __forceinline__ void load(typename F::Frag (&a)[2], int s) {
+    if (s != at) {
+      at = s;
+      if (++in_tap == kpt) {
+        in_tap = 0;
+        ++tap;
+      }
+    }
+#pragma unroll
+    for (int h = 0; h < F::KPL; ++h) {
+      const int k = in_tap * 32 + h * 16 * (F::KPL - 1) + lg * F::EPP;
+#pragma unroll
+      for (int j = 0; j < 2; ++j)
+        a[j].v[h] = rows_load16<typename F::V>(rs, k < K ? off[j] + (unsigned)(tap * K + k) * F::ES : kOutOfRange, 0);
+    }
+  }
+};
+
+// ---- the GEMM of one wave: NB blocks of 16 rows x one group of 32 channels ------------------------------
+// k-steps [s0, s1).  A fragments by `weights`, B rows by `rows`, which yields the byte offset of each row block's lane for the
+// k-step it is advanced to.
+template <class F, int NB, int PL, int D, class Weights, class Rows>
+__device__ __forceinline__ void rows_gemm(floatx4 (&acc)[NB][2], Weights& weights, Rows& rows, int s0, int s1) {
+  using Frag = typename F::Frag;
+  Frag a[D][2], b[D][NB][PL];
+  auto load = [&](int d, int s) {
+    weights.template load<F>(a[d], s);
     rows.template load<F, NB, PL>(b[d], s);
   };
   auto compute = [&](int d) {
@@ -331,12 +390,72 @@ __device__ __forceinline__ void rows_blocks(int n, Fn&& f) {
   }
 }
 
+// ---- calls with few cells --------------------------------------------------------------------------------
+// What bounds them is their launches, 2 to 5 us each of a chain of dependent kernels.  So the copy of x to out, where there is one, has
+// no launch of its own but a part of the next one's workgroups; and where the weights are small too (direct_is_faster) there is
+// no plan: the convolutions read the caller's weights, and a workgroup of conv1 finds the needed pixels of its own run by
+// going through the list itself.  Call sequences, us: fp32 56x56x256, S=4, r=0.6, one image (copy with the plan) 31.0 -> 29.0; bf16
+// 28x20x192, mid 48, S=4, 13 images (no plan) 30.9 -> 28.4; bf16 20x20x320, mid 80, S=2, one image (neither) 31.6 -> 25.7.
+constexpr int kDirectCells = 512;
+
+// Workgroup `block` of `blocks` that copy the whole map (16-byte pieces).
+template <class F>
+__device__ __forceinline__ void rows_copy(const RowsArgs& a, int block, int blocks, const typename F::T* __restrict__ from,
+                                          typename F::T* __restrict__ to) {
+  const size_t n = (size_t)a.g.N * a.g.H * a.g.W * a.g.C * F::ES / 16, step = (size_t)blocks * kRowsThreads;
+  for (size_t i = (size_t)block * kRowsThreads + threadIdx.x; i < n; i += step)
+    reinterpret_cast<uint4*>(to)[i] = reinterpret_cast<const uint4*>(from)[i];
+}
+// (four pieces per thread, to two workgroups per CU)
+template <class F>
+int rows_copy_blocks(const Geom& g) {
+  const long long blocks = ((long long)g.N * g.H * g.W * g.C * F::ES / 16 + 4 * kRowsThreads - 1) / (4 * kRowsThreads);
+  return (int)(blocks < 512 ? blocks : 512);
+}
+
+// Bit i: pixel p0 + i (i < n <= 64) lies in the window of an entry of the list.  Its entries are read together with the count (the
+// list has storage for every cell).
+__device__ __forceinline__ unsigned long long rows_near(const RowsArgs& a, int p0, int n, ROWS_LDS unsigned* near, int tid) {
+  int cells[kDirectCells / kRowsThreads];
+#pragma unroll
+  for (int u = 0; u < kDirectCells / kRowsThreads; ++u) {
+    const int e = tid + u * kRowsThreads;
+    cells[u] = e < a.g.P ? a.idx[e] : -1;
+  }
+  if (tid < 2) near[tid] = 0;
+  const int nact = rows_uni(*a.count), S = a.g.S, H = a.g.H, W = a.g.W;
+  __syncthreads();
+#pragma unroll
+  for (int u = 0; u < kDirectCells / kRowsThreads; ++u) {
+    const int cell = cells[u];
+    if (tid + u * kRowsThreads >= nact || (unsigned)cell >= (unsigned)a.g.P) continue;
+    const int img = div31_by(cell, a.cpi), rem = cell - img * (a.g.G * a.g.GW), gy = div31_by(rem, a.gw), gx = rem - gy * a.g.GW;
+    const int h0 = max(gy * S - 1, 0), h1 = min(gy * S + S, H - 1), w0 = max(gx * S - 1, 0), w1 = min(gx * S + S, W - 1);
+    const int base = img * H * W - p0;
+    if (base + h1 * W + w1 < 0 || base + h0 * W + w0 >= n) continue;
+    unsigned long long m = 0;
+    for (int h = h0; h <= h1; ++h) {
+      const int first = max(base + h * W + w0, 0), last = min(base + h * W + w1, n - 1);
+      if (first <= last) m |= ((2ull << (last - first)) - 1) << first;
+    }
+    if ((unsigned)m) __hip_atomic_fetch_or(near, (unsigned)m, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+    if (m >> 32) __hip_atomic_fetch_or(near + 1, (unsigned)(m >> 32), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+  }
+  __syncthreads();
+  return near[0] | (unsigned long long)near[1] << 32;
+}
+
 // ---- conv1 -----------------------------------------------------------------------------------------------
-template <class F, bool VEC, int NB, int KS>
+template <class F, bool VEC, int NB, int KS, class Weights>
 __global__ __launch_bounds__(kRowsThreads, 2) void rows_conv1_kernel(RowsArgs a, int nsl, const typename F::T* __restrict__ x,
                                                                      const unsigned char* __restrict__ wp,
                                                                      const float* __restrict__ b1,
-                                                                     unsigned char* __restrict__ y1) {
+                                                                     unsigned char* __restrict__ y1,
+                                                                     typename F::T* __restrict__ copy_to) {
+  if (Weights::direct && (int)blockIdx.x >= a.conv_blocks) {
+    rows_copy<F>(a, (int)blockIdx.x - a.conv_blocks, (int)gridDim.x - a.conv_blocks, x, copy_to);
+    return;
+  }
   __shared__ int rowpx[NB * 16];
   __shared__ __attribute__((aligned(16))) float part[KS > 1 ? 4 * NB * 2 * 64 * 4 : 4];
   const int tid = threadIdx.x, lane = tid & 63, l16 = lane & 15, lg = lane >> 4, wave = rows_uni(tid >> 6);
@@ -345,7 +464,16 @@ __global__ __launch_bounds__(kRowsThreads, 2) void rows_conv1_kernel(RowsArgs a,
   const int p0 = unit * NB * 16;
   // the needed pixels of this run, ascending
   static_assert(NB * 16 <= 64, "one ballot");
-  const bool on = lane < NB * 16 && p0 + lane < a.npx && (!a.need || a.need[p0 + lane] != 0);
+  bool on = lane < NB * 16 && p0 + lane < a.npx;
+  if constexpr (Weights::direct) {
+    __shared__ unsigned near[2];
+    if (a.idx) {
+      const unsigned long long needed = rows_near(a, p0, NB * 16, (ROWS_LDS unsigned*)near, tid);      // (by every thread)
+      on = on && (needed >> lane & 1);
+    }
+  } else {
+    on = on && (!a.need || a.need[p0 + lane] != 0);
+  }
   const unsigned long long b = __ballot(on);
   const int U = __popcll(b);
   if (U == 0) return;                            // uniform over the workgroup
@@ -370,8 +498,11 @@ __global__ __launch_bounds__(kRowsThreads, 2) void rows_conv1_kernel(RowsArgs a,
     for (int pair = slice * WC + wave / KS; pair < (KS > 1 ? (a.pairs1 + WC - 1) / WC * WC : a.pairs1); pair += nsl * WC) {
       floatx4 acc[N][2];
       start_at_bias<N>(acc, b1, a.g.M, rows_channel(pair, lg), wave % KS == 0);
-      if (s0 < s1 && pair < a.pairs1)
-        rows_gemm<F, N, F::XP, 2>(acc, rows_rsrc(wp, a.w1_bytes), pair * a.w1.group, a.w1.step, rows, s0, s1, lane);
+      if (s0 < s1 && pair < a.pairs1) {
+        Weights weights;
+        weights.template open<F>(wp, a.w1_bytes, a.w1, pair, a.g.M, a.g.C, a.ks1, s0, lane);
+        rows_gemm<F, N, F::XP, 2>(acc, weights, rows, s0, s1);
+      }
       reduce_over_waves<N, KS>(acc, (ROWS_LDS float*)part, wave, lane);
 #pragma unroll
       for (int i = 0; i < N; ++i) {
@@ -388,7 +519,7 @@ __global__ __launch_bounds__(kRowsThreads, 2) void rows_conv1_kernel(RowsArgs a,
 }
 
 // ---- conv2 -----------------------------------------------------------------------------------------------
-template <class F, int NB, int KS>
+template <class F, int NB, int KS, class Weights>
 __global__ __launch_bounds__(kRowsThreads, 2) void rows_conv2_kernel(RowsArgs a, int nsl, const unsigned char* __restrict__ wp,
                                                                      const float* __restrict__ b2,
                                                                      const unsigned char* __restrict__ y1,
@@ -423,8 +554,11 @@ __global__ __launch_bounds__(kRowsThreads, 2) void rows_conv2_kernel(RowsArgs a,
     floatx4 acc[NB][2];
     start_at_bias<NB>(acc, b2, a.g.M, rows_channel(pair, lg), wave % KS == 0);
     rows.seek(min(s0, total - 1), NB);
-    if (s0 < s1 && pair < a.pairs1)
-      rows_gemm<F, NB, F::YP, 2>(acc, rows_rsrc(wp, a.w2_bytes), pair * a.w2.group, a.w2.step, rows, s0, s1, lane);
+    if (s0 < s1 && pair < a.pairs1) {
+      Weights weights;
+      weights.template open<F>(wp, a.w2_bytes, a.w2, pair, a.g.M, a.g.M, a.ksm, s0, lane);
+      rows_gemm<F, NB, F::YP, 2>(acc, weights, rows, s0, s1);
+    }
     reduce_over_waves<NB, KS>(acc, (ROWS_LDS float*)part, wave, lane);
 #pragma unroll
     for (int i = 0; i < NB; ++i)
@@ -438,7 +572,7 @@ __global__ __launch_bounds__(kRowsThreads, 2) void rows_conv2_kernel(RowsArgs a,
 }
 
 // ---- conv3 + residual ------------------------------------------------------------------------------------
-template <class F, bool VEC, int NB, int KS>
+template <class F, bool VEC, int NB, int KS, class Weights>
 __global__ __launch_bounds__(kRowsThreads, 2) void rows_conv3_kernel(RowsArgs a, int nsl, const typename F::T* __restrict__ x,
                                                                      const unsigned char* __restrict__ wp,
                                                                      const float* __restrict__ b3,
@@ -471,8 +605,11 @@ __global__ __launch_bounds__(kRowsThreads, 2) void rows_conv3_kernel(RowsArgs a,
     floatx4 acc[NB][2];
     const int ch = rows_channel(pair, lg);
     start_at_bias<NB>(acc, b3, C, ch, wave % KS == 0);
-    if (s0 < s1 && pair < a.pairs3)
-      rows_gemm<F, NB, F::YP, 2>(acc, rows_rsrc(wp, a.w3_bytes), pair * a.w3.group, a.w3.step, rows, s0, s1, lane);
+    if (s0 < s1 && pair < a.pairs3) {
+      Weights weights;
+      weights.template open<F>(wp, a.w3_bytes, a.w3, pair, C, a.g.M, a.ksm, s0, lane);
+      rows_gemm<F, NB, F::YP, 2>(acc, weights, rows, s0, s1);
+    }
     reduce_over_waves<NB, KS>(acc, (ROWS_LDS float*)part, wave, lane);
 #pragma unroll
     for (int i = 0; i < NB; ++i)
@@ -513,10 +650,13 @@ constexpr int kNeedPixels = 16384;                // pixels whose bytes one work
 // 224x224x16, S=1, a list of 1.6 M entries: fp32 12.3 ms by scans, 1.9 ms scattered; bf16 14.9 and 1.8.  3136 cells: 29 and 21 us.)
 constexpr int kScanCells = 1024;
 
-// Blocks [0, pack_blocks): the weight fragments, one 8-element lane share per thread.  The others: the need
-// bytes of kNeedPixels pixels each, by a scan of the list (it may be in any order), or cleared for rows_need_kernel.
+// Blocks [0, pack_blocks): the weight fragments, one 8-element lane share per thread.  The next need_blocks: the need
+// bytes of kNeedPixels pixels each, by a scan of the list (it may be in any order), or cleared for rows_need_kernel.  The others
+// copy x to out.
 template <class F>
-__global__ __launch_bounds__(kRowsThreads) void rows_plan_kernel(RowsArgs a, int pack_blocks, int scan, const typename F::T* __restrict__ W1,
+__global__ __launch_bounds__(kRowsThreads) void rows_plan_kernel(RowsArgs a, int pack_blocks, int need_blocks, int scan,
+                                                                 const typename F::T* __restrict__ x, typename F::T* __restrict__ out,
+                                                                 const typename F::T* __restrict__ W1,
                                                                  const typename F::T* __restrict__ W2,
                                                                  const typename F::T* __restrict__ W3,
                                                                  unsigned char* __restrict__ wp, uint8_t* __restrict__ need) {
@@ -563,6 +703,10 @@ __global__ __launch_bounds__(kRowsThreads) void rows_plan_kernel(RowsArgs a, int
       __builtin_memcpy(&o, v, 16);
       *reinterpret_cast<typename F::V*>(dst + h * 1024) = o;
     }
+    return;
+  }
+  if ((int)blockIdx.x >= pack_blocks + need_blocks) {
+    rows_copy<F>(a, (int)blockIdx.x - pack_blocks - need_blocks, (int)gridDim.x - pack_blocks - need_blocks, x, out);
     return;
   }
   __shared__ __attribute__((aligned(16))) uint8_t flag[kNeedPixels];
@@ -662,28 +806,31 @@ bool rows_layout(const Geom& g, RowsLayout& l) {
   if (c.ks == 4) CALL(1, 4); else if (c.nb == 1) CALL(1, 1); else if (c.nb == 2) CALL(2, 1); else CALL(4, 1);
 
 // The three convolutions of the chunk that `a` describes.
-template <class F, bool VEC>
-hipError_t launch_rows_convs(const RowsArgs& a, int chunk, const void* x, const unsigned char* wp1, const unsigned char* wp2,
+template <class F, bool VEC, class Weights>
+hipError_t launch_rows_convs(RowsArgs a, int chunk, const void* x, const unsigned char* wp1, const unsigned char* wp2,
                              const unsigned char* wp3, const float* b1, const float* b2, const float* b3, unsigned char* y1,
-                             unsigned char* y2, void* out, bool post_relu, hipStream_t st) {
+                             unsigned char* y2, void* out, bool post_relu, bool copy, hipStream_t st) {
   typedef typename F::T T;
   const Geom& g = a.g;
   // the list's rows of this chunk are not known here: half of the pixels is a middling activation ratio
   // (and every chunk is cut like the full one, which rows_layout has checked)
   const long long rows = (long long)g.P * g.S * g.S, likely = a.idx ? (chunk + 1) / 2 : chunk;
   RowsCut c = rows_cut(a.npx, chunk, a.pairs1, a.ks1);
+  long long grid = sliced_grid(c.units, c.nsl);
+  a.conv_blocks = (int)grid;
+  if (Weights::direct && copy) grid += rows_copy_blocks<F>(g);
 #define ROWS_CONV1(NB, KS)                                                                                               \
-  hipLaunchKernelGGL((rows_conv1_kernel<F, VEC, NB, KS>), dim3((unsigned)sliced_grid(c.units, c.nsl)), dim3(kRowsThreads), 0, st, a, \
-                     c.nsl, (const T*)x, wp1, b1, y1)
+  hipLaunchKernelGGL((rows_conv1_kernel<F, VEC, NB, KS, Weights>), dim3((unsigned)grid), dim3(kRowsThreads), 0, st, a, \
+                     c.nsl, (const T*)x, wp1, b1, y1, (T*)out)
   ROWS_DISPATCH(c, ROWS_CONV1)
   c = rows_cut(rows, likely, a.pairs1, 9 * a.ksm);
 #define ROWS_CONV2(NB, KS)                                                                                               \
-  hipLaunchKernelGGL((rows_conv2_kernel<F, NB, KS>), dim3((unsigned)sliced_grid(c.units, c.nsl)), dim3(kRowsThreads), 0, st, a,      \
+  hipLaunchKernelGGL((rows_conv2_kernel<F, NB, KS, Weights>), dim3((unsigned)sliced_grid(c.units, c.nsl)), dim3(kRowsThreads), 0, st, a,      \
                      c.nsl, wp2, b2, y1, y2)
   ROWS_DISPATCH(c, ROWS_CONV2)
   c = rows_cut(rows, likely, a.pairs3, a.ksm);
 #define ROWS_CONV3(NB, KS)                                                                                               \
-  hipLaunchKernelGGL((rows_conv3_kernel<F, VEC, NB, KS>), dim3((unsigned)sliced_grid(c.units, c.nsl)), dim3(kRowsThreads), 0, st, a, \
+  hipLaunchKernelGGL((rows_conv3_kernel<F, VEC, NB, KS, Weights>), dim3((unsigned)sliced_grid(c.units, c.nsl)), dim3(kRowsThreads), 0, st, a, \
                      c.nsl, (const T*)x, wp3, b3, y2, (T*)out, (int)post_relu)
   ROWS_DISPATCH(c, ROWS_CONV3)
 #undef ROWS_CONV1

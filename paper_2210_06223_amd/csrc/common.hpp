@@ -65,9 +65,10 @@ hipError_t launch_generic(int dtype, const Geom& g, const void* x, const int32_t
 
 // The row schedule (bottleneck_rows.hpp): the same function as launch_generic on the matrix cores, through a workspace
 // (256-byte aligned, rows_workspace_bytes(); 0: launch_generic is faster, or the map is beyond what its loads address).
+// copy: out = x first.
 size_t rows_workspace_bytes(int dtype, const Geom& g);
 hipError_t launch_rows(int dtype, const Geom& g, const void* x, const int32_t* idx, const int32_t* count,
-                       const BlockWeights& w, void* out, bool post_relu, void* workspace, hipStream_t st);
+                       const BlockWeights& w, void* out, bool post_relu, bool copy, void* workspace, hipStream_t st);
 
 // The slab schedule (bottleneck_slab.hpp): three launches spread over the chip for a few images of a deep stage.  It reads
 // the same packed weights as the fused and tiled kernels; workspace: 256-byte aligned.

@@ -4,12 +4,31 @@
 namespace lasnet {
 namespace {
 
+// Whether the convolutions read the caller's weights.  Read in their natural layout -- 64-byte pieces of 16 rows, which lie a
+// power of two apart at the usual widths -- they cost more per fragment than packed ones, and a tile's reduction that is long
+// stands for them, so it pays where the fragments that the call reads (every pixel active) are few and short.  Direct / with a plan, us:
+//   bf16 fragments  2k  20x20x320 mid 80 25.7 / 31.6    15k 40x40x384 mid 96 26.5 / 29.0    26k 20 x 35x35x128 mid 32 34.2 / 39.0
+//                  27k  13 x 28x20x192 mid 48 28.4 / 30.9 (r=1 36.6 / 41.0)                 31k 2 x 40x40x384 mid 96, r=1 34.7 / 34.5
+//   fp32            2k  8 x 30x30x64 mid 16 26.3 / 28.4    5k 24x24x384 mid 96 28.0 / 28.0   13k 56x56x256 mid 64, r=1 35.3 / 30.3
+//   (32 to 72 k-steps: fp32 14x14x1024 mid 256 42.3 / 36.4, 2 x 28x28x512 mid 128 36.2 / 32.9)
+template <class F>
+bool direct_is_faster(const Geom& g) {
+  const long long tiles = ((long long)g.N * g.H * g.W + 15) / 16, pairs1 = (g.M + 31) / 32, pairs3 = (g.C + 31) / 32;
+  const long long fragments = tiles * (2 * pairs1 * pairs3 + 9 * pairs1 * pairs1);
+  return g.P <= kDirectCells && pairs1 <= 3 && fragments <= (F::ES == 4 ? 7000 : 28000);
+}
+
 template <class F, bool VEC>
 hipError_t run_rows(const Geom& g, const void* x, const int32_t* idx, const int32_t* count, const BlockWeights& w, void* out,
-                    bool post_relu, void* workspace, hipStream_t st) {
+                    bool post_relu, bool copy, void* workspace, hipStream_t st) {
   typedef typename F::T T;
   RowsLayout l;
   if (!rows_layout<F>(g, l)) return hipErrorInvalidValue;
+  const bool direct = VEC && l.images == g.N && g.M % F::EPP == 0 &&
+                      (((uintptr_t)w.W1 | (uintptr_t)w.W2 | (uintptr_t)w.W3) & 15) == 0 && direct_is_faster<F>(g);
+  const bool rides = copy && VEC && g.P <= kDirectCells;     // the copy is a part of the first launch
+  if (copy && !rides)
+    if (hipError_t e = launch_copy(x, out, (size_t)g.N * g.H * g.W * g.C * F::ES, st); e != hipSuccess) return e;
   unsigned char* wp1 = (unsigned char*)workspace;
   unsigned char* wp2 = wp1 + rows_round(l.w1);
   unsigned char* wp3 = wp2 + rows_round(l.w2);
@@ -30,7 +49,22 @@ hipError_t run_rows(const Geom& g, const void* x, const int32_t* idx, const int3
   a.w1_bytes = (unsigned)l.w1;
   a.w2_bytes = (unsigned)l.w2;
   a.w3_bytes = (unsigned)l.w3;
+  a.cpi = div31((unsigned)(g.G * g.GW));
+  a.gw = div31((unsigned)g.GW);
+  a.s2 = div31((unsigned)(g.S * g.S));
+  a.s = div31((unsigned)g.S);
+  a.conv_blocks = 0;
   const int hw = g.H * g.W;
+  if constexpr (VEC)
+    if (direct) {
+      a.px0 = 0;
+      a.npx = g.N * hw;
+      a.need = nullptr;
+      a.w1_bytes = a.w3_bytes = (unsigned)((size_t)g.M * g.C * F::ES);
+      a.w2_bytes = (unsigned)((size_t)9 * g.M * g.M * F::ES);
+      return launch_rows_convs<F, true, call_weights>(a, a.npx, x, (const unsigned char*)w.W1, (const unsigned char*)w.W2, (const unsigned char*)w.W3,
+                                              w.b1, w.b2, w.b3, y1, y2, out, post_relu, copy, st);
+    }
   for (int n0 = 0; n0 < g.N; n0 += l.images) {
     const int n = g.N - n0 < l.images ? g.N - n0 : l.images;
     a.px0 = n0 * hw;
@@ -38,14 +72,15 @@ hipError_t run_rows(const Geom& g, const void* x, const int32_t* idx, const int3
     const long long fragments = (long long)a.pairs1 * a.ks1 + (long long)a.pairs1 * 9 * a.ksm + (long long)a.pairs3 * a.ksm;
     const int pack_blocks = n0 == 0 ? (int)((fragments * 128 + kRowsThreads - 1) / kRowsThreads) : 0;
     const int need_blocks = idx ? (a.npx + kNeedPixels - 1) / kNeedPixels : 0;
-    if (pack_blocks + need_blocks > 0)
-      hipLaunchKernelGGL(rows_plan_kernel<F>, dim3(pack_blocks + need_blocks), dim3(kRowsThreads), 0, st, a, pack_blocks,
-                         (int)(g.P <= kScanCells), (const T*)w.W1, (const T*)w.W2, (const T*)w.W3, wp1, need);
+    const int copy_blocks = rides && n0 == 0 ? rows_copy_blocks<F>(g) : 0;
+    if (pack_blocks + need_blocks + copy_blocks > 0)
+      hipLaunchKernelGGL(rows_plan_kernel<F>, dim3(pack_blocks + need_blocks + copy_blocks), dim3(kRowsThreads), 0, st, a, pack_blocks,
+                         need_blocks, (int)(g.P <= kScanCells), (const T*)x, (T*)out, (const T*)w.W1, (const T*)w.W2, (const T*)w.W3, wp1, need);
     if (idx && g.P > kScanCells) {
       const long long blocks = ((long long)g.P * (g.S + 2) + kRowsThreads - 1) / kRowsThreads;
       hipLaunchKernelGGL(rows_need_kernel, dim3((unsigned)(blocks < 4096 ? blocks : 4096)), dim3(kRowsThreads), 0, st, a, need);
     }
-    if (hipError_t e = launch_rows_convs<F, VEC>(a, l.images * hw, x, wp1, wp2, wp3, w.b1, w.b2, w.b3, y1, y2, out, post_relu, st); e != hipSuccess)
+    if (hipError_t e = launch_rows_convs<F, VEC, plan_weights>(a, l.images * hw, x, wp1, wp2, wp3, w.b1, w.b2, w.b3, y1, y2, out, post_relu, false, st); e != hipSuccess)
       return e;
   }
   return hipSuccess;
@@ -75,15 +110,15 @@ size_t rows_workspace_bytes(int dtype, const Geom& g) {
 }
 
 hipError_t launch_rows(int dtype, const Geom& g, const void* x, const int32_t* idx, const int32_t* count,
-                       const BlockWeights& w, void* out, bool post_relu, void* workspace, hipStream_t st) {
+                       const BlockWeights& w, void* out, bool post_relu, bool copy, void* workspace, hipStream_t st) {
   if (g.P == 0) return hipSuccess;
   const uintptr_t low = (uintptr_t)x | (uintptr_t)out;
   if (dtype == LASNET_BF16) {
-    if (low % 16 == 0 && g.C % 8 == 0) return run_rows<Bf16Wide, true>(g, x, idx, count, w, out, post_relu, workspace, st);
-    return run_rows<Bf16Wide, false>(g, x, idx, count, w, out, post_relu, workspace, st);
+    if (low % 16 == 0 && g.C % 8 == 0) return run_rows<Bf16Wide, true>(g, x, idx, count, w, out, post_relu, copy, workspace, st);
+    return run_rows<Bf16Wide, false>(g, x, idx, count, w, out, post_relu, copy, workspace, st);
   }
-  if (low % 16 == 0 && g.C % 4 == 0) return run_rows<Fp32, true>(g, x, idx, count, w, out, post_relu, workspace, st);
-  return run_rows<Fp32, false>(g, x, idx, count, w, out, post_relu, workspace, st);
+  if (low % 16 == 0 && g.C % 4 == 0) return run_rows<Fp32, true>(g, x, idx, count, w, out, post_relu, copy, workspace, st);
+  return run_rows<Fp32, false>(g, x, idx, count, w, out, post_relu, copy, workspace, st);
 }
 
 }  // namespace lasnet
