@@ -760,19 +760,30 @@ inline size_t rows_round(size_t v) { return (v + 255) / 256 * 256; }
 
 // How a convolution is cut: NB row blocks per wave, KS waves to a tile's reduction, nsl channel slices per row tile.
 // 1024 waves are one per SIMD.  More rows per wave read the weights less often, so NB is as large as leaves the chip
-// that many tiles; with fewer even at NB = 1 the waves of a workgroup share a tile's reduction.
+// that many tiles (NB = 2: `two`); with fewer even at NB = 1 the waves of a workgroup share a tile's reduction.
 struct RowsCut { int nb, ks, units, nsl; };
-inline RowsCut rows_cut(long long rows_max, long long rows_expected, int pairs, int ksteps) {
+inline RowsCut rows_cut(long long rows_max, long long rows_expected, int pairs, int ksteps, long long two = 1024) {
   RowsCut c;
   c.nb = 4;
-  while (c.nb > 1 && (rows_expected + 16 * c.nb - 1) / (16 * c.nb) * pairs < 1024) c.nb /= 2;
+  while (c.nb > 1 && (rows_expected + 16 * c.nb - 1) / (16 * c.nb) * pairs < (c.nb == 2 ? two : 1024)) c.nb /= 2;
   const long long tiles = (rows_expected + 16 * c.nb - 1) / (16 * c.nb);
-  c.ks = tiles * pairs < 1024 && ksteps >= 8 ? 4 : 1;
+  c.ks = c.nb == 1 && tiles * pairs < 1024 && ksteps >= 8 ? 4 : 1;
   c.units = (int)((rows_max + 16 * c.nb - 1) / (16 * c.nb));
   const int wc = 4 / c.ks, most = (pairs + wc - 1) / wc;
   c.nsl = (int)((1024 + tiles - 1) / tiles);
   if (c.nsl > most) c.nsl = most;
   return c;
+}
+
+// conv1, whose rows are known.  1200 to 2047 waves of one row block take as long as half as many of two -- some SIMDs have two of the former --
+// but load 6 KiB per 16 MFMAs instead of 8 per 32: 48 bytes per clock of a CU's L1, near its 64, against 32.  It shows where the
+// reduction is long.  Call sequences, fp32, r=0.5 if not noted, one block / two, us: 14x14x1024, S=2: 13 images 79.5 / 76.3,
+// 16 85.8 / 81.9, 16 at r=1 120.3 / 116.5, 20 at r=0.4 85.6 / 82.0; 7x7x2048: 28 images 135.0 / 127.8, 38 at r=0.8 179.6 / 172.5.  (conv2 and
+// conv3, whose rows are a guess: 14x14x1024, 40 images, r=0.6 177.6 / 186.0; more than one workgroup per CU, of four groups of channels each:
+// bf16 14x14x1024, mid 288, 16 images, r=0.9 93.4 / 99.4.)
+inline RowsCut rows_cut_conv1(long long pixels, long long chunk, int pairs, int ksteps) {
+  const bool one_round = (chunk + 31) / 32 * ((pairs + 3) / 4) <= 256;
+  return rows_cut(pixels, chunk, pairs, ksteps, ksteps >= 32 && one_round ? 600 : 1024);
 }
 
 // false: even one image does not fit (or exceeds the 32-bit offsets of the loads), or a launch would have 2^32 threads.
@@ -791,7 +802,7 @@ bool rows_layout(const Geom& g, RowsLayout& l) {
   if (n == 0) return false;
   l.images = (int)n;
   const long long all = (long long)g.P * g.S * g.S, chunk = (long long)(n * hw);
-  for (const RowsCut& c : {rows_cut(chunk, chunk, (int)pairs1, (int)ks1), rows_cut(all, (chunk + 1) / 2, (int)pairs1, 9 * (int)ksm),
+  for (const RowsCut& c : {rows_cut_conv1(chunk, chunk, (int)pairs1, (int)ks1), rows_cut(all, (chunk + 1) / 2, (int)pairs1, 9 * (int)ksm),
                            rows_cut(all, chunk, (int)pairs1, 9 * (int)ksm), rows_cut(all, (chunk + 1) / 2, (int)pairs3, (int)ksm),
                            rows_cut(all, chunk, (int)pairs3, (int)ksm)})
     if (sliced_grid(c.units, c.nsl) * kRowsThreads >= 1ll << 32) return false;
@@ -815,7 +826,7 @@ hipError_t launch_rows_convs(RowsArgs a, int chunk, const void* x, const unsigne
   // the list's rows of this chunk are not known here: half of the pixels is a middling activation ratio
   // (and every chunk is cut like the full one, which rows_layout has checked)
   const long long rows = (long long)g.P * g.S * g.S, likely = a.idx ? (chunk + 1) / 2 : chunk;
-  RowsCut c = rows_cut(a.npx, chunk, a.pairs1, a.ks1);
+  RowsCut c = rows_cut_conv1(a.npx, chunk, a.pairs1, a.ks1);
   long long grid = sliced_grid(c.units, c.nsl);
   a.conv_blocks = (int)grid;
   if (Weights::direct && copy) grid += rows_copy_blocks<F>(g);
