@@ -28,9 +28,10 @@ FLAGS = [
 
 
 # The k-loops of the matrix-core kernels must be unrolled in full (their register rings are indexed
-# by the loop counter; a ring that is not unrolled lands in scratch memory).  The long reductions of
-# the tiled kernels exceed the compiler's default size limit for `#pragma unroll`.
-PER_FILE_FLAGS = {"tiled_stages.hip": ["-mllvm", "-pragma-unroll-threshold=1048576"]}
+# by the loop counter, and the counts of their barriers are worked out from it: a loop that is not unrolled
+# keeps its ring in scratch memory and picks each count at run time).  The long reductions of the tiled
+# kernels and of the fused kernel at 2048 channels exceed the compiler's default size limit for `#pragma unroll`.
+PER_FILE_FLAGS = {f: ["-mllvm", "-pragma-unroll-threshold=1048576"] for f in ("tiled_stages.hip", "mfma_stage4.hip")}
 
 
 def hipcc() -> str:
