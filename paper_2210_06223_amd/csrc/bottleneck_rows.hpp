@@ -406,11 +406,13 @@ __device__ __forceinline__ void rows_copy(const RowsArgs& a, int block, int bloc
   for (size_t i = (size_t)block * kRowsThreads + threadIdx.x; i < n; i += step)
     reinterpret_cast<uint4*>(to)[i] = reinterpret_cast<const uint4*>(from)[i];
 }
-// (four pieces per thread, to two workgroups per CU)
+// (four pieces per thread, to four workgroups per CU.  Up to 512 / 1024 / 2048 workgroups, a launch of its own, us: fp32 128 images of
+// 14x14x2048, mid 64, S=7 264.2 / 254.4 / 263.8, 259.3; 14x14x4096 492.9 / 471.6 / 497.5, 488.1; 32 of 112x112x256, mid 24, S=28
+// 555.9 / 535.6 / 563.2, 584.2; maps to 50 MB the same with any of the three, 2 to 18 % slower with a launch of its own.)
 template <class F>
 int rows_copy_blocks(const Geom& g) {
   const long long blocks = ((long long)g.N * g.H * g.W * g.C * F::ES / 16 + 4 * kRowsThreads - 1) / (4 * kRowsThreads);
-  return (int)(blocks < 512 ? blocks : 512);
+  return (int)(blocks < 1024 ? blocks : 1024);
 }
 
 // Bit i: pixel p0 + i (i < n <= 64) lies in the window of an entry of the list.  Its entries are read together with the count (the

@@ -37,6 +37,15 @@ def test_routes():
             assert names[1] == plan + convs, (shape, dtype, names[1])
 
 
+def test_workgroups_of_the_copy():
+    """(Host only.)  Four pieces of 16 bytes per thread, up to 1024 workgroups, whichever launch the copy is a part of."""
+    maps = [((1, 8, 8, 64, 32, 1), 1), ((1, 56, 56, 256, 64, 4), 196), ((32, 14, 14, 1024, 256, 7), 1024),
+            ((128, 14, 14, 2048, 64, 7), 1024), ((32, 112, 112, 96, 24, 28), 1024)]
+    got = H.run("result = [[[int(e[2]) for e in call('ex', F32, *a, flags=f)[1] if e[0] == 'launch'] for f in (0, 4)] for a in %r]" % [m[0] for m in maps])
+    for (shape, copy), (with_copy, without) in zip(maps, got):
+        assert [a - b for a, b in zip(with_copy, without)] == [copy] + [0] * (len(without) - 1), (shape, with_copy, without)
+
+
 @pytest.mark.gpu
 @pytest.mark.parametrize("dtype", ["f32", "bf16"])
 @pytest.mark.parametrize("shape", [r[0] for r in ROUTES], ids=lambda s: "x".join(map(str, s)))
