@@ -22,6 +22,7 @@ CASES = [
     (41, 2, 46, 1024, 256, 2, (7, 256, 257, 900)),
     (5, 45, 3, 1024, 256, 1, (64, 600)),
     (17, 56, 56, 256, 64, 8, (1, 255, 257, 700, 833)),      # (the streaming kernel: runs of one, two and four patches)
+    (4, 25, 42, 2048, 512, 1, (1, 257, 2560, 4096)),        # (conv1 of 32 chunks)
 ]
 
 
@@ -58,3 +59,34 @@ def test_every_cut_gives_the_same_bits(N, H, W, C, M, S, counts):
             got = U.bits(out)
             assert np.array_equal(got[up], want[up]), (count, order)
             assert (got[~up] == untouched).all(), (count, order)
+
+
+@pytest.mark.parametrize("N,H,W,C,M,S,counts", CASES[-2:], ids=lambda v: "-".join(map(str, v)) if isinstance(v, tuple) else str(v))
+def test_counted_waits_against_drained_barriers(monkeypatch, N, H, W, C, M, S, counts):
+    """Bit for bit as the build whose barriers wait for everything: runs of several patches (the streaming kernel's windows are requested
+    two patches ahead, and what its stores leave in flight is counted), with entries inside them that store nothing; and every
+    number of row blocks that conv1 of 32 chunks has."""
+    from paper_2210_06223_amd import build
+    check = B.load_library(build.LIB_CHECK)
+    cfg = synth.BlockConfig("counts", N, H, W, C, M, S, "bf16", 1.0, 56)
+    d = U.dev_inputs(synth.make_block_inputs(cfg, want_f64=False))
+    packed = B.lasnet_pack_weights(S, d["W1"], d["W2"], d["W3"])
+    rng = np.random.default_rng(6)
+    lists = [np.sort(rng.permutation(cfg.P)[:n]) for n in counts]
+    if C == 2048:                                            # runs of 1 to 16 cells anywhere: 9 to 96 rows
+        lists = [rng.permutation(cfg.P)[:256 * n] for n in (1, 2, 3, 4, 5, 7, 9, 10, 11, 16)]
+    for cells in lists:
+        for invalid in (False, True):
+            entries = cells.astype(np.int32)
+            if invalid:
+                entries[rng.random(len(entries)) < 0.3] = cfg.P
+            idx, cnt = U.list_tensor(entries, cfg.P), torch.tensor([len(entries)], dtype=torch.int32, device="cuda")
+            outs = []
+            for library in (B.lib(), check):
+                monkeypatch.setattr(B, "_lib", library)
+                out = torch.full_like(d["x"], 777.0)
+                B.lasnet_sparse_bottleneck_packed(d["x"], idx, cnt, S, M, packed, d["b1"], d["b2"], d["b3"], out=out,
+                                                  flags=B.LASNET_FORCE_FUSED | B.LASNET_SKIP_IDENTITY)
+                outs.append(U.bits(out))
+                monkeypatch.undo()
+            assert np.array_equal(*outs), (len(entries), invalid)
