@@ -73,19 +73,21 @@ def fused_runs(nact: int, P: int, PPW: int, slots: int) -> List[Tuple[int, int]]
     grid = -(-P // PPW)
     grid = min(-(-grid // slots) * slots, P)
     nt = min(nt, grid, nact)
+    if nt == 0:
+        return []
+    q, rem = divmod(nact, nt)                                   # run t of the list has q entries, the first `rem` runs one more
     out = []
     for b in range(nt):
-        q = b // slots * slots                                  # the round: its part of the list, the last part first
-        nr, hi = min(slots, nt - q), nact - q * nact // nt
-        lo = nact - (q + nr) * nact // nt
-        xcd, jx = (b - q) & 7, (b - q) >> 3
+        r0 = b // slots * slots                                 # the round: its part of the list, the last part first
+        nr = min(slots, nt - r0)
+        t0 = nt - r0 - nr
+        longer = min(t0 + nr, rem) - min(t0, rem)
+        xcd, jx = (b - r0) & 7, (b - r0) >> 3
         first = xcd * (nr >> 3) + min(xcd, nr & 7)
-        runs = (nr >> 3) + (1 if xcd < (nr & 7) else 0)
-        xb, xe = lo + first * (hi - lo) // nr, lo + (first + runs) * (hi - lo) // nr
-        len0 = (xe - xb) // runs
-        extra = (xe - xb) - len0 * runs
-        tb = xb + jx * len0 + min(jx, extra)
-        out.append((tb, tb + len0 + (1 if jx < extra else 0)))
+        first_longer = xcd * (longer >> 3) + min(xcd, longer & 7)
+        extra = (longer >> 3) + (1 if xcd < (longer & 7) else 0)
+        tb = t0 * q + min(t0, rem) + (first + jx) * q + first_longer + min(jx, extra)
+        out.append((tb, tb + q + (1 if jx < extra else 0)))
     return out
 
 

@@ -35,6 +35,23 @@ def test_runs_of_several_rounds_cover_the_list_once():
         assert max(b - a for a, b in spans) <= PPW and min(b - a for a, b in spans) >= 1, (nact, P)
 
 
+def test_runs_are_dealt_to_the_xcds_as_the_kernel_does():
+    """The list's first runs are the longer ones; a round's share of them is spread over the 8 XCDs, whose runs are neighbours."""
+    for nact, P, PPW, slots in ((50176, 50176, 4, 512), (20071, 50176, 4, 512), (3236, 6272, 32, 256), (1025, 1027, 1, 512), (6271, 6272, 16, 256)):
+        spans = LM.fused_runs(nact, P, PPW, slots)
+        nt, q = len(spans), nact // len(spans)
+        for r0 in range(0, nt, slots):
+            part = spans[r0:r0 + slots]
+            t0 = nt - r0 - len(part)                               # the round's first run in the list
+            longer = min(t0 + len(part), nact - q * nt) - min(t0, nact - q * nt)
+            assert part[0][0] == t0 * q + min(t0, nact - q * nt)
+            for k in range(8):
+                mine = part[k::8]
+                n = longer // 8 + (k < longer % 8)
+                assert [b - a for a, b in mine] == [q + 1] * n + [q] * (len(mine) - n), (nact, r0, k)
+                assert [a for a, _ in mine[1:]] == [b for _, b in mine[:-1]]
+
+
 def test_window_pixels_counts():
     assert len(LM.window_pixels([(0, 0, 0)], 2, 14, 14)) == 9          # corner patch: 3 x 3 in the image
     assert len(LM.window_pixels([(0, 3, 3)], 2, 14, 14)) == 16         # interior: 4 x 4
