@@ -47,7 +47,7 @@ constexpr int kRowBits = 10;
 
 // C, M, S: block shape.  PPW: patches per batch (max).  R1MAX: rows of y1 kept in LDS (unique
 // window pixels of a batch; a batch is cut short if it would need more).  NSTG: LDS stages of
-// the x stream (KC channels each; x chunks are in flight NSTG-1 chunks ahead).  WRi x WCi:
+// the x stream (KC channels each; x chunks are in flight NSTG chunks ahead).  WRi x WCi:
 // wave grid of conv i.  RD2/RD3: k-steps of weights a wave keeps in flight in conv2/conv3.
 // NB3: channel tiles per conv3 pass.
 template <int C_, int M_, int S_, int PPW_, int R1MAX_, int NW_, int KC_, int NSTG_, int WR1_,
@@ -302,7 +302,7 @@ __device__ __forceinline__ bf16x8 buf_load16(rsrc_t r, int lane_bytes, int unifo
 
 // ---- phase 1: conv1 over the NB1*16 rows of unique window pixels -------------------------
 // x reaches LDS by direct global->LDS loads (16 bytes per lane, a wave fills 8 rows x 128 B;
-// the lane picks the global chunk whose swizzled position it writes), three stages deep;
+// the lane picks the global chunk whose swizzled position it writes), NSTG stages deep;
 // the weights of the next two chunks are always in flight in registers.
 // The weight ring of conv1: WD chunks of KS k-steps, NBW1 fragments each.
 template <class K>

@@ -3,6 +3,8 @@
 //
 //   plan   (a) the weights -> MFMA A-fragments in the order a wave reads them, zero-padded to whole fragments
 //          (b) one byte per pixel: does some active patch's (S+2)x(S+2) window hold it
+//          (calls with few cells and small weights have none, direct_is_faster: the convolutions read the caller's weights, and
+//          conv1 finds its needed pixels in the list; with few cells the copy of x to out is a part of the first launch)
 //   conv1  rows = the needed pixels of a run of consecutive pixels           y1[pixel] = ReLU(b1 + W1 x)
 //   conv2  rows = the list's pixels, S*S per entry, in the list's order      y2[pixel] = ReLU(b2 + W2 * y1 around it)
 //   conv3  the same rows                                                     out[pixel] = x + b3 + W3 y2
@@ -16,8 +18,8 @@
 // added in a fixed order through LDS); else they take four neighbouring groups of 32 channels (KS = 1).
 //
 // Measured, whole call sequence (masker, list, block) against the scalar one-kernel path: fp32 56x56x256, S=4, r=0.6, one
-// image 672 -> 35 us; fp32 14x14x1024, S=2, r=0.5, 16 images 7900 -> 87 us (conv1 28, conv2 30, conv3 17 us: 50 TFLOP/s
-// of the 154 that a large fp32 matrix product reaches); bf16 28x20x192, mid 48, S=4, 13 images 371 -> 36 us.
+// image 672 -> 29 us; fp32 14x14x1024, S=2, r=0.5, 16 images 7900 -> 82 us (conv1 24, conv2 31, conv3 17 us: 63 TFLOP/s
+// of the 154 that a large fp32 matrix product reaches); bf16 28x20x192, mid 48, S=4, 13 images 371 -> 28 us.
 //
 // Number formats (products and sums are never narrower than fp32, and nothing is rounded between the convolutions):
 //   Fp32     v_mfma_f32_16x16x4_f32 throughout
@@ -778,11 +780,14 @@ inline RowsCut rows_cut(long long rows_max, long long rows_expected, int pairs, 
 }
 
 // conv1, whose rows are known.  1200 to 2047 waves of one row block take as long as half as many of two -- some SIMDs have two of the former --
-// but load 6 KiB per 16 MFMAs instead of 8 per 32: 48 bytes per clock of a CU's L1, near its 64, against 32.  It shows where the
-// reduction is long.  Call sequences, fp32, r=0.5 if not noted, one block / two, us: 14x14x1024, S=2: 13 images 79.5 / 76.3,
-// 16 85.8 / 81.9, 16 at r=1 120.3 / 116.5, 20 at r=0.4 85.6 / 82.0; 7x7x2048: 28 images 135.0 / 127.8, 38 at r=0.8 179.6 / 172.5.  (conv2 and
-// conv3, whose rows are a guess: 14x14x1024, 40 images, r=0.6 177.6 / 186.0; more than one workgroup per CU, of four groups of channels each:
-// bf16 14x14x1024, mid 288, 16 images, r=0.9 93.4 / 99.4.)
+// but (fp32) load 6 KiB per 16 MFMAs instead of 8 per 32: 48 bytes per clock of a CU's L1, near its 64, against 32.  It shows where the
+// reduction is long.  Call sequences, r=0.5 if not noted, one block / two, us.  Above the line: fp32 14x14x1024, S=2: 13 images 79.4 / 75.8,
+// 16 85.9 / 82.2, 16 at r=1 120.3 / 116.5, 20 87.6 / 83.9; 7x7x2048: 28 images 136.0 / 128.7, 38 147.9 / 140.6; bf16 14x14x1024, mid 160, 20
+// images 52.6 / 50.8, mid 200, 17 images 57.2 / 55.4, mid 224, 16 images 57.2 / 55.6.  Below it, down to 544 tiles, two are still faster: fp32
+// 14x14x1024, 11 images 78.7 / 75.0, 7x7x2048, 24 images 134.8 / 127.2, bf16 mid 200, 13 images 56.2 / 54.8; under 512 one is: 10 images
+// 58.2 / 63.4, 7x7x2048, 20 images 89.6 / 101.3, bf16 mid 160, 12 images 41.7 / 45.9.  16 k-steps: fp32 28x28x512, S=4: 8 images
+// 56.6 / 54.9, 5 41.2 / 43.2.  (conv2 and conv3, whose rows are a guess: 14x14x1024, 40 images, r=0.6 177.6 / 186.0; more than one workgroup per
+// CU, of four groups of channels each: bf16 14x14x1024, mid 288, 16 images, r=0.9 93.4 / 99.4.)
 inline RowsCut rows_cut_conv1(long long pixels, long long chunk, int pairs, int ksteps) {
   const bool one_round = (chunk + 31) / 32 * ((pairs + 3) / 4) <= 256;
   return rows_cut(pixels, chunk, pairs, ksteps, ksteps >= 32 && one_round ? 600 : 1024);

@@ -27,8 +27,9 @@ struct BlockWeights {
   const void* W3; const float* b3;
 };
 
-// n / d for 0 <= n < 2^31 by a multiplication: floor(n * m / 2^(31 + l)) with l = ceil(log2 d) and m = floor(2^(31 + l) / d) + 1, which
-// exceeds 2^(31 + l) / d by at most 2^l / d of itself, too little to matter below 2^31 (d = 1 has no such m: m = 0).
+// n / d for 0 <= n < 2^31 by a multiplication: floor(n * m / 2^(31 + l)) with l = ceil(log2 d) and m = floor(2^(31 + l) / d) + 1. m
+// exceeds 2^(31 + l) / d by at most 1, so n * m / 2^(31 + l) exceeds n / d by at most n / 2^(31 + l) < 2^-l <= 1 / d: not enough to
+// reach the next whole number (d = 1 has no 32-bit m: m = 0).
 struct Div31 { unsigned m, s; };
 inline Div31 div31(unsigned d) {
   if (d <= 1) return Div31{0, 0};

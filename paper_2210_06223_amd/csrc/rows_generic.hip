@@ -7,9 +7,12 @@ namespace {
 // Whether the convolutions read the caller's weights.  Read in their natural layout -- 64-byte pieces of 16 rows, which lie a
 // power of two apart at the usual widths -- they cost more per fragment than packed ones, and a tile's reduction that is long
 // stands for them, so it pays where the fragments that the call reads (every pixel active) are few and short.  Direct / with a plan, us:
-//   bf16 fragments  2k  20x20x320 mid 80 25.7 / 31.6    15k 40x40x384 mid 96 26.5 / 29.0    26k 20 x 35x35x128 mid 32 34.2 / 39.0
-//                  27k  13 x 28x20x192 mid 48 28.4 / 30.9 (r=1 36.6 / 41.0)                 31k 2 x 40x40x384 mid 96, r=1 34.7 / 34.5
-//   fp32            2k  8 x 30x30x64 mid 16 26.3 / 28.4    5k 24x24x384 mid 96 28.0 / 28.0   13k 56x56x256 mid 64, r=1 35.3 / 30.3
+//   bf16 fragments  2k  20x20x320 mid 80 25.7 / 31.6          15k 40x40x384 mid 96 26.4 / 30.2 (r=1 27.0 / 30.3)
+//                  27k  13 x 28x20x192 mid 48 28.1 / 30.9 (r=1 36.8 / 40.9)
+//           beyond 29k  14 x 28x20x192 28.4 / 31.2 (r=1 37.0 / 41.1)                  31k 2 x 40x40x384, r=0.6 28.9 / 30.4, r=1 33.0 / 32.1
+//                  46k  3 x 40x40x384, r=0.3 30.0 / 30.3, r=0.6 35.0 / 33.6, r=1 40.1 / 39.4
+//   fp32            2k  8 x 30x30x64 mid 16 26.4 / 29.5          5k 24x24x384 mid 96 28.0 / 29.6 (r=1 27.6 / 29.7)
+//           beyond 10k  2 x 24x24x384 28.3 / 29.6 (r=1 28.0 / 29.7)                   13k 56x56x256 mid 64, r=1 35.3 / 30.3
 //   (32 to 72 k-steps: fp32 14x14x1024 mid 256 42.3 / 36.4, 2 x 28x28x512 mid 128 36.2 / 32.9)
 template <class F>
 bool direct_is_faster(const Geom& g) {
