@@ -904,7 +904,7 @@ __global__ __launch_bounds__(K::NT, K::WAVES_PER_SIMD) void fused_bneck_kernel(
     // dependent steps -- count, entries, claims, barrier -- so there is one pass and one barrier, and cells are decoded with
     // multiplications.  (A pass to claim, one to number the rows and one to look them up, with divisions: 10.2k clocks to conv1
     // and 6.1k more to its first chunk at 14x14x1024, S=2, batch 128; so 4.7k and 4.2k.  The block 46.6 -> 42.9 us, of one
-    // region per image at 28x28x512, S=4, batch 128, 51.5 -> 48.8, at 56x56x256, S=4, batch 256 136 -> 130.)
+    // region per image at 28x28x512, S=4, batch 128, 51.5 -> 48.8.)
     constexpr int NU = cdiv(K::PPW * WW, K::NT);
     int npb = min(te - e0, K::PPW);                        // patches in this batch
     int U;                                                 // unique window pixels = y1 rows

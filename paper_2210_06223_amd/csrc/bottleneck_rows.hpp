@@ -18,7 +18,7 @@
 // added in a fixed order through LDS); else they take four neighbouring groups of 32 channels (KS = 1).
 //
 // Measured, whole call sequence (masker, list, block) against the scalar one-kernel path: fp32 56x56x256, S=4, r=0.6, one
-// image 672 -> 29 us; fp32 14x14x1024, S=2, r=0.5, 16 images 7900 -> 82 us (conv1 24, conv2 31, conv3 17 us: 63 TFLOP/s
+// image 672 -> 29 us; fp32 14x14x1024, S=2, r=0.5, 16 images 7900 -> 82 us (conv1 23, conv2 29, conv3 17 us: 63 TFLOP/s
 // of the 154 that a large fp32 matrix product reaches); bf16 28x20x192, mid 48, S=4, 13 images 371 -> 28 us.
 //
 // Number formats (products and sums are never narrower than fp32, and nothing is rounded between the convolutions):
