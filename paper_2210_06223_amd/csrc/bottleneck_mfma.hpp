@@ -116,6 +116,16 @@ struct Cfg {
   // Waves a SIMD holds when the CU is full of these workgroups: the register budget per wave
   // is 512 / that (a 4-wave workgroup alone on its CU may use the accumulation registers too).
   static constexpr int WAVES_PER_SIMD = cmax(1, ((160 * 1024) / LDS_BYTES) * NW / 4);
+  // Lists of at most CUs * ONE2 / 2 patches are cut into one run per CU, not one per place of a workgroup: a CU then streams the
+  // weights once, and that stream, with the batch's chain of latencies, is what bounds a launch in which no place gets a second
+  // batch.  Small patches: up to what the y1 rows hold whatever the windows share (a batch that is cut streams them twice after all: 73x104x512,
+  // S=1, r=0.77, 23 patches per run 23.8 / 28.1); S=4: up to 2.5 patches; where the weights are small (56x56x256), S=2: up to 2.
+  // Block alone, one run per place / per CU, us, iid: 28x28x512 (0.56 MB of weights), S=4: 2 images of 100x168, r=0.2 15.4 / 13.3, r=0.3 (2.5
+  // per CU) 16.2 / 14.7, r=0.36 16.7 / 19.3; 1 of 72x104, r=0.9 15.5 / 13.0; S=2: 16 images, r=0.5 16.2 / 13.4, 72x104, r=0.9 (6.6 per CU)
+  // 16.3 / 15.4; S=1: 73x104, r=0.1 12.1 / 9.7, r=0.4 (12 per CU) 15.6 / 13.6.  56x56x256 (0.14 MB): S=1, r=0.6 6.5 / 6.0, 2 images,
+  // r=0.6 (15 per CU) 7.1 / 7.2; S=2, 2 images, r=0.3 6.1 / 5.5, r=0.6 6.6 / 6.6; S=4 7.0 / 7.3.
+  static constexpr int ONE2 = M == 128 ? (S <= 2 ? 2 * (R1MAX / WW) : S == 4 ? 5 : 0) : M == 64 ? (S == 1 ? 2 * (R1MAX / WW) : S == 2 ? 4 : 0) : 0;
+  static_assert(ONE2 <= 2 * PPW, "a run of such a list is one batch");
   static_assert(NW * 2048 <= R1MAX * LDY * 2, "conv3's per-wave transpose areas sit in the y1 rows below the zero row");
 };
 
@@ -809,10 +819,11 @@ __device__ LASNET_PHASE_INLINE void conv3_core(Conv3Ring<K>& ring, g_bf16_p x, g
 }
 
 struct FusedDivs { Div31 cpi, gw, slots; };                // cells per image, cells per row of cells, tile_slots
+struct OnePerCu { int most, runs; };                       // lists of up to `most` entries are cut into `runs` (Cfg::ONE2)
 
 template <class K>
 __global__ __launch_bounds__(K::NT, K::WAVES_PER_SIMD) void fused_bneck_kernel(
-    Geom g, FusedDivs dv, int tile_slots, const __bf16* __restrict__ x, const int32_t* __restrict__ idx,
+    Geom g, FusedDivs dv, OnePerCu one, int tile_slots, const __bf16* __restrict__ x, const int32_t* __restrict__ idx,
     const int32_t* __restrict__ count, const __bf16* __restrict__ W1,
     const float* __restrict__ b1, const __bf16* __restrict__ W2, const float* __restrict__ b2,
     const __bf16* __restrict__ W3, const float* __restrict__ b3, __bf16* __restrict__ out,
@@ -857,11 +868,11 @@ __global__ __launch_bounds__(K::NT, K::WAVES_PER_SIMD) void fused_bneck_kernel(
   // ---- which entries of the index list are this workgroup's ------------------------------
   // The list is cut into `nt` near-equal runs, nt = the number of PPW-sized tiles rounded up
   // to a multiple of `tile_slots` (workgroups the chip holds at once), so that every round
-  // of workgroups is full whatever the count turns out to be.
+  // of workgroups is full whatever the count turns out to be.  A short list is cut into one run per CU (Cfg::ONE2).
   const int nact = uni(idx ? min(*count, g.P) : g.P);
   if (nact <= 0) return;
   int nt = (nact + K::PPW - 1) / K::PPW;
-  nt = div31_by(nt + tile_slots - 1, dv.slots) * tile_slots;
+  nt = nact <= one.most ? one.runs : div31_by(nt + tile_slots - 1, dv.slots) * tile_slots;
   nt = min(min(nt, (int)gridDim.x), nact);
   if ((int)blockIdx.x >= nt) return;                       // uniform over the workgroup
   // Workgroup b runs on XCD b % 8 (round-robin dispatch), and each XCD has its own L2.  Runs
@@ -1088,7 +1099,7 @@ hipError_t launch_one(const Geom& g, const void* x, const int32_t* idx, const in
   auto k = fused_bneck_kernel<K>;
   if (hipError_t e = prepare_one<K>(); e != hipSuccess) return e;
   // the list is cut for two workgroups per CU also where three fit (tiles for three: 5 % slower at 56x56x256)
-  const int fit = (160 * 1024) / K::LDS_BYTES, slots = device_cu_count() * (fit > 2 ? 2 : fit);
+  const int fit = (160 * 1024) / K::LDS_BYTES, cus = device_cu_count(), slots = cus * (fit > 2 ? 2 : fit);
   int grid = (g.P + K::PPW - 1) / K::PPW;
   grid = (grid + slots - 1) / slots * slots;
   if (grid > g.P) grid = g.P;
@@ -1096,8 +1107,8 @@ hipError_t launch_one(const Geom& g, const void* x, const int32_t* idx, const in
   const __bf16* p2 = p1 + (size_t)K::M * K::C;
   const __bf16* p3 = p2 + 9 * (size_t)K::M * K::M;
   const FusedDivs dv{div31((unsigned)(g.G * g.GW)), div31((unsigned)g.GW), div31((unsigned)slots)};
-  hipLaunchKernelGGL(k, dim3(grid), dim3(K::NT), K::LDS_BYTES, st, g, dv, slots, (const __bf16*)x, idx,
-                     count, p1, b1, p2, b2, p3, b3, (__bf16*)out, (int)post_relu);
+  hipLaunchKernelGGL(k, dim3(grid), dim3(K::NT), K::LDS_BYTES, st, g, dv, OnePerCu{cus * K::ONE2 / 2, cus}, slots,
+                     (const __bf16*)x, idx, count, p1, b1, p2, b2, p3, b3, (__bf16*)out, (int)post_relu);
   return hipGetLastError();
 }
 

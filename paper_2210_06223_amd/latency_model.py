@@ -36,10 +36,11 @@ import numpy as np
 N_CU = 256
 
 # Integer parameters of the kernels' configurations (mirrors csrc/mfma_stage*.hip and tiled_stages.hip):
-# (C, M, S) -> patches per batch, y1 rows per batch, workgroups per CU.
+# (C, M, S) -> patches per batch, y1 rows per batch, workgroups per CU, half the patches per CU up to which a list is cut
+# into one run per CU.
 FUSED = {
     (256, 64, 8): dict(kind="stream"),
-    (512, 128, 4): dict(kind="fused", PPW=4, R1MAX=112, wg_per_cu=2),
+    (512, 128, 4): dict(kind="fused", PPW=4, R1MAX=112, wg_per_cu=2, one2=5),
     (1024, 256, 2): dict(kind="fused", PPW=32, R1MAX=160, wg_per_cu=1),
     (2048, 512, 1): dict(kind="fused", PPW=16, R1MAX=96, wg_per_cu=1),
 }
@@ -66,10 +67,11 @@ def window_pixels(cells: Iterable[Tuple[int, int, int]], S: int, H: int, W: int)
     return out
 
 
-def fused_runs(nact: int, P: int, PPW: int, slots: int) -> List[Tuple[int, int]]:
-    """Per workgroup of fused_bneck_kernel, in launch order, its run of the list (first entry, one past the last)."""
+def fused_runs(nact: int, P: int, PPW: int, slots: int, one: int = 0) -> List[Tuple[int, int]]:
+    """Per workgroup of fused_bneck_kernel, in launch order, its run of the list (first entry, one past the last).
+    one: the most entries for which there is one run per CU."""
     nt = -(-nact // PPW)
-    nt = -(-nt // slots) * slots
+    nt = N_CU if nact <= one else -(-nt // slots) * slots
     grid = -(-P // PPW)
     grid = min(-(-grid // slots) * slots, P)
     nt = min(nt, grid, nact)
@@ -104,7 +106,7 @@ def simulate_fused(idx: np.ndarray, N: int, H: int, W: int, C: int, M: int, S: i
     n, gy, gx = _cells(idx, G, GW)
     cells = list(zip(n.tolist(), gy.tolist(), gx.tolist()))
     wgs = []
-    for tb, te in fused_runs(nact, N * G * GW, PPW, slots):
+    for tb, te in fused_runs(nact, N * G * GW, PPW, slots, N_CU * p.get("one2", 0) // 2):
         batches = []
         e0 = tb
         while e0 < te:

@@ -52,6 +52,13 @@ def test_runs_are_dealt_to_the_xcds_as_the_kernel_does():
                 assert [a for a, _ in mine[1:]] == [b for _, b in mine[:-1]]
 
 
+def test_short_lists_have_one_run_per_cu():
+    for nact, runs in ((1, 1), (255, 255), (300, 256), (640, 256), (641, 512)):
+        spans = LM.fused_runs(nact, 2100, 4, 512, 640)
+        assert len(spans) == runs and sorted(i for a, b in spans for i in range(a, b)) == list(range(nact)), nact
+        assert max(b - a for a, b in spans) <= 4
+
+
 def test_window_pixels_counts():
     assert len(LM.window_pixels([(0, 0, 0)], 2, 14, 14)) == 9          # corner patch: 3 x 3 in the image
     assert len(LM.window_pixels([(0, 3, 3)], 2, 14, 14)) == 16         # interior: 4 x 4
