@@ -221,11 +221,21 @@ struct call_weights {
   }
 };
 
+// Calls f(integral_constant<n>) for the run-time n in [LO, HI].
+template <int LO, int HI, class Fn>
+__device__ __forceinline__ void rows_count(int n, Fn&& f) {
+  if constexpr (LO == HI) f(std::integral_constant<int, LO>{});
+  else if (n == LO) f(std::integral_constant<int, LO>{});
+  else rows_count<LO + 1, HI>(n, static_cast<Fn&&>(f));
+}
+
 // ---- the GEMM of one wave: NB blocks of 16 rows x one group of 32 channels ------------------------------
 // k-steps [s0, s1).  A fragments by `weights`, B rows by `rows`, which yields the byte offset of each row block's lane for the
-// k-step it is advanced to.
-template <class F, int NB, int PL, int D, class Weights, class Rows>
-__device__ __forceinline__ void rows_gemm(floatx4 (&acc)[NB][2], Weights& weights, Rows& rows, int s0, int s1) {
+// k-step it is advanced to.  `meanwhile` runs once the first loads have gone out: what it requests is waited for with them, or after.
+struct RowsNothing { __device__ __forceinline__ void operator()() const {} };
+template <class F, int NB, int PL, int D, class Weights, class Rows, class Meanwhile = RowsNothing>
+__device__ __forceinline__ void rows_gemm(floatx4 (&acc)[NB][2], Weights& weights, Rows& rows, int s0, int s1,
+                                          Meanwhile meanwhile = Meanwhile{}) {
   using Frag = typename F::Frag;
   Frag a[D][2], b[D][NB][PL];
   auto load = [&](int d, int s) {
@@ -244,20 +254,72 @@ __device__ __forceinline__ void rows_gemm(floatx4 (&acc)[NB][2], Weights& weight
 #pragma unroll
             for (int j = 0; j < 2; ++j) F::mma(acc[i][j], a[d][j], b[d][i][p], h, e);
   };
+  if constexpr (NB == 4) {
+    // (256 registers do not hold four blocks beside the ends below: past the end the last step is requested again, unused)
 #pragma unroll
-  for (int d = 0; d < D; ++d) load(d, min(s0 + d, s1 - 1));
+    for (int d = 0; d < D; ++d) load(d, min(s0 + d, s1 - 1));
+    meanwhile();
+    int s = s0;
+    for (; s + D <= s1; s += D) {
+#pragma unroll
+      for (int d = 0; d < D; ++d) {
+        compute(d);
+        load(d, min(s + D + d, s1 - 1));
+        __builtin_amdgcn_sched_barrier(0);
+      }
+    }
+#pragma unroll
+    for (int d = 0; d < D - 1; ++d)
+      if (s + d < s1) compute(d);
+    return;
+  }
+  // Nothing is requested past the end (a CU's L1 is near its rate, and what is loaded to fill a round up delays what follows it): the
+  // steady loop leaves 1 to 2D-1 k-steps, whose number is a constant in each of as many straight-line ends.  Against a ring that is
+  // filled up with repeats of the last step (2 of 10 k-steps where four waves share 36), call sequences, us: bf16 28x20x192, mid 48, S=4, 13 images
+  // 29.6 -> 27.0, r=1 38.3 -> 33.3; fp32 56x56x256, S=4, 4 images 46.3 -> 43.3; 14x14x1024, S=2, 16 images 82.8 -> 79.7; 28x28x512, S=4,
+  // r=0.9, 16 images 115.5 -> 112.1.  (Rings 3 and 4 deep: the same to 3 us slower.)
   int s = s0;
-  for (; s + D <= s1; s += D) {
+  auto end = [&](auto left) {
+    constexpr int L = decltype(left)::value;
+    if constexpr (L < D) {                       // (the whole reduction: nothing has been requested yet)
 #pragma unroll
-    for (int d = 0; d < D; ++d) {
-      compute(d);
-      load(d, min(s + D + d, s1 - 1));           // (past the end the last step again: not used)
+      for (int d = 0; d < L; ++d) {
+        load(d, s + d);
+        __builtin_amdgcn_sched_barrier(0);
+      }
+      meanwhile();
       __builtin_amdgcn_sched_barrier(0);
     }
-  }
 #pragma unroll
-  for (int d = 0; d < D - 1; ++d)
-    if (s + d < s1) compute(d);
+    for (int d = 0; d < (L < D ? L : D); ++d) {
+      compute(d);
+      if (d < L - D) load(d, s + D + d);
+      __builtin_amdgcn_sched_barrier(0);
+    }
+#pragma unroll
+    for (int d = 0; d < L - D; ++d) {
+      compute(d);
+      __builtin_amdgcn_sched_barrier(0);
+    }
+  };
+  if (s1 - s0 >= D) {
+#pragma unroll
+    for (int d = 0; d < D; ++d) {
+      load(d, s + d);
+      __builtin_amdgcn_sched_barrier(0);         // (in the loop's order: what it waits for is counted)
+    }
+    meanwhile();
+    __builtin_amdgcn_sched_barrier(0);
+    for (; s + 2 * D <= s1; s += D) {
+#pragma unroll
+      for (int d = 0; d < D; ++d) {
+        compute(d);
+        load(d, s + D + d);
+        __builtin_amdgcn_sched_barrier(0);
+      }
+    }
+  }
+  rows_count<1, 2 * D - 1>(s1 - s, end);
 }
 
 // B rows of conv1: pixels of x.  VEC: 16-byte pieces (C and the pointers allow them), else element by element; the
@@ -348,7 +410,7 @@ __device__ __forceinline__ void start_at_bias(floatx4 (&acc)[NB][2], const float
   for (int j = 0; j < 2; ++j)
 #pragma unroll
     for (int v = 0; v < 4; ++v) {
-      const float b = mine ? __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(rs, (ch + j * 4 + v) * 4, 0, 0)) : 0.f;
+      const float b = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(rs, mine ? (ch + j * 4 + v) * 4 : (int)kOutOfRange, 0, 0));
 #pragma unroll
       for (int i = 0; i < NB; ++i) acc[i][j][v] = b;
     }
@@ -451,7 +513,7 @@ __device__ __forceinline__ unsigned long long rows_near(const RowsArgs& a, int p
 
 // ---- conv1 -----------------------------------------------------------------------------------------------
 template <class F, bool VEC, int NB, int KS, class Weights>
-__global__ __launch_bounds__(kRowsThreads, 2) void rows_conv1_kernel(RowsArgs a, int nsl, const typename F::T* __restrict__ x,
+__global__ __launch_bounds__(kRowsThreads, VEC && NB == 4 ? 3 : 2) void rows_conv1_kernel(RowsArgs a, int nsl, const typename F::T* __restrict__ x,
                                                                      const unsigned char* __restrict__ wp,
                                                                      const float* __restrict__ b1,
                                                                      unsigned char* __restrict__ y1,
@@ -609,10 +671,28 @@ __global__ __launch_bounds__(kRowsThreads, 2) void rows_conv3_kernel(RowsArgs a,
     floatx4 acc[NB][2];
     const int ch = rows_channel(pair, lg);
     start_at_bias<NB>(acc, b3, C, ch, wave % KS == 0);
+    // The residual of the row blocks that this wave will store, requested behind the first k-steps (four blocks have no registers
+    // for it): after the reduction it would be one more access to memory in the chain.
+    typedef T Piece __attribute__((ext_vector_type(16 / F::ES)));
+    constexpr int E = 16 / F::ES;
+    constexpr bool EARLY = VEC && NB <= 2;
+    Piece res[NB][8 / E];
+    const auto request = [&] {
+      if constexpr (EARLY) {
+#pragma unroll
+        for (int i = 0; i < NB; ++i)
+#pragma unroll
+          for (int q = 0; q < 8 / E; ++q)        // (rows and channels that do not exist read x's first, unused)
+            if (KS == 1 || i % KS == wave % KS)
+              res[i][q] = reinterpret_cast<const Piece*>(x + (px[i] >= 0 && ch + q * E < C ? (size_t)px[i] * C + ch : 0))[px[i] >= 0 && ch + q * E < C ? q : 0];
+      }
+    };
     if (s0 < s1 && pair < a.pairs3) {
       Weights weights;
       weights.template open<F>(wp, a.w3_bytes, a.w3, pair, C, a.g.M, a.ksm, s0, lane);
-      rows_gemm<F, NB, F::YP, 2>(acc, weights, rows, s0, s1);
+      rows_gemm<F, NB, F::YP, 2>(acc, weights, rows, s0, s1, request);
+    } else {
+      request();
     }
     reduce_over_waves<NB, KS>(acc, (ROWS_LDS float*)part, wave, lane);
 #pragma unroll
@@ -627,12 +707,12 @@ __global__ __launch_bounds__(kRowsThreads, 2) void rows_conv3_kernel(RowsArgs a,
           else return __builtin_bit_cast(uint16_t, (__bf16)r);
         };
         if constexpr (VEC) {                     // (C is then a whole number of the lane's 16-byte pieces)
-          typedef T Piece __attribute__((ext_vector_type(16 / F::ES)));
-          constexpr int E = 16 / F::ES;
 #pragma unroll
           for (int q = 0; q < 8 / E; ++q)
             if (q == 0 || ch + q * E < C) {
-              const Piece xv = reinterpret_cast<const Piece*>(xp)[q];
+              Piece xv;
+              if constexpr (EARLY) xv = res[i][q];
+              else xv = reinterpret_cast<const Piece*>(xp)[q];
               Piece o;
 #pragma unroll
               for (int u = 0; u < E; ++u) o[u] = result(q * E + u, xv[u]);
