@@ -106,7 +106,7 @@ def main():
         print("bench.py: no GPU visible; the HIP path has no CPU fallback", file=sys.stderr)
         sys.exit(2)
     from paper_2210_06223_amd import build as _build
-    if not os.path.exists(_build.LIB):            # a tree that was never built: build it, then load it
+    if not (os.path.exists(_build.LIB) and os.path.exists(_build.MARSHAL)):      # a tree that was never built: build it, then load it
         _build.build_all(verbose=False)
     B.lib()  # fail loudly if the library cannot be loaded
     dev = torch.device("cuda:0")

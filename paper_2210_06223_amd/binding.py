@@ -15,6 +15,7 @@ import torch
 _LIB_PATH = os.environ.get("LASNET_LIBRARY") or os.path.join(
     os.path.dirname(os.path.abspath(__file__)), "liblasnet.so")
 _lib = None
+_marshal = None
 
 LASNET_F32, LASNET_BF16 = 0, 1
 LASNET_POST_RELU, LASNET_FORCE_GENERIC, LASNET_SKIP_IDENTITY, LASNET_FORCE_FUSED, LASNET_FORCE_TILED = 1, 2, 4, 8, 16
@@ -50,6 +51,7 @@ def load_library(path: str) -> ctypes.CDLL:
         raise RuntimeError(
             "liblasnet.so is not built (%s missing): run `python -m paper_2210_06223_amd.build`; "
             "there is no CPU fallback" % path)
+    _load_marshal()
     L = ctypes.CDLL(path)
     vp, ip, tp = ctypes.c_void_p, ctypes.c_int, ctypes.POINTER(lasnet_tensor)
     L.lasnet_version.restype = ip
@@ -91,7 +93,22 @@ def load_library(path: str) -> ctypes.CDLL:
     L.lasnet_sparse_bottleneck_packed.restype = ip
     L.lasnet_sparse_bottleneck_packed.argtypes = [tp, vp, vp, ip, ip, vp, vp, vp, vp, tp,
                                                   ctypes.c_uint32, vp]
+    # the entry points that _marshal calls, by address
+    L.at_masker_ex, L.at_ex, L.at_dense, L.at_packed, L.at_planned, L.at_packed_bytes = (
+        ctypes.cast(f, vp).value for f in (L.lasnet_masker_ex, L.lasnet_sparse_bottleneck_ex, L.lasnet_dense_bottleneck,
+                                           L.lasnet_sparse_bottleneck_packed, L.lasnet_sparse_bottleneck_planned,
+                                           L.lasnet_packed_weights_bytes))
     return L
+
+
+def _load_marshal() -> None:
+    global _marshal
+    if _marshal is None:
+        try:
+            from . import _marshal as m
+        except ImportError as e:
+            raise RuntimeError("the binding's marshalling (_marshal.so) is not built: run `python -m paper_2210_06223_amd.build`") from e
+        _marshal = m
 
 
 def lib() -> ctypes.CDLL:
@@ -102,9 +119,13 @@ def lib() -> ctypes.CDLL:
     return _lib
 
 
-# Host time per call matters at a few images, where a block's kernels take 20 us: addresses go to ctypes as plain
-# integers (argtypes makes them pointers), and the current stream's handle is read without building a
-# torch.cuda.Stream object (3.0 -> 0.2 us).  masker_ex + packed block: 25.4 -> 18.0 us, of which 10 are the launches.
+# Host time per call matters at a few images, where a block's kernels take 20 us.  A call whose arguments are all there and of the
+# plain form (tensors as the checks below ask for, on the current stream) is marshalled natively (csrc/marshal.cpp); it
+# answers None for any other, which then goes through the checks, conversions and ctypes call below.  There addresses go to
+# ctypes as plain integers (argtypes makes them pointers), and the current stream's handle is read without building a
+# torch.cuda.Stream object (3.0 -> 0.2 us).  masker_ex + packed block, one
+# 14x14x1024 image: 25.4 us without any of it, 24.2 with ctypes and integers, 16.3 marshalled natively, of which the five launches
+# take 16.
 def _ptr(t: Optional[torch.Tensor]) -> Optional[int]:
     return None if t is None else t.data_ptr()
 
@@ -154,6 +175,12 @@ def lasnet_masker(x: torch.Tensor, Wm: torch.Tensor, bm: float, S: int, thr: flo
                   count: Optional[torch.Tensor] = None, stream=None
                   ) -> Tuple[torch.Tensor, torch.Tensor, torch.Tensor]:
     """mask uint8 [N,G,GW], idx int32 [N*G*GW] (first count valid), count int32 [1]; all on device."""
+    if stream is None:
+        L = lib()
+        st = _marshal.masker_ex(L.at_masker_ex, x, Wm, bm, S, thr, mask, idx, count, None)
+        if st is not None:
+            _check(st, "lasnet_masker")
+            return mask, idx, count
     d = _as_tensor_desc(x)
     N, H, W, _ = x.shape
     if S <= 0 or H % S or W % S:
@@ -176,6 +203,12 @@ def lasnet_masker_ex(x: torch.Tensor, Wm: torch.Tensor, bm: float, S: int, thr: 
                      count: Optional[torch.Tensor] = None, pass_out: Optional[torch.Tensor] = None,
                      stream=None) -> Tuple[torch.Tensor, torch.Tensor, torch.Tensor]:
     """lasnet_masker that also copies every inactive cell of x to pass_out (may be None)."""
+    if stream is None:
+        L = lib()
+        st = _marshal.masker_ex(L.at_masker_ex, x, Wm, bm, S, thr, mask, idx, count, pass_out)
+        if st is not None:
+            _check(st, "lasnet_masker_ex")
+            return mask, idx, count
     d = _as_tensor_desc(x)
     N, H, W, _ = x.shape
     if S <= 0 or H % S or W % S:
@@ -242,6 +275,12 @@ def lasnet_sparse_bottleneck(x: torch.Tensor, idx: Optional[torch.Tensor],
                              count: Optional[torch.Tensor], S: int, W1, b1, W2, b2, W3, b3,
                              out: Optional[torch.Tensor] = None, flags: int = 0,
                              stream=None) -> torch.Tensor:
+    if stream is None:
+        L = lib()
+        st = _marshal.block_ex(L.at_ex, x, idx, count, S, W1, b1, W2, b2, W3, b3, out, flags)
+        if st is not None:
+            _check(st, "lasnet_sparse_bottleneck")
+            return out
     d = _as_tensor_desc(x)
     if out is None:
         out = torch.empty_like(x)
@@ -270,6 +309,12 @@ def lasnet_sparse_bottleneck_planned(x: torch.Tensor, idx: Optional[torch.Tensor
                                      packed: torch.Tensor, b1, b2, b3, out: torch.Tensor,
                                      workspace: Optional[torch.Tensor], flags: int = 0, stream=None) -> torch.Tensor:
     """The explicit form: packed weights, workspace (a uint8 device tensor or None) and out are the caller's."""
+    if stream is None:
+        L = lib()
+        st = _marshal.block_planned(L.at_planned, x, idx, count, mask, S, M, packed, b1, b2, b3, out, workspace, flags)
+        if st is not None:
+            _check(st, "lasnet_sparse_bottleneck_planned")
+            return out
     d = _as_tensor_desc(x)
     o = _as_tensor_desc(out)
     _check_list(d, idx, count, int(S))
@@ -304,6 +349,12 @@ def lasnet_sparse_bottleneck_noalloc(x: torch.Tensor, idx: Optional[torch.Tensor
 def lasnet_dense_bottleneck(x: torch.Tensor, W1, b1, W2, b2, W3, b3,
                             out: Optional[torch.Tensor] = None, flags: int = 0,
                             stream=None) -> torch.Tensor:
+    if stream is None:
+        L = lib()
+        st = _marshal.block_dense(L.at_dense, x, W1, b1, W2, b2, W3, b3, out, flags)
+        if st is not None:
+            _check(st, "lasnet_dense_bottleneck")
+            return out
     d = _as_tensor_desc(x)
     if out is None:
         out = torch.empty_like(x)
@@ -342,6 +393,12 @@ def lasnet_sparse_bottleneck_packed(x: torch.Tensor, idx: Optional[torch.Tensor]
                                     packed: torch.Tensor, b1, b2, b3,
                                     out: Optional[torch.Tensor] = None, flags: int = 0,
                                     stream=None) -> torch.Tensor:
+    if stream is None:
+        L = lib()
+        st = _marshal.block_packed(L.at_packed, x, idx, count, S, M, packed, L.at_packed_bytes, b1, b2, b3, out, flags)
+        if st is not None:
+            _check(st, "lasnet_sparse_bottleneck_packed")
+            return out
     d = _as_tensor_desc(x)
     if out is None:
         out = torch.empty_like(x)

@@ -15,6 +15,8 @@ LIB = os.path.join(PKG, "liblasnet.so")
 # for all outstanding memory operations.  Only the tests load it (to compare the two bit for bit).
 LIB_CHECK = os.path.join(PKG, "liblasnet_check.so")
 CHECK_FLAGS = ("-DLASNET_DRAIN_AT_BARRIERS",)
+# The binding's native argument marshalling: host code against torch's headers, no HIP in it.
+MARSHAL = os.path.join(PKG, "_marshal.so")
 SOURCES = ["tiled_stages.hip", "mfma_stage3.hip", "mfma_stage2.hip", "mfma_stage1.hip", "mfma_stage4.hip",   # slowest first
            "rows_generic.hip", "slab_stages.hip",
            "api.hip", "masker.hip", "bottleneck_generic.hip", "bottleneck_mfma.hip", "microbench.hip"]
@@ -85,9 +87,31 @@ def build_library(verbose: bool = True, extra_flags=(), out: str = LIB, build_di
     return out
 
 
+def build_marshal(verbose: bool = True) -> str:
+    import sysconfig
+    import torch
+    inc, lib = (os.path.join(os.path.dirname(torch.__file__), d) for d in ("include", "lib"))
+    tmp = MARSHAL + ".tmp"
+    cmd = ["g++", "-O2", "-std=c++17", "-fPIC", "-shared", "-fvisibility=hidden",
+           "-D_GLIBCXX_USE_CXX11_ABI=%d" % torch._C._GLIBCXX_USE_CXX11_ABI,
+           "-I" + inc, "-I" + os.path.join(inc, "torch", "csrc", "api", "include"), "-I" + sysconfig.get_paths()["include"],
+           "-I" + os.path.join(ROOT, "include"), os.path.join(CSRC, "marshal.cpp"), "-o", tmp,
+           "-L" + lib, "-Wl,-rpath," + lib, "-ltorch_python", "-ltorch_cpu", "-lc10"]
+    r = subprocess.run(cmd, capture_output=True, text=True)
+    if r.returncode != 0:
+        raise RuntimeError("g++ failed on marshal.cpp:\n" + r.stderr)
+    os.replace(tmp, MARSHAL)
+    if verbose:
+        print("built", MARSHAL)
+    return MARSHAL
+
+
 def build_all(verbose: bool = True) -> None:
-    build_variants([(LIB, os.path.join(PKG, "_build"), ()),
-                    (LIB_CHECK, os.path.join(PKG, "_build", "check"), CHECK_FLAGS)], verbose)
+    with ThreadPoolExecutor(max_workers=1) as ex:
+        marshal = ex.submit(build_marshal, verbose)
+        build_variants([(LIB, os.path.join(PKG, "_build"), ()),
+                        (LIB_CHECK, os.path.join(PKG, "_build", "check"), CHECK_FLAGS)], verbose)
+        marshal.result()
 
 
 if __name__ == "__main__":

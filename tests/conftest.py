@@ -13,7 +13,7 @@ def pytest_configure(config):
     # The tests load the library that is built in-tree; only where there is none (a fresh checkout) do
     # they build it first (hipcc cross-compiles for gfx950 without a GPU).
     from paper_2210_06223_amd import build
-    if not (os.path.exists(build.LIB) and os.path.exists(build.LIB_CHECK)):
+    if not all(os.path.exists(f) for f in (build.LIB, build.LIB_CHECK, build.MARSHAL)):
         build.build_all(verbose=False)
 
 
