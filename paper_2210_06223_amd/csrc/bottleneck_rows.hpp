@@ -11,15 +11,15 @@
 //
 // What bounds it: the matrix cores at batch size (fp32: 256 FLOP per clock and CU), launches and load latency
 // at a few images.  So the work is cut fine -- a wave computes NB blocks of 16 pixels times 32 output channels,
-// and nothing but the four waves of a workgroup has to meet -- and both operands come straight from memory
-// into registers, D k-steps ahead: a 32-deep fp32 k-step is 8 MFMAs of 32 clocks per 16x16 tile, so even with
-// no reuse through LDS a CU asks its L1 for less than half of the 64 bytes a clock it delivers.  When the
+// and nothing but the four waves of a workgroup has to meet -- and a wave loads both operands for itself, D
+// k-steps ahead, the weights into registers and the rows through LDS of its own: a 32-deep fp32 k-step is 8 MFMAs of 32 clocks per
+// 16x16 tile, so even with no reuse between the waves a CU asks its L1 for less than half of the 64 bytes a clock it delivers.  When the
 // rows are too few to fill the chip the four waves share one tile and split its reduction (KS = 4, partial sums
 // added in a fixed order through LDS); else they take four neighbouring groups of 32 channels (KS = 1).
 //
 // Measured, whole call sequence (masker, list, block) against the scalar one-kernel path: fp32 56x56x256, S=4, r=0.6, one
-// image 672 -> 29 us; fp32 14x14x1024, S=2, r=0.5, 16 images 7900 -> 82 us (conv1 23, conv2 29, conv3 17 us: 63 TFLOP/s
-// of the 154 that a large fp32 matrix product reaches); bf16 28x20x192, mid 48, S=4, 13 images 371 -> 28 us.
+// image 672 -> 25 us; fp32 14x14x1024, S=2, r=0.5, 16 images 7900 -> 74 us (conv1 20, conv2 24, conv3 15 us: 71 TFLOP/s
+// of the 154 that a large fp32 matrix product reaches); bf16 28x20x192, mid 48, S=4, 13 images 371 -> 24 us.
 //
 // Number formats (products and sums are never narrower than fp32, and nothing is rounded between the convolutions):
 //   Fp32     v_mfma_f32_16x16x4_f32 throughout
@@ -75,14 +75,17 @@ struct RowsArgs {
 __device__ __forceinline__ int rows_active(const RowsArgs& a) {
   return rows_uni(a.idx ? max(min(*a.count, a.g.P), 0) : a.g.P) * (a.g.S * a.g.S);     // (P * S * S < 2^31)
 }
-// Its pixel, or -1: past the end of the list, not a cell of the map, or not of this chunk.
+// Its pixel, or -1: past the end of the list, not a cell of the map, or not of this chunk.  The entry is read beside the count, not after
+// it (row_cell comes before rows_active; the list has storage for every cell of the map).
 struct RowPixel { int px, h, w; };
-__device__ __forceinline__ RowPixel row_pixel(const RowsArgs& a, int r, int nrows) {
+__device__ __forceinline__ int row_cell(const RowsArgs& a, int r) {
+  const int e = div31_by(r, a.s2);
+  return e < a.g.P ? (a.idx ? a.idx[e] : e) : -1;
+}
+__device__ __forceinline__ RowPixel row_pixel(const RowsArgs& a, int cell, int r, int nrows) {
   RowPixel p{-1, 0, 0};
-  if (r >= nrows) return p;
-  const int S = a.g.S, e = div31_by(r, a.s2), q = r - e * (S * S);
-  const int cell = a.idx ? a.idx[e] : e;
-  if ((unsigned)cell >= (unsigned)a.g.P) return p;
+  if (r >= nrows || (unsigned)cell >= (unsigned)a.g.P) return p;
+  const int S = a.g.S, q = r - div31_by(r, a.s2) * (S * S);
   const int n = div31_by(cell, a.cpi), rem = cell - n * (a.g.G * a.g.GW), gy = div31_by(rem, a.gw), gx = rem - gy * a.g.GW;
   const int qy = div31_by(q, a.s);
   p.h = gy * S + qy;
@@ -221,6 +224,14 @@ struct call_weights {
   }
 };
 
+// Calls f(integral_constant<j>) for j = 0 .. N-1.
+template <int N, int J = 0, class Fn>
+__device__ __forceinline__ void rows_each(Fn&& f) {
+  if constexpr (J < N) {
+    f(std::integral_constant<int, J>{});
+    rows_each<N, J + 1>(static_cast<Fn&&>(f));
+  }
+}
 // Calls f(integral_constant<n>) for the run-time n in [LO, HI].
 template <int LO, int HI, class Fn>
 __device__ __forceinline__ void rows_count(int n, Fn&& f) {
@@ -229,20 +240,88 @@ __device__ __forceinline__ void rows_count(int n, Fn&& f) {
   else rows_count<LO + 1, HI>(n, static_cast<Fn&&>(f));
 }
 
+// ---- the wave's ring of rows ------------------------------------------------------------------------------
+// A wave's B rows come through LDS of its own: the next D k-steps are on their way by direct loads that nobody but the wave waits for.
+// What it saves is lookups: a CU's L1 takes the addresses of four lanes at a time, and in a fragment's lanes (lane % 16 the row) those are
+// four rows', so a load of 1 KiB costs 64 lookups.  Here four lanes in a row load one row's 64 bytes: 16 lookups, as for the weights, and
+// the fragment's lanes find their pieces in LDS.  (fp32, per k-step and wave, one row block: 192 of them against 512 clocks of MFMAs,
+and there are four waves to a CU's L1; now 96.)  Four row blocks have no room for it, and lose least: they read straight into registers.
+// Piece lg of row i lies at place i*4 + (lg ^ i/4): the 16 rows that are read together are in different banks.
+// Call sequences, rows straight into registers / through LDS, us: fp32 14x14x1024, S=2, 16 images, r=0.1 55.4 / 54.8, r=0.5 79.4 / 74.2, r=0.9
+// 100.9 / 91.0, static block 107.5 / 97.3; 28x28x512, S=4, 16 images 88.0 / 80.9; 56x56x256, S=4, 4 images 43.1 / 40.7, 12 images (four blocks)
+// 85.9 / 85.5; 7x7x2048, 16 images 90.1 / 79.8; bf16 28x20x192, mid 48, S=4, 13 images 27.2 / 24.8, r=1 33.8 / 30.2; 40x40x192, 40
+// images 92.9 / 86.8; 32x32x96, mid 24, 2 images 19.7 / 19.1.  Rings of 4 k-steps and 2 (one block): 75.0 and 79.8 where 3 take 73.3.
+constexpr bool rows_through_lds(int nb) { return nb <= 2; }
+constexpr int rows_depth(int nb, int pl) { return nb == 1 ? 3 : nb == 2 ? (pl == 3 ? 2 : 3) : 2; }
+template <class F>
+constexpr int rows_ring_bytes(int nb, int pl) {              // of one wave, for up to nb row blocks
+  const int one = rows_depth(1, pl) * pl * F::KPL * 1024, two = rows_depth(2, pl) * 2 * pl * F::KPL * 1024;
+  return nb == 1 || one > two ? one : two;
+}
+__device__ __forceinline__ int ring_row(int lane) { return lane >> 2; }                        // what lane loads
+__device__ __forceinline__ int ring_piece(int lane) { return (lane & 3) ^ (lane >> 4); }
+__device__ __forceinline__ int ring_place(int l16, int lg) { return l16 * 4 + (lg ^ (l16 >> 2)); }
+
+// 64 x 16 bytes from base + the lanes' offsets to 1 KiB of LDS.  (asm: the compiler must not know that it writes LDS, or it waits for
+// everything before each read.)
+__device__ __forceinline__ void ring_load(const unsigned char* base, unsigned off, unsigned to) {
+  asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, %1" ::"v"(off), "s"(base), "s"(to) : "memory");
+}
+// All but the youngest VM of the wave's memory operations have ended.  (With LASNET_DRAIN_AT_BARRIERS all have: the check build.)
+template <int VM>
+__device__ __forceinline__ void ring_wait() {
+  static_assert(VM >= 0 && VM < 64, "vmcnt is 6 bits");
+  __builtin_amdgcn_sched_barrier(0);
+#ifdef LASNET_DRAIN_AT_BARRIERS
+  asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+#else
+  asm volatile("s_waitcnt vmcnt(%0)" ::"n"(VM) : "memory");
+#endif
+  __builtin_amdgcn_sched_barrier(0);
+}
+
 // ---- the GEMM of one wave: NB blocks of 16 rows x one group of 32 channels ------------------------------
-// k-steps [s0, s1).  A fragments by `weights`, B rows by `rows`, which yields the byte offset of each row block's lane for the
-// k-step it is advanced to.  `meanwhile` runs once the first loads have gone out: what it requests is waited for with them, or after.
-struct RowsNothing { __device__ __forceinline__ void operator()() const {} };
-template <class F, int NB, int PL, int D, class Weights, class Rows, class Meanwhile = RowsNothing>
-__device__ __forceinline__ void rows_gemm(floatx4 (&acc)[NB][2], Weights& weights, Rows& rows, int s0, int s1,
-                                          Meanwhile meanwhile = Meanwhile{}) {
+// k-steps [s0, s1).  A fragments by `weights`, B rows by `rows`; RING: through the wave's ring, else into registers.  `meanwhile` runs once
+// the first loads have gone out (what it loads only makes the waits for them longer).
+struct RowsNothing {
+  __device__ __forceinline__ void operator()() const {}
+};
+template <class F, int NB, int PL, bool RING, class Weights, class Rows, class Meanwhile = RowsNothing>
+__device__ __forceinline__ void rows_gemm(floatx4 (&acc)[NB][2], Weights& weights, Rows& rows, int s0, int s1, ROWS_LDS unsigned char* ring,
+                                          int lane, Meanwhile meanwhile = Meanwhile{}) {
   using Frag = typename F::Frag;
-  Frag a[D][2], b[D][NB][PL];
+  constexpr int D = RING ? rows_depth(NB, PL) : 2;
+  constexpr int NA = 2 * F::KPL, NL = NB * PL * F::KPL;      // a k-step's loads of weights and of rows
+  Frag a[D][2], b[RING ? 1 : D][NB][PL];
+  const unsigned ring0 = (unsigned)rows_uni((int)(unsigned)(size_t)ring);
+  const int mine = ring_place(lane & 15, lane >> 4) * 16;
   auto load = [&](int d, int s) {
+    if constexpr (RING) {
+      // the place's last k-step has been read: not only its reads requested, which a load that finds its rows in L1 could overtake
+      __builtin_amdgcn_sched_barrier(0);
+      asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+      rows.template direct<F, NB, PL>(ring0 + d * NL * 1024, s);
+      __builtin_amdgcn_sched_barrier(0);         // (before the weights: the waits are counted so)
+    }
     weights.template load<F>(a[d], s);
-    rows.template load<F, NB, PL>(b[d], s);
+    if constexpr (!RING) rows.template load<F, NB, PL>(b[d], s);
   };
-  auto compute = [&](int d) {
+  auto read = [&](int d, int p, int h) {
+#pragma unroll
+    for (int i = 0; i < NB; ++i)
+      b[0][i][p].v[h] = *reinterpret_cast<const ROWS_LDS typename F::V*>(ring + (d * NL + (p * NB + i) * F::KPL + h) * 1024 + mine);
+  };
+  // k-step d of the ring, behind which `after` k-steps have been requested.  (Reading each fragment of the next one into the registers that
+  // the MFMAs have just left: 1 to 2 % faster for a few images, as much slower for more, whose SIMDs then hold a wave less.)
+  auto compute = [&](int d, auto after) {
+    if constexpr (RING) {
+      ring_wait<NA + decltype(after)::value * (NA + NL)>();
+#pragma unroll
+      for (int p = 0; p < PL; ++p)
+#pragma unroll
+        for (int h = 0; h < F::KPL; ++h) read(d, p, h);
+    }
+    Frag(&bd)[NB][PL] = b[RING ? 0 : d];
 #pragma unroll
     for (int p = 0; p < PL; ++p)
 #pragma unroll
@@ -252,8 +331,9 @@ __device__ __forceinline__ void rows_gemm(floatx4 (&acc)[NB][2], Weights& weight
 #pragma unroll
           for (int i = 0; i < NB; ++i)
 #pragma unroll
-            for (int j = 0; j < 2; ++j) F::mma(acc[i][j], a[d][j], b[d][i][p], h, e);
+            for (int j = 0; j < 2; ++j) F::mma(acc[i][j], a[d][j], bd[i][p], h, e);
   };
+  typedef std::integral_constant<int, D - 1> All;
   if constexpr (NB == 4) {
     // (256 registers do not hold four blocks beside the ends below: past the end the last step is requested again, unused)
 #pragma unroll
@@ -263,21 +343,21 @@ __device__ __forceinline__ void rows_gemm(floatx4 (&acc)[NB][2], Weights& weight
     for (; s + D <= s1; s += D) {
 #pragma unroll
       for (int d = 0; d < D; ++d) {
-        compute(d);
+        compute(d, All{});
         load(d, min(s + D + d, s1 - 1));
         __builtin_amdgcn_sched_barrier(0);
       }
     }
 #pragma unroll
     for (int d = 0; d < D - 1; ++d)
-      if (s + d < s1) compute(d);
+      if (s + d < s1) compute(d, All{});
     return;
   }
   // Nothing is requested past the end (a CU's L1 is near its rate, and what is loaded to fill a round up delays what follows it): the
   // steady loop leaves 1 to 2D-1 k-steps, whose number is a constant in each of as many straight-line ends.  Against a ring that is
   // filled up with repeats of the last step (2 of 10 k-steps where four waves share 36), call sequences, us: bf16 28x20x192, mid 48, S=4, 13 images
   // 29.6 -> 27.0, r=1 38.3 -> 33.3; fp32 56x56x256, S=4, 4 images 46.3 -> 43.3; 14x14x1024, S=2, 16 images 82.8 -> 79.7; 28x28x512, S=4,
-  // r=0.9, 16 images 115.5 -> 112.1.  (Rings 3 and 4 deep: the same to 3 us slower.)
+  // r=0.9, 16 images 115.5 -> 112.1.
   int s = s0;
   auto end = [&](auto left) {
     constexpr int L = decltype(left)::value;
@@ -290,17 +370,12 @@ __device__ __forceinline__ void rows_gemm(floatx4 (&acc)[NB][2], Weights& weight
       meanwhile();
       __builtin_amdgcn_sched_barrier(0);
     }
-#pragma unroll
-    for (int d = 0; d < (L < D ? L : D); ++d) {
-      compute(d);
-      if (d < L - D) load(d, s + D + d);
+    rows_each<L>([&](auto j) {                   // step j of those left: the steps up to j + D have been requested
+      constexpr int J = decltype(j)::value;
+      compute(J % D, std::integral_constant<int, (J + D < L ? J + D : L) - 1 - J>{});
+      if constexpr (J + D < L) load(J % D, s + D + J);
       __builtin_amdgcn_sched_barrier(0);
-    }
-#pragma unroll
-    for (int d = 0; d < L - D; ++d) {
-      compute(d);
-      __builtin_amdgcn_sched_barrier(0);
-    }
+    });
   };
   if (s1 - s0 >= D) {
 #pragma unroll
@@ -313,7 +388,7 @@ __device__ __forceinline__ void rows_gemm(floatx4 (&acc)[NB][2], Weights& weight
     for (; s + 2 * D <= s1; s += D) {
 #pragma unroll
       for (int d = 0; d < D; ++d) {
-        compute(d);
+        compute(d, All{});
         load(d, s + D + d);
         __builtin_amdgcn_sched_barrier(0);
       }
@@ -329,6 +404,15 @@ struct XRows {
   rows_rsrc_t rs;
   unsigned off[4];         // byte offset of the lane's row in the chunk, kOutOfRange for rows that do not exist
   int C, lg;
+  const unsigned char* base;             // for direct(): the chunk's first pixel; off is of the row and piece that the lane loads there
+  // (rows that do not exist are some row that does, and C is a whole number of k-steps)
+  template <class F, int NB, int PL>
+  __device__ __forceinline__ void direct(unsigned to, int s) {
+#pragma unroll
+    for (int i = 0; i < NB; ++i)
+#pragma unroll
+      for (int h = 0; h < F::KPL; ++h) ring_load(base + (unsigned)(s * F::STEP + h * 64), off[i], to + (i * F::KPL + h) * 1024);
+  }
   template <class F, int NB, int PL>
   __device__ __forceinline__ void load(typename F::Frag (&b)[NB][PL], int s) {
     static_assert(PL == 1, "x is one term");
@@ -354,10 +438,13 @@ struct XRows {
   }
 };
 
-// B rows of conv3: the row's own y2; of conv2: y1 of the pixel that tap s / ksm names, zeros outside the image.
-template <bool TAPS>
+// B rows of conv3: the row's own y2; of conv2: y1 of the pixel that tap s / ksm names, zeros outside the image.  RING: by direct(), then
+// px, h and w are of the row that the lane loads, and outside the image, where a buffer load gives zeros, is y1's row of zeros.
+template <bool TAPS, bool RING>
 struct YRows {
   rows_rsrc_t rs;
+  const unsigned char* base;
+  unsigned outside;
   unsigned off[4];         // TAPS: of the current tap
   unsigned pitch;
   int ksm, lg;
@@ -369,8 +456,32 @@ struct YRows {
     for (int i = 0; i < 4; ++i)
       if (i < nb) {
         const bool in = px[i] >= 0 && (unsigned)(h[i] + dy) < (unsigned)H && (unsigned)(w[i] + dx) < (unsigned)W;
-        off[i] = in ? (unsigned)(px[i] + dy * W + dx) * pitch + lg * 16 : kOutOfRange;
+        off[i] = in ? (unsigned)(px[i] + dy * W + dx) * pitch + lg * 16 : outside;
       }
+  }
+  // (to the k-step after the last one, or the last one again: its place within the tap)
+  __device__ __forceinline__ int advance(int s, int nb) {
+    if constexpr (!TAPS) return s;
+    if (s != at) {
+      at = s;
+      if (++in_tap == ksm) {
+        in_tap = 0;
+        ++tap;
+        set_tap(nb);
+      }
+    }
+    return in_tap;
+  }
+  template <class F, int NB, int PL>
+  __device__ __forceinline__ void direct(unsigned to, int s) {
+    const int so = advance(s, NB);
+#pragma unroll
+    for (int p = 0; p < PL; ++p)
+#pragma unroll
+      for (int i = 0; i < NB; ++i)
+#pragma unroll
+        for (int h2 = 0; h2 < F::KPL; ++h2)
+          ring_load(base + (unsigned)(so * F::STEP + p * ksm * F::STEP + h2 * 64), off[i], to + ((p * NB + i) * F::KPL + h2) * 1024);
   }
   __device__ __forceinline__ void seek(int s, int nb) {
     at = s;
@@ -380,18 +491,7 @@ struct YRows {
   }
   template <class F, int NB, int PL>
   __device__ __forceinline__ void load(typename F::Frag (&b)[NB][PL], int s) {
-    int so = s;
-    if constexpr (TAPS) {
-      if (s != at) {
-        at = s;
-        if (++in_tap == ksm) {
-          in_tap = 0;
-          ++tap;
-          set_tap(NB);
-        }
-      }
-      so = in_tap;
-    }
+    const int so = advance(s, NB);
 #pragma unroll
     for (int p = 0; p < PL; ++p)
 #pragma unroll
@@ -524,9 +624,14 @@ __global__ __launch_bounds__(kRowsThreads, VEC && NB == 4 ? 3 : 2) void rows_con
   }
   __shared__ int rowpx[NB * 16];
   __shared__ __attribute__((aligned(16))) float part[KS > 1 ? 4 * NB * 2 * 64 * 4 : 4];
+  constexpr int RINGB = VEC && rows_through_lds(NB) ? rows_ring_bytes<F>(NB, F::XP) : 4;
+  __shared__ __attribute__((aligned(1024))) unsigned char rings[4 * RINGB];
   const int tid = threadIdx.x, lane = tid & 63, l16 = lane & 15, lg = lane >> 4, wave = rows_uni(tid >> 6);
   int unit, slice;
   if (!unit_and_slice((a.npx + NB * 16 - 1) / (NB * 16), nsl, unit, slice)) return;
+  if (unit == 0 && slice == 0)                   // the row of zeros behind y1's last
+    for (unsigned i = tid; i < y_pitch<F>(a.ksm) / 4; i += kRowsThreads)
+      reinterpret_cast<unsigned*>(y1 + (size_t)a.npx * y_pitch<F>(a.ksm))[i] = 0;
   const int p0 = unit * NB * 16;
   // the needed pixels of this run, ascending
   static_assert(NB * 16 <= 64, "one ballot");
@@ -553,12 +658,16 @@ __global__ __launch_bounds__(kRowsThreads, VEC && NB == 4 ? 3 : 2) void rows_con
     constexpr int N = decltype(nbc)::value;
     XRows<VEC> rows;
     rows.rs = rows_rsrc(x + (size_t)a.px0 * a.g.C, (unsigned)a.npx * a.g.C * F::ES);
+    rows.base = (const unsigned char*)(x + (size_t)a.px0 * a.g.C);
     rows.C = a.g.C;
     rows.lg = lg;
+    // (the next pixel's values must not meet the zero weights past channel C)
+    constexpr bool MAY_RING = VEC && rows_through_lds(NB);     // (fewer blocks in a kernel of four read as its four do: its registers)
+    const bool ring = MAY_RING && a.g.C % 32 == 0;
 #pragma unroll
     for (int i = 0; i < N; ++i) {
-      const int px = rowpx[i * 16 + l16];
-      rows.off[i] = px >= 0 ? (unsigned)px * a.g.C * F::ES : kOutOfRange;
+      const int px = rowpx[i * 16 + (ring ? ring_row(lane) : l16)];
+      rows.off[i] = ring ? (unsigned)max(px, p0) * a.g.C * F::ES + ring_piece(lane) * 16 : px >= 0 ? (unsigned)px * a.g.C * F::ES : kOutOfRange;
     }
     const int kq = (a.ks1 + KS - 1) / KS, s0 = min(wave % KS * kq, a.ks1), s1 = min(s0 + kq, a.ks1);
     for (int pair = slice * WC + wave / KS; pair < (KS > 1 ? (a.pairs1 + WC - 1) / WC * WC : a.pairs1); pair += nsl * WC) {
@@ -567,7 +676,13 @@ __global__ __launch_bounds__(kRowsThreads, VEC && NB == 4 ? 3 : 2) void rows_con
       if (s0 < s1 && pair < a.pairs1) {
         Weights weights;
         weights.template open<F>(wp, a.w1_bytes, a.w1, pair, a.g.M, a.g.C, a.ks1, s0, lane);
-        rows_gemm<F, N, F::XP, 2>(acc, weights, rows, s0, s1);
+        ROWS_LDS unsigned char* mine = (ROWS_LDS unsigned char*)rings + wave * RINGB;
+        if constexpr (MAY_RING) {
+          if (ring) rows_gemm<F, N, F::XP, true>(acc, weights, rows, s0, s1, mine, lane);
+          else rows_gemm<F, N, F::XP, false>(acc, weights, rows, s0, s1, mine, lane);
+        } else {
+          rows_gemm<F, N, F::XP, false>(acc, weights, rows, s0, s1, mine, lane);
+        }
       }
       reduce_over_waves<N, KS>(acc, (ROWS_LDS float*)part, wave, lane);
 #pragma unroll
@@ -591,27 +706,37 @@ __global__ __launch_bounds__(kRowsThreads, 2) void rows_conv2_kernel(RowsArgs a,
                                                                      const unsigned char* __restrict__ y1,
                                                                      unsigned char* __restrict__ y2) {
   __shared__ __attribute__((aligned(16))) float part[KS > 1 ? 4 * NB * 2 * 64 * 4 : 4];
+  constexpr bool RING = rows_through_lds(NB);
+  constexpr int RINGB = RING ? rows_ring_bytes<F>(NB, F::YP) : 4;
+  __shared__ __attribute__((aligned(1024))) unsigned char rings[4 * RINGB];
   const int tid = threadIdx.x, lane = tid & 63, l16 = lane & 15, lg = lane >> 4, wave = rows_uni(tid >> 6);
-  int unit, slice;
+  int unit, slice, cell[NB];
+  unit_and_slice(0, nsl, unit, slice);           // (a unit past the last has no rows)
+  const int r0 = unit * NB * 16, rl = RING ? ring_row(lane) : l16;         // rl: row of a block that the lane loads
+#pragma unroll
+  for (int i = 0; i < NB; ++i) cell[i] = row_cell(a, r0 + i * 16 + rl);
   const int nrows = rows_active(a);
-  if (!unit_and_slice((nrows + NB * 16 - 1) / (NB * 16), nsl, unit, slice)) return;
-  const int r0 = unit * NB * 16;
-  YRows<true> rows;
+  if (r0 >= nrows) return;
+  YRows<true, RING> rows;
   const unsigned pitch = y_pitch<F>(a.ksm);
+  int px[NB];                                    // of the lane's row of the result
   bool any = false;
 #pragma unroll
   for (int i = 0; i < NB; ++i) {
-    const RowPixel p = row_pixel(a, r0 + i * 16 + l16, nrows);
+    const RowPixel p = row_pixel(a, cell[i], r0 + i * 16 + rl, nrows);
     rows.px[i] = p.px < 0 ? -1 : p.px - a.px0;
     rows.h[i] = p.h;
     rows.w[i] = p.w;
     any |= p.px >= 0;
+    px[i] = RING ? __shfl(rows.px[i], l16 * 4) : rows.px[i];
   }
   if (!__any(any)) return;                       // (the same rows in every wave)
   rows.rs = rows_rsrc(y1, (unsigned)a.npx * pitch);
+  rows.base = y1;
   rows.pitch = pitch;
   rows.ksm = a.ksm;
-  rows.lg = lg;
+  rows.lg = RING ? ring_piece(lane) : lg;
+  rows.outside = RING ? (unsigned)a.npx * pitch + ring_piece(lane) * 16 : kOutOfRange;
   rows.H = a.g.H;
   rows.W = a.g.W;
   constexpr int WC = 4 / KS;
@@ -623,16 +748,16 @@ __global__ __launch_bounds__(kRowsThreads, 2) void rows_conv2_kernel(RowsArgs a,
     if (s0 < s1 && pair < a.pairs1) {
       Weights weights;
       weights.template open<F>(wp, a.w2_bytes, a.w2, pair, a.g.M, a.g.M, a.ksm, s0, lane);
-      rows_gemm<F, NB, F::YP, 2>(acc, weights, rows, s0, s1);
+      rows_gemm<F, NB, F::YP, RING>(acc, weights, rows, s0, s1, (ROWS_LDS unsigned char*)rings + wave * RINGB, lane);
     }
     reduce_over_waves<NB, KS>(acc, (ROWS_LDS float*)part, wave, lane);
 #pragma unroll
     for (int i = 0; i < NB; ++i)
-      if ((KS == 1 || i % KS == wave % KS) && pair < a.pairs1 && rows.px[i] >= 0) {
+      if ((KS == 1 || i % KS == wave % KS) && pair < a.pairs1 && px[i] >= 0) {
         float v[8];
 #pragma unroll
         for (int u = 0; u < 8; ++u) v[u] = fmaxf(acc[i][u / 4][u % 4], 0.f);
-        store_y<F>(y2 + (size_t)rows.px[i] * pitch, rows_channel(pair, lg), a.ksm, v);
+        store_y<F>(y2 + (size_t)px[i] * pitch, rows_channel(pair, lg), a.ksm, v);
       }
   }
 }
@@ -646,22 +771,33 @@ __global__ __launch_bounds__(kRowsThreads, 2) void rows_conv3_kernel(RowsArgs a,
                                                                      typename F::T* __restrict__ out, int post_relu) {
   __shared__ __attribute__((aligned(16))) float part[KS > 1 ? 4 * NB * 2 * 64 * 4 : 4];
   typedef typename F::T T;
+  constexpr bool RING = rows_through_lds(NB);
+  constexpr int RINGB = RING ? rows_ring_bytes<F>(NB, F::YP) : 4;
+  __shared__ __attribute__((aligned(1024))) unsigned char rings[4 * RINGB];
   const int tid = threadIdx.x, lane = tid & 63, l16 = lane & 15, lg = lane >> 4, wave = rows_uni(tid >> 6);
-  int unit, slice;
-  const int nrows = rows_active(a);
-  if (!unit_and_slice((nrows + NB * 16 - 1) / (NB * 16), nsl, unit, slice)) return;
+  int unit, slice, cell[NB];
+  unit_and_slice(0, nsl, unit, slice);           // (a unit past the last has no rows)
   const int r0 = unit * NB * 16;
-  YRows<false> rows;
+#pragma unroll
+  for (int i = 0; i < NB; ++i) cell[i] = row_cell(a, r0 + i * 16 + l16);
+  const int nrows = rows_active(a);
+  if (r0 >= nrows) return;
+  YRows<false, RING> rows;
   const unsigned pitch = y_pitch<F>(a.ksm);
-  int px[NB];
-  bool any = false;
+  int px[NB], some = -1;
 #pragma unroll
   for (int i = 0; i < NB; ++i) {
-    px[i] = row_pixel(a, r0 + i * 16 + l16, nrows).px;
-    rows.off[i] = px[i] < 0 ? kOutOfRange : (unsigned)(px[i] - a.px0) * pitch + lg * 16;
-    any |= px[i] >= 0;
+    px[i] = row_pixel(a, cell[i], r0 + i * 16 + l16, nrows).px;
+    some = max(some, px[i]);
   }
-  if (!__any(any)) return;
+#pragma unroll
+  for (int o = 8; o > 0; o >>= 1) some = max(some, __shfl_xor(some, o, 16));
+  if (some < 0) return;                          // (the same rows in every wave)
+#pragma unroll
+  for (int i = 0; i < NB; ++i)                   // (a row that does not exist loads one that does, unused)
+    rows.off[i] = RING ? (unsigned)__shfl((px[i] < 0 ? some : px[i]) - a.px0, ring_row(lane)) * pitch + ring_piece(lane) * 16
+                       : px[i] < 0 ? kOutOfRange : (unsigned)(px[i] - a.px0) * pitch + lg * 16;
+  rows.base = y2;
   rows.rs = rows_rsrc(y2, (unsigned)a.npx * pitch);
   rows.ksm = a.ksm;
   rows.lg = lg;
@@ -690,7 +826,7 @@ __global__ __launch_bounds__(kRowsThreads, 2) void rows_conv3_kernel(RowsArgs a,
     if (s0 < s1 && pair < a.pairs3) {
       Weights weights;
       weights.template open<F>(wp, a.w3_bytes, a.w3, pair, C, a.g.M, a.ksm, s0, lane);
-      rows_gemm<F, NB, F::YP, 2>(acc, weights, rows, s0, s1, request);
+      rows_gemm<F, NB, F::YP, RING>(acc, weights, rows, s0, s1, (ROWS_LDS unsigned char*)rings + wave * RINGB, lane, request);
     } else {
       request();
     }
@@ -894,7 +1030,7 @@ bool rows_layout(const Geom& g, RowsLayout& l) {
                            rows_cut(all, chunk, (int)pairs3, (int)ksm)})
     if (sliced_grid(c.units, c.nsl) * kRowsThreads >= 1ll << 32) return false;
   l.need = (n * hw + kNeedPixels - 1) / kNeedPixels * kNeedPixels;
-  l.y = rows_round(n * hw * ypx);
+  l.y = rows_round((n * hw + 1) * ypx);          // (a row of zeros behind the last)
   l.total = rows_round(l.w1) + rows_round(l.w2) + rows_round(l.w3) + l.need + 2 * l.y;
   return true;
 }
