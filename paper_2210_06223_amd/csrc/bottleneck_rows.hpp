@@ -245,7 +245,7 @@ __device__ __forceinline__ void rows_count(int n, Fn&& f) {
 // What it saves is lookups: a CU's L1 takes the addresses of four lanes at a time, and in a fragment's lanes (lane % 16 the row) those are
 // four rows', so a load of 1 KiB costs 64 lookups.  Here four lanes in a row load one row's 64 bytes: 16 lookups, as for the weights, and
 // the fragment's lanes find their pieces in LDS.  (fp32, per k-step and wave, one row block: 192 of them against 512 clocks of MFMAs,
-and there are four waves to a CU's L1; now 96.)  Four row blocks have no room for it, and lose least: they read straight into registers.
+// and there are four waves to a CU's L1; now 96.)  Four row blocks have no room for it, and lose least: they read straight into registers.
 // Piece lg of row i lies at place i*4 + (lg ^ i/4): the 16 rows that are read together are in different banks.
 // Call sequences, rows straight into registers / through LDS, us: fp32 14x14x1024, S=2, 16 images, r=0.1 55.4 / 54.8, r=0.5 79.4 / 74.2, r=0.9
 // 100.9 / 91.0, static block 107.5 / 97.3; 28x28x512, S=4, 16 images 88.0 / 80.9; 56x56x256, S=4, 4 images 43.1 / 40.7, 12 images (four blocks)
