@@ -6,19 +6,24 @@ namespace {
 
 // Whether the convolutions read the caller's weights.  Read in their natural layout -- 64-byte pieces of 16 rows, which lie a
 // power of two apart at the usual widths -- they cost more per fragment than packed ones, and a tile's reduction that is long
-// stands for them, so it pays where the fragments that the call reads (every pixel active) are few and short.  Direct / with a plan, us:
-//   bf16 fragments  2k  20x20x320 mid 80 25.7 / 31.6          15k 40x40x384 mid 96 26.4 / 30.2 (r=1 27.0 / 30.3)
-//                  27k  13 x 28x20x192 mid 48 28.1 / 30.9 (r=1 36.8 / 40.9)
-//           beyond 29k  14 x 28x20x192 28.4 / 31.2 (r=1 37.0 / 41.1)                  31k 2 x 40x40x384, r=0.6 28.9 / 30.4, r=1 33.0 / 32.1
-//                  46k  3 x 40x40x384, r=0.3 30.0 / 30.3, r=0.6 35.0 / 33.6, r=1 40.1 / 39.4
-//   fp32            2k  8 x 30x30x64 mid 16 26.4 / 29.5          5k 24x24x384 mid 96 28.0 / 29.6 (r=1 27.6 / 29.7)
-//           beyond 10k  2 x 24x24x384 28.3 / 29.6 (r=1 28.0 / 29.7)                   13k 56x56x256 mid 64, r=1 35.3 / 30.3
-//   (32 to 72 k-steps: fp32 14x14x1024 mid 256 42.3 / 36.4, 2 x 28x28x512 mid 128 36.2 / 32.9)
+// stands for them, so it pays where the fragments that the call reads (every pixel active) are few and conv1's reduction is short (fp32 from
+// 12 k-steps on, it never did).  Direct / with a plan, r=0.5 if not noted, us:
+//   bf16, up to six k-steps:      26k  24 x 32x32x128 mid 32 26.8 / 30.5              28k  5 x 40x40x160 mid 40 24.1 / 26.6 (r=1 29.4 / 33.3)
+//     31k  32 x 32x32x96 mid 24 28.6 / 32.3 (r=1 38.3 / 41.1)  35k  32 x 32x32x128 30.8 / 34.4 (r=1 37.3 / 40.4)
+//     beyond  38k  18 x 28x20x192 mid 48 31.7 / 31.7           41k  16 x 56x56x64 mid 16 41.1 / 41.0 (47k  16 x 28x28x192, S=7 31.4 / 33.0)
+//   bf16, more:  2k  20x20x320 mid 80 21.9 / 24.5               15k  40x40x384 mid 96 23.6 / 25.1
+//     beyond  31k  2 x 40x40x384, r=0.6 27.5 / 27.9, r=1 30.3 / 30.2           46k  3 x 40x40x384, r=0.3 28.0 / 28.0, r=0.6 32.1 / 31.3
+//   fp32, up to six:  4k  4 x 32x32x128 21.8 / 23.5             12k  4 x 28x28x192 25.1 / 26.0         13k  12 x 32x32x128 26.6 / 28.7
+//     beyond  15k  16 x 32x32x96 26.8 / 28.8                    17k  16 x 32x32x128 28.9 / 29.7 but r=1 36.3 / 33.2
+//   fp32, 7 to 11:  3k  20x20x320 25.3 / 26.2                   7k  28x28x320 mid 80 25.5 / 26.4, 2 x 28x28x256 mid 64 24.2 / 24.5
+//     beyond  13k  2 x 40x40x224 mid 56 26.9 / 26.4, 56x56x256 26.2 / 25.6 (r=1 29.9 / 28.4)
+//   fp32, 12:  1k  8x8x384 mid 96 26.2 / 25.5                   5k  24x24x384 27.2 / 26.6              11k  2 x 24x24x384 28.2 / 26.8
 template <class F>
 bool direct_is_faster(const Geom& g) {
   const long long tiles = ((long long)g.N * g.H * g.W + 15) / 16, pairs1 = (g.M + 31) / 32, pairs3 = (g.C + 31) / 32;
   const long long fragments = tiles * (2 * pairs1 * pairs3 + 9 * pairs1 * pairs1);
-  return g.P <= kDirectCells && pairs1 <= 3 && fragments <= (F::ES == 4 ? 7000 : 28000);
+  const long long few = F::ES == 2 ? (pairs3 <= 6 ? 36000 : 28000) : pairs3 <= 6 ? 14000 : pairs3 < 12 ? 7000 : 0;
+  return g.P <= kDirectCells && pairs1 <= 3 && fragments <= few;
 }
 
 template <class F, bool VEC>

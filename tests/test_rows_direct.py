@@ -21,6 +21,34 @@ ROUTES = [
     ((3, 21, 14, 68, 36, 7), True, True),                # bf16 cannot read 16-byte pieces of it: its copy and plan as ever
 ]
 
+# (dtype, shape) -> whether there is no plan: both sides of each line of direct_is_faster
+EDGES = [
+    ("f32", (11, 32, 32, 128, 32, 8), True),             # 12.0 thousand fragments, four k-steps
+    ("f32", (5, 28, 28, 192, 48, 4), False),             # 14.7 thousand, six
+    ("f32", (1, 28, 28, 320, 80, 4), True),              # 6.9 thousand, ten
+    ("f32", (1, 28, 28, 352, 88, 4), False),             # 7.2 thousand, eleven
+    ("f32", (1, 8, 8, 384, 96, 4), False),               # twelve
+    ("bf16", (32, 32, 32, 128, 32, 8), True),            # 34.8 thousand, four
+    ("bf16", (10, 28, 35, 192, 48, 7), False),           # 36.8 thousand, six
+    ("bf16", (4, 32, 32, 224, 56, 4), True),             # 16.4 thousand, seven
+    ("bf16", (8, 32, 32, 224, 56, 8), False),            # 32.8 thousand, seven
+]
+
+
+@pytest.mark.parametrize("dtype,shape,direct", EDGES)
+def test_where_the_plan_begins(dtype, shape, direct):
+    """(Host only.)"""
+    names = H.run("result = kernels(call('ex', %s, *%r)[1])" % ("F32" if dtype == "f32" else "BF16", shape))
+    names = [H.kernel_name(n).split("<")[0] for n in names]
+    assert names == ([] if direct else ["rows_plan_kernel"]) + ["rows_conv%d_kernel" % k for k in (1, 2, 3)], names
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("dtype,shape,direct", EDGES)
+def test_either_side_of_the_line(dtype, shape, direct):
+    cfg = synth.BlockConfig("direct", *shape, dtype, 0.4, 137)
+    _run_case(cfg, k=max(1, int(round(cfg.r * cfg.P))))
+
 
 def test_routes():
     """(Host only.)"""
