@@ -558,7 +558,7 @@ __device__ __forceinline__ void rows_blocks(int n, Fn&& f) {
 // What bounds them is their launches, 2 to 5 us each of a chain of dependent kernels.  So the copy of x to out, where there is one, has
 // no launch of its own but a part of the next one's workgroups; and where the weights are small too (direct_is_faster) there is
 // no plan: the convolutions read the caller's weights, and a workgroup of conv1 finds the needed pixels of its own run by
-// going through the list itself.  Call sequences, us: fp32 56x56x256, S=4, r=0.6, one image (copy with the plan) 31.0 -> 29.0; bf16
+// going through the list itself.  Call sequences (rows straight into registers; through LDS each is 3 to 4 us shorter), us: fp32 56x56x256, S=4, r=0.6, one image (copy with the plan) 31.0 -> 29.0; bf16
 // 28x20x192, mid 48, S=4, 13 images (no plan) 30.9 -> 28.4; bf16 20x20x320, mid 80, S=2, one image (neither) 31.6 -> 25.7.
 constexpr int kDirectCells = 512;
 
@@ -996,14 +996,12 @@ inline RowsCut rows_cut(long long rows_max, long long rows_expected, int pairs, 
 }
 
 // conv1, whose rows are known.  1200 to 2047 waves of one row block take as long as half as many of two -- some SIMDs have two of the former --
-// but (fp32) load 6 KiB per 16 MFMAs instead of 8 per 32: 48 bytes per clock of a CU's L1, near its 64, against 32.  It shows where the
-// reduction is long.  Call sequences, r=0.5 if not noted, one block / two, us.  Above the line: fp32 14x14x1024, S=2: 13 images 79.4 / 75.8,
-// 16 85.9 / 82.2, 16 at r=1 120.3 / 116.5, 20 87.6 / 83.9; 7x7x2048: 28 images 136.0 / 128.7, 38 147.9 / 140.6; bf16 14x14x1024, mid 160, 20
-// images 52.6 / 50.8, mid 200, 17 images 57.2 / 55.4, mid 224, 16 images 57.2 / 55.6.  Below it, down to 544 tiles, two are still faster: fp32
-// 14x14x1024, 11 images 78.7 / 75.0, 7x7x2048, 24 images 134.8 / 127.2, bf16 mid 200, 13 images 56.2 / 54.8; under 512 one is: 10 images
-// 58.2 / 63.4, 7x7x2048, 20 images 89.6 / 101.3, bf16 mid 160, 12 images 41.7 / 45.9.  16 k-steps: fp32 28x28x512, S=4: 8 images
-// 56.6 / 54.9, 5 41.2 / 43.2.  (conv2 and conv3, whose rows are a guess: 14x14x1024, 40 images, r=0.6 177.6 / 186.0; more than one workgroup per
-// CU, of four groups of channels each: bf16 14x14x1024, mid 288, 16 images, r=0.9 93.4 / 99.4.)
+// and ask the L1 for 6 KiB of weights and rows (fp32, per two k-steps' MFMAs of a block) where two blocks share the weights.  Call sequences,
+// r=0.5 if not noted, one block / two, us.  Above the line there is little between them: fp32 14x14x1024, S=2: 13 images 69.8 / 69.7, 16
+// 74.1 / 73.9, 16 at r=1 100.8 / 100.4, 20 76.3 / 76.2; 7x7x2048, 28 images 120.6 / 120.8; bf16 14x14x1024, mid 200, 17 images 48.5 / 48.0,
+// mid 224, 16 images 48.3 / 47.7; below it, down to 544 tiles, as little: fp32 11 images 68.3 / 68.2, 28x28x512, S=4, 8 images 51.1 / 50.7; under
+// 512 one is the faster: 14x14x1024, 10 images 53.2 / 59.1, 7x7x2048, 16 images 80.2 / 94.5, 20 79.9 / 93.9, 28x28x512, 5 images 38.4 / 41.3,
+// 56x56x256, 4 images 40.7 / 43.8.  (Before the rows came through LDS two blocks were 3 to 5 % faster above the line.)
 inline RowsCut rows_cut_conv1(long long pixels, long long chunk, int pairs, int ksteps) {
   const bool one_round = (chunk + 31) / 32 * ((pairs + 3) / 4) <= 256;
   return rows_cut(pixels, chunk, pairs, ksteps, ksteps >= 32 && one_round ? 600 : 1024);

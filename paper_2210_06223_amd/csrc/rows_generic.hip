@@ -97,7 +97,7 @@ hipError_t run_rows(const Geom& g, const void* x, const int32_t* idx, const int3
 // Whether the scalar kernel is the faster one (then no workspace is asked for): where one launch of it is over before three
 // or four short ones are, and where its work per pixel is so small that the row schedule, whose MFMAs and y rows are 32 channels
 // wide, does several times as much.  `chain` is the FMAs that a thread does one after the other for a patch (45 to 90 ns each),
-// 2048 the patches that run at once (half of the cells are active).  Measured, scalar / row schedule, us, fp32:
+// 2048 the patches that run at once (half of the cells are active).  Measured, scalar / row schedule (its rows straight into registers), us, fp32:
 //   8x8x16 M=4 S=2      10 / 18   28x28x32 M=8 S=2     11 / 18   4 x 28x28x32 M=8 S=4   15 / 18   16 x 28x28x16 M=4 S=2  12 / 21
 //   2 x 8x8x48 M=12 S=2 16 / 19   8x8x48 M=12 S=4      22 / 18   16 x 28x28x32 M=8 S=2  26 / 21   64 x 28x28x64 M=4 S=4  36 / 33
 //   64 x 112x112x16 M=4 S=7 109 / 274   256 x 28x28x16 M=4 S=4 36 / 82   S=2 417 / 278   64 x 112x112x32 M=8 S=4 677 / 274
