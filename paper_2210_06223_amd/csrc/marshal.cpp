@@ -38,10 +38,14 @@ struct Plain {                                       // false from any of these:
     return true;
   }
   template <class T>
-  T* of_type(PyObject* o, at::ScalarType ty, int64_t numel = -1) {
+  T* of_type(PyObject* o, at::ScalarType ty) {
     const at::Tensor* t = tensor(o);
-    if (!need(t && t->defined() && t->scalar_type() == ty && t->is_cuda() && t->is_contiguous() && (numel < 0 || t->numel() == numel))) return nullptr;
+    if (!need(t && t->defined() && t->scalar_type() == ty && t->is_cuda() && t->is_contiguous())) return nullptr;
     return (T*)t->data_ptr();
+  }
+  const float* bias(PyObject* o, int64_t n) {
+    const float* p = of_type<const float>(o, at::kFloat);
+    return ok && need(tensor(o)->numel() == n) ? p : nullptr;
   }
   template <class T>
   T* any(PyObject* o) {                              // what the Python function passes on unchecked
@@ -147,8 +151,7 @@ PyObject* block_packed(PyObject*, PyObject* const* a, Py_ssize_t n) {
     if (!p.ok) return 0;
     const size_t need = entry<decltype(lasnet_packed_weights_bytes)>(a[7])(LASNET_BF16, x.c, M, S);
     p.need((size_t)tensor(a[6])->nbytes() >= need);
-    const float *b1 = p.of_type<const float>(a[8], at::kFloat, M), *b2 = p.of_type<const float>(a[9], at::kFloat, M);
-    const float* b3 = p.of_type<const float>(a[10], at::kFloat, x.c);
+    const float *b1 = p.bias(a[8], M), *b2 = p.bias(a[9], M), *b3 = p.bias(a[10], x.c);
     p.map(a[11], o);
     if (!p.ok) return 0;
     auto* f = entry<decltype(lasnet_sparse_bottleneck_packed)>(a[0]);
@@ -167,8 +170,7 @@ PyObject* block_planned(PyObject*, PyObject* const* a, Py_ssize_t n) {
     const uint8_t* mask = a[4] == Py_None ? nullptr : p.of_type<const uint8_t>(a[4], at::kByte);
     const void* packed = p.any<const void>(a[7]);
     if (!p.ok) return 0;
-    const float *b1 = p.of_type<const float>(a[8], at::kFloat, M), *b2 = p.of_type<const float>(a[9], at::kFloat, M);
-    const float* b3 = p.of_type<const float>(a[10], at::kFloat, x.c);
+    const float *b1 = p.bias(a[8], M), *b2 = p.bias(a[9], M), *b3 = p.bias(a[10], x.c);
     p.map(a[11], o);
     void* workspace = a[12] == Py_None ? nullptr : p.any<void>(a[12]);
     if (!p.ok) return 0;
@@ -186,11 +188,11 @@ inline void weights(Plain& p, PyObject* const* w, const lasnet_tensor& x, Weight
   const int64_t M = W1->size(0);
   r.M = (int)M;
   r.W1 = p.weight(w[0], x, {M, x.c});
-  r.b1 = p.of_type<const float>(w[1], at::kFloat, M);
+  r.b1 = p.bias(w[1], M);
   r.W2 = p.weight(w[2], x, {M, 3, 3, M});
-  r.b2 = p.of_type<const float>(w[3], at::kFloat, M);
+  r.b2 = p.bias(w[3], M);
   r.W3 = p.weight(w[4], x, {x.c, M});
-  r.b3 = p.of_type<const float>(w[5], at::kFloat, x.c);
+  r.b3 = p.bias(w[5], x.c);
 }
 
 // (x, idx, count, S, W1, b1, W2, b2, W3, b3, out, flags)

@@ -116,3 +116,18 @@ def test_other_forms_are_converted_or_refused_as_ever():
         B.lasnet_sparse_bottleneck(c.x, idx, count, 3, *c.w, out=out)
     with pytest.raises(B.LasnetError):
         B.lasnet_dense_bottleneck(c.x, *c.w, out=c.x)
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("M", [-1, -256])
+def test_a_negative_mid_width_is_refused_as_in_the_python_path(M):
+    """(Both before anything is enqueued.)"""
+    c = _Case("bf16")
+    mask, idx, count = c.masker
+    p = B.lasnet_pack_weights(c.S, c.w[0], c.w[2], c.w[4])
+    b, out = (c.d["b1"], c.d["b2"], c.d["b3"]), torch.empty_like(c.x)
+    for stream in (None, torch.cuda.current_stream()):
+        with pytest.raises(ValueError, match="biases"):
+            B.lasnet_sparse_bottleneck_packed(c.x, idx, count, c.S, M, p, *b, out=out, stream=stream)
+        with pytest.raises(ValueError, match="biases"):
+            B.lasnet_sparse_bottleneck_planned(c.x, idx, count, mask, c.S, M, p, *b, out, None, stream=stream)
