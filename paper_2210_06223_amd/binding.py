@@ -7,6 +7,7 @@ from __future__ import annotations
 
 import ctypes
 import os
+import warnings
 from typing import Optional, Tuple
 
 import torch
@@ -101,13 +102,21 @@ def load_library(path: str) -> ctypes.CDLL:
     return L
 
 
+class _AllThroughCtypes:
+    """In place of the native marshalling where it does not load: no call is of its form."""
+    masker_ex = block_ex = block_dense = block_packed = block_planned = staticmethod(lambda *args: None)
+
+
 def _load_marshal() -> None:
+    """The extension saves host time and nothing else: the ctypes calls below are complete without it."""
     global _marshal
     if _marshal is None:
         try:
             from . import _marshal as m
-        except ImportError as e:
-            raise RuntimeError("the binding's marshalling (_marshal.so) is not built: run `python -m paper_2210_06223_amd.build`") from e
+        except ImportError as e:                 # not built, or built against another torch
+            warnings.warn("the native marshalling does not load (%s); calls take some 5 us longer on the host until "
+                          "`python -m paper_2210_06223_amd.build` has made it anew" % e, RuntimeWarning, stacklevel=3)
+            m = _AllThroughCtypes
         _marshal = m
 
 

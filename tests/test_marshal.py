@@ -1,11 +1,14 @@
 """The binding's native marshalling: it takes calls of the plain form, with the results of the Python path, and leaves every other call
 to that path and its errors."""
+import sys
+
 import numpy as np
 import pytest
 import torch
 
+import paper_2210_06223_amd as pkg
 from paper_2210_06223_amd import binding as B
-from paper_2210_06223_amd import synth
+from paper_2210_06223_amd import build, synth
 from tests import _util as U
 
 
@@ -26,6 +29,35 @@ def test_tensors_that_are_not_on_the_gpu_are_left_to_the_python_path():
         B.lasnet_masker(x, f, 0.0, 2, mask=i, idx=i, count=i)
     with pytest.raises(ValueError, match="device memory"):
         B.lasnet_dense_bottleneck(x, *w, out=x)
+
+
+class _Refuses:
+    """An import hook: the extension does not load."""
+    def find_spec(self, name, path=None, target=None):
+        if name == pkg.__name__ + "._marshal":
+            raise ImportError("undefined symbol: of_another_torch")
+
+
+@pytest.fixture(params=["missing", "of another torch"])
+def without(request, monkeypatch):
+    """The binding in a process where the extension is not there, or does not load."""
+    name = pkg.__name__ + "._marshal"
+    monkeypatch.delattr(pkg, "_marshal", raising=False)
+    if request.param == "missing":
+        monkeypatch.setitem(sys.modules, name, None)
+    else:
+        monkeypatch.delitem(sys.modules, name, raising=False)
+        monkeypatch.setattr(sys, "meta_path", [_Refuses()] + sys.meta_path)
+    monkeypatch.setattr(B, "_marshal", None)
+    with pytest.warns(RuntimeWarning, match="undefined symbol" if request.param != "missing" else "_marshal"):
+        monkeypatch.setattr(B, "_lib", B.load_library(build.LIB))
+
+
+def test_the_library_loads_without_the_extension(without):
+    assert B.lasnet_version() == 100
+    x, f, i = torch.zeros(1, 4, 4, 8), torch.zeros(8), torch.zeros(4, dtype=torch.int32)
+    with pytest.raises(ValueError, match="device memory"):
+        B.lasnet_masker(x, f, 0.0, 2, mask=i, idx=i, count=i)
 
 
 class _Case:
@@ -88,6 +120,17 @@ def test_same_results_as_the_python_path(dtype, monkeypatch):
         assert handled == [True, True], name                 # (with a stream the marshalling is not asked)
         for other in outs[1:]:
             assert all(np.array_equal(a, b) for a, b in zip(outs[0], other)), name
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("dtype", ["bf16", "f32"])
+def test_same_results_without_the_extension(dtype, without):
+    c = _Case(dtype)
+    for name, call in _calls(c):
+        o, p = torch.full_like(c.x, 777.0), torch.full_like(c.x, 777.0)
+        call(o)
+        call(p, stream=torch.cuda.current_stream())
+        assert np.array_equal(U.bits(o), U.bits(p)), name
 
 
 @pytest.mark.gpu
