@@ -128,9 +128,9 @@ def lib() -> ctypes.CDLL:
     return _lib
 
 
-# Host time per call matters at a few images, where a block's kernels take 20 us.  A call whose arguments are all there and of the
-# plain form (tensors as the checks below ask for, on the current stream) is marshalled natively (csrc/marshal.cpp); it
-# answers None for any other, which then goes through the checks, conversions and ctypes call below.  There addresses go to
+# Host time per call matters at a few images, where a block's kernels take 20 us.  A call on the current stream that brings all of its
+# outputs is offered to the native marshalling (csrc/marshal.cpp), which takes it if its arguments are of the plain form (tensors as the
+# checks below ask for) and answers None for any other; that, and a call that is not offered, goes through the checks, conversions and ctypes call below.  There addresses go to
 # ctypes as plain integers (argtypes makes them pointers), and the current stream's handle is read without building a
 # torch.cuda.Stream object (3.0 -> 0.2 us).  masker_ex + packed block, one
 # 14x14x1024 image: 25.4 us without any of it, 24.2 with ctypes and integers, 16.3 marshalled natively, of which the five launches
@@ -184,7 +184,7 @@ def lasnet_masker(x: torch.Tensor, Wm: torch.Tensor, bm: float, S: int, thr: flo
                   count: Optional[torch.Tensor] = None, stream=None
                   ) -> Tuple[torch.Tensor, torch.Tensor, torch.Tensor]:
     """mask uint8 [N,G,GW], idx int32 [N*G*GW] (first count valid), count int32 [1]; all on device."""
-    if stream is None:
+    if stream is None and mask is not None and idx is not None and count is not None:
         L = lib()
         st = _marshal.masker_ex(L.at_masker_ex, x, Wm, bm, S, thr, mask, idx, count, None)
         if st is not None:
@@ -212,7 +212,7 @@ def lasnet_masker_ex(x: torch.Tensor, Wm: torch.Tensor, bm: float, S: int, thr: 
                      count: Optional[torch.Tensor] = None, pass_out: Optional[torch.Tensor] = None,
                      stream=None) -> Tuple[torch.Tensor, torch.Tensor, torch.Tensor]:
     """lasnet_masker that also copies every inactive cell of x to pass_out (may be None)."""
-    if stream is None:
+    if stream is None and mask is not None and idx is not None and count is not None:
         L = lib()
         st = _marshal.masker_ex(L.at_masker_ex, x, Wm, bm, S, thr, mask, idx, count, pass_out)
         if st is not None:
@@ -284,7 +284,7 @@ def lasnet_sparse_bottleneck(x: torch.Tensor, idx: Optional[torch.Tensor],
                              count: Optional[torch.Tensor], S: int, W1, b1, W2, b2, W3, b3,
                              out: Optional[torch.Tensor] = None, flags: int = 0,
                              stream=None) -> torch.Tensor:
-    if stream is None:
+    if stream is None and out is not None:
         L = lib()
         st = _marshal.block_ex(L.at_ex, x, idx, count, S, W1, b1, W2, b2, W3, b3, out, flags)
         if st is not None:
@@ -358,7 +358,7 @@ def lasnet_sparse_bottleneck_noalloc(x: torch.Tensor, idx: Optional[torch.Tensor
 def lasnet_dense_bottleneck(x: torch.Tensor, W1, b1, W2, b2, W3, b3,
                             out: Optional[torch.Tensor] = None, flags: int = 0,
                             stream=None) -> torch.Tensor:
-    if stream is None:
+    if stream is None and out is not None:
         L = lib()
         st = _marshal.block_dense(L.at_dense, x, W1, b1, W2, b2, W3, b3, out, flags)
         if st is not None:
@@ -402,7 +402,7 @@ def lasnet_sparse_bottleneck_packed(x: torch.Tensor, idx: Optional[torch.Tensor]
                                     packed: torch.Tensor, b1, b2, b3,
                                     out: Optional[torch.Tensor] = None, flags: int = 0,
                                     stream=None) -> torch.Tensor:
-    if stream is None:
+    if stream is None and out is not None:
         L = lib()
         st = _marshal.block_packed(L.at_packed, x, idx, count, S, M, packed, L.at_packed_bytes, b1, b2, b3, out, flags)
         if st is not None:

@@ -31,6 +31,23 @@ def test_tensors_that_are_not_on_the_gpu_are_left_to_the_python_path():
         B.lasnet_dense_bottleneck(x, *w, out=x)
 
 
+def test_calls_that_leave_their_outputs_out_are_not_offered(monkeypatch):
+    """(The attempt could only fail.)"""
+    B.lib()
+
+    class Never:
+        def __getattr__(self, name):
+            raise AssertionError(name)
+    monkeypatch.setattr(B, "_marshal", Never())
+    x, f, i = torch.zeros(1, 4, 4, 8), torch.zeros(8), torch.zeros(4, dtype=torch.int32)
+    w = (torch.zeros(2, 8), torch.zeros(2), torch.zeros(2, 3, 3, 2), torch.zeros(2), torch.zeros(8, 2), f)
+    for call in (lambda: B.lasnet_masker(x, f, 0.0, 2), lambda: B.lasnet_masker_ex(x, f, 0.0, 2, mask=i, idx=i, pass_out=x),
+                 lambda: B.lasnet_sparse_bottleneck(x, i, i, 2, *w), lambda: B.lasnet_dense_bottleneck(x, *w),
+                 lambda: B.lasnet_sparse_bottleneck_packed(x, i, i, 2, 2, f, f, f, f)):
+        with pytest.raises(ValueError, match="device memory"):
+            call()
+
+
 class _Refuses:
     """An import hook: the extension does not load."""
     def find_spec(self, name, path=None, target=None):
