@@ -78,7 +78,12 @@ struct Cfg {
   static constexpr bool Y1_TO_GLOBAL = false, Y2_TO_GLOBAL = false;   // conv1 / conv2 results stay in LDS
   static constexpr int W_KSTEP_BYTES = M * 64;
   static constexpr unsigned W1_BYTES = M * C * 2, W2_BYTES = 9 * M * M * 2, W3_BYTES = C * M * 2;
-  static constexpr int HT = pow2_at_least(cmax(2 * R1MAX, PPW * (S + 2) * (S + 2) + 1));  // hash table slots
+  // Hash table slots: more than the windows' pixels, and four times the y1 rows where a batch has several windows.  (A row of a window lies in the table as a
+  // regular pattern, and those of windows apart from each other can fill each other's gaps: with twice the y1 rows some batches had chains of 30 to 40
+  // slots, one LDS atomic after the other, and a launch waits for its slowest batch.  Longest probe over lists of all ratios on maps 7 to 336 wide, twice / four
+  // times: S=4 43 / 5, S=2 38 / 8, S=1 33 / 6.  Block alone, us: 2 maps of 100x168x512, S=4, 544 cells anywhere, one run per CU 17.2 / 15.7, 640 18.3 / 15.9; 56x56x256, S=2,
+  // 1024 of 2 maps 6.55 / 6.39, S=1, 3072 6.14 / 5.94, S=4, 10000 of 128 maps 78.2 / 77.6; cells of one region the same to 4 % less.)
+  static constexpr int HT = pow2_at_least(cmax((PPW > 1 ? 4 : 2) * R1MAX, PPW * (S + 2) * (S + 2) + 1));
   // LDS map (bytes)
   static constexpr int OFF_HKEY = 0;                            // int  [HT]     pixel+1 or 0
   static constexpr int OFF_HVAL = OFF_HKEY + HT * 4;            // short[HT]     row of that pixel and its key
