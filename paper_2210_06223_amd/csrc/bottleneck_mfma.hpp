@@ -121,16 +121,19 @@ struct Cfg {
   // Waves a SIMD holds when the CU is full of these workgroups: the register budget per wave
   // is 512 / that (a 4-wave workgroup alone on its CU may use the accumulation registers too).
   static constexpr int WAVES_PER_SIMD = cmax(1, ((160 * 1024) / LDS_BYTES) * NW / 4);
-  // Lists of at most CUs * ONE2 / 2 patches are cut into one run per CU, not one per place of a workgroup: a CU then streams the
+  // Lists of at most CUs * ONE patches are cut into one run per CU, not one per place of a workgroup: a CU then streams the
   // weights once, and that stream, with the batch's chain of latencies, is what bounds a launch in which no place gets a second
-  // batch.  Small patches: up to what the y1 rows hold whatever the windows share (a batch that is cut streams them twice after all: 73x104x512,
-  // S=1, r=0.77, 23 patches per run 23.8 / 28.1); S=4: up to 2.5 patches; where the weights are small (56x56x256), S=2: up to 2.
-  // Block alone, one run per place / per CU, us, iid: 28x28x512 (0.56 MB of weights), S=4: 2 images of 100x168, r=0.2 15.4 / 13.3, r=0.3 (2.5
-  // per CU) 16.2 / 14.7, r=0.36 16.7 / 19.3; 1 of 72x104, r=0.9 15.5 / 13.0; S=2: 16 images, r=0.5 16.2 / 13.4, 72x104, r=0.9 (6.6 per CU)
-  // 16.3 / 15.4; S=1: 73x104, r=0.1 12.1 / 9.7, r=0.4 (12 per CU) 15.6 / 13.6.  56x56x256 (0.14 MB): S=1, r=0.6 6.5 / 6.0, 2 images,
-  // r=0.6 (15 per CU) 7.1 / 7.2; S=2, 2 images, r=0.3 6.1 / 5.5, r=0.6 6.6 / 6.6; S=4 7.0 / 7.3.
-  static constexpr int ONE2 = M == 128 ? (S <= 2 ? 2 * (R1MAX / WW) : S == 4 ? 5 : 0) : M == 64 ? (S == 1 ? 2 * (R1MAX / WW) : S == 2 ? 4 : 0) : 0;
-  static_assert(ONE2 <= 2 * PPW, "a run of such a list is one batch");
+  // batch.  At mid 128 up to what the y1 rows hold whatever the windows share (a batch that is cut streams the weights twice after all).  At mid 64, whose
+  // weights are a quarter: S=1 likewise, S=2 up to four patches, which are one block of output rows; S=4 never.
+  // Block alone on lists of so many cells, one run per place / per CU, us; cells anywhere, then in one region per image, whose windows overlap:
+  //   28x28x512 (0.56 MB of weights), S=4, 2 maps of 100x168: 384 15.4 / 13.3, 15.0 / 12.5; 512 16.0 / 13.4, 15.6 / 12.8; 640 17.1 / 15.9, 16.6 / 14.9; 768 17.8 / 16.0,
+  //     17.2 / 15.3; beyond 800 18.8 / 23.4, 18.2 / 22.8.  14 images, 640 16.2 / 14.8, 16.2 / 14.8
+  //   S=2: 1024 14.1 / 10.9, 13.6 / 10.2; 1792 15.2 / 12.6, 15.1 / 12.5; beyond 2048 16.3 / 20.7, 15.5 / 12.9
+  //   S=1: 1536 13.8 / 10.5, 13.0 / 9.3; 3072 14.6 / 11.9, 13.5 / 10.2; beyond, 23 per CU (73x104, r=0.77) 23.8 / 28.1
+  //   56x56x256 (0.14 MB), S=1: 512 5.9 / 5.3, 5.9 / 5.2; 3072 6.3 / 5.9, 6.3 / 6.0; beyond, 15 per CU 7.1 / 7.2
+  //   S=2: 512 6.1 / 5.5, 6.1 / 5.4; 1024 6.4 / 6.1, 6.4 / 6.0; beyond 1280 6.7 / 7.0, 6.6 / 6.7.  S=4: 384 7.3 / 7.5, 7.3 / 7.5; 512 7.4 / 7.6, 7.4 / 7.5
+  static constexpr int ONE = M == 128 ? (S <= 4 ? R1MAX / WW : 0) : M == 64 ? (S == 1 ? R1MAX / WW : S == 2 ? 4 : 0) : 0;
+  static_assert(ONE <= PPW, "a run of such a list is one batch");
   static_assert(NW * 2048 <= R1MAX * LDY * 2, "conv3's per-wave transpose areas sit in the y1 rows below the zero row");
 };
 
@@ -824,7 +827,7 @@ __device__ LASNET_PHASE_INLINE void conv3_core(Conv3Ring<K>& ring, g_bf16_p x, g
 }
 
 struct FusedDivs { Div31 cpi, gw, slots; };                // cells per image, cells per row of cells, tile_slots
-struct OnePerCu { int most, runs; };                       // lists of up to `most` entries are cut into `runs` (Cfg::ONE2)
+struct OnePerCu { int most, runs; };                       // lists of up to `most` entries are cut into `runs` (Cfg::ONE)
 
 template <class K>
 __global__ __launch_bounds__(K::NT, K::WAVES_PER_SIMD) void fused_bneck_kernel(
@@ -873,7 +876,7 @@ __global__ __launch_bounds__(K::NT, K::WAVES_PER_SIMD) void fused_bneck_kernel(
   // ---- which entries of the index list are this workgroup's ------------------------------
   // The list is cut into `nt` near-equal runs, nt = the number of PPW-sized tiles rounded up
   // to a multiple of `tile_slots` (workgroups the chip holds at once), so that every round
-  // of workgroups is full whatever the count turns out to be.  A short list is cut into one run per CU (Cfg::ONE2).
+  // of workgroups is full whatever the count turns out to be.  A short list is cut into one run per CU (Cfg::ONE).
   const int nact = uni(idx ? min(*count, g.P) : g.P);
   if (nact <= 0) return;
   int nt = (nact + K::PPW - 1) / K::PPW;
@@ -1112,7 +1115,7 @@ hipError_t launch_one(const Geom& g, const void* x, const int32_t* idx, const in
   const __bf16* p2 = p1 + (size_t)K::M * K::C;
   const __bf16* p3 = p2 + 9 * (size_t)K::M * K::M;
   const FusedDivs dv{div31((unsigned)(g.G * g.GW)), div31((unsigned)g.GW), div31((unsigned)slots)};
-  hipLaunchKernelGGL(k, dim3(grid), dim3(K::NT), K::LDS_BYTES, st, g, dv, OnePerCu{cus * K::ONE2 / 2, cus}, slots,
+  hipLaunchKernelGGL(k, dim3(grid), dim3(K::NT), K::LDS_BYTES, st, g, dv, OnePerCu{cus * K::ONE, cus}, slots,
                      (const __bf16*)x, idx, count, p1, b1, p2, b2, p3, b3, (__bf16*)out, (int)post_relu);
   return hipGetLastError();
 }

@@ -36,11 +36,11 @@ import numpy as np
 N_CU = 256
 
 # Integer parameters of the kernels' configurations (mirrors csrc/mfma_stage*.hip and tiled_stages.hip):
-# (C, M, S) -> patches per batch, y1 rows per batch, workgroups per CU, half the patches per CU up to which a list is cut
-# into one run per CU.
+# (C, M, S) -> patches per batch, y1 rows per batch, workgroups per CU, the patches per CU up to which a list is cut into one
+# run per CU.
 FUSED = {
     (256, 64, 8): dict(kind="stream"),
-    (512, 128, 4): dict(kind="fused", PPW=4, R1MAX=112, wg_per_cu=2, one2=5),
+    (512, 128, 4): dict(kind="fused", PPW=4, R1MAX=112, wg_per_cu=2, one=3),
     (1024, 256, 2): dict(kind="fused", PPW=32, R1MAX=160, wg_per_cu=1),
     (2048, 512, 1): dict(kind="fused", PPW=16, R1MAX=96, wg_per_cu=1),
 }
@@ -106,7 +106,7 @@ def simulate_fused(idx: np.ndarray, N: int, H: int, W: int, C: int, M: int, S: i
     n, gy, gx = _cells(idx, G, GW)
     cells = list(zip(n.tolist(), gy.tolist(), gx.tolist()))
     wgs = []
-    for tb, te in fused_runs(nact, N * G * GW, PPW, slots, N_CU * p.get("one2", 0) // 2):
+    for tb, te in fused_runs(nact, N * G * GW, PPW, slots, N_CU * p.get("one", 0)):
         batches = []
         e0 = tb
         while e0 < te:
@@ -183,7 +183,8 @@ def features(idx: np.ndarray, N: int, H: int, W: int, C: int, M: int, S: int, sc
         nact = len(idx)
         nt = min(N_CU, nact)
         return dict(maxrun=-(-nact // nt) if nt else 0, any=int(nact > 0))
-    return dict(wgs=simulate_fused(idx, N, H, W, C, M, S), slots=N_CU * FUSED[(C, M, S)]["wg_per_cu"])
+    wgs, per_cu = simulate_fused(idx, N, H, W, C, M, S), FUSED[(C, M, S)]["wg_per_cu"]
+    return dict(wgs=wgs, slots=N_CU * per_cu, alone=per_cu > 1 and len(wgs) <= N_CU)
 
 
 def _predict(f: dict, k: Dict[str, float], schedule: str, kind: str) -> float:
@@ -197,6 +198,8 @@ def _predict(f: dict, k: Dict[str, float], schedule: str, kind: str) -> float:
         return k["t0"] + k["c"] * f["maxrun"]
     times = [k["w0"] + sum(k["a"] + k["b"] * b1 + k["c"] * b2 + (k.get("d", 0.0) if b2 > 4 else 0.0) for b1, b2 in wg)
              for wg in f["wgs"]]
+    if f["alone"]:                               # on its CU: nobody shares its matrix cores, L1 and LDS
+        times = [t * k.get("alone", 1.0) for t in times]
     return k["t0"] + _makespan(times, f["slots"])
 
 
@@ -231,6 +234,8 @@ def fit(points: List[dict]) -> Dict[str, Dict[str, float]]:
         names = {"tiled": ["F", "g1", "g2", "p"], "slab": ["t0", "px", "rows"], "stream": ["t0", "c"]}.get(kind, ["t0", "w0", "a", "b", "c"])
         if kind == "fused" and FUSED[(pts[0]["C"], pts[0]["M"], pts[0]["S"])]["PPW"] * pts[0]["S"] ** 2 > 64:
             names.append("d")
+        if any(f.get("alone") for f in feats):
+            names.append("alone")
         x0 = np.full(len(names), 1.0)
 
         def resid(v):

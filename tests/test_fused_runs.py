@@ -15,10 +15,11 @@ pytestmark = pytest.mark.gpu
 # cells (a divisor of one) and with sides that are no powers of two.
 CASES = [
     # the last list with one run per CU and the first with one per place of a workgroup
-    (14, 28, 28, 512, 128, 4, (640, 641)),
+    (16, 28, 28, 512, 128, 4, (640, 641, 768, 769)),
     (10, 28, 28, 512, 128, 2, (1792, 1793)),
     (4, 28, 28, 512, 128, 1, (3072, 3073)),
     (1, 56, 56, 256, 64, 1, (3072, 3073)),
+    (2, 56, 56, 256, 64, 2, (1024, 1025)),
     (6, 56, 56, 256, 64, 2, (1, 255, 511, 513, 4095, 4097, 4600)),
     (3, 12, 84, 256, 64, 4, (1, 9, 63, 180)),
     (40, 8, 2, 512, 128, 2, (3, 100, 159)),

@@ -59,6 +59,13 @@ def test_short_lists_have_one_run_per_cu():
         assert max(b - a for a, b in spans) <= 4
 
 
+def test_short_lists_are_predicted_with_their_workgroups_alone():
+    """Measured on 2 maps of 100x168x512, S=4, cells anywhere: either side of the line, where the second workgroup of a CU comes in."""
+    for nact, us in ((256, 11.2), (512, 13.4), (640, 15.9), (768, 16.0), (769, 17.9), (1024, 19.7), (2000, 35.2)):
+        idx = np.sort(np.random.default_rng(0).choice(2100, nact, replace=False))
+        assert abs(LM.predict_us(idx, 2, 100, 168, 512, 128, 4, "fused") / us - 1) < 0.15, nact
+
+
 def test_window_pixels_counts():
     assert len(LM.window_pixels([(0, 0, 0)], 2, 14, 14)) == 9          # corner patch: 3 x 3 in the image
     assert len(LM.window_pixels([(0, 3, 3)], 2, 14, 14)) == 16         # interior: 4 x 4
