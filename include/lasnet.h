@@ -201,7 +201,7 @@ LASNET_API size_t lasnet_workspace_bytes(int dtype, int N, int H, int W, int C, 
  * large as the call needs); all are kept until
  * the process ends.  So those entry points cannot be stream-captured before the stream's buffer has its
  * final size.  Shapes and types without a matrix-core kernel of their own (all of fp32), unless there is little to do,
- * keep y1 and y2 there as well, at most 256 MiB of them at a time; where that memory cannot be had, and under capture, they run a
+ * keep y1 and y2 there as well, at most 256 MiB of them (and a row of zeros) at a time; where that memory cannot be had, and under capture, they run a
  * slower kernel that needs none.
  * Weights of an inference model do not change, so a caller can instead
  * repack once, like it folded BN once (Sec. 3.4), and pass the result to

@@ -13,8 +13,8 @@
 // at a few images.  So the work is cut fine -- a wave computes NB blocks of 16 pixels times 32 output channels,
 // and nothing but the four waves of a workgroup has to meet -- and a wave loads both operands for itself, D
 // k-steps ahead, the weights into registers and the rows through LDS of its own: a 32-deep fp32 k-step is 8 MFMAs of 32 clocks per
-// 16x16 tile, so even with no reuse between the waves a CU asks its L1 for less than half of the 64 bytes a clock it delivers.  When the
-// rows are too few to fill the chip the four waves share one tile and split its reduction (KS = 4, partial sums
+// 16x16 tile, so with no reuse between its four waves a CU asks its L1 for 48, 32 and 24 of the 64 bytes a clock it delivers with 1, 2 and 4 row
+// blocks per wave (4 KiB of weights and 2 KiB of rows per block in each k-step).  When the rows are too few to fill the chip the four waves share one tile and split its reduction (KS = 4, partial sums
 // added in a fixed order through LDS); else they take four neighbouring groups of 32 channels (KS = 1).
 //
 // Measured, whole call sequence (masker, list, block) against the scalar one-kernel path: fp32 56x56x256, S=4, r=0.6, one
@@ -241,11 +241,16 @@ __device__ __forceinline__ void rows_count(int n, Fn&& f) {
 }
 
 // ---- the wave's ring of rows ------------------------------------------------------------------------------
-// A wave's B rows come through LDS of its own: the next D k-steps are on their way by direct loads that nobody but the wave waits for.
+// A wave's B rows come through LDS of its own: the next D k-steps are requested by direct loads that nobody but the wave waits for.
 // What it saves is lookups: a CU's L1 takes the addresses of four lanes at a time, and in a fragment's lanes (lane % 16 the row) those are
 // four rows', so a load of 1 KiB costs 64 lookups.  Here four lanes in a row load one row's 64 bytes: 16 lookups, as for the weights, and
 // the fragment's lanes find their pieces in LDS.  (fp32, per k-step and wave, one row block: 192 of them against 512 clocks of MFMAs,
-// and there are four waves to a CU's L1; now 96.)  Four row blocks have no room for it, and lose least: they read straight into registers.
+// and there are four waves to a CU's L1; now 96.)  Four row blocks would take 64 KiB (fp32) or 96 (bf16) of LDS for two k-steps and need the fewest lookups
+// to begin with, 576 per 2048 clocks: they read straight into registers.
+// The compiler does not count these loads, so where the MFMAs of a k-step wait for its weights it leaves (D-1) * NA operations outstanding
+// and not (D-1) * (NA + NL): by then the next k-step's rows have landed too (in bf16's conv2 and conv3, one block, a third of those after it as well).  So
+// of the D k-steps' distance a row has D-1 in the steady loop, the depths below were measured with that, and the ring's own counts decide only what a reduction's
+// first k-step and its ends read.
 // Piece lg of row i lies at place i*4 + (lg ^ i/4): the 16 rows that are read together are in different banks.
 // Call sequences, rows straight into registers / through LDS, us: fp32 14x14x1024, S=2, 16 images, r=0.1 55.4 / 54.8, r=0.5 79.4 / 74.2, r=0.9
 // 100.9 / 91.0, static block 107.5 / 97.3; 28x28x512, S=4, 16 images 88.0 / 80.9; 56x56x256, S=4, 4 images 43.1 / 40.7, 12 images (four blocks)
@@ -612,6 +617,9 @@ __device__ __forceinline__ unsigned long long rows_near(const RowsArgs& a, int p
 }
 
 // ---- conv1 -----------------------------------------------------------------------------------------------
+// (Three waves per SIMD where four row blocks come straight into registers: what hides their loads is other waves.  Call sequences, two / three, us:
+// fp32 56x56x256, S=4, 12 images 94.7 / 85.8, 16 images r=0.1 67.2 / 64.3, r=0.5 118.7 / 110.3, r=1 157.8 / 149.8; 40x40x192, 32 images 108.9 / 102.8; bf16, which
+// has them anyway, the same.)
 template <class F, bool VEC, int NB, int KS, class Weights>
 __global__ __launch_bounds__(kRowsThreads, VEC && NB == 4 ? 3 : 2) void rows_conv1_kernel(RowsArgs a, int nsl, const typename F::T* __restrict__ x,
                                                                      const unsigned char* __restrict__ wp,
@@ -996,12 +1004,12 @@ inline RowsCut rows_cut(long long rows_max, long long rows_expected, int pairs, 
 }
 
 // conv1, whose rows are known.  1200 to 2047 waves of one row block take as long as half as many of two -- some SIMDs have two of the former --
-// and ask the L1 for 6 KiB of weights and rows (fp32, per two k-steps' MFMAs of a block) where two blocks share the weights.  Call sequences,
-// r=0.5 if not noted, one block / two, us.  Above the line there is little between them: fp32 14x14x1024, S=2: 13 images 69.8 / 69.7, 16
-// 74.1 / 73.9, 16 at r=1 100.8 / 100.4, 20 76.3 / 76.2; 7x7x2048, 28 images 120.6 / 120.8; bf16 14x14x1024, mid 200, 17 images 48.5 / 48.0,
-// mid 224, 16 images 48.3 / 47.7; below it, down to 544 tiles, as little: fp32 11 images 68.3 / 68.2, 28x28x512, S=4, 8 images 51.1 / 50.7; under
-// 512 one is the faster: 14x14x1024, 10 images 53.2 / 59.1, 7x7x2048, 16 images 80.2 / 94.5, 20 79.9 / 93.9, 28x28x512, 5 images 38.4 / 41.3,
-// 56x56x256, 4 images 40.7 / 43.8.  (Before the rows came through LDS two blocks were 3 to 5 % faster above the line.)
+// and ask the L1 for 6 KiB of weights and rows (fp32, per two k-steps' MFMAs of a block) where two blocks share the weights.  Before the rows
+// came through LDS two blocks were 3 to 5 % faster from this line on; now, call sequences, r=0.5 if not noted, one block / two, us, they are 0.2 to 0.4 faster at
+// 14x14 and 0.2 slower at 7x7: bf16 14x14x1024, S=2, mid 200, 16 images 48.1 / 47.8, 17 48.7 / 48.3, 20 51.8 / 51.7, mid 224, 16 images 48.3 / 48.1; fp32 mid 256, 14
+// images 70.6 / 70.3, 16 74.3 / 74.1, 16 at r=1 101.0 / 100.8, 20 76.5 / 76.4; 7x7x2048, 28 images 120.5 / 120.7.  Below it, down to 544 tiles, there is as little:
+// fp32 11 images 68.3 / 68.2, 28x28x512, S=4, 8 images 51.1 / 50.7; and under 512 one is the faster: 14x14x1024, 10 images 53.2 / 59.1,
+// 7x7x2048, 16 images 80.2 / 94.5, 20 79.9 / 93.9, 28x28x512, 5 images 38.4 / 41.3, 56x56x256, 4 images 40.7 / 43.8.
 inline RowsCut rows_cut_conv1(long long pixels, long long chunk, int pairs, int ksteps) {
   const bool one_round = (chunk + 31) / 32 * ((pairs + 3) / 4) <= 256;
   return rows_cut(pixels, chunk, pairs, ksteps, ksteps >= 32 && one_round ? 600 : 1024);

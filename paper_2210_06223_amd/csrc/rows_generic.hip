@@ -10,11 +10,13 @@ namespace {
 // 12 k-steps on, it never did).  Direct / with a plan, r=0.5 if not noted, us:
 //   bf16, up to six k-steps:      26k  24 x 32x32x128 mid 32 26.8 / 30.5              28k  5 x 40x40x160 mid 40 24.1 / 26.6 (r=1 29.4 / 33.3)
 //     31k  32 x 32x32x96 mid 24 28.6 / 32.3 (r=1 38.3 / 41.1)  35k  32 x 32x32x128 30.8 / 34.4 (r=1 37.3 / 40.4)
-//     beyond  38k  18 x 28x20x192 mid 48 31.7 / 31.7           41k  16 x 56x56x64 mid 16 41.1 / 41.0 (47k  16 x 28x28x192, S=7 31.4 / 33.0)
+//     beyond  38k  18 x 28x20x192 mid 48 31.7 / 31.7           41k  16 x 56x56x64 mid 16 41.1 / 41.0 (47k  16 x 28x28x192, S=7 31.5 / 33.0, r=1 40.9 / 41.5)
 //   bf16, more:  2k  20x20x320 mid 80 21.9 / 24.5               15k  40x40x384 mid 96 23.6 / 25.1
 //     beyond  31k  2 x 40x40x384, r=0.6 27.5 / 27.9, r=1 30.3 / 30.2           46k  3 x 40x40x384, r=0.3 28.0 / 28.0, r=0.6 32.1 / 31.3
+//       of seven to nine k-steps it would still pay there: 29k  7 x 32x32x224 mid 56 25.5 / 26.8, 33k  8 of them 25.7 / 27.1 (r=1 30.9 / 33.1),
+//       35k  4 x 32x32x288 mid 72 25.4 / 27.6 (r=1 27.9 / 29.3)
 //   fp32, up to six:  4k  4 x 32x32x128 21.8 / 23.5             12k  4 x 28x28x192 25.1 / 26.0         13k  12 x 32x32x128 26.6 / 28.7
-//     beyond  15k  16 x 32x32x96 26.8 / 28.8                    17k  16 x 32x32x128 28.9 / 29.7 but r=1 36.3 / 33.2
+//     beyond  15k  16 x 32x32x96 26.8 / 28.9 but r=1 33.9 / 32.9  17k  16 x 32x32x128 28.9 / 29.7 but r=1 36.3 / 33.2
 //   fp32, 7 to 11:  3k  20x20x320 25.3 / 26.2                   7k  28x28x320 mid 80 25.5 / 26.4, 2 x 28x28x256 mid 64 24.2 / 24.5
 //     beyond  13k  2 x 40x40x224 mid 56 26.9 / 26.4, 56x56x256 26.2 / 25.6 (r=1 29.9 / 28.4)
 //   fp32, 12:  1k  8x8x384 mid 96 26.2 / 25.5                   5k  24x24x384 27.2 / 26.6              11k  2 x 24x24x384 28.2 / 26.8
@@ -97,10 +99,14 @@ hipError_t run_rows(const Geom& g, const void* x, const int32_t* idx, const int3
 // Whether the scalar kernel is the faster one (then no workspace is asked for): where one launch of it is over before three
 // or four short ones are, and where its work per pixel is so small that the row schedule, whose MFMAs and y rows are 32 channels
 // wide, does several times as much.  `chain` is the FMAs that a thread does one after the other for a patch (45 to 90 ns each),
-// 2048 the patches that run at once (half of the cells are active).  Measured, scalar / row schedule (its rows straight into registers), us, fp32:
-//   8x8x16 M=4 S=2      10 / 18   28x28x32 M=8 S=2     11 / 18   4 x 28x28x32 M=8 S=4   15 / 18   16 x 28x28x16 M=4 S=2  12 / 21
-//   2 x 8x8x48 M=12 S=2 16 / 19   8x8x48 M=12 S=4      22 / 18   16 x 28x28x32 M=8 S=2  26 / 21   64 x 28x28x64 M=4 S=4  36 / 33
-//   64 x 112x112x16 M=4 S=7 109 / 274   256 x 28x28x16 M=4 S=4 36 / 82   S=2 417 / 278   64 x 112x112x32 M=8 S=4 677 / 274
+// 2048 the patches that run at once (half of the cells are active).  Where it says so the scalar kernel is the faster one, but for the calls marked *; it
+// would be in others too, of many cells and little work (marked +).  Block alone on a drawn list, scalar / row schedule, us, fp32 (bf16):
+//   8x8x16 M=4 S=2      7.1 / 13.0 (6.9 / 15.1)     28x28x32 M=8 S=2       11.2 / 13.1 (10.9 / 12.6)    4 x 28x28x32 M=8 S=4*  15.3 / 13.1 (14.4 / 12.7)
+//   16 x 28x28x16 M=4 S=2 8.3 / 19.0 (8.3 / 18.5)   256 x 28x28x16 M=4 S=4 34.4 / 69.3 (31.4 / 48.6)    64 x 112x112x16 M=4 S=7 100 / 220 (86 / 179)
+//   beyond: 2 x 8x8x48 M=12 S=2 16.2 / 12.8 (15.6 / 15.0)    8x8x48 M=12 S=4 22.2 / 12.3 (21.5 / 14.7)     16x16x64 M=16 S=2 25.2 / 13.3 (25.3 / 12.6)
+//     256 x 28x28x16 M=4 S=2 105 / 71 (106 / 51)             64 x 112x112x32 M=8 S=4 730 / 247 (504 / 200)
+//     8 x 28x28x32 M=8 S=2+ 12.8 / 17.7 (11.8 / 17.2)        16 x 28x28x32 M=8 S=2+ 17.6 / 19.1 (15.5 / 18.5)   64 x 28x28x64 M=4 S=4+ 25.8 / 36.3 (23.2 / 31.4)
+//     32 x 28x28x16 M=4 S=2+ 14.1 / 22.6 (14.2 / 21.1)
 bool scalar_is_faster(const Geom& g) {
   const double S2 = (double)g.S * g.S, W2 = (double)(g.S + 2) * (g.S + 2), M = g.M, C = g.C;
   const auto rounds = [](double n) { return (double)(long long)((n + 255) / 256); };       // of a workgroup's 256 threads

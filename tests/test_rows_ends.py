@@ -1,5 +1,5 @@
-"""Row schedule: reductions of every length around the ring of two k-steps, so that each of the GEMM's straight-line ends runs (one
-k-step; two; three; whole rounds and each of these), in one wave and shared by four (some of whose shares are empty)."""
+"""Row schedule: reductions of every length around the rings of two and three k-steps, so that each of the GEMM's straight-line ends runs (one
+to five k-steps; whole rounds and each of these), in one wave and shared by four (some of whose shares are empty)."""
 import pytest
 
 from paper_2210_06223_amd import synth

@@ -1,5 +1,8 @@
 """Row schedule: rows through LDS rings with counted waits, against the build whose waits are for everything, bit for bit; and the zeros that
-conv2 reads outside the image, in a workspace that holds anything."""
+conv2 reads outside the image, in a workspace that holds anything.
+
+What the comparison can show is a place overwritten before it was read, and a count too large for a reduction's first k-step or its ends: in the steady loop the
+compiler's waits for the weights are for the next k-step's rows too."""
 import numpy as np
 import pytest
 import torch
